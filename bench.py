@@ -45,7 +45,7 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0
 METRIC = "Arnoldi steps/s and phi_combo/s at N=1M,m=64; HBM GB/s vs peak; err vs FP64"
-KERNEL = "kp::k_run<double, false>"
+KERNEL = "kp::k_blk<4>"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_run_allen_cahn_1024_traffic.txt")
 BATCH_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_batch_uneven_512_traffic.txt")
 FP32_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_run_fp32_basis_brusselator_2048_traffic.txt")
@@ -135,6 +135,28 @@ def basis_bytes_per_call(schedule, p, c, n, s):
     for _, m in schedule:
         total += sum(s * (2 * jj + 5) + 8 * (p + c) for jj in range(m)) + s + s * m + 8
     return (total + 8) * n
+
+
+def block_vectors_per_call(schedule, p, c, keep):
+    """Vector passes (each N float64) that a call of the float64 H-GSMGS form
+    moves: its kernel makes two Arnoldi steps per reduction, so a pass of
+    inner products and one of linear combinations over the basis serve both.
+    From the newest column j (0-based) the matvecs read p columns of B and c
+    fields (once: the second product finds them in cache), the inner products
+    the j older columns, the combination the columns 0..j, and it writes two
+    columns (one in a single last step).  keep: x_j, w1 and w2 stay in LDS;
+    otherwise x_j is read, w1 written, read and read again by the
+    combination, w2 written and read, and B and the fields read twice."""
+    total = (p + 1) + 1
+    for _, m in schedule:
+        total += 2                                     # column 0 from the state
+        for j in range(0, m, 2):
+            n = min(2, m - j)
+            total += 2 * j + 1 + p + c + n
+            if not keep:
+                total += 3 if n == 1 else 6 + p + c
+        total += m + 1
+    return total + 1
 
 
 def onchip_bytes(info, n, s=8):
@@ -266,9 +288,11 @@ def timeline_summary(T, rate=100e6):
     measured from the previous phase's release (t0): the median workgroup's
     release seen, update done, halo flags seen and arrival, the last
     arrival, the leader's reduction after the last arrival, its serial step
-    and release, and the whole step (release to release).  Other phases:
-    count and mean duration by kind.  Also the least-squares line of the
-    step duration in the step index j."""
+    and release, and the whole step (release to release).  A phase that
+    makes two steps (the next phase's j says so) is one row and counts as
+    two; a process's first phase, which has no update, counts for its second
+    step only.  Other phases: count and mean duration by kind.  Also the
+    least-squares line of the phase duration in the step index j."""
     import numpy as np
     T = np.asarray(T, dtype=np.float64)
     us = 1e6 / rate
@@ -279,14 +303,19 @@ def timeline_summary(T, rate=100e6):
     # of the grid only meet the barriers)
     owners = np.nonzero(T[live, :, 1].max(axis=0) > 0)[0]
     others = owners[owners > 0]
-    steps, other = [], {}
-    for a, b in zip(live[:-1], live[1:]):
+    steps, other, made = [], {}, 0
+    codes = [int(T[k, 0, 4]) for k in live]
+    for i, (a, b) in enumerate(zip(live[:-1], live[1:])):
+        nxt = codes[i + 2] if i + 2 < len(live) else 0
+        pair = (codes[i + 1] // 1000 == 1 and nxt // 1000 in (1, 2)
+                and nxt % 1000 == codes[i + 1] % 1000 + 2)
         code = int(T[b, 0, 4])
         ph, j = code // 1000, code % 1000
         t0 = T[a, 0, 7]
         dur = (T[b, 0, 7] - t0) * us
         w = T[b, others]
         if ph == 1 and j >= 1 and len(others) and w[:, 1].min() > 0:
+            made += 2 if pair else 1
             arr = T[b, owners, 3]
             steps.append([j, dur,
                           (np.median(w[:, 0]) - t0) * us,
@@ -298,11 +327,12 @@ def timeline_summary(T, rate=100e6):
                           (T[b, 0, 6] - T[b, 0, 5]) * us,
                           (T[b, 0, 7] - T[b, 0, 6]) * us])
         else:
+            made += 1 if ph == 1 and pair else 0
             other.setdefault(names.get(ph, str(ph)), []).append(dur)
     cols = ["j", "step_us", "release_seen_us", "update_done_us", "halo_flags_us",
             "arrival_median_us", "arrival_last_us", "reduction_after_last_us",
             "serial_us", "release_us"]
-    out = {"arnoldi_steps": len(steps)}
+    out = {"arnoldi_steps": made, "step_phases": len(steps)}
     if steps:
         S = np.array(steps)
         out["step_mean_us"] = {c: round(float(S[:, i].mean()), 2) for i, c in enumerate(cols)
@@ -459,10 +489,17 @@ def main():
     avg_ms = float(np.mean(launch_ms))
     steps_per_call = info["arnoldi_steps"]
     value = steps_per_call * args.steps / wall
-    vec = vectors_per_call(sched, p, c_fields, args.orth)
+    block = args.orth == "h-gsmgs" and args.basis == "f64"
+    if block:
+        # (what moves; x_j, w1 and w2 stay on chip at this size)
+        vec = block_vectors_per_call(sched, p, c_fields, info["onchip_passes"] > 0)
+        kept = 0.0
+    else:
+        vec = vectors_per_call(sched, p, c_fields, args.orth)
+        kept = onchip_bytes(info, N, 8 if args.basis == "f64" else 4)
     bytes_per_call = vec * 8.0 * N
+    two_pass_bytes = vectors_per_call(sched, p, c_fields, args.orth) * 8.0 * N
     achieved = bytes_per_call / (avg_ms * 1e-3) / 1e9
-    kept = onchip_bytes(info, N, 8 if args.basis == "f64" else 4)
     # what a plain streaming read reaches on this device (1 GiB, same launch shape)
     read_ceiling = ctx.read_bandwidth(1 << 30, 20)
     log(f"plain streaming read: {read_ceiling:.1f} GB/s")
@@ -502,6 +539,8 @@ def main():
                      "bytes_per_launch": bytes_per_call, "avg_launch_ms": round(avg_ms, 4),
                      "read_ceiling_GBps": round(read_ceiling, 1),
                      "frac_of_read_ceiling": round(achieved / read_ceiling, 4),
+                     # one step per reduction (two passes over the basis a step)
+                     "two_pass_bytes": two_pass_bytes,
                      # of bytes_per_launch, what the kernel keeps in LDS
                      # between the matvec pass and the update, and the
                      # fraction of peak counting only the bytes that move
@@ -535,12 +574,16 @@ def main():
             fms = float(np.median(ms))
             if orth == args.orth:
                 y_fixed = out.cpu().numpy().copy()
-            fvec = vectors_per_call([(pr.h, 64)], p, c_fields, orth)
+            fvec = (block_vectors_per_call([(pr.h, 64)], p, c_fields, 2 * args.side <= 4096)
+                    if orth == "h-gsmgs" and args.basis == "f64"
+                    else vectors_per_call([(pr.h, 64)], p, c_fields, orth))
             leg = {"ms_per_substep": round(fms, 4),
                    "us_per_arnoldi_step": round(1e3 * fms / 64, 2),
                    "arnoldi_steps_per_s": round(64 / (fms * 1e-3), 1),
-                   "grid_syncs_per_substep": sum(syncs_per_step(jj, orth) for jj in range(64))
-                   + (1 if orth not in ("mgs", "iocgs") else 0),
+                   "grid_syncs_per_substep": (
+                       33 if orth == "h-gsmgs" and args.basis == "f64"
+                       else sum(syncs_per_step(jj, orth) for jj in range(64))
+                       + (1 if orth not in ("mgs", "iocgs") else 0)),
                    "achieved_GBps": round(fvec * 8.0 * N / (fms * 1e-3) / 1e9, 1),
                    "frac": round(fvec * 8.0 * N / (fms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
                    "bytes_per_launch": fvec * 8.0 * N}
@@ -659,7 +702,9 @@ def main():
             c3.close()
             # (the two fields U and W, npt = N/2 elements each, are one
             # N-vector of coefficient data per matvec: c = 1)
-            byts = basis_bytes_per_call(sch3, p3.p, 1, p3.op.n, sz)
+            byts = (basis_bytes_per_call(sch3, p3.p, 1, p3.op.n, sz)
+                    if sz == 4 or args.orth != "h-gsmgs"
+                    else 8.0 * p3.op.n * block_vectors_per_call(sch3, p3.p, 1, False))
             leg[basis] = {"ms_per_call": round(ms3, 3), "arnoldi_steps": inf3["arnoldi_steps"],
                           "substeps": inf3["substeps"], "rejected": inf3["rejected"],
                           "arnoldi_steps_per_s": round(inf3["arnoldi_steps"] / (ms3 * 1e-3), 1),
@@ -794,8 +839,9 @@ def main():
         batch_wall = (time.perf_counter() - t0) / nrep
         batch_ms = float(np.mean([a.elapsed_time(b) for a, b in zip(e0, e1)]))
         steps4 = sum(r["arnoldi_steps"] for r in inf4)
-        bytes4 = sum(vectors_per_call(c4.batch_schedule(i), q.p, 0) * 8.0 * q.op.n
-                     for i, q in enumerate(probs4))
+        bytes4 = sum((block_vectors_per_call(c4.batch_schedule(i), q.p, 0, False)
+                      if args.orth == "h-gsmgs" else vectors_per_call(c4.batch_schedule(i), q.p, 0))
+                     * 8.0 * q.op.n for i, q in enumerate(probs4))
         _, _, plan_s, work_s = kp.batch_plan([q.op for q in probs4], [q.p for q in probs4], hs4,
                                              m_max=mm4, n_wg=256)
         # one plain call per problem into separate outputs (the largest first,

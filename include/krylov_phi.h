@@ -171,7 +171,9 @@ typedef struct kp_info {
                                 most 2048, a one-reduction form) the update
                                 takes x_j and w from the matvec pass before
                                 it, that pass reads the updated x_{j+1} from
-                                LDS, and w is never stored; 0 otherwise */
+                                LDS, and w is never stored: 4 per step (1 at a
+                                step without an update, 2 at the close), also
+                                where two steps share one pass; 0 otherwise */
     double  err_max;         /* largest substep error estimate */
     double  mu;              /* power-of-two balance of the augmented block */
     double  t_end;           /* time reached (h on success) */
@@ -215,8 +217,11 @@ int kp_phi_combo(kp_ctx* ctx, const kp_op* A, const double* B, int32_t p,
  * same computation, kernels and arguments as kp_phi_combo (the same result to
  * the bit), but the whole workspace (basis, state vector, partial sums, halo
  * rows, control and state blocks, small-exponential scratch) is carved from
- * one static device array of KP_NOALLOC_BYTES per GPU, which the loaded
- * library holds until the process ends; the call makes no allocation.
+ * one static device array per GPU, which the loaded library holds until the
+ * process ends; the call makes no allocation.  A problem is accepted when its
+ * workspace, counted on a partition of at least 4096 elements per workgroup
+ * and with one buffer of halo rows, fits KP_NOALLOC_BYTES; the array is
+ * 32 MiB larger, for the finer partition the float64 forms run on.
  * The workspace needs about (m_max + 2) (N + 64 + 128 planes) elements of the
  * basis type plus 8 (N + 64) bytes and ~1.3 MB of fixed blocks (float64 basis,
  * m_max = 64: N up to about 115,000).

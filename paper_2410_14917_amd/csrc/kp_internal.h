@@ -36,10 +36,12 @@ constexpr int kWaves = kThreads / 64;
 constexpr int kMMax = KP_MMAX;
 constexpr int kPMax = KP_PMAX;
 constexpr int kKStride = 2 * kMMax + 8;   // partial-sum slots per workgroup
-// The partial-sum area holds three [part_rows][kKStride] buffers: buffer 0 for the
-// phases whose arrivals are counted (stage, close), buffers 1 and 2 for the
-// Arnoldi steps, alternating with the barrier number (see step_part).
-constexpr int kPartBuffers = 3;
+// The partial-sum area: a [part_rows][kCStride] buffer for the phases whose
+// arrivals are counted (stage, close, projections: at most kCStride sums),
+// then two [part_rows][stride] buffers for the Arnoldi steps, alternating with
+// the barrier number (step_part, block_part; stride kKStride, or Args::bstride
+// for block steps), then for block steps two [bstride] buffers of their sums.
+constexpr int kCStride = 8;
 // Marks a step-buffer slot that has not been written since it was consumed:
 // a signalling NaN, which no arithmetic produces (results are quiet NaNs).
 constexpr unsigned long long kPartEmpty = 0xFFF4A5A5A5A5A5A5ull;
@@ -87,7 +89,7 @@ constexpr int kFlagStride = 16;           // unsigned per workgroup flag (64 B)
 struct Pub {
   int phase;
   int j;            // completed Arnoldi steps of the current substep
-  int upd;          // the update producing x_j is still pending (PH_STEP/CLOSE)
+  int upd;          // pending updates producing the newest column(s) (PH_STEP/CLOSE)
   int m_eff;        // Krylov dimension available (combine uses it)
   int last;         // the accepted substep ends at h
   int status;
@@ -95,6 +97,7 @@ struct Pub {
   double inv_mu;
   double xscale;            // MGS / ioCGS: unit scale of the column the next matvec multiplies
   double coef[kMMax + 2];   // coefficients of the pending update / of the combine
+  double coef2[kMMax + 2];  // block steps: coefficients of the second pending column
 };
 
 // Private state of the call, read and written only by the leader (and by the
@@ -109,7 +112,8 @@ struct State {
   int zero;           // the start vector is zero
   int m_last;
   int onchip;         // vector passes of the two-pass count kept in LDS (keep_xw)
-  int pad_[2];
+  int nopair;         // block steps: this Arnoldi process goes on in single steps
+  int pad_;
   double t, tau, beta, mu, err_max, omega, err, last_nrm2;
   double omega_prev;  // normalised error of the last accepted substep (PI control)
   double sigma[kMMax + 2];   // unit scale of stored basis column i
@@ -141,12 +145,13 @@ struct Args {
   const double* f1;
   double* out;
   double* dout;       // tangent mode: the directional derivative (plane 0)
-  double* part;       // [kPartBuffers][part_rows][kKStride] partial sums (coherent)
+  double* part;       // partial sums (coherent; see kCStride)
   unsigned* sync;     // [0] arrivals, [1] releases, [2] abort (coherent)
   State* st;          // the leader only
   Pub* pub;           // coherent
   double* ex;         // small-exponential scratch (the leader)
   double* hx;         // halo rows [nwg][nplanes][2][nx]      (coherent)
+  double* hx2;        // block steps: the halo rows of w1     (coherent)
   double* tx;         // tail values [kTailPad]               (coherent)
   unsigned* flags;    // per-workgroup production counters, kFlagStride apart
   int64_t ld, npt_pad, tail_off;
@@ -154,6 +159,10 @@ struct Args {
   int pb;             // number of phi terms beyond b_0 (columns b_1..b_pb of B)
   int tangent;        // 1: Van Loan block operator [[Atilde, dAtilde], [0, Atilde]]
   int nwg, rows_per_wg;   // workgroups that own rows; rows per workgroup
+  int block;          // one-reduction float64 kernels: two Arnoldi steps per reduction (k_blk)
+  int pairs;          // ... where the form allows pairs (0: single steps only)
+  int bstride;        // block steps: slots of a row of the step buffers
+  int tile_r;         // block steps: element pairs per thread and sub-tile
   int part_rows;      // rows of each partial-sum buffer (>= nwg, the same for every team class)
   int nteam, wg0;     // workgroups meeting at the barriers (>= nwg); first workgroup of the run of such teams
   int kind, transpose;
@@ -277,27 +286,32 @@ constexpr int kSyncAbort = 4;
 struct Ctl {
   int phase;
   int j;        // completed Arnoldi steps of the current substep
-  int upd;      // the update producing x_j is still pending (PH_STEP/CLOSE)
+  int upd;      // pending updates producing the newest column(s) (PH_STEP/CLOSE)
   int m_eff;    // Krylov dimension available (small exponential, combine)
   int last;     // the accepted substep ends at h
   int status;
   int i;        // PH_PROJ: column of the next inner product (j + 1: the norm)
+  int na;       // block steps: column j - 1 is unmeasured too
+  int two;      // block steps: the step phase makes two steps
 };
 
 __device__ inline unsigned ctl_pack(const Ctl& c) {
-  return (unsigned)c.phase | ((unsigned)c.j << 4) | ((unsigned)c.upd << 11) |
+  return (unsigned)c.phase | ((unsigned)c.j << 4) | ((unsigned)(c.upd & 1) << 11) |
          ((unsigned)c.m_eff << 12) | ((unsigned)c.last << 19) | ((unsigned)c.status << 20) |
-         ((unsigned)c.i << 22);
+         ((unsigned)c.i << 22) | ((unsigned)(c.upd >> 1) << 29) | ((unsigned)c.na << 30) |
+         ((unsigned)c.two << 31);
 }
 __device__ inline Ctl ctl_unpack(unsigned w) {
   Ctl c;
   c.phase = (int)(w & 15u);
   c.j = (int)((w >> 4) & 127u);
-  c.upd = (int)((w >> 11) & 1u);
+  c.upd = (int)(((w >> 11) & 1u) | (((w >> 29) & 1u) << 1));
   c.m_eff = (int)((w >> 12) & 127u);
   c.last = (int)((w >> 19) & 1u);
   c.status = (int)((w >> 20) & 3u);
   c.i = (int)((w >> 22) & 127u);
+  c.na = (int)((w >> 30) & 1u);
+  c.two = (int)(w >> 31);
   return c;
 }
 
@@ -370,7 +384,7 @@ __device__ inline void bar_count(const Args& a) {
 // leader consumed that buffer at barrier k - 1, before releasing it), and the
 // reset reaches the coherent level before any of its later stores does.
 __device__ inline double* step_part(const Args& a, unsigned k) {
-  return a.part + (int64_t)(1 + (int)(k & 1u)) * a.part_rows * kKStride;
+  return a.part + (int64_t)a.part_rows * kCStride + (int64_t)(k & 1u) * a.part_rows * kKStride;
 }
 
 // Leader: wait for every arrival at barrier k.  *ok (LDS) = false when
@@ -423,16 +437,16 @@ __device__ inline void bar_wait(const Args& a, unsigned k, Ctl* cur, int* ok) {
 }
 
 // Point-to-point: this workgroup has published the halo rows / tail of the
-// vector it produced in the phase of barrier k.
+// vector numbered k (the phase's barrier number; block steps publish two per
+// phase, 2k and 2k + 1).
 __device__ inline void flag_publish(const Args& a, unsigned k) {
   wait_all_stores();
   __syncthreads();
-  KP_TS(a, k, 1);
   if (kp_tid() == 0) cstore(a.flags + (int64_t)wg_rank(a) * kFlagStride, k);
 }
 
 // Wait until the two row neighbours (halo) and workgroup 0 (tail) have
-// published the vector of barrier k (the three flags are polled together).
+// published vector k (the three flags are polled together).
 __device__ inline void flag_wait_neighbours(const Args& a, unsigned k) {
   if (kp_tid() == 0) {
     const int b = wg_rank(a), nw = a.nwg;
@@ -449,7 +463,6 @@ __device__ inline void flag_wait_neighbours(const Args& a, unsigned k) {
     }
   }
   __syncthreads();
-  KP_TS(a, k, 2);
 }
 
 }  // namespace kp

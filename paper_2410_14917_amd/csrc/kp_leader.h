@@ -31,7 +31,7 @@ __device__ __attribute__((always_inline)) inline void reduce_partials(const Args
   constexpr int kQ = 32;               // workgroups per thread per pass
   const int g = kp_tid() / kP, l = kp_tid() % kP;
   const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-      a.part, (short)0, a.nwg * kKStride * (int)sizeof(double), kBufWord3);
+      a.part, (short)0, a.nwg * kCStride * (int)sizeof(double), kBufWord3);
   for (int kb = 0; kb < nslot; kb += 2 * kP) {
     const int k = kb + 2 * l;
     if (k < nslot) {
@@ -42,7 +42,7 @@ __device__ __attribute__((always_inline)) inline void reduce_partials(const Args
         for (int q = 0; q < kQ; ++q) {
           const int w = w0 + g + kRg * q;
           v[q] = __builtin_amdgcn_raw_buffer_load_b128(
-              rs, (w * kKStride + k) * (int)sizeof(double), 0, kCoherentAux);
+              rs, (w * kCStride + k) * (int)sizeof(double), 0, kCoherentAux);
         }
 #pragma unroll
         for (int q = 0; q < kQ; ++q) {
@@ -142,12 +142,24 @@ __device__ inline int step_phase(const Args& a) {
   return orth_multi_sync(a.orth) ? (int)PH_MVEC : (int)PH_STEP;
 }
 
+// Opens the steps from column j on, without a pending update; na: column
+// j - 1 is unmeasured too (block steps).
+template <typename LT>
+__device__ inline void begin_steps(const Args& a, const LT& L, Ctl& nx, int j, int na) {
+  nx.j = j;
+  nx.upd = 0;
+  nx.na = na;
+  nx.two = pair_ok(a, L, j);
+  nx.phase = step_phase(a);
+}
+
 // ---- stage leader: balance mu, augmented tail, first phase -----------------
-__device__ __attribute__((always_inline)) inline void leader_stage(const Args& a, double* red, Ctl& nx) {
+template <typename LT>
+__device__ __attribute__((always_inline)) inline void leader_stage(const Args& a, double* red, LT& L, Ctl& nx) {
   double m0 = 0.0, m1 = 0.0;
   for (int w = kp_tid(); w < a.nwg; w += kThreads) {
-    m0 = fmax(m0, cload(a.part + (int64_t)w * kKStride + 0));
-    m1 = fmax(m1, cload(a.part + (int64_t)w * kKStride + 1));
+    m0 = fmax(m0, cload(a.part + (int64_t)w * kCStride + 0));
+    m1 = fmax(m1, cload(a.part + (int64_t)w * kCStride + 1));
   }
   const double mx = block_max(m0, red);
   const double bad = block_max(m1, red);
@@ -173,9 +185,7 @@ __device__ __attribute__((always_inline)) inline void leader_stage(const Args& a
     } else if (a.h == 0.0) {
       nx.phase = (int)PH_FINISH;
     } else {
-      nx.j = 0;
-      nx.upd = 0;
-      nx.phase = step_phase(a);
+      begin_steps(a, L, nx, 0, 0);
     }
   }
 }
@@ -197,6 +207,13 @@ struct LeadLds {
   double wn2[kMMax + 8];
   int fallback_cur, m_target, breakdown, n_fallback, arnoldi_steps, onchip;
 };
+
+// What the shared controller code asks of a kernel's tables (the block
+// kernels' versions are with LeadB).
+__device__ inline int pair_ok(const Args&, const LeadLds&, int) { return 0; }
+__device__ inline void new_process(LeadLds&) {}
+__device__ inline double beta_of(const Args& a, const LeadLds&) { return a.st->beta; }
+__device__ inline const double* hess_of(const Args& a, const LeadLds&) { return a.st->H; }
 
 __device__ inline void load_tables(const Args& a, LeadLds& L) {
   const State* st = a.st;
@@ -569,7 +586,8 @@ __device__ inline double tau_factor_pi(double omega, double omega_prev, int m) {
   return fmin(4.0, fmax(0.2, f));
 }
 
-__device__ __attribute__((always_inline)) inline void expm_phase(const Args& a, double* lds, LeadLds& L,
+template <typename LT>
+__device__ __attribute__((always_inline)) inline void expm_phase(const Args& a, double* lds, LT& L,
                                                                 Ctl& nx) {
   __shared__ int s_dec;
   __shared__ double s_tau;
@@ -578,12 +596,12 @@ __device__ __attribute__((always_inline)) inline void expm_phase(const Args& a, 
   const bool fixed = a.fixed_m > 0;
   const int m = nx.m_eff;
   const bool happy = L.breakdown != 0;
-  const double t = st->t, beta = st->beta;
+  const double t = st->t, beta = beta_of(a, L);
   double tau = st->tau;
   if (happy && !fixed) tau = a.h - t;
   int dec = D_ACCEPT;
   while (true) {
-    expm_hbar(a, st->H, kLdh, m, tau, happy, st->F, lds);
+    expm_hbar(a, hess_of(a, L), kLdh, m, tau, happy, st->F, lds);
     if (kp_tid() == 0) {
       st->expm_evals += 1;
       const double err = happy ? 0.0 : beta * fabs(st->F[m]);
@@ -616,7 +634,7 @@ __device__ __attribute__((always_inline)) inline void expm_phase(const Args& a, 
   }
   if (dec == D_ACCEPT) {
     for (int i = kp_tid(); i < m; i += kThreads)
-      cstore(&pb->coef[i], beta * st->F[i] * st->sigma[i]);
+      cstore(&pb->coef[i], beta * st->F[i] * L.sigma[i]);
     if (kp_tid() == 0) {
       st->tau = tau;
       const int last = fixed ? (st->substeps + 1 >= a.fixed_substeps) : (tau >= a.h - t);
@@ -629,8 +647,7 @@ __device__ __attribute__((always_inline)) inline void expm_phase(const Args& a, 
       st->m_target = st->m_cur;
       L.m_target = st->m_cur;
       st->tau = tau;
-      nx.upd = 0;
-      nx.phase = step_phase(a);
+      begin_steps(a, L, nx, nx.j, nx.na);
     }
   } else {
     if (kp_tid() == 0) {
@@ -642,7 +659,8 @@ __device__ __attribute__((always_inline)) inline void expm_phase(const Args& a, 
 }
 
 // ---- after the combine: advance time, next substep -------------------------
-__device__ __attribute__((always_inline)) inline void leader_combine(const Args& a, LeadLds& L, Ctl& nx) {
+template <typename LT>
+__device__ __attribute__((always_inline)) inline void leader_combine(const Args& a, LT& L, Ctl& nx) {
   if (kp_tid() != 0) return;
   State* st = a.st;
   const bool fixed = a.fixed_m > 0;
@@ -681,9 +699,8 @@ __device__ __attribute__((always_inline)) inline void leader_combine(const Args&
   st->m_target = fixed ? a.fixed_m : st->m_cur;
   L.breakdown = 0;
   L.m_target = st->m_target;
-  nx.j = 0;
-  nx.upd = 0;
-  nx.phase = step_phase(a);
+  new_process(L);
+  begin_steps(a, L, nx, 0, 0);
 }
 
 }  // namespace kp

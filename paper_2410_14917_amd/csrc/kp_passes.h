@@ -270,18 +270,19 @@ __device__ inline int64_t halo_at(const Args& a, int w, int s, int side, int ix)
 // element pair (e, e+1) of segment sg with the values as stored; lanes outside
 // the boundary rows store nothing.  (The tail is published by tail_update /
 // tail_combine.)
-__device__ inline void publish_elem(const Args& a, const Seg& sg, int64_t e, double v) {
+// hx: the halo buffer (a.hx, or a.hx2 for the first product of a block step).
+__device__ inline void publish_elem(const Args& a, double* hx, const Seg& sg, int64_t e, double v) {
   if (e >= sg.end) return;
   const int64_t off = e - sg.beg, last0 = sg.end - sg.beg - a.nx;
-  if (off < a.nx) cstore(a.hx + halo_at(a, wg_rank(a), sg.plane, 0, (int)off), v);
-  if (off >= last0) cstore(a.hx + halo_at(a, wg_rank(a), sg.plane, 1, (int)(off - last0)), v);
+  if (off < a.nx) cstore(hx + halo_at(a, wg_rank(a), sg.plane, 0, (int)off), v);
+  if (off >= last0) cstore(hx + halo_at(a, wg_rank(a), sg.plane, 1, (int)(off - last0)), v);
 }
 
-__device__ inline void publish_pair(const Args& a, const Seg& sg, int64_t e, double v0,
+__device__ inline void publish_pair(const Args& a, double* hx, const Seg& sg, int64_t e, double v0,
                                     double v1) {
   if (e - sg.beg < a.nx || e + 1 >= sg.end - a.nx) {
-    publish_elem(a, sg, e, v0);
-    publish_elem(a, sg, e + 1, v1);
+    publish_elem(a, hx, sg, e, v0);
+    publish_elem(a, hx, sg, e + 1, v1);
   }
 }
 
@@ -289,14 +290,14 @@ __device__ inline void publish_pair(const Args& a, const Seg& sg, int64_t e, dou
 // workgroup, the last row of the previous one, periodic) into LDS:
 // hl[s * nx + ix] = row r1 (mod ny), hl[(nplanes + s) * nx + ix] = row r0 - 1.
 template <typename TB>
-__device__ inline void stage_halo(const Args& a, const Rows& o, double* hl) {
+__device__ inline void stage_halo(const Args& a, const double* hx, const Rows& o, double* hl) {
   const int nx = a.nx, b = wg_rank(a);
   const int wn = (o.r1 == a.ny) ? 0 : b + 1;
   const int ws = (o.r0 == 0) ? a.nwg - 1 : b - 1;
   for (int s = 0; s < a.nplanes; ++s)
     for (int ix = kp_tid(); ix < nx; ix += kThreads) {
-      hl[s * nx + ix] = rnd<TB>(cload(a.hx + halo_at(a, wn, s, 0, ix)));
-      hl[(a.nplanes + s) * nx + ix] = rnd<TB>(cload(a.hx + halo_at(a, ws, s, 1, ix)));
+      hl[s * nx + ix] = rnd<TB>(cload(hx + halo_at(a, wn, s, 0, ix)));
+      hl[(a.nplanes + s) * nx + ix] = rnd<TB>(cload(hx + halo_at(a, ws, s, 1, ix)));
     }
 }
 
@@ -307,7 +308,7 @@ __device__ inline void stage_halo(const Args& a, const Rows& o, double* hl) {
 // basis column, or LDS where the update left x_j); the rows just outside come from the LDS halo copy (HL) or from the coherent halo
 // slots.  All loads are unconditional (dummy indices where unused).
 template <typename TB, bool HL, typename XS>
-__device__ inline double op_elem(const Args& a, const Rows& o, const XS& x, const double* hl,
+__device__ inline double op_elem(const Args& a, const double* hx, const Rows& o, const XS& x, const double* hl,
                                  int s, int64_t e, int q, bool valid) {
   const int nx = a.nx;
   int row = (int)((double)q * a.inv_nx);   // q / nx, corrected by one step
@@ -337,11 +338,11 @@ __device__ inline double op_elem(const Args& a, const Rows& o, const XS& x, cons
   } else {
     if (!hn) {
       const int rn = (row + 1 == a.ny) ? 0 : row + 1;
-      xn = rnd<TB>(cload(a.hx + halo_at(a, (int)((unsigned)rn / (unsigned)a.rows_per_wg), s, 0, ix)));
+      xn = rnd<TB>(cload(hx + halo_at(a, (int)((unsigned)rn / (unsigned)a.rows_per_wg), s, 0, ix)));
     }
     if (!hs) {
       const int rs = (row == 0) ? a.ny - 1 : row - 1;
-      xs = rnd<TB>(cload(a.hx + halo_at(a, (int)((unsigned)rs / (unsigned)a.rows_per_wg), s, 1, ix)));
+      xs = rnd<TB>(cload(hx + halo_at(a, (int)((unsigned)rs / (unsigned)a.rows_per_wg), s, 1, ix)));
     }
   }
   // (the multiply-adds are written out, so that every instantiation of the
@@ -364,11 +365,11 @@ __device__ inline double op_elem(const Args& a, const Rows& o, const XS& x, cons
     } else {
       if (!hn) {
         const int rn = (row + 1 == a.ny) ? 0 : row + 1;
-        n1 = rnd<TB>(cload(a.hx + halo_at(a, (int)((unsigned)rn / (unsigned)a.rows_per_wg), 1, 0, ix)));
+        n1 = rnd<TB>(cload(hx + halo_at(a, (int)((unsigned)rn / (unsigned)a.rows_per_wg), 1, 0, ix)));
       }
       if (!hs) {
         const int rs = (row == 0) ? a.ny - 1 : row - 1;
-        s1 = rnd<TB>(cload(a.hx + halo_at(a, (int)((unsigned)rs / (unsigned)a.rows_per_wg), 1, 1, ix)));
+        s1 = rnd<TB>(cload(hx + halo_at(a, (int)((unsigned)rs / (unsigned)a.rows_per_wg), 1, 1, ix)));
       }
     }
     const double dadv = __builtin_fma(a.dadx, e1 - w1, a.dady * (n1 - s1));
@@ -395,8 +396,8 @@ __device__ inline double op_elem(const Args& a, const Rows& o, const XS& x, cons
 // (Atilde x) on the kR pairs of a sub-tile of plane segment sg:
 // A x_top + sum_c tc[c] b_{p-c} (the tail rows, K x_tail, are done by
 // tail_matvec_dots); zero in the padding.
-template <typename TB, bool HL, typename XS>
-__device__ inline void aug_tile(const Args& a, const Rows& o, const Seg& sg, const XS& x,
+template <typename TB, bool HL, typename XS, int R = kR>
+__device__ inline void aug_tile(const Args& a, const double* hx, const Rows& o, const Seg& sg, const XS& x,
                                 const double* hl, int64_t t0, const uint32_t* lo,
                                 const double* tc, double2* w) {
   const int64_t base = (int64_t)sg.plane * a.npt_pad;
@@ -404,13 +405,13 @@ __device__ inline void aug_tile(const Args& a, const Rows& o, const Seg& sg, con
   // B-hat x_tail / mu: the columns b_{p-c}, two at a time with all their
   // loads issued before the first use (the first two go out with the
   // stencil's loads)
-  double b0[2][kR][2];
+  double b0[2][R][2];
 #pragma unroll
   for (int c = 0; c < 2; ++c) {
     if (c < a.pb) {
       const int64_t col = (int64_t)(a.pb - c) * a.ldb + xoff - base;
 #pragma unroll
-      for (int r = 0; r < kR; ++r) {
+      for (int r = 0; r < R; ++r) {
         const int64_t e = t0 + lo[r];
         b0[c][r][0] = a.B[col + e];
         b0[c][r][1] = a.B[col + ((e + 1 < sg.end) ? e + 1 : e)];
@@ -418,12 +419,12 @@ __device__ inline void aug_tile(const Args& a, const Rows& o, const Seg& sg, con
     }
   }
 #pragma unroll
-  for (int r = 0; r < kR; ++r) {
+  for (int r = 0; r < R; ++r) {
     const int64_t e = t0 + lo[r];
     const bool v1 = e + 1 < sg.end;
     const int q = (int)(e - base);
-    w[r].x = op_elem<TB, HL>(a, o, x, hl, sg.plane, e, q, true);
-    const double y = op_elem<TB, HL>(a, o, x, hl, sg.plane, v1 ? e + 1 : e, v1 ? q + 1 : q, v1);
+    w[r].x = op_elem<TB, HL>(a, hx, o, x, hl, sg.plane, e, q, true);
+    const double y = op_elem<TB, HL>(a, hx, o, x, hl, sg.plane, v1 ? e + 1 : e, v1 ? q + 1 : q, v1);
     w[r].y = v1 ? y : 0.0;
   }
 #pragma unroll
@@ -431,7 +432,7 @@ __device__ inline void aug_tile(const Args& a, const Rows& o, const Seg& sg, con
     if (c < a.pb) {
       const double t = tc[c];
 #pragma unroll
-      for (int r = 0; r < kR; ++r) {
+      for (int r = 0; r < R; ++r) {
         const bool v1 = t0 + lo[r] + 1 < sg.end;
         w[r].x = __builtin_fma(t, b0[c][r][0], w[r].x);
         w[r].y = v1 ? __builtin_fma(t, b0[c][r][1], w[r].y) : w[r].y;
@@ -439,13 +440,13 @@ __device__ inline void aug_tile(const Args& a, const Rows& o, const Seg& sg, con
     }
   }
   for (int c0 = 2; c0 < a.pb; c0 += 2) {
-    double bv[2][kR][2];
+    double bv[2][R][2];
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
       if (c0 + c < a.pb) {
         const int64_t col = (int64_t)(a.pb - c0 - c) * a.ldb + xoff - base;
 #pragma unroll
-        for (int r = 0; r < kR; ++r) {
+        for (int r = 0; r < R; ++r) {
           const int64_t e = t0 + lo[r];
           bv[c][r][0] = a.B[col + e];
           bv[c][r][1] = a.B[col + ((e + 1 < sg.end) ? e + 1 : e)];
@@ -457,7 +458,7 @@ __device__ inline void aug_tile(const Args& a, const Rows& o, const Seg& sg, con
       if (c0 + c < a.pb) {
         const double t = tc[c0 + c];
 #pragma unroll
-        for (int r = 0; r < kR; ++r) {
+        for (int r = 0; r < R; ++r) {
           const bool v1 = t0 + lo[r] + 1 < sg.end;
           w[r].x = __builtin_fma(t, bv[c][r][0], w[r].x);
           w[r].y = v1 ? __builtin_fma(t, bv[c][r][1], w[r].y) : w[r].y;
@@ -719,14 +720,14 @@ __device__ __attribute__((always_inline)) inline void stage_pass(const Args& a, 
         }
       }
       a.u[e] = v;
-      publish_elem(a, sg, e, v);   // the tail is staged by the leader
+      publish_elem(a, a.hx, sg, e, v);   // the tail is staged by the leader
     }
   }
   mx = block_max(mx, red);
   bad = block_max(bad, red);
   if (kp_tid() == 0) {
-    cstore(a.part + (int64_t)wg_rank(a) * kKStride + 0, mx);
-    cstore(a.part + (int64_t)wg_rank(a) * kKStride + 1, bad);
+    cstore(a.part + (int64_t)wg_rank(a) * kCStride + 0, mx);
+    cstore(a.part + (int64_t)wg_rank(a) * kCStride + 1, bad);
   }
 }
 
@@ -800,7 +801,7 @@ __device__ __attribute__((always_inline)) inline void matvec_dots_pass(const Arg
   const Rows o = own_rows(a);
   double* hh = KEEP ? hl + 2 * kR * kThreads : hl;   // the halo copy
   for (int k = kp_tid(); k < kWaves * kKStride; k += kThreads) sacc[k] = 0.0;
-  if (HL) stage_halo<TB>(a, o, hh);
+  if (HL) stage_halo<TB>(a, a.hx, o, hh);
   const double inv_mu = cload(&a.pub->inv_mu);
   TB* xcol = V + (int64_t)jj * ld;
   TB* wcol = V + (int64_t)(jj + 1) * ld;
@@ -839,14 +840,14 @@ __device__ __attribute__((always_inline)) inline void matvec_dots_pass(const Arg
         const LdsX lx{hl, t0};   // (one sub-tile: t0 is the block's first pair)
 #pragma unroll
         for (int r = 0; r < kR; ++r) xv[r] = *reinterpret_cast<const double2*>(hl + lo[r]);
-        aug_tile<TB, HL>(a, o, sg, lx, hh, t0, lo, tc, wv2);
+        aug_tile<TB, HL>(a, a.hx, o, sg, lx, hh, t0, lo, tc, wv2);
       } else {
 #pragma unroll
         for (int r = 0; r < kR; ++r) xv[r] = xc.pair(t0 + lo[r]);
         if constexpr (JT)
           aug_tile_br2<TB, HL>(a, o, sg, xc, hh, t0, lo, tc, wv2);
         else
-          aug_tile<TB, HL>(a, o, sg, xc, hh, t0, lo, tc, wv2);
+          aug_tile<TB, HL>(a, a.hx, o, sg, xc, hh, t0, lo, tc, wv2);
       }
 #pragma unroll
       for (int r = 0; r < kR; ++r) {
@@ -976,7 +977,7 @@ __device__ __attribute__((always_inline)) inline void update_pass(const Args& a,
           if (kxw) reinterpret_cast<double2*>(kxw)[r * kThreads + kp_tid()] = make_double2(y0, y1);
           Pair<TB>::store(wcol + t0 + lo[r], y0, y1);
           ss += y0 * y0 + y1 * y1;
-          publish_pair(a, sg, t0 + lo[r], y0, y1);
+          publish_pair(a, a.hx, sg, t0 + lo[r], y0, y1);
         }
       }
     }
@@ -985,7 +986,7 @@ __device__ __attribute__((always_inline)) inline void update_pass(const Args& a,
     ss += tail_combine_cols<TB, TB>(a, V, jj + 1, coef, jj + 1, cw, wcol, true);
   if (want_norm) {
     ss = block_sum(ss, red);
-    if (kp_tid() == 0) cstore(a.part + (int64_t)wg_rank(a) * kKStride, ss);
+    if (kp_tid() == 0) cstore(a.part + (int64_t)wg_rank(a) * kCStride, ss);
   }
 }
 
@@ -1017,7 +1018,7 @@ __device__ __attribute__((always_inline)) inline void combine_pass(const Args& a
         if (ok[r]) {
           const int64_t e = t0 + lo[r];
           *reinterpret_cast<double2*>(a.u + e) = acc[r];
-          if (!last) publish_pair(a, sg, e, acc[r].x, acc[r].y);
+          if (!last) publish_pair(a, a.hx, sg, e, acc[r].x, acc[r].y);
           if (last) {
             if (e < sg.end) outp[e] = acc[r].x;
             if (e + 1 < sg.end) outp[e + 1] = acc[r].y;
@@ -1082,7 +1083,7 @@ __device__ __attribute__((always_inline)) inline void mvec_pass(const Args& a, i
   const int lane = kp_tid() & 63, wv = kp_tid() >> 6;
   const Rows o = own_rows(a);
   for (int k = kp_tid(); k < kWaves * kMvSlots; k += kThreads) sacc[k] = 0.0;
-  if (HL) stage_halo<TB>(a, o, hl);
+  if (HL) stage_halo<TB>(a, a.hx, o, hl);
   const double inv_mu = cload(&a.pub->inv_mu);
   const double xs = jj == 0 ? 1.0 : cload(&a.pub->xscale);
   TB* xcol = V + (int64_t)jj * ld;
@@ -1114,7 +1115,7 @@ __device__ __attribute__((always_inline)) inline void mvec_pass(const Args& a, i
         xv[r] = xc.pair(t0 + lo[r]);
         av[r] = (acol >= 0) ? load_at(ac, lo[r] * (uint32_t)sizeof(TB)) : make_double2(0.0, 0.0);
       }
-      aug_tile<TB, HL>(a, o, sg, xc, hl, t0, lo, tc, wv2);
+      aug_tile<TB, HL>(a, a.hx, o, sg, xc, hl, t0, lo, tc, wv2);
 #pragma unroll
       for (int r = 0; r < kR; ++r) {
         wv2[r].x = rnd<TB>(xs * wv2[r].x);
@@ -1148,7 +1149,7 @@ __device__ __attribute__((always_inline)) inline void mvec_pass(const Args& a, i
   if (kp_tid() < kMvSlots) {
     double s = 0.0;
     for (int w = 0; w < kWaves; ++w) s += sacc[w * kMvSlots + kp_tid()];
-    cstore(a.part + (int64_t)wg_rank(a) * kKStride + kp_tid(), s);
+    cstore(a.part + (int64_t)wg_rank(a) * kCStride + kp_tid(), s);
   }
 }
 
@@ -1192,7 +1193,7 @@ __device__ __attribute__((always_inline)) inline void proj_pass(const Args& a, i
           Pair<TB>::store(wcol + t0 + lo[r], y0, y1);
           if (want_norm) {
             ss += y0 * y0 + y1 * y1;
-            publish_pair(a, sg, t0 + lo[r], y0, y1);
+            publish_pair(a, a.hx, sg, t0 + lo[r], y0, y1);
           } else {
             ss += dv[r].x * y0 + dv[r].y * y1;
           }
@@ -1217,7 +1218,7 @@ __device__ __attribute__((always_inline)) inline void proj_pass(const Args& a, i
     }
   }
   ss = block_sum(ss, red);
-  if (kp_tid() == 0) cstore(a.part + (int64_t)wg_rank(a) * kKStride, ss);
+  if (kp_tid() == 0) cstore(a.part + (int64_t)wg_rank(a) * kCStride, ss);
 }
 
 // ---- finish: out = u_top (or NaN when the input was not finite) -------------

@@ -19,8 +19,10 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <type_traits>
 #include <vector>
 
+#include "kp_block.h"
 #include "kp_internal.h"
 #include "kp_leader.h"
 #include "kp_passes.h"
@@ -103,7 +105,9 @@ __device__ __attribute__((always_inline)) inline void run_phase(const Args& a, d
       if (c.upd) {
         update_pass<TB>(a, c.j - 1, a.pub->coef, red, false, xl ? hl : nullptr);
         flag_publish(a, k);
+        KP_TS(a, k, 1);
         flag_wait_neighbours(a, k);
+        KP_TS(a, k, 2);
       } else {
         wait_all_stores();
       }
@@ -187,7 +191,7 @@ __device__ __attribute__((always_inline)) inline void run_phase(const Args& a, d
   }
   switch (c.phase) {
     case PH_STAGE:
-      leader_stage(a, red, nxt);
+      leader_stage(a, red, L, nxt);
       break;
     case PH_STEP:
       gather_step_partials(a, step_part(a, k), 2 * c.j + 3, own, tv, grp, &ok);
@@ -230,6 +234,179 @@ __device__ __attribute__((always_inline)) inline void run_phase(const Args& a, d
   if (kp_tid() == 0) cur = nxt;
 }
 
+// ---- block steps (the one-reduction forms with a float64 basis) ---------------
+// LDS carve-up (doubles): per-wave sums (the leader's serial work reuses
+// them), block-reduction scratch, reduced sums (the workgroup's own row
+// first), the coefficients of two columns, and the region that holds the
+// halo rows or x_j, w1, w2 (matvec_block).  The small exponential uses the
+// whole buffer.
+constexpr int kOffBRed = kWaves * kBSlots;
+constexpr int kOffBTv = kOffBRed + 4 * kWaves;
+constexpr int kOffBCf = kOffBTv + kBSlots;
+constexpr int kOffBHl = (kOffBCf + 2 * kCoefLd + 15) / 16 * 16;
+constexpr int kLdsDoublesB = kOffBHl + kHaloCap;
+static_assert(kLdsDoublesB >= 2 * kNmPad * kNmPad, "the small exponential does not fit the phase buffer");
+static_assert(8 * 72 <= kWaves * kBSlots && kRg * kKStride <= kWaves * kBSlots, "leader scratch");
+static_assert(kBSlots <= kThreads, "one thread per slot");
+
+// One phase of the call for this workgroup (as run_phase).
+template <int R>
+__device__ __attribute__((always_inline)) inline void run_phase_block(const Args& a, double* lds, LeadB& L,
+                                                                      Ctl& cur, Ctl& nxt, int& ok, unsigned k) {
+  double* sacc = lds;
+  double* red = lds + kOffBRed;
+  double* tv = lds + kOffBTv;
+  double* cf = lds + kOffBCf;
+  double* hl = lds + kOffBHl;
+  const bool lead = wg_rank(a) == 0, owner = wg_rank(a) < a.nwg;
+  const Ctl c = cur;
+  const int nslot = 4 * (c.j - c.na) + 10;
+  KP_TS(a, k, 0);
+  if (lead) KP_TSV(a, k, 4, c.phase * 1000 + c.j);
+  if (owner) block_reset(a, k);
+  if (owner) switch (c.phase) {
+    case PH_STAGE:
+      stage_pass(a, red);
+      break;
+    case PH_STEP:
+      if (c.upd) {
+        load_coefs(a, cf);
+        if (c.upd == 2)
+          update_block<R, 2>(a, c.j, cf, hl, red, false);
+        else
+          update_block<R, 1>(a, c.j, cf, hl, red, false);
+        flag_publish(a, 2 * k);
+        KP_TS(a, k, 1);
+        flag_wait_neighbours(a, 2 * k);
+        KP_TS(a, k, 2);
+      } else {
+        wait_all_stores();   // (the resets, before the partial sums)
+      }
+      if (a.keep_xw)         // (implies halo_lds)
+        matvec_block<R, true, true>(a, c.j, c.na, c.two, c.upd != 0, sacc, hl, k);
+      else if (a.halo_lds)
+        matvec_block<R, false, true>(a, c.j, c.na, c.two, c.upd != 0, sacc, hl, k);
+      else
+        matvec_block<R, false, false>(a, c.j, c.na, c.two, c.upd != 0, sacc, hl, k);
+      if (kp_tid() < nslot) {
+        double s = 0.0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) s += sacc[w * kBSlots + kp_tid()];
+        if (lead) tv[kp_tid()] = s;
+        if (a.nwg > kDirectRows || !lead)
+          cstore(block_part(a, k) + (int64_t)wg_rank(a) * a.bstride + kp_tid(), s);
+      }
+      break;
+    case PH_CLOSE:
+      load_coefs(a, cf);
+      if (c.upd == 2)
+        update_block<R, 2>(a, c.j, cf, hl, red, true);
+      else
+        update_block<R, 1>(a, c.j, cf, hl, red, true);
+      break;
+    case PH_COMBINE:
+      load_coefs(a, cf);
+      combine_block<R>(a, c.m_eff, cf, c.last != 0);
+      break;
+    case PH_FINISH:
+      finish_pass(a, c.status == KP_STATUS_NONFINITE);
+      break;
+    default:
+      break;
+  }
+  KP_TS(a, k, 3);
+  if (c.phase != PH_STEP) {
+    bar_arrive(a);
+  } else {
+    if (owner && a.nwg > kDirectRows)
+      reduce_quads(a, block_part(a, k), block_sums(a, k), nslot, red, &ok);
+    if (!lead) bar_count(a);
+  }
+  if (!lead) {
+    bar_wait(a, k, &cur, &ok);
+    KP_TS(a, k, 4);
+    return;
+  }
+  if (c.phase != PH_STEP) {
+    bar_gather(a, k, &ok);
+    if (!ok) return;
+  }
+  if (kp_tid() == 0) nxt = c;
+  if (a.keep_xw && kp_tid() == 0 && c.phase == PH_CLOSE) L.onchip += 2;
+  switch (c.phase) {
+    case PH_STAGE:
+      leader_stage(a, red, L, nxt);
+      break;
+    case PH_STEP: {
+      __syncthreads();   // (tv: its own row, and nxt)
+      const int steps0 = L.arnoldi_steps;
+      block_gather(a, k, nslot, tv, tv, &ok);
+      if (!ok) return;
+      KP_TS(a, k, 5);
+      block_scalar(a, c.j, c.na, c.two, tv, L, sacc, nxt);
+      // vector passes of Algorithm 4's count that stayed in LDS: 4 per step
+      // (x_j and w in the update, x_j in the matvec, the store of w), but 1
+      // where the step starts without an update
+      if (a.keep_xw && kp_tid() == 0)
+        L.onchip += 4 * max(1, L.arnoldi_steps - steps0) - (c.upd ? 0 : 3);
+      break;
+    }
+    case PH_CLOSE:
+      reduce_partials(a, 2, tv, sacc);
+      block_close(a, tv[0], tv[1], L, nxt);
+      break;
+    case PH_EXPM:
+      store_tables_b(a, L, false, c.j);
+      expm_phase(a, lds, L, nxt);
+      break;
+    case PH_COMBINE:
+      leader_combine(a, L, nxt);
+      break;
+    case PH_FINISH:
+      store_tables_b(a, L, false, c.j);
+      if (kp_tid() == 0) nxt.phase = PH_DONE;
+      break;
+    default:
+      break;
+  }
+  KP_TS(a, k, 6);
+  bar_release(a, k, nxt, a.pub);
+  KP_TS(a, k, 7);
+  if (c.phase == PH_STEP) {
+    bar_count(a);
+    block_post(c.j, L);
+  }
+  if (kp_tid() == 0) cur = nxt;
+}
+
+template <int R>
+__global__ __launch_bounds__(kThreads) void k_blk(Args a, int arnoldi_only) {
+  __shared__ __attribute__((aligned(16))) double lds[kLdsDoublesB];
+  __shared__ LeadB lead;
+  __shared__ Ctl cur, nxt;
+  __shared__ int ok;
+  __shared__ unsigned s_k;
+  if (kp_tid() == 0) {
+    const unsigned long long w = cload(release_word(a));
+    s_k = (unsigned)(w >> 32);
+    cur = ctl_unpack((unsigned)w);
+    ok = aborted(a) ? 0 : 1;
+  }
+  if (wg_rank(a) == 0) load_tables_b(a, lead, arnoldi_only != 0);
+  __syncthreads();
+  unsigned k = s_k;
+  for (;;) {
+    __syncthreads();
+    if (!ok || cur.phase == PH_DONE) break;
+    if (arnoldi_only && (cur.phase == PH_EXPM || cur.phase == PH_COMBINE || cur.phase == PH_FINISH ||
+                         (cur.phase == PH_STEP && cur.j >= a.stop_j)))
+      break;
+    ++k;
+    run_phase_block<R>(a, lds, lead, cur, nxt, ok, k);
+  }
+  if (arnoldi_only && wg_rank(a) == 0) store_tables_b(a, lead, true, cur.j);
+}
+
 // The whole call (or, for the step-by-step entry, the steps up to stop_j).
 template <typename TB, bool MS>
 __global__ __launch_bounds__(kThreads) void k_run(Args a, int arnoldi_only) {
@@ -262,23 +439,28 @@ __global__ __launch_bounds__(kThreads) void k_run(Args a, int arnoldi_only) {
   }
 }
 
-// Reset of the call state; the Hessenberg and correction matrices are zeroed
-// so that entries outside their triangles read as zero.  Run by one
-// workgroup of any size before the launch that solves the problem.
-__device__ inline void init_problem(const Args& a, int m_target, int nflags) {
+// Reset of the call state by nb workgroups of any size, this one being number
+// b, before the launch that solves the problem: the step buffers are marked
+// empty; the Hessenberg and correction matrices are zeroed so that entries
+// outside their triangles read as zero (block steps keep them in LDS and
+// mask instead).
+__device__ inline void init_problem(const Args& a, int m_target, int nflags, int b, int nb) {
   State* st = a.st;
-  for (int i = kp_tid(); i < kLdh * kMMax; i += blockDim.x) st->H[i] = 0.0;
-  for (int i = kp_tid(); i < kLdt * kMMax; i += blockDim.x) {
-    st->Lm[i] = 0.0;
-    st->Minv[i] = 0.0;
-  }
-  for (int i = kp_tid(); i < kMMax + 2; i += blockDim.x) a.pub->coef[i] = 0.0;
-  for (int i = kp_tid(); i < nflags; i += blockDim.x) a.flags[i] = 0u;
   {
-    double* sp = step_part(a, 0);   // both step buffers, consecutive
+    double* sp = a.part + (int64_t)a.part_rows * kCStride;
+    const int n = a.block ? 2 * (a.part_rows + 1) * a.bstride : 2 * a.part_rows * kKStride;
     const double empty = __builtin_bit_cast(double, kPartEmpty);
-    for (int i = kp_tid(); i < 2 * a.part_rows * kKStride; i += blockDim.x) sp[i] = empty;
+    for (int i = b * (int)blockDim.x + kp_tid(); i < n; i += nb * (int)blockDim.x) sp[i] = empty;
   }
+  if (b != 0) return;
+  for (int i = kp_tid(); i < kMMax + 2; i += blockDim.x) a.pub->coef[i] = a.pub->coef2[i] = 0.0;
+  for (int i = kp_tid(); i < nflags; i += blockDim.x) a.flags[i] = 0u;
+  if (!a.block) for (int i = kp_tid(); i < kLdh * kMMax; i += blockDim.x) st->H[i] = 0.0;
+  if (!a.block)
+    for (int i = kp_tid(); i < kLdt * kMMax; i += blockDim.x) {
+      st->Lm[i] = 0.0;
+      st->Minv[i] = 0.0;
+    }
   if (kp_tid() != 0) return;
   for (int i = 0; i < 16; ++i) a.sync[i] = 0u;   // counters, release word (STAGE), abort
   Pub* pb = a.pub;
@@ -298,6 +480,7 @@ __device__ inline void init_problem(const Args& a, int m_target, int nflags) {
   st->n_fallback = st->breakdowns = st->nlog = st->zero = 0;
   st->m_last = 0;
   st->onchip = 0;
+  st->nopair = 0;
   st->t = 0.0;
   st->tau = a.tau0;
   st->beta = 0.0;
@@ -305,17 +488,18 @@ __device__ inline void init_problem(const Args& a, int m_target, int nflags) {
   st->err_max = st->omega = st->err = st->last_nrm2 = st->omega_prev = 0.0;
 }
 
-// The one-reduction float64 kernel (the main call's) is instantiated first, so
-// that it leads the code object and its placement does not move when the
-// other kernels change size (its run time varied by about 1 % with placement
-// alone, with identical instructions).
-template __global__ void k_run<double, false>(Args, int);
+// The main call's kernel is instantiated first, so that it leads the code
+// object and its placement does not move when the other kernels change size
+// (its run time varied by about 1 % with placement alone, with identical
+// instructions).
+template __global__ void k_blk<kR>(Args, int);
+template __global__ void k_blk<1>(Args, int);
 template __global__ void k_run<float, false>(Args, int);
 template __global__ void k_run<double, true>(Args, int);
 template __global__ void k_run<float, true>(Args, int);
 
 __global__ __launch_bounds__(256) void k_init(Args a, int m_target) {
-  init_problem(a, m_target, a.nwg * kFlagStride);
+  init_problem(a, m_target, a.nwg * kFlagStride, (int)blockIdx.x, (int)gridDim.x);
 }
 
 // ---- batched call ------------------------------------------------------------
@@ -383,7 +567,7 @@ __global__ __launch_bounds__(256) void k_batch_init(BatchDesc d) {
   int nflags = 0;
   for (int c = 0; c < d.nclass; ++c)
     nflags = max(nflags, batch_args(d.args, c * d.nprob + i).nwg * kFlagStride);
-  init_problem(a, a.m0, nflags);
+  init_problem(a, a.m0, nflags, 0, 1);
   if (i == 0) {
     for (int c = kp_tid(); c < d.nclass; c += blockDim.x)
       d.queue[c] = (unsigned long long)(d.class_first[c + 1] - d.class_first[c]) << 32;
@@ -393,8 +577,9 @@ __global__ __launch_bounds__(256) void k_batch_init(BatchDesc d) {
 
 template <typename TB, bool MS>
 __global__ __launch_bounds__(kThreads) void k_batch(BatchDesc d) {
-  __shared__ __attribute__((aligned(16))) double lds[kLdsDoubles];
-  __shared__ LeadLds lead;
+  constexpr bool BLK = sizeof(TB) == 8 && !MS;   // block steps, as in k_blk
+  __shared__ __attribute__((aligned(16))) double lds[BLK ? kLdsDoublesB : kLdsDoubles];
+  __shared__ std::conditional_t<BLK, LeadB, LeadLds> lead;
   __shared__ Ctl cur, nxt;
   __shared__ int ok, s_pi;
   __shared__ int kept;   // keep_xw is off in batched calls; never set
@@ -441,14 +626,22 @@ __global__ __launch_bounds__(kThreads) void k_batch(BatchDesc d) {
       cur = ctl_unpack((unsigned)w);
       ok = aborted(a) ? 0 : 1;
     }
-    if (wg_rank(a) == 0) load_tables(a, lead);
+    if (wg_rank(a) == 0) {
+      if constexpr (BLK)
+        load_tables_b(a, lead, false);
+      else
+        load_tables(a, lead);
+    }
     __syncthreads();
     unsigned k = s_k;
     for (;;) {
       __syncthreads();
       if (!ok || cur.phase == PH_DONE) break;
       ++k;
-      run_phase<TB, MS>(a, lds, lead, cur, nxt, ok, kept, k);
+      if constexpr (BLK)
+        run_phase_block<kR>(a, lds, lead, cur, nxt, ok, k);
+      else
+        run_phase<TB, MS>(a, lds, lead, cur, nxt, ok, kept, k);
     }
     __syncthreads();
     if (!ok) break;   // a bounded wait gave up: this team stops
@@ -698,10 +891,11 @@ __global__ __launch_bounds__(kThreads) void k_expm_test(Args a, int m, double ta
 }
 
 // Workspace of the allocation-free entry point (kp_phi_combo_noalloc): one
-// array per GPU, held by the loaded code object until the process ends.  Host
+// array per GPU, 32 MiB above KP_NOALLOC_BYTES for the halo rows and partial
+// sums of the block steps' finer partition (noalloc_need), held by the loaded code object until the process ends.  Host
 // code reaches it only through the address hipGetSymbolAddress returns for
 // the current device (the array's name in host code is a host-side stand-in).
-constexpr size_t kScratchBytes = (size_t)KP_NOALLOC_BYTES;
+constexpr size_t kScratchBytes = (size_t)KP_NOALLOC_BYTES + ((size_t)32 << 20);
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 }  // namespace kp
@@ -741,7 +935,7 @@ struct kp_ctx {
   size_t aux_bytes = 0;
   double* integ = nullptr;         // integrators: state and right-hand-side history, columns
   size_t integ_bytes = 0;
-  int occ[4] = {-1, -1, -1, -1};
+  int occ[5] = {-1, -1, -1, -1, -1};
   Args last{};
   int have_begin = 0;
   int arn_target = 0;
@@ -866,31 +1060,49 @@ int build_args(const kp_ctx* ctx, const kp_op* A, const double* B, int p, int64_
                            : (cfg.tau_init > 0.0 ? std::min(cfg.tau_init, h) : h);
   r.stop_j = INT_MAX;
   r.basis_f32 = cfg.basis_dtype == KP_BASIS_F32 ? 1 : 0;
+  r.block = (!r.basis_f32 && !kp::orth_multi_sync(r.orth)) ? 1 : 0;
+  r.bstride = 4 * m_max + 8;
+  r.tile_r = kp::kR;
   r.h = h;
   r.tol = tol > 0.0 ? tol : 1.0;
   r.delta = cfg.fallback_delta == 0.0 ? 1e-10 : (cfg.fallback_delta < 0.0 ? 0.0 : cfg.fallback_delta);
   r.eps_bd = cfg.breakdown_eps == 0.0 ? 1e-12 : cfg.breakdown_eps;
+  // two steps per reduction: H-GSMGS only (see kp_block.h); a fallback
+  // threshold above the pair guard takes the exact norm at every step, so
+  // there is no estimate to divide a first vector by
+  r.pairs = (r.block && r.orth == KP_ORTH_H_GSMGS && r.delta <= kp::kGuard) ? 1 : 0;
   *a = r;
   return KP_OK;
 }
 
-template <typename TB, bool MS>
-int occupancy(kp_ctx* ctx, int which) {
+int occupancy(kp_ctx* ctx, const void* kernel, int which) {
   if (ctx->occ[which] < 0) {
     int occ = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &occ, reinterpret_cast<const void*>(&kp::k_run<TB, MS>), kp::kThreads, 0);
+    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, kp::kThreads, 0);
     if (e != hipSuccess) return -1;
     ctx->occ[which] = occ;
   }
   return ctx->occ[which];
 }
 
-// Co-resident workgroups per CU of the kernel that runs a's process.
-int kernel_occupancy(kp_ctx* ctx, const Args& a) {
+// The persistent kernel that runs a's process.
+const void* run_kernel(const Args& a) {
+  if (a.block)
+    return a.tile_r == 1 ? reinterpret_cast<const void*>(&kp::k_blk<1>)
+                         : reinterpret_cast<const void*>(&kp::k_blk<kp::kR>);
   if (kp::orth_multi_sync(a.orth))
-    return a.basis_f32 ? occupancy<float, true>(ctx, 3) : occupancy<double, true>(ctx, 2);
-  return a.basis_f32 ? occupancy<float, false>(ctx, 1) : occupancy<double, false>(ctx, 0);
+    return a.basis_f32 ? reinterpret_cast<const void*>(&kp::k_run<float, true>)
+                       : reinterpret_cast<const void*>(&kp::k_run<double, true>);
+  return reinterpret_cast<const void*>(&kp::k_run<float, false>);
+}
+
+// Co-resident workgroups per CU of that kernel (block steps: of both tile
+// sizes, since the geometry, which needs it, chooses between them).
+int kernel_occupancy(kp_ctx* ctx, const Args& a) {
+  if (!a.block)
+    return occupancy(ctx, run_kernel(a), kp::orth_multi_sync(a.orth) ? (a.basis_f32 ? 3 : 2) : 1);
+  return std::min(occupancy(ctx, reinterpret_cast<const void*>(&kp::k_blk<kp::kR>), 0),
+                  occupancy(ctx, reinterpret_cast<const void*>(&kp::k_blk<1>), 4));
 }
 
 int device_setup(kp_ctx* ctx) {
@@ -939,7 +1151,15 @@ int grow(kp_ctx* ctx, void** p, size_t* have, size_t need) {
 // count whose rows fit one sub-tile is taken instead when the co-resident
 // workgroups still cover the grid with it: x_j and w then stay on chip
 // between the passes (keep_xw below).
-void geometry(int ncu_slots, int rows_cfg, Args* a) {
+//
+// Block steps (kp_block.h) spread a grid further: down to kSpread elements
+// per workgroup, since below one workgroup per CU a finer split takes the
+// streaming time down and adds only partial rows to the reduction.
+// spread = false: the partition without that rule (kp_phi_combo_noalloc's
+// capacity is stated for it).
+constexpr int64_t kSpread = 512;
+
+void geometry(int ncu_slots, int rows_cfg, Args* a, bool spread = true) {
   const int64_t per_wg_min = (int64_t)kp::kThreads * kp::kR * 2;
   int64_t rows = (per_wg_min + (int64_t)a->nx * a->nplanes - 1) / ((int64_t)a->nx * a->nplanes);
   if (rows_cfg <= 0 && a->nplanes == 1 && 2 * (int64_t)a->nx <= per_wg_min &&
@@ -947,6 +1167,9 @@ void geometry(int ncu_slots, int rows_cfg, Args* a) {
     int64_t rk = per_wg_min / a->nx;
     if ((a->nx & 1) && (rk & 1) && rk < a->ny) --rk;
     if (rk >= 1 && rk < rows && (a->ny + rk - 1) / rk <= ncu_slots) rows = rk;
+  }
+  if (rows_cfg <= 0 && a->block && spread) {
+    rows = (kSpread + (int64_t)a->nx * a->nplanes - 1) / ((int64_t)a->nx * a->nplanes);
   }
   if (rows_cfg > 0) rows = rows_cfg;
   rows = std::max<int64_t>(rows, (a->ny + ncu_slots - 1) / ncu_slots);
@@ -965,7 +1188,19 @@ void geometry(int ncu_slots, int rows_cfg, Args* a) {
                 2 * (int64_t)a->nx <= 2 * (int64_t)kp::kThreads * kp::kR &&
                 !kp::orth_multi_sync(a->orth) && 4 * kp::kR * kp::kThreads <= kp::kHaloCap)
                    ? 1 : 0;
+  if (a->block) a->tile_r = rows * a->nx <= 2 * (int64_t)kp::kThreads ? 1 : kp::kR;
 }
+
+// Partial sums (doubles) of nwg workgroups: the counted buffer, the two step
+// buffers and, for block steps, the two buffers of their sums.
+size_t part_doubles(const Args& a, int nwg) {
+  return (size_t)nwg * kp::kCStride +
+         2 * (a.block ? (size_t)(nwg + 1) * a.bstride : (size_t)nwg * kp::kKStride);
+}
+
+// Halo rows (doubles) of nwg workgroups, one buffer; pairs need a second one.
+size_t halo_doubles(const Args& a, int nwg) { return (size_t)nwg * a.nplanes * 2 * a.nx; }
+int halo_buffers(const Args& a) { return a.pairs ? 2 : 1; }
 
 // Allocate the workspace for a problem and finish Args.
 int prepare(kp_ctx* ctx, Args* a) {
@@ -984,10 +1219,10 @@ int prepare(kp_ctx* ctx, Args* a) {
   }
   geometry(ctx->ncu * occ, ctx->cfg.rows_per_wg, a);
   if ((rc = grow(ctx, reinterpret_cast<void**>(&ctx->part), &ctx->part_bytes,
-                 (size_t)kp::kPartBuffers * a->nwg * kp::kKStride * sizeof(double))))
+                 part_doubles(*a, a->nwg) * sizeof(double))))
     return rc;
   if ((rc = grow(ctx, reinterpret_cast<void**>(&ctx->hx), &ctx->hx_bytes,
-                 (size_t)a->nwg * a->nplanes * 2 * a->nx * sizeof(double))))
+                 halo_buffers(*a) * halo_doubles(*a, a->nwg) * sizeof(double))))
     return rc;
   if ((rc = grow(ctx, reinterpret_cast<void**>(&ctx->flags), &ctx->flags_bytes,
                  (size_t)a->nwg * kp::kFlagStride * sizeof(unsigned))))
@@ -1003,6 +1238,7 @@ int prepare(kp_ctx* ctx, Args* a) {
   a->u = ctx->u;
   a->part = ctx->part;
   a->hx = ctx->hx;
+  a->hx2 = ctx->hx + halo_doubles(*a, a->nwg);
   a->tx = ctx->tx;
   a->flags = ctx->flags;
   a->sync = ctx->sync;
@@ -1032,8 +1268,8 @@ size_t carve(Args* a, char* base) {
   char* sync = take(64);
   char* ex = take(sizeof(double) * kp::kExSlots * kp::kNmPad * kp::kNmPad);
   char* tx = take(sizeof(double) * kp::kTailPad);
-  char* part = take((size_t)kp::kPartBuffers * a->nwg * kp::kKStride * sizeof(double));
-  char* hx = take((size_t)a->nwg * a->nplanes * 2 * a->nx * sizeof(double));
+  char* part = take(part_doubles(*a, a->nwg) * sizeof(double));
+  char* hx = take(halo_buffers(*a) * halo_doubles(*a, a->nwg) * sizeof(double));
   char* flags = take((size_t)a->nwg * kp::kFlagStride * sizeof(unsigned));
   char* u = take((size_t)a->ld * sizeof(double));
   char* V = take((size_t)a->ld * (size_t)(a->m_max + 2) * esz);
@@ -1045,6 +1281,7 @@ size_t carve(Args* a, char* base) {
     a->tx = reinterpret_cast<double*>(tx);
     a->part = reinterpret_cast<double*>(part);
     a->hx = reinterpret_cast<double*>(hx);
+    a->hx2 = a->hx + halo_doubles(*a, a->nwg);
     a->flags = reinterpret_cast<unsigned*>(flags);
     a->u = reinterpret_cast<double*>(u);
     a->V = V;
@@ -1052,26 +1289,37 @@ size_t carve(Args* a, char* base) {
   return off;
 }
 
-template <typename TB, bool MS>
-int launch_run(kp_ctx* ctx, Args a, int arnoldi_only) {
+// Bytes by which kp_phi_combo_noalloc's capacity is counted: the workspace on
+// the partition of at least 4096 elements per workgroup, with three partial
+// rows and one halo buffer.  The block steps' own layout takes up to 32 N
+// bytes more of halo rows, which the array holds beyond KP_NOALLOC_BYTES, so
+// the problems accepted do not depend on the partition.
+size_t noalloc_need(int ncu_slots, int rows_cfg, const Args& a) {
+  Args g = a;
+  geometry(ncu_slots, rows_cfg, &g, false);
+  const size_t esz = a.basis_f32 ? sizeof(float) : sizeof(double);
+  const size_t parts[] = {sizeof(State), sizeof(Pub), 64,
+                          sizeof(double) * kp::kExSlots * kp::kNmPad * kp::kNmPad,
+                          sizeof(double) * kp::kTailPad,
+                          (size_t)3 * g.nwg * kp::kKStride * sizeof(double),
+                          halo_doubles(g, g.nwg) * sizeof(double),
+                          (size_t)g.nwg * kp::kFlagStride * sizeof(unsigned),
+                          (size_t)g.ld * sizeof(double),
+                          (size_t)g.ld * (size_t)(g.m_max + 2) * esz};
+  size_t off = 0;
+  for (size_t b : parts) off += (b + 255) / 256 * 256;
+  return off;
+}
+
+int launch(kp_ctx* ctx, Args a, int arnoldi_only) {
   void* args[] = {&a, &arnoldi_only};
-  KP_HIP(ctx, hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&kp::k_run<TB, MS>),
-                                         dim3(a.nwg), dim3(kp::kThreads), args, 0,
+  KP_HIP(ctx, hipLaunchCooperativeKernel(run_kernel(a), dim3(a.nwg), dim3(kp::kThreads), args, 0,
                                          ctx->stream));
   return KP_OK;
 }
 
-int launch(kp_ctx* ctx, const Args& a, int arnoldi_only) {
-  if (kp::orth_multi_sync(a.orth))
-    return a.basis_f32 ? launch_run<float, true>(ctx, a, arnoldi_only)
-                       : launch_run<double, true>(ctx, a, arnoldi_only);
-  return a.basis_f32 ? launch_run<float, false>(ctx, a, arnoldi_only)
-                     : launch_run<double, false>(ctx, a, arnoldi_only);
-}
-
-
 int launch_init(kp_ctx* ctx, const Args& a, int m_target) {
-  hipLaunchKernelGGL(kp::k_init, dim3(1), dim3(256), 0, ctx->stream, a, m_target);
+  hipLaunchKernelGGL(kp::k_init, dim3((a.nwg + 7) / 8), dim3(256), 0, ctx->stream, a, m_target);
   KP_HIP(ctx, hipGetLastError());
   return KP_OK;
 }
@@ -1231,8 +1479,8 @@ ProbBufs prob_bufs(const Args& a, int nwg_max) {
   ProbBufs r;
   r.v = align256((size_t)a.ld * (a.m_max + 2) * esz);
   r.u = align256((size_t)a.ld * sizeof(double));
-  r.part = align256((size_t)kp::kPartBuffers * nwg_max * kp::kKStride * sizeof(double));
-  r.hx = align256((size_t)nwg_max * a.nplanes * 2 * a.nx * sizeof(double));
+  r.part = align256(part_doubles(a, nwg_max) * sizeof(double));
+  r.hx = align256(halo_buffers(a) * halo_doubles(a, nwg_max) * sizeof(double));
   r.ex = align256(sizeof(double) * kp::kExSlots * kp::kNmPad * kp::kNmPad);
   r.tx = align256(sizeof(double) * kp::kTailPad);
   return r;
@@ -1401,6 +1649,7 @@ void batch_fill_args(BatchCache* b, const std::vector<Args>& as, int64_t wait_ti
     a.u = reinterpret_cast<double*>(base + z.v);
     a.part = reinterpret_cast<double*>(base + z.v + z.u);
     a.hx = reinterpret_cast<double*>(base + z.v + z.u + z.part);
+    a.hx2 = a.hx + halo_doubles(a, b->prob_nwg[i]);
     a.ex = reinterpret_cast<double*>(base + z.v + z.u + z.part + z.hx);
     a.tx = reinterpret_cast<double*>(base + z.v + z.u + z.part + z.hx + z.ex);
     a.st = b->st + i;
@@ -1598,11 +1847,11 @@ int kp_phi_combo_noalloc(kp_ctx* ctx, const kp_op* A, const double* B, int32_t p
     return KP_EHIP;
   }
   geometry(ctx->ncu * occ, ctx->cfg.rows_per_wg, &a);
-  const size_t need = carve(&a, nullptr);
-  if (need > kp::kScratchBytes) {
+  const size_t need = noalloc_need(ctx->ncu * occ, ctx->cfg.rows_per_wg, a);
+  if (need > (size_t)KP_NOALLOC_BYTES || carve(&a, nullptr) > kp::kScratchBytes) {
     snprintf(ctx->err, sizeof(ctx->err),
              "workspace of %zu bytes exceeds the static scratch of %zu bytes", need,
-             kp::kScratchBytes);
+             (size_t)KP_NOALLOC_BYTES);
     return KP_ETOOLARGE;
   }
   char* base = static_cast<char*>(scratch_address(ctx));
