@@ -45,7 +45,7 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0
 METRIC = "Arnoldi steps/s and phi_combo/s at N=1M,m=64; HBM GB/s vs peak; err vs FP64"
-KERNEL = "kp::k_blk<4>"
+KERNEL = "kp::k_blk<2>"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_run_allen_cahn_1024_traffic.txt")
 BATCH_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_batch_uneven_512_traffic.txt")
 FP32_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_run_fp32_basis_brusselator_2048_traffic.txt")
@@ -139,22 +139,23 @@ def basis_bytes_per_call(schedule, p, c, n, s):
 
 def block_vectors_per_call(schedule, p, c, keep):
     """Vector passes (each N float64) that a call of the float64 H-GSMGS form
-    moves: its kernel makes two Arnoldi steps per reduction, so a pass of
-    inner products and one of linear combinations over the basis serve both.
-    From the newest column j (0-based) the matvecs read p columns of B and c
-    fields (once: the second product finds them in cache), the inner products
-    the j older columns, the combination the columns 0..j, and it writes two
-    columns (one in a single last step).  keep: x_j, w1 and w2 stay in LDS;
-    otherwise x_j is read, w1 written, read and read again by the
-    combination, w2 written and read, and B and the fields read twice."""
+    moves: its kernel makes up to three Arnoldi steps per reduction, so a pass
+    of inner products and one of linear combinations over the basis serve all
+    of them.  A block of n steps from the newest column j (0-based): the
+    products read p columns of B and c fields (once: the later ones find them
+    in cache), the inner products the columns 0..j, the combination the same
+    again, and it writes n columns.  keep: x_j and the last two of the n
+    products stay in LDS (the first of three is written and read twice);
+    otherwise the products read x_j and each other, all of them are written
+    and read by the inner products and the combination, and B and the fields
+    are read each time."""
     total = (p + 1) + 1
     for _, m in schedule:
         total += 2                                     # column 0 from the state
-        for j in range(0, m, 2):
-            n = min(2, m - j)
-            total += 2 * j + 1 + p + c + n
-            if not keep:
-                total += 3 if n == 1 else 6 + p + c
+        for j in range(0, m, 3):
+            n = min(3, m - j)
+            total += 2 * (j + 1) + p + c + n
+            total += (3 if n == 3 else 0) if keep else 4 * n - 1 + (n - 1) * (p + c)
         total += m + 1
     return total + 1
 
@@ -289,9 +290,9 @@ def timeline_summary(T, rate=100e6):
     release seen, update done, halo flags seen and arrival, the last
     arrival, the leader's reduction after the last arrival, its serial step
     and release, and the whole step (release to release).  A phase that
-    makes two steps (the next phase's j says so) is one row and counts as
-    two; a process's first phase, which has no update, counts for its second
-    step only.  Other phases: count and mean duration by kind.  Also the
+    makes several steps (the next phase's j says so) is one row and counts
+    as that many; a process's first phase, which has no update, counts for
+    its later steps only.  Other phases: count and mean duration by kind.  Also the
     least-squares line of the phase duration in the step index j."""
     import numpy as np
     T = np.asarray(T, dtype=np.float64)
@@ -307,15 +308,15 @@ def timeline_summary(T, rate=100e6):
     codes = [int(T[k, 0, 4]) for k in live]
     for i, (a, b) in enumerate(zip(live[:-1], live[1:])):
         nxt = codes[i + 2] if i + 2 < len(live) else 0
-        pair = (codes[i + 1] // 1000 == 1 and nxt // 1000 in (1, 2)
-                and nxt % 1000 == codes[i + 1] % 1000 + 2)
+        n = (max(1, nxt % 1000 - codes[i + 1] % 1000)
+             if codes[i + 1] // 1000 == 1 and nxt // 1000 in (1, 2) else 1)
         code = int(T[b, 0, 4])
         ph, j = code // 1000, code % 1000
         t0 = T[a, 0, 7]
         dur = (T[b, 0, 7] - t0) * us
         w = T[b, others]
         if ph == 1 and j >= 1 and len(others) and w[:, 1].min() > 0:
-            made += 2 if pair else 1
+            made += n
             arr = T[b, owners, 3]
             steps.append([j, dur,
                           (np.median(w[:, 0]) - t0) * us,
@@ -327,7 +328,7 @@ def timeline_summary(T, rate=100e6):
                           (T[b, 0, 6] - T[b, 0, 5]) * us,
                           (T[b, 0, 7] - T[b, 0, 6]) * us])
         else:
-            made += 1 if ph == 1 and pair else 0
+            made += n - 1 if ph == 1 else 0
             other.setdefault(names.get(ph, str(ph)), []).append(dur)
     cols = ["j", "step_us", "release_seen_us", "update_done_us", "halo_flags_us",
             "arrival_median_us", "arrival_last_us", "reduction_after_last_us",
@@ -581,7 +582,7 @@ def main():
                    "us_per_arnoldi_step": round(1e3 * fms / 64, 2),
                    "arnoldi_steps_per_s": round(64 / (fms * 1e-3), 1),
                    "grid_syncs_per_substep": (
-                       33 if orth == "h-gsmgs" and args.basis == "f64"
+                       23 if orth == "h-gsmgs" and args.basis == "f64"
                        else sum(syncs_per_step(jj, orth) for jj in range(64))
                        + (1 if orth not in ("mgs", "iocgs") else 0)),
                    "achieved_GBps": round(fvec * 8.0 * N / (fms * 1e-3) / 1e9, 1),

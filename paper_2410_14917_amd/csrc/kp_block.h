@@ -1,45 +1,45 @@
-// The one-reduction Arnoldi process with a float64 basis, two steps per
+// The one-reduction Arnoldi process with a float64 basis, up to kS = 3 steps per
 // grid-wide reduction (block steps): streaming passes and the leader's scalar
 // work of kernels k_blk and k_batch<double, false>.
 //
 // A step of Algorithm 4 reads the basis twice (inner products, then the
-// projection) and synchronises the grid once.  Both costs are halved by taking
-// two Krylov vectors from one reduction: with x the newest column,
-//     w1 = Atilde x,  w2 = Atilde w1,
+// projection) and synchronises the grid once.  Both costs are shared by kS
+// Krylov vectors from one reduction: with x_j the newest column and theta a
+// shift (the last diagonal entry of H, which keeps the w_k apart),
+//     w_1 = Atilde x_j,  w_{k+1} = (Atilde - theta) w_k,
 // one pass over the basis forms the inner products of every column with the
-// unmeasured columns and with w1 and w2, and one pass forms the two new
-// columns
-//     y1 = w1 - U h,  y2 = w2 - U q,          h = T U'w1, q = T U'w2,
-//     x_{j+1} = y1 / g1,  x_{j+2} = (y2 - e y1) / g2,
-//     e = <y1, y2> / <y1, y1>,  g2^2 = <y2, y2> - e <y1, y2>,
-// with T the GSMGS correction of Algorithm 7 over all measured columns and
-// the products of the y formed from those of the w (<y1, y2> = <w1, w2> -
-// (U'w1)' q).  With A U_{<j} = U H_{<j} (the columns made before), the two
-// new columns of the Hessenberg matrix are exact combinations,
-//     A u_j     = U h + g1 x_{j+1},
-//     A x_{j+1} = [U (q - H_{<j} h_{<j} - h_j h) + (e - h_j) y1 + g2 x_{j+2}] / g1,
-// the same H as two single steps to rounding (Krylov dimension 64 on the
-// benchmark operators: 3e-14 against 2e-14 relative, both against modified
-// Gram-Schmidt).  The two new columns are unmeasured: their norms and
-// products with the older columns come with the next reduction (the lagged
-// norms of Algorithm 4, for two columns).  Where w1 or w2 lies almost inside
-// the span already there (guard kGuard on the squared norms), only x_{j+1} is
-// made and the process goes on in single steps.  The forms H-CWY and H-NCWY
-// always take single steps: their one-sided corrections do not remove the
-// measured loss of orthogonality to first order, which a pair needs.
+// unmeasured columns and with the w_k, and one pass forms the new columns
+//     [x_{j+1} .. x_{j+s}] = (W - U C) R^{-1},  C = T U'W,  R'R = W'W - (U'W)'C
+// (R upper triangular), with T the GSMGS correction of Algorithm 7 over all
+// measured columns.  The Hessenberg columns are exact combinations: with
+// Atilde w_k = w_{k+1} + theta w_k and Atilde U_{<j} = U H_{<j} (the columns
+// made before),
+//     Atilde u_j = U c_1 + X R e_1,
+//     Atilde (W - U C)_k = U (c_{k+1} + theta c_k - H_{<j} c_k - c_{kj} c_1)
+//                          + X (R_{k+1} + theta R_k - c_{kj} R_1),
+// times R^{-1}: the same H as single steps to rounding (Krylov dimension 64 on
+// the benchmark operators: 3e-14 to 7e-14 relative, single steps 2e-14 to 4e-14,
+// both against modified Gram-Schmidt; loss of orthogonality 2e-13.  Four
+// steps with the shift lose 4e-12, and two steps without it what three lose
+// with it).  The new columns are unmeasured: their norms and products come
+// with the next reduction (the lagged norms of Algorithm 4, for s columns).
+// Where a w_k lies almost inside the span already there (guard kGuard on the
+// squared norms), the columns before it are made and the next block starts
+// there; kMaxShort blocks in a row that made one step end the attempts.  The forms H-CWY and H-NCWY always take single steps: their
+// one-sided corrections do not remove the measured loss of orthogonality to
+// first order, which a block needs.
 //
 // What bounds it: HBM (or Infinity Cache) bytes of the basis at large grids,
-// the latency chain of a step (release, coefficients, halo flags, partial
-// sums, scalar work) at small ones.  R element pairs per thread and sub-tile:
+// the latency chain of a phase (release, coefficients, halo flags, partial
+// sums, scalar work) at small ones.  A sub-tile is R element pairs per thread:
 // a workgroup of few elements takes R = 1, with more columns in flight per
 // thread for the same registers, instead of lanes that repeat the last pair.
 //
-// Measured against single steps on the partition of >= 4096 elements per
-// workgroup (one call): 64 x 64, m = 40 fixed 1576 -> 708 us; 256^2 adaptive
-// (tol 1e-8, m <= 48) 10.48 -> 5.16 ms; 1024^2 Allen-Cahn benchmark call 93.7 ->
-// 59.5 ms; 2 x 1000 x 1200 Brusselator 102.3 -> 66.8 ms; 512 uneven problems in
-// one launch 1333 -> 841 ms.  H-CWY, which takes single steps here, gains from
-// the partition alone (501 x 300: 13.4 -> 9.6 ms).
+// Measured (one call; single steps on workgroups of >= 4096 elements, then two
+// steps per reduction, then three): 64 x 64, m = 40 fixed 1576, 708, 622 us;
+// 256^2 adaptive (tol 1e-8, m <= 48) 10.48, 5.16, 4.40 ms; 1024^2 Allen-Cahn
+// benchmark call 93.7, 59.5, 51.3 ms; 2 x 1000 x 1200 Brusselator 102.3, 66.8,
+// 49.8 ms; 512 uneven problems in one launch 1333, 841, 603 ms.
 #pragma once
 
 #include "kp_leader.h"
@@ -47,27 +47,42 @@
 
 namespace kp {
 
-constexpr int kBSlots = 4 * kMMax + 8;   // LDS stride of a wave's sums: 4 per column, 10 products of the new vectors
-constexpr double kGuard = 1e-4;          // a pair needs ||y||^2 > kGuard ||w||^2 for both vectors
-constexpr int kCoefLd = kMMax + 4;       // coefficients of one new column: basis columns, then w1, w2
+constexpr int kS = 3;                        // steps per reduction at most
+constexpr int kNv = 2 * kS;                  // vectors of its products: kS - 1 unmeasured columns, x, kS new ones
+constexpr int kGram = kNv * (kNv + 1) / 2;   // products among them
+constexpr int kBSlots = kNv * kMMax + 24;    // LDS stride of a wave's sums
+constexpr double kGuard = 1e-4;              // a new vector needs ||y||^2 > kGuard ||w||^2
+constexpr int kMaxShort = 3;                 // blocks in a row that made one step: then single steps
+constexpr double kSmallL = 1e-9;             // below it the correction's second order is under rounding
+constexpr int kCoefLd = kMMax + 4;           // coefficients of one new column: basis columns, then the w_k
 // Workgroups whose partial rows the leader reads itself; above, each quad of
 // slots is summed over the rows by one workgroup first (reduce_quads).
 constexpr int kDirectRows = 16;
 
+// Slot of the product of block vectors p <= q (0 .. kS-2 unmeasured columns,
+// kS-1 x, then w_1 ..) after the column slots.
+__device__ constexpr int gram_at(int p, int q) { return p * kNv - p * (p - 1) / 2 + (q - p); }
+__device__ inline int block_slots(int jo) { return kNv * jo + kGram + 1; }   // (even)
+
+// Packed upper Hessenberg matrix: column k holds its k + 2 entries.
+__device__ inline int hcol(int k) { return k * (k + 3) / 2; }
+struct HessPacked {
+  const double* p;
+  __device__ double operator()(int i, int k) const { return p[hcol(k) + i]; }
+};
+
 // What the leader's serial work reads, in LDS for the whole launch.
 struct LeadB {
-  // (row r, column k) of M^{-1} = (I + L)^{-1} at tab[k * kTabLd + r], r >= k,
-  // and of L at tab[r * kTabLd + k], r > k: the two triangles of one table
-  double tab[kMMax * kTabLd + 8];
-  double H[kLdh * kMMax + 8];      // Hessenberg, column-major
+  double tab[kMMax * kTabLd];      // <u_r, u_k> at [r * kTabLd + k], r != k (L + L')
+  double H[kMMax * (kMMax + 3) / 2 + 8];   // Hessenberg, packed (hcol)
   double sigma[kMMax + 8];         // unit scale of column i
-  double gamma[kMMax + 8];         // divisor applied to column i + 1
-  double wn2[kMMax + 8];           // ||A u_j||^2
-  double h[kMMax + 8], q[kMMax + 8];   // projections of w1, w2 (last block step)
-  double rp[kMMax + 8];            // raw second Hessenberg column of the last pair
-  double beta, e, g1;
+  double c[kS][kMMax + 8];         // projections C of the last block
+  double rp[kS - 1][kMMax + 8];    // raw Hessenberg columns of its later vectors: rows of U,
+  double hx[kS - 1][kS + 1];       // and rows of X
+  double rr[6], ri[6];             // R and R^{-1}: 00 01 02 11 12 22
+  double beta, wn2, theta, theta_used;
   int fallback_cur, m_target, breakdown, n_fallback, arnoldi_steps, onchip;
-  int nopair, pend, post;
+  int nopair, big, pend, post;
 };
 
 __device__ inline void load_tables_b(const Args& a, LeadB& L, bool resume) {
@@ -75,25 +90,27 @@ __device__ inline void load_tables_b(const Args& a, LeadB& L, bool resume) {
   if (resume) {
     for (int idx = kp_tid(); idx < kMMax * kMMax; idx += kThreads) {
       const int k = idx / kMMax, r = idx - k * kMMax;
-      if (r >= k) L.tab[k * kTabLd + r] = st->Minv[(int64_t)k * kLdt + r];
-      if (r > k) L.tab[r * kTabLd + k] = st->Lm[(int64_t)k * kLdt + r];
+      if (r > k) L.tab[k * kTabLd + r] = L.tab[r * kTabLd + k] = st->Lm[(int64_t)k * kLdt + r];
     }
-    for (int idx = kp_tid(); idx < kLdh * kMMax; idx += kThreads) L.H[idx] = st->H[idx];
-    for (int i = kp_tid(); i < kMMax + 2; i += kThreads) {
-      L.sigma[i] = st->sigma[i];
-      L.gamma[i] = st->gamma[i];
-      L.wn2[i] = st->wn2[i];
+    for (int idx = kp_tid(); idx < kLdh * kMMax; idx += kThreads) {
+      const int k = idx / kLdh, r = idx - k * kLdh;
+      if (r <= k + 1) L.H[hcol(k) + r] = st->H[idx];
     }
+    for (int i = kp_tid(); i < kMMax + 2; i += kThreads) L.sigma[i] = st->sigma[i];
   }
   if (kp_tid() == 0) {
     L.beta = st->beta;
+    L.wn2 = st->wn2[0];
+    L.rr[0] = st->gamma[0];
+    L.theta = st->theta;
     L.fallback_cur = st->fallback_cur;
     L.m_target = st->m_target;
     L.breakdown = st->breakdown;
     L.n_fallback = st->n_fallback;
     L.arnoldi_steps = st->arnoldi_steps;
     L.onchip = st->onchip;
-    L.nopair = st->nopair;
+    L.nopair = st->nopair >> 1;
+    L.big = st->nopair & 1;
     L.pend = 0;
     L.post = 0;
   }
@@ -108,38 +125,42 @@ __device__ inline void store_tables_b(const Args& a, const LeadB& L, bool all, i
   if (all) {
     for (int idx = kp_tid(); idx < kMMax * kMMax; idx += kThreads) {
       const int k = idx / kMMax, r = idx - k * kMMax;
-      st->Minv[(int64_t)k * kLdt + r] = (r >= k && r <= j) ? L.tab[k * kTabLd + r] : 0.0;
       st->Lm[(int64_t)k * kLdt + r] = (r > k && r <= j) ? L.tab[r * kTabLd + k] : 0.0;
     }
     for (int idx = kp_tid(); idx < kLdh * kMMax; idx += kThreads) {
       const int k = idx / kLdh, r = idx - k * kLdh;
-      st->H[idx] = (k < j && r <= k + 1) ? L.H[idx] : 0.0;
+      st->H[idx] = (k < j && r <= k + 1) ? L.H[hcol(k) + r] : 0.0;
     }
-    for (int i = kp_tid(); i < kMMax + 2; i += kThreads) {
-      st->sigma[i] = L.sigma[i];
-      st->gamma[i] = L.gamma[i];
-      st->wn2[i] = L.wn2[i];
-    }
+    for (int i = kp_tid(); i < kMMax + 2; i += kThreads) st->sigma[i] = L.sigma[i];
   }
   if (kp_tid() == 0) {
     st->beta = L.beta;
+    st->wn2[0] = L.wn2;
+    st->gamma[0] = L.rr[0];
+    st->theta = L.theta;
     st->fallback_cur = L.fallback_cur;
     st->breakdown = L.breakdown;
     st->n_fallback = L.n_fallback;
     st->arnoldi_steps = L.arnoldi_steps;
     st->onchip = L.onchip;
-    st->nopair = L.nopair;
+    st->nopair = (L.nopair << 1) | L.big;
   }
 }
 
-// Whether the step phase that nx opens makes two steps.
-__device__ inline int pair_ok(const Args& a, const LeadB& L, int j) {
-  return (a.pairs && !L.nopair && j + 2 <= min(L.m_target, a.stop_j)) ? 1 : 0;
+// Steps the phase that continues from column j makes.
+__device__ inline int block_steps(const Args& a, const LeadB& L, int j) {
+  if (!a.pairs || L.nopair >= kMaxShort) return 1;
+  return max(1, min(kS, min(L.m_target, a.stop_j) - j));
 }
-
-__device__ inline void new_process(LeadB& L) { L.nopair = 0; }
+// (The shift starts from 0: the last one of the substep before belongs to the
+// end of its process, and the first vectors of this one are smooth.)
+__device__ inline void new_process(const Args& a, LeadB& L) {
+  L.nopair = L.big = 0;
+  L.theta = 0.0;
+  cstore(&a.pub->shift, 0.0);
+}
 __device__ inline double beta_of(const Args&, const LeadB& L) { return L.beta; }
-__device__ inline const double* hess_of(const Args&, const LeadB& L) { return L.H; }
+__device__ inline HessPacked hess_of(const Args&, const LeadB& L) { return HessPacked{L.H}; }
 
 // ---- reductions of four values ------------------------------------------------
 
@@ -157,20 +178,31 @@ __device__ inline double add_perm32(double v) {
   const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
   return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
 }
+__device__ inline double wave_sum2(double v0, double v1) {   // lane l: value l & 1
+  const bool b0 = kp_tid() & 1;
+  double s = (b0 ? v1 : v0) + dpp_mov<0xB1>(b0 ? v0 : v1);   // quad_perm [1,0,3,2]
+  s += dpp_mov<0x4E>(s);                                     // quad_perm [2,3,0,1]
+  s += dpp_mov<0x124>(s);                                    // row_ror:4
+  s += dpp_mov<0x128>(s);                                    // row_ror:8
+  return add_perm32(add_perm16(s));
+}
 __device__ inline double wave_sum4(double v0, double v1, double v2, double v3) {
   const bool b0 = kp_tid() & 1, b1 = kp_tid() & 2;
-  const double k01 = b0 ? v1 : v0, p01 = b0 ? v0 : v1;
-  const double k23 = b0 ? v3 : v2, p23 = b0 ? v2 : v3;
-  const double s01 = k01 + dpp_mov<0xB1>(p01);   // quad_perm [1,0,3,2]
-  const double s23 = k23 + dpp_mov<0xB1>(p23);
-  const double k = b1 ? s23 : s01, p = b1 ? s01 : s23;
-  double s = k + dpp_mov<0x4E>(p);               // quad_perm [2,3,0,1]
-  s += dpp_mov<0x124>(s);                        // row_ror:4
-  s += dpp_mov<0x128>(s);                        // row_ror:8
+  const double s01 = (b0 ? v1 : v0) + dpp_mov<0xB1>(b0 ? v0 : v1);
+  const double s23 = (b0 ? v3 : v2) + dpp_mov<0xB1>(b0 ? v2 : v3);
+  double s = (b1 ? s23 : s01) + dpp_mov<0x4E>(b1 ? s01 : s23);
+  s += dpp_mov<0x124>(s);
+  s += dpp_mov<0x128>(s);
   return add_perm32(add_perm16(s));
 }
 
 // ---- passes ------------------------------------------------------------------
+//
+// A workgroup's on-chip region (keep_xw; one plane) is two LDS buffers of kR *
+// kThreads pairs.  A holds the vector the next product multiplies (x_j, then
+// the w_k but the last) and B its halo rows; after the last product B takes
+// the last w.  So at the next update the last w is in B, the one before it in
+// A, and a third one in memory (w_1 of three steps).
 
 template <int R>
 __device__ inline void tile_pairs_r(int64_t q0, int64_t pend, uint32_t* lo, bool* ok) {
@@ -181,20 +213,22 @@ __device__ inline void tile_pairs_r(int64_t q0, int64_t pend, uint32_t* lo, bool
     lo[r] = (uint32_t)(2 * ((ok[r] ? q : pend - 1) - q0));
   }
 }
+// Whether this wave has a pair in the sub-tile (a wave without one skips it).
+__device__ inline bool wave_in_tile(int64_t q0, int64_t pend) {
+  return __builtin_amdgcn_readfirstlane((int)(q0 + (kp_tid() & ~63) < pend)) != 0;
+}
 
-// Basis columns per chunk: the linear combinations keep about 20 pair loads
+// Basis columns per chunk: the linear combinations keep 16 to 20 pair loads
 // in flight per thread, the inner products two chunks of 8.
-template <int R> constexpr int kUpdCols = R == 4 ? 5 : (R == 2 ? 10 : 16);
+template <int R> constexpr int kUpdCols = R == 1 ? 16 : 20 / R;
 template <int R> constexpr int kDotCols = 8 / R;
 
-// acc1 += sum_i c1[i] V_i, acc2 += sum_i c2[i] V_i over the columns i0, i0 +
-// step, ... (nc of them; the columns past nc repeat the last one with
-// coefficient 0, so that all loads issue before the first multiply-add).
-// The coefficients are in LDS.
+// acc[l] += sum_i cf[l][i] V_i over the columns i0, i0 + step, ... (nc of
+// them; the columns past nc repeat the last one with coefficient 0, so that
+// all loads issue before the first multiply-add); cf in LDS, stride kCoefLd.
 template <int R, int C, int U>
 __device__ inline void axpy_block(const double* V, int64_t ld, int64_t t0, int i0, int step, int nc,
-                                  const double* c1, const double* c2, const uint32_t* lo,
-                                  double2* acc1, double2* acc2) {
+                                  const double* cf, const uint32_t* lo, double2 (&acc)[U][R]) {
   double2 v[C][R];
 #pragma unroll
   for (int c = 0; c < C; ++c) {
@@ -205,166 +239,183 @@ __device__ inline void axpy_block(const double* V, int64_t ld, int64_t t0, int i
 #pragma unroll
   for (int c = 0; c < C; ++c) {
     const int i = i0 + min(c, nc - 1) * step;
-    const double a1 = (c < nc) ? c1[i] : 0.0;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      acc1[r].x = __builtin_fma(a1, v[c][r].x, acc1[r].x);
-      acc1[r].y = __builtin_fma(a1, v[c][r].y, acc1[r].y);
-    }
-    if constexpr (U == 2) {
-      const double a2 = (c < nc) ? c2[i] : 0.0;
+    for (int l = 0; l < U; ++l) {
+      const double w = (c < nc) ? cf[l * kCoefLd + i] : 0.0;
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        acc2[r].x = __builtin_fma(a2, v[c][r].x, acc2[r].x);
-        acc2[r].y = __builtin_fma(a2, v[c][r].y, acc2[r].y);
+        acc[l][r].x = __builtin_fma(w, v[c][r].x, acc[l][r].x);
+        acc[l][r].y = __builtin_fma(w, v[c][r].y, acc[l][r].y);
       }
     }
   }
 }
 
-// Published coefficients to LDS (one coherent round trip).
+// Published coefficients (kS columns) and the shift to LDS: one coherent round
+// trip.
 __device__ inline void load_coefs(const Args& a, double* cf) {
   const int t = kp_tid();
-  if (t < kCoefLd) cf[t] = cload(&a.pub->coef[min(t, kMMax + 1)]);
-  if (t >= 128 && t < 128 + kCoefLd) cf[kCoefLd + t - 128] = cload(&a.pub->coef2[min(t - 128, kMMax + 1)]);
+  if (t < kS * kCoefLd) {
+    const int l = t / kCoefLd, i = t - l * kCoefLd;
+    cf[t] = cload(&a.pub->coefs[l][min(i, kMMax + 1)]);
+  } else if (t == kS * kCoefLd) {
+    cf[t] = cload(&a.pub->shift);
+  }
   __syncthreads();
 }
 
-// The tails (p <= 8 entries per column) of the U new columns: lane i of wave
-// 0 of workgroup 0 takes column i; the newest one is published.
+// The tails (p <= 8 entries per column) of the U new columns: lane i of the
+// last wave of workgroup 0 takes column i; the newest one is published.
 template <int U>
-__device__ inline void tail_update_b(const Args& a, double* V, int base, const double* cf,
-                                     double& ss1, double& ss2) {
-  const int t = kp_tid();
-  if (t >= 64) return;
+__device__ inline void tail_update_b(const Args& a, double* V, int nc, const double* cf, double (&ss)[U]) {
+  const int t = kp_tid() & 63;
   const int64_t T0 = a.tail_off, ld = a.ld;
-  const int nc = base + 1;
-  double p1[kPMax], p2[kPMax];
+  double p[U][kPMax];
 #pragma unroll
-  for (int k = 0; k < kPMax; ++k) p1[k] = p2[k] = 0.0;
+  for (int l = 0; l < U; ++l)
+#pragma unroll
+    for (int k = 0; k < kPMax; ++k) p[l][k] = 0.0;
 #pragma unroll
   for (int hh = 0; hh < 2; ++hh) {
     const int i = t + 64 * hh;
     const bool on = i < nc + U;
-    const double c1 = (i <= nc) ? cf[min(i, kCoefLd - 1)] : 0.0;
-    const double c2 = (U == 2 && on) ? cf[kCoefLd + min(i, kCoefLd - 1)] : 0.0;
     const double* vc = V + (int64_t)(on ? i : 0) * ld + T0;
+    double w[U];
+#pragma unroll
+    for (int l = 0; l < U; ++l) w[l] = (i <= nc + l) ? cf[l * kCoefLd + min(i, kCoefLd - 1)] : 0.0;
 #pragma unroll
     for (int k = 0; k < kPMax; ++k)
       if (k < a.p && on) {
         const double v = vc[k];
-        p1[k] += c1 * v;
-        if (U == 2) p2[k] += c2 * v;
+#pragma unroll
+        for (int l = 0; l < U; ++l) p[l][k] += w[l] * v;
       }
   }
 #pragma unroll
   for (int k = 0; k < kPMax; ++k) {
     if (k < a.p) {
-      const double y1 = wave_sum(p1[k]);
-      const double y2 = U == 2 ? wave_sum(p2[k]) : 0.0;
-      if (t == 0) {
-        V[(int64_t)nc * ld + T0 + k] = y1;
-        if (U == 2) V[(int64_t)(nc + 1) * ld + T0 + k] = y2;
-        cstore(a.tx + k, U == 2 ? y2 : y1);
-        ss1 += y1 * y1;
-        ss2 += y2 * y2;
+#pragma unroll
+      for (int l = 0; l < U; ++l) {
+        const double y = wave_sum(p[l][k]);
+        if (t == 0) {
+          V[(int64_t)(nc + l) * ld + T0 + k] = y;
+          if (l == U - 1) cstore(a.tx + k, y);
+          ss[l] += y * y;
+        }
       }
     }
   }
 }
 
-// The U pending columns (newest: column j) from the columns 0 .. j - U and
-// w1 (and w2), which sit in LDS (keep_xw) or in the columns they become.
-// cf: coefficients in LDS.  keep_xw also leaves x_j in the A half of the LDS
-// region.  The halo rows of x_j are published.  want_norm: partial slot 0 =
-// ||x_j||^2, slot 1 = ||x_{j-1}||^2 (U == 2).
+// The U pending columns j - U + 1 .. j (column l: weights cf[l] on the columns
+// 0 .. j - U, then on w_1 .. w_{l+1}), in place of the w_k.  pns: vectors the
+// previous phase made (>= U), which says where keep_xw left them.  keep_xw
+// also leaves x_j in A.  The halo rows of x_j are published.  want_norm:
+// partial slot l = the squared norm of new column l.
 template <int R, int U>
-__device__ __attribute__((always_inline)) inline void update_block(const Args& a, int j, const double* cf,
+__device__ __attribute__((always_inline)) inline void update_block(const Args& a, int j, int pns, const double* cf,
                                                                    double* hl, double* red, bool want_norm) {
   double* V = reinterpret_cast<double*>(a.V);
   const int64_t ld = a.ld;
-  const int base = j - U, nc = base + 1;
-  double* w1col = V + (int64_t)nc * ld;
-  double* w2col = V + (int64_t)(nc + 1) * ld;
-  const double* c1 = cf;
-  const double* c2 = cf + kCoefLd;
-  const double c1w = c1[nc], c2w1 = U == 2 ? c2[nc] : 0.0, c2w2 = U == 2 ? c2[nc + 1] : 0.0;
+  const int nc = j - U + 1;
   const bool keep = a.keep_xw != 0;
-  double2* A2 = reinterpret_cast<double2*>(hl);                       // w2, then x_j
-  const double2* B2 = reinterpret_cast<const double2*>(hl) + kR * kThreads;   // w1
+  double2* A2 = reinterpret_cast<double2*>(hl);
+  const double2* B2 = reinterpret_cast<const double2*>(hl) + kR * kThreads;
   const Rows o = own_rows(a);
-  double ss1 = 0.0, ss2 = 0.0;
+  double ss[U];
+#pragma unroll
+  for (int l = 0; l < U; ++l) ss[l] = 0.0;
+  if (wg_rank(a) == 0 && kp_tid() >= kThreads - 64) tail_update_b<U>(a, V, nc, cf, ss);
   constexpr int C = kUpdCols<R>;
   for (int si = 0; si < num_segs(a); ++si) {
     const Seg sg = seg_at(a, o, si);
-    const int64_t pend = (sg.end + 1) >> 1;
-    for (int64_t q0 = sg.beg >> 1; q0 < pend; q0 += (int64_t)kThreads * R) {
+    const int64_t pbeg = sg.beg >> 1, pend = (sg.end + 1) >> 1;
+    for (int64_t q0 = pbeg; q0 < pend; q0 += (int64_t)kThreads * R) {
+      if (!wave_in_tile(q0, pend)) break;
       const int64_t t0 = 2 * q0;
       uint32_t lo[R];
       bool ok[R];
       tile_pairs_r<R>(q0, pend, lo, ok);
-      double2 acc1[R], acc2[R];
+      double2 acc[U][R];
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const double2 w1 = keep ? B2[r * kThreads + kp_tid()] : Pair<double>::load(w1col + t0 + lo[r]);
-        acc1[r] = make_double2(c1w * w1.x, c1w * w1.y);
-        if constexpr (U == 2) {
-          const double2 w2 = keep ? A2[r * kThreads + kp_tid()] : Pair<double>::load(w2col + t0 + lo[r]);
-          acc2[r] = make_double2(__builtin_fma(c2w2, w2.x, c2w1 * w1.x),
-                                 __builtin_fma(c2w2, w2.y, c2w1 * w1.y));
+      for (int l = 0; l < U; ++l)
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc[l][r] = make_double2(0.0, 0.0);
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        const double* wcol = V + (int64_t)(nc + k) * ld + t0;
+        const int slot = (int)(q0 - pbeg) + kp_tid();
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          double2 w;
+          if (keep && k >= pns - 2)
+            w = (k == pns - 1) ? B2[slot + r * kThreads] : A2[slot + r * kThreads];
+          else
+            w = Pair<double>::load(wcol + lo[r]);
+#pragma unroll
+          for (int l = k; l < U; ++l) {
+            const double c = cf[l * kCoefLd + nc + k];
+            acc[l][r].x = __builtin_fma(c, w.x, acc[l][r].x);
+            acc[l][r].y = __builtin_fma(c, w.y, acc[l][r].y);
+          }
         }
       }
       for (int i1 = nc - 1; i1 >= 0; i1 -= C)
-        axpy_block<R, C, U>(V, ld, t0, i1, -1, min(C, i1 + 1), c1, c2, lo, acc1, acc2);
+        axpy_block<R, C, U>(V, ld, t0, i1, -1, min(C, i1 + 1), cf, lo, acc);
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         if (ok[r]) {
-          Pair<double>::store(w1col + t0 + lo[r], acc1[r].x, acc1[r].y);
-          ss1 += acc1[r].x * acc1[r].x + acc1[r].y * acc1[r].y;
-          double2 x = acc1[r];
-          if constexpr (U == 2) {
-            Pair<double>::store(w2col + t0 + lo[r], acc2[r].x, acc2[r].y);
-            ss2 += acc2[r].x * acc2[r].x + acc2[r].y * acc2[r].y;
-            x = acc2[r];
+#pragma unroll
+          for (int l = 0; l < U; ++l) {
+            Pair<double>::store(V + (int64_t)(nc + l) * ld + t0 + lo[r], acc[l][r].x, acc[l][r].y);
+            ss[l] += acc[l][r].x * acc[l][r].x + acc[l][r].y * acc[l][r].y;
           }
-          if (keep) A2[r * kThreads + kp_tid()] = x;
+          const double2 x = acc[U - 1][r];
+          if (keep) A2[(int)(q0 - pbeg) + kp_tid() + r * kThreads] = x;
           publish_pair(a, a.hx, sg, t0 + lo[r], x.x, x.y);
         }
       }
     }
   }
-  if (wg_rank(a) == 0) tail_update_b<U>(a, V, base, cf, ss1, ss2);
   if (want_norm) {
-    ss1 = block_sum(ss1, red);
-    if constexpr (U == 2) ss2 = block_sum(ss2, red);
-    if (kp_tid() == 0) {
-      double* pr = a.part + (int64_t)wg_rank(a) * kCStride;
-      cstore(pr, U == 2 ? ss2 : ss1);
-      cstore(pr + 1, U == 2 ? ss1 : 0.0);
+    double* pr = a.part + (int64_t)wg_rank(a) * kCStride;
+#pragma unroll
+    for (int l = 0; l < U; ++l) {
+      const double s = block_sum(ss[l], red);
+      if (kp_tid() == 0) cstore(pr + l, s);
     }
   }
 }
 
-// Products of C columns with xa, x, w1, w2: four sums per column, added to
-// the wave's row of sacc.
-template <int R, int C>
-__device__ inline void dots_block(const double2 (&v)[C][R], const double2* xa, const double2* xv,
-                                  const double2* w1, const double2* w2, int i0, int nc, double* sacc) {
-  const int lane = kp_tid() & 63, wv = kp_tid() >> 6;
+// Products of C columns with the block's vectors, added to the wave's row of
+// sacc.  FULL: all kNv; else only x and w_1 (a single step after a single
+// step), in the same slots.
+template <int R, int C, bool FULL>
+__device__ inline void dots_block(const double2 (&v)[C][R], const double2 (&b)[kNv][R], int i0, int nc,
+                                  double* sacc) {
+  const int lane = kp_tid() & 63;
+  double* srow = sacc + (kp_tid() >> 6) * kBSlots + kNv * i0;
 #pragma unroll
   for (int c = 0; c < C; ++c) {
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+    double s[kNv];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const double vx = v[c][r].x, vy = v[c][r].y;
-      s0 = __builtin_fma(vy, xa[r].y, __builtin_fma(vx, xa[r].x, s0));
-      s1 = __builtin_fma(vy, xv[r].y, __builtin_fma(vx, xv[r].x, s1));
-      s2 = __builtin_fma(vy, w1[r].y, __builtin_fma(vx, w1[r].x, s2));
-      s3 = __builtin_fma(vy, w2[r].y, __builtin_fma(vx, w2[r].x, s3));
+    for (int q = 0; q < kNv; ++q) {
+      s[q] = 0.0;
+      if (FULL || q == kS - 1 || q == kS) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+          s[q] = __builtin_fma(v[c][r].y, b[q][r].y, __builtin_fma(v[c][r].x, b[q][r].x, s[q]));
+      }
     }
     if (c < nc) {
-      const double s = wave_sum4(s0, s1, s2, s3);
-      if (lane < 4) sacc[wv * kBSlots + 4 * (i0 + c) + lane] += s;
+      if constexpr (FULL) {
+        const double s4 = wave_sum4(s[0], s[1], s[2], s[3]), s2 = wave_sum2(s[4], s[5]);
+        if (lane < 4) srow[kNv * c + lane] += s4;
+        if (lane < 2) srow[kNv * c + 4 + lane] += s2;
+      } else {
+        const double s2 = wave_sum2(s[kS - 1], s[kS]);
+        if (lane < 2) srow[kNv * c + kS - 1 + lane] += s2;
+      }
     }
   }
 }
@@ -380,290 +431,307 @@ __device__ inline void load_block(const double* V, int64_t ld, int64_t t0, int i
   }
 }
 
-// The older columns of one sub-tile (double-buffered chunks; the first one is
-// in flight in va already) and the products of the new vectors.
-template <int R>
-__device__ __attribute__((always_inline)) inline void tile_dots(
-    const double* V, int64_t ld, int64_t t0, int jo, const uint32_t* lo, const double2* xa,
-    const double2* xv, const double2* w1, const double2* w2, double2 (&va)[kDotCols<R>][R], double* sacc) {
+// The older columns of one sub-tile, double-buffered chunks (the first one is
+// in flight in va already).
+template <int R, bool FULL>
+__device__ __attribute__((always_inline)) inline void columns_block(
+    const double* V, int64_t ld, int64_t t0, int jo, const uint32_t* lo, const double2 (&b)[kNv][R],
+    double2 (&va)[kDotCols<R>][R], double* sacc) {
   constexpr int C = kDotCols<R>;
-  const int lane = kp_tid() & 63, wv = kp_tid() >> 6;
-  double g[10];
-#pragma unroll
-  for (int k = 0; k < 10; ++k) g[k] = 0.0;
-  auto acc = [](double s, const double2& p, const double2& q) {
-    return __builtin_fma(p.y, q.y, __builtin_fma(p.x, q.x, s));
-  };
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    g[0] = acc(g[0], xa[r], xa[r]);
-    g[1] = acc(g[1], xa[r], xv[r]);
-    g[2] = acc(g[2], xa[r], w1[r]);
-    g[3] = acc(g[3], xa[r], w2[r]);
-    g[4] = acc(g[4], xv[r], xv[r]);
-    g[5] = acc(g[5], xv[r], w1[r]);
-    g[6] = acc(g[6], xv[r], w2[r]);
-    g[7] = acc(g[7], w1[r], w1[r]);
-    g[8] = acc(g[8], w1[r], w2[r]);
-    g[9] = acc(g[9], w2[r], w2[r]);
-  }
-  {
-    double* srow = sacc + wv * kBSlots + 4 * jo;
-    const double s0 = wave_sum4(g[0], g[1], g[2], g[3]);
-    const double s1 = wave_sum4(g[4], g[5], g[6], g[7]);
-    const double s2 = wave_sum4(g[8], g[9], 0.0, 0.0);
-    if (lane < 4) {
-      srow[lane] += s0;
-      srow[4 + lane] += s1;
-      if (lane < 2) srow[8 + lane] += s2;
-    }
-  }
   double2 vb[C][R];
   for (int i0 = 0; i0 < jo; i0 += 2 * C) {
     const int i1 = i0 + C;
     if (i1 < jo) load_block<R, C>(V, ld, t0, i1, min(C, jo - i1), lo, vb);
-    dots_block<R, C>(va, xa, xv, w1, w2, i0, min(C, jo - i0), sacc);
+    dots_block<R, C, FULL>(va, b, i0, min(C, jo - i0), sacc);
     if (i1 >= jo) break;
     const int i2 = i1 + C;
     if (i2 < jo) load_block<R, C>(V, ld, t0, i2, min(C, jo - i2), lo, va);
-    dots_block<R, C>(vb, xa, xv, w1, w2, i1, min(C, jo - i1), sacc);
+    dots_block<R, C, FULL>(vb, b, i1, min(C, jo - i1), sacc);
   }
 }
 
-// Tail rows of the block step (wave 0 of workgroup 0): w1 = K x, w2 = K w1
-// (upward shifts within each block of pb entries), stored, and their share of
-// the products (column t by lane t; those of the new vectors by lane 0).
-__device__ inline void tail_block(const Args& a, int j, int na, int two, double* V, double* sacc) {
-  const int t = kp_tid();
-  if (t >= 64) return;
+// All products of one sub-tile.
+template <int R>
+__device__ __attribute__((always_inline)) inline void tile_dots(const double* V, int64_t ld, int64_t t0, int jo,
+                                                                bool full, const uint32_t* lo,
+                                                                const double2 (&b)[kNv][R],
+                                                                double2 (&va)[kDotCols<R>][R], double* sacc) {
+  const int lane = kp_tid() & 63;
+  {
+    double* srow = sacc + (kp_tid() >> 6) * kBSlots + kNv * jo;
+    double g[kGram + 3];
+#pragma unroll
+    for (int p = 0; p < kNv; ++p)
+#pragma unroll
+      for (int q = p; q < kNv; ++q) {
+        double s = 0.0;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+          s = __builtin_fma(b[p][r].y, b[q][r].y, __builtin_fma(b[p][r].x, b[q][r].x, s));
+        g[gram_at(p, q)] = s;
+      }
+#pragma unroll
+    for (int k = kGram; k < kGram + 3; ++k) g[k] = 0.0;
+#pragma unroll
+    for (int k = 0; k < kGram; k += 4) {
+      const double s = wave_sum4(g[k], g[k + 1], g[k + 2], g[k + 3]);
+      if (lane < 4 && k + lane < kGram) srow[k + lane] += s;
+    }
+  }
+  if (full)
+    columns_block<R, true>(V, ld, t0, jo, lo, b, va, sacc);
+  else
+    columns_block<R, false>(V, ld, t0, jo, lo, b, va, sacc);
+}
+
+// Tail rows of a block step (the last wave of workgroup 0, while the others
+// wait for their neighbours' halo rows): t_1 = K x, t_{k+1} = (K - theta) t_k
+// (upward shift within each block of pb entries), stored, and their products
+// (column t by lane t; those of the block's vectors by lane 0), in ts.
+__device__ inline void tail_block(const Args& a, int j, int na, int ns, double theta, double* ts) {
+  const int t = kp_tid() & 63;
+  double* V = reinterpret_cast<double*>(a.V);
   const int64_t T0 = a.tail_off, ld = a.ld;
   const int p = a.p, jo = j - na;
-  const double* xs = j == 0 ? a.u + T0 : V + (int64_t)j * ld + T0;
-  const double* as = V + (int64_t)(na ? j - 1 : 0) * ld + T0;
-  double xt[kPMax + 2], at[kPMax], w1[kPMax + 1], w2[kPMax];
+  double b[kNv][kPMax];
 #pragma unroll
-  for (int k = 0; k < kPMax + 2; ++k) xt[k] = (k < p) ? xs[k] : 0.0;
+  for (int q = 0; q < kS; ++q) {
+    const int col = j - (kS - 1) + q;        // column of vector q; x is q = kS - 1
+    const bool on = q == kS - 1 || col >= jo;
+    const double* src = (j == 0 ? a.u : V + (int64_t)max(col, 0) * ld) + T0;
 #pragma unroll
-  for (int k = 0; k < kPMax; ++k) at[k] = (na && k < p) ? as[k] : 0.0;
+    for (int k = 0; k < kPMax; ++k) b[q][k] = (on && k < p) ? src[k] : 0.0;
+  }
 #pragma unroll
-  for (int k = 0; k < kPMax + 1; ++k) w1[k] = (k < kPMax && tail_shift_in(a, k)) ? xt[k + 1] : 0.0;
-#pragma unroll
-  for (int k = 0; k < kPMax; ++k) w2[k] = (two && tail_shift_in(a, k)) ? w1[k + 1] : 0.0;
-  if (t == 0) {
+  for (int s = 0; s < kS; ++s) {
 #pragma unroll
     for (int k = 0; k < kPMax; ++k) {
-      if (k < p) {
-        if (j == 0) V[T0 + k] = xt[k];
-        V[(int64_t)(j + 1) * ld + T0 + k] = w1[k];
-        if (two) V[(int64_t)(j + 2) * ld + T0 + k] = w2[k];
-      }
+      const double up = (k + 1 < kPMax && tail_shift_in(a, k)) ? b[kS - 1 + s][(k + 1) % kPMax] : 0.0;
+      b[kS + s][k] = (s < ns) ? (s ? up - theta * b[kS - 1 + s][k] : up) : 0.0;
+      if (t == 0 && k < p && s < ns) V[(int64_t)(j + 1 + s) * ld + T0 + k] = b[kS + s][k];
     }
   }
+  if (t == 0 && j == 0)
+#pragma unroll
+    for (int k = 0; k < kPMax; ++k)
+      if (k < p) V[T0 + k] = b[kS - 1][k];
   if (t < jo) {
     const double* vc = V + (int64_t)t * ld + T0;
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+    double s[kNv];
 #pragma unroll
-    for (int k = 0; k < kPMax; ++k) {
+    for (int q = 0; q < kNv; ++q) s[q] = 0.0;
+#pragma unroll
+    for (int k = 0; k < kPMax; ++k)
       if (k < p) {
         const double v = vc[k];
-        s0 += v * at[k];
-        s1 += v * xt[k];
-        s2 += v * w1[k];
-        s3 += v * w2[k];
+#pragma unroll
+        for (int q = 0; q < kNv; ++q) s[q] += v * b[q][k];
       }
-    }
-    sacc[4 * t] += s0;
-    sacc[4 * t + 1] += s1;
-    sacc[4 * t + 2] += s2;
-    sacc[4 * t + 3] += s3;
+#pragma unroll
+    for (int q = 0; q < kNv; ++q) ts[kNv * t + q] = s[q];
   }
   if (t == 0) {
-    double* s = sacc + 4 * jo;
 #pragma unroll
-    for (int k = 0; k < kPMax; ++k) {
-      s[0] += at[k] * at[k];
-      s[1] += at[k] * xt[k];
-      s[2] += at[k] * w1[k];
-      s[3] += at[k] * w2[k];
-      s[4] += xt[k] * xt[k];
-      s[5] += xt[k] * w1[k];
-      s[6] += xt[k] * w2[k];
-      s[7] += w1[k] * w1[k];
-      s[8] += w1[k] * w2[k];
-      s[9] += w2[k] * w2[k];
-    }
+    for (int g = 0; g < kNv; ++g)
+#pragma unroll
+      for (int q = g; q < kNv; ++q) {
+        double s = 0.0;
+#pragma unroll
+        for (int k = 0; k < kPMax; ++k) s += b[g][k] * b[q][k];
+        ts[kNv * jo + gram_at(g, q)] = s;
+      }
+    ts[kNv * jo + kGram] = 0.0;
   }
 }
 
-// tc[c] = entry c + sh of the tail block of plane `plane`, over mu (zero past
-// the block): the weights of b_{pb-c} in A w for w = K^sh x.
-__device__ inline void tail_weights(const Args& a, int plane, int sh, double inv_mu, double* tc) {
+// Tail entries of x over mu, then of the next products: tt[c] multiplies
+// b_{pb-c} in Atilde v for the vector v whose tail it is.
+__device__ inline void tail_of_x(const Args& a, int plane, double inv_mu, double* tt) {
   const int toff = (a.tangent && plane == 1) ? a.pb : 0;
 #pragma unroll
+  for (int c = 0; c < kPMax; ++c) tt[c] = (c < a.pb) ? cload(a.tx + toff + c) * inv_mu : 0.0;
+}
+__device__ inline void tail_next(const Args& a, double shift, double* tt) {
+#pragma unroll
   for (int c = 0; c < kPMax; ++c)
-    tc[c] = (c + sh < a.pb) ? cload(a.tx + toff + c + sh) * inv_mu : 0.0;
+    tt[c] = ((c + 1 < kPMax && c + 1 < a.pb) ? tt[(c + 1) % kPMax] : 0.0) - shift * tt[c];
 }
 
-// Block step j: w1 = Atilde x_j, w2 = Atilde w1 (two) and the partial sums of
-// the reduction.  na: column j - 1 is unmeasured too.  upd: the update of this
-// phase has left x_j in LDS (keep_xw).  The rows of w1 the neighbours need
-// go through a second halo buffer and the same flags (value 2k + 1; the
-// update published 2k).  KEEP (keep_xw): one sub-tile; the LDS region holds
-// x_j in its A half while w1 is formed (the halo rows in B), then w1 in B (the
-// halo rows in A), and w2 in A at the end, for the next update.
-template <int R, bool KEEP, bool HL>
-__device__ __attribute__((always_inline)) inline void matvec_block(const Args& a, int j, int na, int two,
-                                                                   bool upd, double* sacc, double* hl,
-                                                                   unsigned k) {
+// The block step from column j: w_1 .. w_ns and the partial sums of the
+// reduction.  na: unmeasured columns before x_j.  upd: the update of this
+// phase has left x_j in A (keep_xw).  The rows of w_k the neighbours need go
+// through the two halo buffers in turn (a neighbour has read the rows of w_{k-1}
+// before it publishes w_k, which this workgroup has seen before it publishes
+// w_{k+1}) and the same flags (value 4k + e; the update published 4k).
+template <int R, int T, bool HL>
+__device__ __attribute__((always_inline)) inline void matvec_keep(const Args& a, int j, int na, int ns, bool upd,
+                                                                  double theta, double inv_mu, double* sacc,
+                                                                  double* hl, unsigned k) {
   double* V = reinterpret_cast<double*>(a.V);
   const int64_t ld = a.ld;
   const Rows o = own_rows(a);
   const int jo = j - na;
   constexpr int C = kDotCols<R>;
-  for (int t = kp_tid(); t < kWaves * kBSlots; t += kThreads) sacc[t] = 0.0;
-  const double inv_mu = cload(&a.pub->inv_mu);
+  double* lA = hl;
+  double* lB = hl + 2 * kR * kThreads;
+  double2* A2 = reinterpret_cast<double2*>(lA);
+  double2* B2 = reinterpret_cast<double2*>(lB);
   double* xcol = V + (int64_t)j * ld;
-  double* acol = V + (int64_t)(na ? j - 1 : 0) * ld;
-  double* w1col = V + (int64_t)(j + 1) * ld;
-  double* w2col = V + (int64_t)(j + 2) * ld;
-  double2 va[C][R];
-  if constexpr (KEEP) {
-    double* lA = hl;
-    double* lB = hl + 2 * kR * kThreads;
-    double2* A2 = reinterpret_cast<double2*>(lA);
-    double2* B2 = reinterpret_cast<double2*>(lB);
-    const Seg sg = seg_at(a, o, 0);
-    const int64_t pend = (sg.end + 1) >> 1, q0 = sg.beg >> 1, t0 = 2 * q0;
+  const Seg sg = seg_at(a, o, 0);
+  const int64_t pend = (sg.end + 1) >> 1, pbeg = sg.beg >> 1;
+  if (!upd) {
+    const double* src = j == 0 ? a.u : xcol;
+    for (int64_t q = pbeg + kp_tid(); q < pend; q += kThreads) {
+      const double2 v = Pair<double>::load(src + 2 * q);
+      A2[q - pbeg] = v;
+      if (j == 0) Pair<double>::store(xcol + 2 * q, v.x, v.y);
+    }
+  }
+  double tt[kPMax];
+  tail_of_x(a, 0, inv_mu, tt);
+  stage_halo<double>(a, a.hx, o, lB);
+  __syncthreads();
+  double2 w[T][R];
+  for (int s = 0; s < ns; ++s) {
+    const LdsX x{lA, sg.beg};
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      const int64_t q0 = pbeg + (int64_t)t * kThreads * R;
+      if (wave_in_tile(q0, pend)) {
+        uint32_t lo[R];
+        bool ok[R];
+        tile_pairs_r<R>(q0, pend, lo, ok);
+        aug_tile<double, HL, LdsX, R>(a, a.hx, o, sg, x, lB, 2 * q0, lo, tt, w[t]);
+        if (s)
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            const double2 c = A2[(int)(q0 - pbeg) + (lo[r] >> 1)];
+            w[t][r].x = __builtin_fma(-theta, c.x, w[t][r].x);
+            w[t][r].y = __builtin_fma(-theta, c.y, w[t][r].y);
+          }
+      }
+    }
+    __syncthreads();   // every stencil read of A and B is done
+    if (s + 1 == ns) break;
+    double* const hxs = (s & 1) ? a.hx : a.hx2;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      const int64_t q0 = pbeg + (int64_t)t * kThreads * R;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int64_t q = q0 + (int64_t)r * kThreads + kp_tid();
+        if (q < pend) {
+          A2[q - pbeg] = w[t][r];
+          publish_pair(a, hxs, sg, 2 * q, w[t][r].x, w[t][r].y);
+          if (s + 3 == ns) Pair<double>::store(V + (int64_t)(j + 1) * ld + 2 * q, w[t][r].x, w[t][r].y);
+        }
+      }
+    }
+    flag_publish(a, 4 * k + 1 + s);
+    tail_next(a, s ? theta : 0.0, tt);
+    flag_wait_neighbours(a, 4 * k + 1 + s);
+    stage_halo<double>(a, hxs, o, lB);
+    __syncthreads();
+  }
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    const int64_t q0 = pbeg + (int64_t)t * kThreads * R, t0 = 2 * q0;
+    if (!wave_in_tile(q0, pend)) break;
     uint32_t lo[R];
     bool ok[R];
     tile_pairs_r<R>(q0, pend, lo, ok);
-    double2 xa[R], xv[R], w1[R], w2[R];
-    if (!upd) {
-      const double* src = j == 0 ? a.u : xcol;
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const double2 v = Pair<double>::load(src + t0 + lo[r]);
-        if (ok[r]) {
-          A2[r * kThreads + kp_tid()] = v;
-          if (j == 0) Pair<double>::store(xcol + t0 + lo[r], v.x, v.y);
-        }
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-      xa[r] = na ? Pair<double>::load(acol + t0 + lo[r]) : make_double2(0.0, 0.0);
-    stage_halo<double>(a, a.hx, o, lB);
-    double tc[kPMax];
-    tail_weights(a, 0, 0, inv_mu, tc);
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < R; ++r) xv[r] = *reinterpret_cast<const double2*>(lA + lo[r]);
-    aug_tile<double, true, LdsX, R>(a, a.hx, o, sg, LdsX{lA, t0}, lB, t0, lo, tc, w1);
+    double2 va[C][R], b[kNv][R];
+    if (jo > 0) load_block<R, C>(V, ld, t0, 0, min(C, jo), lo, va);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      if (!ok[r]) xa[r] = xv[r] = w1[r] = make_double2(0.0, 0.0);
-      w2[r] = make_double2(0.0, 0.0);
-    }
-    if (two) {
-      __syncthreads();
+      const int slot = (int)(q0 - pbeg) + r * kThreads + kp_tid();
+      const double2 z = make_double2(0.0, 0.0);
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        B2[r * kThreads + kp_tid()] = w1[r];
-        if (ok[r]) publish_pair(a, a.hx2, sg, t0 + lo[r], w1[r].x, w1[r].y);
+      for (int q = 0; q < kS; ++q) {
+        const int col = j - (kS - 1) + q;
+        b[q][r] = (ok[r] && (q == kS - 1 || col >= jo))
+                      ? Pair<double>::load(V + (int64_t)max(col, 0) * ld + t0 + lo[r]) : z;
       }
-      flag_publish(a, 2 * k + 1);
-      if (jo > 0) load_block<R, C>(V, ld, t0, 0, min(C, jo), lo, va);
-      tail_weights(a, 0, 1, inv_mu, tc);
-      flag_wait_neighbours(a, 2 * k + 1);
-      stage_halo<double>(a, a.hx2, o, lA);
-      __syncthreads();
-      aug_tile<double, true, LdsX, R>(a, a.hx2, o, sg, LdsX{lB, t0}, lA, t0, lo, tc, w2);
+      if (ok[r]) B2[slot] = w[t][r];
 #pragma unroll
-      for (int r = 0; r < R; ++r)
-        if (!ok[r]) w2[r] = make_double2(0.0, 0.0);
-    } else if (jo > 0) {
-      load_block<R, C>(V, ld, t0, 0, min(C, jo), lo, va);
+      for (int s = 0; s < kS; ++s) b[kS + s][r] = z;
+      if (ok[r]) {
+        b[kS][r] = ns == 1 ? w[t][r] : (ns == 2 ? A2[slot] : Pair<double>::load(V + (int64_t)(j + 1) * ld + t0 + lo[r]));
+        if (ns >= 2) b[kS + 1][r] = ns == 2 ? w[t][r] : A2[slot];
+        if (ns >= 3) b[kS + 2][r] = w[t][r];
+      }
     }
-    tile_dots<R>(V, ld, t0, jo, lo, xa, xv, w1, w2, va, sacc);
-    if (wg_rank(a) == 0) tail_block(a, j, na, two, V, sacc);
+    tile_dots<R>(V, ld, t0, jo, na + ns > 1, lo, b, va, sacc);
+  }
+}
+
+// The same with every vector in memory (several sub-tiles or planes).
+template <int R, bool HL>
+__device__ __attribute__((always_inline)) inline void matvec_stream(const Args& a, int j, int na, int ns,
+                                                                    double theta, double inv_mu, double* sacc,
+                                                                    double* hl, unsigned k) {
+  double* V = reinterpret_cast<double*>(a.V);
+  const int64_t ld = a.ld;
+  const Rows o = own_rows(a);
+  const int jo = j - na;
+  constexpr int C = kDotCols<R>;
+  if (j == 0) copy_state<double>(a, o, V);
+  const double* hxs = a.hx;
+  for (int s = 0; s < ns; ++s) {
+    const bool last = s + 1 == ns;
+    const double th = s ? theta : 0.0;
+    if (HL) stage_halo<double>(a, hxs, o, hl);
     __syncthreads();
-    // (every stencil read of the halo rows is done: the new vectors' pairs)
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      if (two)
-        A2[r * kThreads + kp_tid()] = w2[r];
-      else
-        B2[r * kThreads + kp_tid()] = w1[r];
-    }
-  } else {
-    if (j == 0) copy_state<double>(a, o, xcol);
-    if (HL) stage_halo<double>(a, a.hx, o, hl);
-    __syncthreads();
-    if (two) {
-      for (int si = 0; si < num_segs(a); ++si) {
-        const Seg sg = seg_at(a, o, si);
-        const int64_t pend = (sg.end + 1) >> 1;
-        double tc[kPMax];
-        tail_weights(a, sg.plane, 0, inv_mu, tc);
-        for (int64_t q0 = sg.beg >> 1; q0 < pend; q0 += (int64_t)kThreads * R) {
-          const int64_t t0 = 2 * q0;
-          uint32_t lo[R];
-          bool ok[R];
-          tile_pairs_r<R>(q0, pend, lo, ok);
-          double2 w[R];
-          aug_tile<double, HL, Col<double>, R>(a, a.hx, o, sg, Col<double>{xcol}, hl, t0, lo, tc, w);
-#pragma unroll
-          for (int r = 0; r < R; ++r)
-            if (ok[r]) {
-              Pair<double>::store(w1col + t0 + lo[r], w[r].x, w[r].y);
-              publish_pair(a, a.hx2, sg, t0 + lo[r], w[r].x, w[r].y);
-            }
-        }
-      }
-      flag_publish(a, 2 * k + 1);
-      flag_wait_neighbours(a, 2 * k + 1);
-      if (HL) {
-        stage_halo<double>(a, a.hx2, o, hl);
-        __syncthreads();
-      }
-    }
-    const double* hxs = two ? a.hx2 : a.hx;
-    const Col<double> xc{two ? w1col : xcol};
-    double* dst = two ? w2col : w1col;
+    const Col<double> xc{V + (int64_t)(j + s) * ld};
+    double* wcol = V + (int64_t)(j + s + 1) * ld;
+    double* const hxn = (s & 1) ? a.hx : a.hx2;
     for (int si = 0; si < num_segs(a); ++si) {
       const Seg sg = seg_at(a, o, si);
       const int64_t pend = (sg.end + 1) >> 1;
-      double tc[kPMax];
-      tail_weights(a, sg.plane, two, inv_mu, tc);
+      double tt[kPMax];
+      tail_of_x(a, sg.plane, inv_mu, tt);
+      for (int e = 0; e < s; ++e) tail_next(a, e ? theta : 0.0, tt);
       for (int64_t q0 = sg.beg >> 1; q0 < pend; q0 += (int64_t)kThreads * R) {
+        if (!wave_in_tile(q0, pend)) break;
         const int64_t t0 = 2 * q0;
         uint32_t lo[R];
         bool ok[R];
         tile_pairs_r<R>(q0, pend, lo, ok);
-        double2 xa[R], xv[R], w1[R], w2[R], t[R];
-        if (jo > 0) load_block<R, C>(V, ld, t0, 0, min(C, jo), lo, va);
+        double2 va[C][R], w[R];
+        if (last && jo > 0) load_block<R, C>(V, ld, t0, 0, min(C, jo), lo, va);
+        aug_tile<double, HL, Col<double>, R>(a, hxs, o, sg, xc, hl, t0, lo, tt, w);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-          xv[r] = Pair<double>::load(xcol + t0 + lo[r]);
-          xa[r] = na ? Pair<double>::load(acol + t0 + lo[r]) : make_double2(0.0, 0.0);
-          w1[r] = two ? Pair<double>::load(w1col + t0 + lo[r]) : make_double2(0.0, 0.0);
-        }
-        aug_tile<double, HL, Col<double>, R>(a, hxs, o, sg, xc, hl, t0, lo, tc, t);
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
+          const double2 c = xc.pair(t0 + lo[r]);
+          w[r].x = __builtin_fma(-th, c.x, w[r].x);
+          w[r].y = __builtin_fma(-th, c.y, w[r].y);
           if (ok[r]) {
-            Pair<double>::store(dst + t0 + lo[r], t[r].x, t[r].y);
-            w2[r] = two ? t[r] : make_double2(0.0, 0.0);
-            w1[r] = two ? w1[r] : t[r];
-          } else {
-            xa[r] = xv[r] = w1[r] = w2[r] = make_double2(0.0, 0.0);
+            Pair<double>::store(wcol + t0 + lo[r], w[r].x, w[r].y);
+            if (!last) publish_pair(a, hxn, sg, t0 + lo[r], w[r].x, w[r].y);
           }
         }
-        tile_dots<R>(V, ld, t0, jo, lo, xa, xv, w1, w2, va, sacc);
+        if (last) {
+          double2 b[kNv][R];
+#pragma unroll
+          for (int q = 0; q < kNv; ++q) {
+            const int col = j - (kS - 1) + q;
+            const bool on = q < kS ? (q == kS - 1 || col >= jo) : (q - kS + 1 < ns);
+            const bool isw = q - kS + 1 == ns;
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+              b[q][r] = !ok[r] ? make_double2(0.0, 0.0)
+                               : (isw ? w[r] : (on ? Pair<double>::load(V + (int64_t)max(col, 0) * ld + t0 + lo[r])
+                                                   : make_double2(0.0, 0.0)));
+          }
+          tile_dots<R>(V, ld, t0, jo, na + ns > 1, lo, b, va, sacc);
+        }
       }
     }
-    if (wg_rank(a) == 0) tail_block(a, j, na, two, V, sacc);
-    __syncthreads();
+    if (!last) {
+      flag_publish(a, 4 * k + 1 + s);
+      flag_wait_neighbours(a, 4 * k + 1 + s);
+      hxs = hxn;
+    }
   }
 }
 
@@ -681,30 +749,31 @@ __device__ __attribute__((always_inline)) inline void combine_block(const Args& 
     const int64_t pend = (sg.end + 1) >> 1;
     double* const outp = out_plane(a, sg.plane) - (int64_t)sg.plane * a.npt_pad;
     for (int64_t q0 = sg.beg >> 1; q0 < pend; q0 += (int64_t)kThreads * R) {
+      if (!wave_in_tile(q0, pend)) break;
       const int64_t t0 = 2 * q0;
       uint32_t lo[R];
       bool ok[R];
       tile_pairs_r<R>(q0, pend, lo, ok);
-      double2 acc[R];
+      double2 acc[1][R];
 #pragma unroll
-      for (int r = 0; r < R; ++r) acc[r] = make_double2(0.0, 0.0);
+      for (int r = 0; r < R; ++r) acc[0][r] = make_double2(0.0, 0.0);
       for (int i0 = 0; i0 < m; i0 += C)
-        axpy_block<R, C, 1>(V, ld, t0, i0, 1, min(C, m - i0), cf, cf, lo, acc, acc);
+        axpy_block<R, C, 1>(V, ld, t0, i0, 1, min(C, m - i0), cf, lo, acc);
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         if (ok[r]) {
           const int64_t e = t0 + lo[r];
-          *reinterpret_cast<double2*>(a.u + e) = acc[r];
-          if (!last) publish_pair(a, a.hx, sg, e, acc[r].x, acc[r].y);
+          *reinterpret_cast<double2*>(a.u + e) = acc[0][r];
+          if (!last) publish_pair(a, a.hx, sg, e, acc[0][r].x, acc[0][r].y);
           if (last) {
-            if (e < sg.end) outp[e] = acc[r].x;
-            if (e + 1 < sg.end) outp[e + 1] = acc[r].y;
+            if (e < sg.end) outp[e] = acc[0][r].x;
+            if (e + 1 < sg.end) outp[e + 1] = acc[0][r].y;
           }
         }
       }
     }
   }
-  if (wg_rank(a) == 0) tail_combine_cols<double, double>(a, V, m, a.pub->coef, -1, 0.0, a.u, !last);
+  if (wg_rank(a) == 0) tail_combine_cols<double, double>(a, V, m, a.pub->coefs[0], -1, 0.0, a.u, !last);
 }
 
 // ---- the grid-wide reduction ---------------------------------------------------
@@ -715,8 +784,8 @@ __device__ __attribute__((always_inline)) inline void combine_block(const Args& 
 // kDirectRows rows are read by the leader.  Above, the rows are summed by
 // slot quads first: workgroup q of the first nq reads quad q of every row (one
 // 16-byte load per thread at 256 rows) and stores four sums, and the leader
-// reads those: one workgroup reading 256 rows of 260 slots took 6 to 11 us
-// per step on its share of the coherent path, the two hops about 4.
+// reads those: one workgroup reading 256 rows of 130 slots took 5 to 6 us
+// per step on its share of the coherent path; the two hops take 5 for 260.
 
 __device__ inline double* block_part(const Args& a, unsigned k) {
   return a.part + (int64_t)a.part_rows * kCStride + (int64_t)(k & 1u) * a.part_rows * a.bstride;
@@ -851,105 +920,134 @@ __device__ __attribute__((always_inline)) inline void block_gather(const Args& a
 }
 
 // ---- scalar work of the leader ---------------------------------------------------
+//
+// With measured products below kSmallL the GSMGS correction is T = I - L - L'
+// (its second order is under rounding), so C = B - (L + L') B is one product
+// with the symmetric table: two workgroup barriers between the reduced sums
+// and the coefficients, against five for M^{-1} kept row by row (serial part
+// of a three-step phase at 64 x 64 5.4 us, of a two-step phase that way 5.9 us).  Above it, one wave
+// solves with M = I + L by substitution, exactly Algorithm 7's two sweeps.
 
-// Row r of a table times two vectors (as row_mv, for two right-hand sides).
-template <int MODE, bool TR>
-__device__ inline void row_mv2(int hi, const double* tab, const double* v, const double* w, int r,
-                               double& ov, double& ow) {
+// Row r of the table times the kS columns of b (stride 72): sum over k <= hi, k
+// != r (lower: k < r); 8 lanes per row as in row_mv.
+__device__ inline void row_mvs(int hi, const double* tab, const double* b, int r, bool lower, double (&out)[kS]) {
   const int s = kp_tid() & 7;
-  double av = 0.0, aw = 0.0;
+#pragma unroll
+  for (int l = 0; l < kS; ++l) out[l] = 0.0;
 #pragma unroll
   for (int t = 0; t < kMMax / 8; ++t) {
     if (8 * t > hi) break;                     // uniform
     const int k = s + 8 * t;
-    const double x = TR ? tab[r * kTabLd + k] : tab[k * kTabLd + r];
-    const double xv = x * v[k], xw = x * w[k];
-    const bool in = (k <= hi) && ((MODE == 0) ? (k <= r) : (MODE == 1 ? (k < r) : (k > r)));
-    if (in) {
-      av += xv;
-      aw += xw;
+    const double x = tab[r * kTabLd + k];
+    const bool in = k <= hi && k != r && r <= hi && !(lower && k > r);
+#pragma unroll
+    for (int l = 0; l < kS; ++l) {
+      const double v = x * b[72 * l + k];
+      out[l] += in ? v : 0.0;
     }
   }
-  av += dpp_mov<0xB1>(av);
-  aw += dpp_mov<0xB1>(aw);
-  av += dpp_mov<0x4E>(av);
-  aw += dpp_mov<0x4E>(aw);
-  av += dpp_mov<0x141>(av);
-  aw += dpp_mov<0x141>(aw);
-  ov = av;
-  ow = aw;
+#pragma unroll
+  for (int l = 0; l < kS; ++l) {
+    out[l] += dpp_mov<0xB1>(out[l]);
+    out[l] += dpp_mov<0x4E>(out[l]);
+    out[l] += dpp_mov<0x141>(out[l]);
+  }
 }
 
-// Row c of M^{-1} (compact-WY recursion) and of L from the measured products
-// sl of column c with the older ones, appended to the table.
-__device__ inline void append_row(LeadB& L, int c, const double* sl, int r, bool row_lead) {
-  const double mr = -row_mv<2, true>(c - 1, L.tab, sl, r);
-  if (row_lead) {
-    if (r < c) {
-      L.tab[r * kTabLd + c] = mr - sl[r];
-      L.tab[c * kTabLd + r] = sl[r];
-    } else if (r == c) {
-      L.tab[c * kTabLd + c] = 1.0;
+// C = T B by substitution in one wave (row i = lane): M y = b, p = b - L' y, M c
+// = p (H-CWY: c = y).  Only where the measured products are not small.
+__device__ inline void solve_exact(const Args& a, int j, const double* tab, double (&v)[kS]) {
+  const int i = kp_tid() & 63;
+  double y[kS], p[kS];
+  auto forward = [&](double (&x)[kS]) {
+    for (int k = 0; k < j; ++k) {
+      const double l = (i > k && i <= j) ? tab[i * kTabLd + k] : 0.0;
+#pragma unroll
+      for (int q = 0; q < kS; ++q) x[q] -= l * __shfl(x[q], k, 64);
     }
+  };
+#pragma unroll
+  for (int q = 0; q < kS; ++q) y[q] = v[q];
+  forward(y);
+  if (a.orth == KP_ORTH_H_CWY) {
+#pragma unroll
+    for (int q = 0; q < kS; ++q) v[q] = y[q];
+    return;
+  }
+#pragma unroll
+  for (int q = 0; q < kS; ++q) p[q] = v[q];
+  for (int k = 1; k <= j; ++k) {
+    const double l = (i < k) ? tab[k * kTabLd + i] : 0.0;
+#pragma unroll
+    for (int q = 0; q < kS; ++q) p[q] -= l * __shfl(y[q], k, 64);
+  }
+  forward(p);
+#pragma unroll
+  for (int q = 0; q < kS; ++q) v[q] = p[q];
+}
+
+// The Hessenberg columns of the last block once the norms al[0 .. n) of its
+// new columns base + 1 .. base + n are known: column base + k takes the factor
+// 1 / al[k-1] (its vector's unit scale) and row base + 1 + l the factor al[l].
+__device__ inline void finish_block_columns(LeadB& L, int base, int n, const double* al, int i) {
+  if (i == 0) L.H[hcol(base) + base + 1] = L.rr[0] * al[0];
+  for (int k = 1; k < n; ++k) {
+    const double s = 1.0 / al[k - 1];
+    if (i <= base) L.H[hcol(base + k) + i] = s * L.rp[k - 1][i];
+    if (i <= k) L.H[hcol(base + k) + base + 1 + i] = s * L.hx[k - 1][i] * al[i];
   }
 }
 
-// The second Hessenberg column of a pair (column c, subdiagonal divisor
-// gamma[c]) and the subdiagonal of the first, once the norms alpha_c and
-// alpha_{c+1} are known; lanes i <= c.
-__device__ inline void finish_pair_column(LeadB& L, int c, double alc, double aln, int i) {
-  const double sc = 1.0 / alc;
-  if (i < c) L.H[c * kLdh + i] = sc * L.rp[i];
-  if (i == c) {
-    L.H[c * kLdh + c] = L.rp[c];
-    L.H[c * kLdh + c + 1] = sc * L.gamma[c] * aln;
-    L.H[(c - 1) * kLdh + c] = L.gamma[c - 1] * alc;
-  }
-}
-
-// tv: the reduced sums of step j (four per measured column i < j - na: xa.x_i,
-// x.x_i, w1.x_i, w2.x_i with xa = column j - 1, x = column j; then the ten
-// products of xa, x, w1, w2).  Stored columns carry unit scales sigma_i as in
-// scalar_step; the single-step rules (lagged norm, norm estimate, fallback,
-// breakdown) are those of scalar_step.
-__device__ __attribute__((always_inline)) inline void block_scalar(const Args& a, int j, int na, int two,
-                                                                   const double* tv, LeadB& L, double* wk,
+// tv: the reduced sums of the step from column j (slots: block_slots).
+// Stored columns carry unit scales sigma_i as in scalar_step; the single-step
+// rules (lagged norm, norm estimate, fallback, breakdown) are those of
+// scalar_step.
+__device__ __attribute__((always_inline)) inline void block_scalar(const Args& a, int j, int na, int ns,
+                                                                   const double* tv, LeadB& L, double* sb,
                                                                    Ctl& nx) {
   State* st = a.st;
   Pub* pb = a.pub;
-  double* sla = wk;
-  double* slj = wk + 72;
-  double* sb = wk + 2 * 72;
-  double* sq = wk + 3 * 72;
-  double* sy = wk + 4 * 72;
-  double* syq = wk + 5 * 72;
-  double* sp = wk + 6 * 72;
-  double* spq = wk + 7 * 72;
   const int i = kp_tid();
   const bool w0 = i < 64;
-  const int jo = j - na, ja = j - 1;
-  const double* G = tv + 4 * jo;
-  const double al = sqrt(G[4]), ala = na ? sqrt(G[0]) : 1.0, cww = G[7];
-  if (na && (!(ala > 0.0) || !isfinite(ala))) {
+  const int jo = j - na;
+  const double* G = tv + kNv * jo;
+  // norms of the columns jo .. j (vectors kS - 1 - na .. kS - 1)
+  double al[kS];
+  bool okn = true;
+#pragma unroll
+  for (int q = 0; q < kS; ++q) {
+    const double g = (q >= kS - 1 - na) ? G[gram_at(q, q)] : 1.0;
+    al[q] = sqrt(g);
+    if (q < kS - 1) okn = okn && al[q] > 0.0 && isfinite(al[q]);
+  }
+  const double alj = al[kS - 1], cww = G[gram_at(kS, kS)];
+  if (!okn) {
     if (i == 0) {
       nx.status = (int)KP_STATUS_NONFINITE;
       nx.phase = (int)PH_FINISH;
     }
     return;
   }
-  if (na && L.pend && w0) finish_pair_column(L, ja, ala, al, i);
-  if (!(al > 0.0) || !isfinite(al) || !isfinite(cww)) {
+  if (na && L.pend && w0) {
+    double an[kS];
+#pragma unroll
+    for (int q = 0; q < kS; ++q) an[q] = (na == 2) ? al[q] : (q + 1 < kS ? al[(q + 1) % kS] : 1.0);
+    finish_block_columns(L, j - na - 1, na + 1, an, i);
+  }
+  if (!(alj > 0.0) || !isfinite(alj) || !isfinite(cww)) {
     if (i == 0) {
-      if (na) L.sigma[ja] = 1.0 / ala;
-      if (j == 0 && al == 0.0) {            // zero start vector: result is zero
+#pragma unroll
+      for (int q = 0; q < kS - 1; ++q)
+        if (q >= kS - 1 - na) L.sigma[j - (kS - 1) + q] = 1.0 / al[q];
+      if (j == 0 && alj == 0.0) {            // zero start vector: result is zero
         st->zero = 1;
         L.beta = 0.0;
         nx.phase = (int)PH_FINISH;
-      } else if (al == 0.0) {               // exact invariance already reached
+      } else if (alj == 0.0) {               // exact invariance already reached
         L.breakdown = 1;
         nx.m_eff = j;
         nx.upd = 0;
-        L.H[(j - 1) * kLdh + j] = 0.0;
+        L.H[hcol(j - 1) + j] = 0.0;
         nx.phase = (int)PH_EXPM;
       } else {
         nx.status = (int)KP_STATUS_NONFINITE;
@@ -958,12 +1056,12 @@ __device__ __attribute__((always_inline)) inline void block_scalar(const Args& a
     }
     return;
   }
-  if (j > 0 && L.fallback_cur && al <= a.eps_bd * sqrt(L.wn2[j - 1])) {
+  if (j > 0 && L.fallback_cur && alj <= a.eps_bd * sqrt(L.wn2)) {
     // the exact norm of the vector produced with the fallback is negligible:
     // lucky breakdown at the previous step (this step's products are unused)
     if (i == 0) {
       L.breakdown = 1;
-      L.H[(j - 1) * kLdh + j] = 0.0;
+      L.H[hcol(j - 1) + j] = 0.0;
       nx.j = j;
       nx.m_eff = j;
       nx.upd = 0;
@@ -971,98 +1069,142 @@ __device__ __attribute__((always_inline)) inline void block_scalar(const Args& a
     }
     return;
   }
-  const double sj = 1.0 / al, sa = 1.0 / ala;
-  const double sig = (w0 && i < jo) ? L.sigma[i] : (i == j ? sj : (na && i == ja ? sa : 0.0));
+  // vector q (< kS) is column j - (kS - 1) + q; a lane's own vector, if any
+  const int qi = i - (j - (kS - 1));
+  double sig = 0.0;
   if (w0) {
-    const bool act = i < jo, ia = na && i == ja, ij = i == j;
-    const double s = sig * sj;
-    sla[i] = act ? sig * sa * tv[4 * i] : 0.0;
-    slj[i] = act ? s * tv[4 * i + 1] : (ia ? s * G[1] : 0.0);
-    sb[i] = act ? s * tv[4 * i + 2] : (ia ? s * G[2] : (ij ? s * G[5] : 0.0));
-    sq[i] = act ? s * tv[4 * i + 3] : (ia ? s * G[3] : (ij ? s * G[6] : 0.0));
-  }
-  __syncthreads();
-  const int r = (kp_tid() >> 6) * 8 + ((kp_tid() & 63) >> 3);
-  const bool row_lead = (kp_tid() & 7) == 0;
-  if (na) {
-    append_row(L, ja, sla, r, row_lead);
-    __syncthreads();
-  }
-  append_row(L, j, slj, r, row_lead);
-  __syncthreads();
-  double h, q = 0.0;
-  if (a.orth == KP_ORTH_H_NCWY) {
-    h = sb[r] - row_mv<1, true>(j, L.tab, sb, r);      // T = I - L
-  } else {
-    double y, yq;
-    row_mv2<0, false>(j, L.tab, sb, sq, r, y, yq);     // M^{-1} b (CWY: H)
-    h = y;
-    if (a.orth == KP_ORTH_H_GSMGS) {
-      // p = b - L^T y, then M^{-1} p (Algorithm 7's second sweep)
-      if (row_lead) {
-        sy[r] = y;
-        syq[r] = yq;
+    const double sj = 1.0 / alj;
+    if (i < jo) {
+      sig = L.sigma[i];
+#pragma unroll
+      for (int q = 0; q < kS; ++q) {
+        const int col = j - (kS - 1) + q;
+        if (col >= jo) {
+          const double l = sig / al[q] * tv[kNv * i + q];
+          L.tab[i * kTabLd + col] = L.tab[col * kTabLd + i] = l;
+          if (!(fabs(l) <= kSmallL)) L.big = 1;
+        }
+        sb[72 * q + i] = sig * sj * tv[kNv * i + kS + q];
       }
-      __syncthreads();
-      double p, pq;
-      row_mv2<2, false>(j, L.tab, sy, syq, r, p, pq);
-      if (row_lead) {
-        sp[r] = sb[r] - p;
-        spq[r] = sq[r] - pq;
+    } else if (i <= j) {
+#pragma unroll
+      for (int p = 0; p < kS; ++p) {
+        if (qi == p) {
+          sig = 1.0 / al[p];
+#pragma unroll
+          for (int q = p + 1; q < kS; ++q) {
+            const int col = j - (kS - 1) + q;
+            const double l = sig / al[q] * G[gram_at(p, q)];
+            L.tab[i * kTabLd + col] = L.tab[col * kTabLd + i] = l;
+            if (!(fabs(l) <= kSmallL)) L.big = 1;
+          }
+#pragma unroll
+          for (int q = 0; q < kS; ++q) sb[72 * q + i] = sig * sj * G[gram_at(p, kS + q)];
+        }
       }
-      __syncthreads();
-      row_mv2<0, false>(j, L.tab, sp, spq, r, h, q);
+    } else {
+#pragma unroll
+      for (int q = 0; q < kS; ++q) sb[72 * q + i] = 0.0;
     }
   }
-  if (row_lead) {
-    L.h[r] = h;
-    L.q[r] = q;
+  __syncthreads();
+  const bool ncwy = a.orth == KP_ORTH_H_NCWY, gs = a.orth == KP_ORTH_H_GSMGS;
+  if (!L.big || ncwy) {
+    const int r = (kp_tid() >> 6) * 8 + ((kp_tid() & 63) >> 3);
+    double s[kS];
+    row_mvs(j, L.tab, sb, r, !gs, s);
+    if ((kp_tid() & 7) == 0)
+#pragma unroll
+      for (int q = 0; q < kS; ++q) L.c[q][r] = sb[72 * q + r] - s[q];
+  } else if (w0) {
+    double v[kS];
+#pragma unroll
+    for (int q = 0; q < kS; ++q) v[q] = sb[72 * q + i];
+    solve_exact(a, j, L.tab, v);
+#pragma unroll
+    for (int q = 0; q < kS; ++q) L.c[q][i] = v[q];
   }
   __syncthreads();
   if (!w0) return;
   const bool in = i <= j;
-  const double hi = in ? L.h[i] : 0.0, qi = in ? L.q[i] : 0.0;
-  const double b = in ? sb[i] : 0.0, bq = in ? sq[i] : 0.0;
-  const double wn2 = cww * sj * sj;
-  const double sums = wave_sum4(b * b, b * hi, b * qi, bq * qi);
-  const double ss = readlane_d(sums, 0);
+  const double sj = 1.0 / alj, sj2 = sj * sj;
+  double b[kS], c[kS];
+#pragma unroll
+  for (int q = 0; q < kS; ++q) {
+    b[q] = in ? sb[72 * q + i] : 0.0;
+    c[q] = in ? L.c[q][i] : 0.0;
+  }
+  const double wn2 = cww * sj2;
+  const double t4 = wave_sum4(b[0] * b[0], b[0] * c[0], b[0] * c[1], b[0] * c[2]);
+  const double ss = readlane_d(t4, 0);
   const double est2 = wn2 - ss;
   const int fallback = (est2 <= a.delta * wn2) ? 1 : 0;
   const double gam = fallback ? 1.0 : sqrt(est2);
   const int bd = (!fallback && gam <= a.eps_bd * sqrt(wn2)) ? 1 : 0;
-  const bool bad = !isfinite(wave_sum(hi));
-  // the second vector of a pair
+  const bool bad = !isfinite(readlane_d(t4, 1));
+  // R'R = W'W - B'C, as far as the guard lets it
   int done = 1;
-  double e = 0.0, g2 = 1.0;
-  if (two) {
-    const double n1 = wn2 - readlane_d(sums, 1), n12 = G[8] * sj * sj - readlane_d(sums, 2);
-    const double nw2 = G[9] * sj * sj, n22 = nw2 - readlane_d(sums, 3);
-    e = n12 / n1;
-    const double d2 = n22 - e * n12;
-    const bool qok = isfinite(wave_sum(qi));
-    if (!bad && !fallback && !bd && est2 > kGuard * wn2 && n1 > 0.0 && qok && isfinite(d2) &&
-        d2 > kGuard * nw2) {
+  double r00 = gam, r01 = 0.0, r02 = 0.0, r11 = 1.0, r12 = 0.0, r22 = 1.0;
+  if (ns > 1 && !bad && !fallback && !bd && est2 > kGuard * wn2) {
+    const double u4 = wave_sum4(b[1] * c[1], b[1] * c[2], b[2] * c[2], 0.0);
+    const double n00 = wn2 - readlane_d(t4, 1), n01 = G[gram_at(kS, kS + 1)] * sj2 - readlane_d(t4, 2);
+    const double g11 = G[gram_at(kS + 1, kS + 1)] * sj2, n11 = g11 - readlane_d(u4, 0);
+    const double q00 = sqrt(n00), q01 = n01 / q00, d1 = n11 - q01 * q01;
+    if (n00 > 0.0 && isfinite(g11) && d1 > kGuard * g11) {
       done = 2;
-      g2 = sqrt(d2);
+      r00 = q00;
+      r01 = q01;
+      r11 = sqrt(d1);
+      if (ns > 2) {
+        const double g22 = G[gram_at(kS + 2, kS + 2)] * sj2, n22 = g22 - readlane_d(u4, 2);
+        const double n02 = G[gram_at(kS, kS + 2)] * sj2 - readlane_d(t4, 3);
+        const double n12 = G[gram_at(kS + 1, kS + 2)] * sj2 - readlane_d(u4, 1);
+        const double q02 = n02 / r00, q12 = (n12 - r01 * q02) / r11, d2 = n22 - q02 * q02 - q12 * q12;
+        if (isfinite(g22) && d2 > kGuard * g22) {
+          done = 3;
+          r02 = q02;
+          r12 = q12;
+          r22 = sqrt(d2);
+        }
+      }
     }
   }
+  const double i00 = 1.0 / r00, i11 = 1.0 / r11, i22 = 1.0 / r22;
+  const double i01 = -r01 * i00 * i11, i12 = -r12 * i11 * i22, i02 = -(r01 * i12 + r02 * i22) * i00;
   if (in) {
-    L.H[j * kLdh + i] = hi;
-    cstore(&pb->coef[i], -hi * sig / gam);
-    if (done == 2) cstore(&pb->coef2[i], (e * hi - qi) * sig / g2);
+    L.H[hcol(j) + i] = c[0];
+    cstore(&pb->coefs[0][i], -c[0] * i00 * sig);
+    if (done > 1) cstore(&pb->coefs[1][i], -(c[0] * i01 + c[1] * i11) * sig);
+    if (done > 2) cstore(&pb->coefs[2][i], -(c[0] * i02 + c[1] * i12 + c[2] * i22) * sig);
   }
+  // the unit scales of the columns measured here
+  if (in && i >= jo) L.sigma[i] = sig;
+  if (i == j) cstore(&pb->shift, c[0]);   // theta of the next block: H_jj
   if (i == 0) {
-    if (na) L.sigma[ja] = sa;
-    L.sigma[j] = sj;
-    cstore(&pb->coef[j + 1], sj / gam);
-    if (done == 2) {
-      cstore(&pb->coef2[j + 1], -e * sj / g2);
-      cstore(&pb->coef2[j + 2], sj / g2);
+    cstore(&pb->coefs[0][j + 1], i00 * sj);
+    if (done > 1) {
+      cstore(&pb->coefs[1][j + 1], i01 * sj);
+      cstore(&pb->coefs[1][j + 2], i11 * sj);
     }
-    if (j > 0 && !na) L.H[(j - 1) * kLdh + j] = L.gamma[j - 1] * al;
-    L.gamma[j] = gam;
-    L.wn2[j] = wn2;
-    if (j == 0) L.beta = al;
+    if (done > 2) {
+      cstore(&pb->coefs[2][j + 1], i02 * sj);
+      cstore(&pb->coefs[2][j + 2], i12 * sj);
+      cstore(&pb->coefs[2][j + 3], i22 * sj);
+    }
+    if (j > 0 && !na) L.H[hcol(j - 1) + j] = L.rr[0] * alj;
+    L.rr[0] = r00;
+    L.rr[1] = r01;
+    L.rr[2] = r02;
+    L.rr[3] = r11;
+    L.rr[4] = r12;
+    L.rr[5] = r22;
+    L.ri[0] = i00;
+    L.ri[1] = i01;
+    L.ri[3] = i11;
+    L.wn2 = wn2;
+    L.theta_used = L.theta;
+    L.theta = L.c[0][j];
+    if (j == 0) L.beta = alj;
     L.fallback_cur = fallback;
     L.n_fallback += fallback;
     L.pend = 0;
@@ -1070,7 +1212,7 @@ __device__ __attribute__((always_inline)) inline void block_scalar(const Args& a
       nx.status = (int)KP_STATUS_NONFINITE;
       nx.phase = (int)PH_FINISH;
     } else if (bd) {
-      L.H[j * kLdh + j + 1] = 0.0;
+      L.H[hcol(j) + j + 1] = 0.0;
       L.breakdown = 1;
       ++L.arnoldi_steps;
       nx.j = j + 1;
@@ -1079,47 +1221,63 @@ __device__ __attribute__((always_inline)) inline void block_scalar(const Args& a
       nx.na = 0;
       nx.phase = (int)PH_EXPM;
     } else {
-      if (done == 2) {
-        L.post = 1;
-        L.e = e;
-        L.g1 = gam;
-        L.gamma[j + 1] = g2 / gam;
-        L.wn2[j + 1] = 0.0;   // (read only after a fallback, which ends a pair)
-      } else if (two) {
-        L.nopair = 1;
-      }
+      L.post = done - 1;
+      L.nopair = (ns > 1 && done == 1) ? L.nopair + 1 : 0;
       L.arnoldi_steps += done;
       nx.j = j + done;
       nx.m_eff = nx.j;
       nx.upd = done;
       nx.na = done - 1;
+      nx.pns = ns;
       nx.phase = (int)((nx.j >= L.m_target || nx.j >= a.stop_j) ? PH_CLOSE : PH_STEP);
-      nx.two = nx.phase == PH_STEP ? pair_ok(a, L, nx.j) : 0;
+      nx.ns = block_steps(a, L, nx.j);
     }
   }
 }
 
-// After the release of a pair's barrier: the raw second Hessenberg column,
-// rp = (q - H_{<j} h_{<j} - h_j h) / g1 and rp_{j+1} = e - h_j, needed at the
-// next reduction only (finish_pair_column).
+// After the release of a block's barrier: the raw Hessenberg columns of its
+// later vectors (see the top of this file), needed at the next reduction only.
 __device__ __attribute__((always_inline)) inline void block_post(int j, LeadB& L) {
-  if (!L.post) return;   // (uniform: set before the release's barrier)
+  const int n = L.post;   // (uniform: set before the release's barrier)
+  if (n == 0) return;
   const int s = kp_tid() & 7;
   const int r = (kp_tid() >> 6) * 8 + ((kp_tid() & 63) >> 3);
-  double acc = 0.0;
+  double g[kS - 1];
+#pragma unroll
+  for (int l = 0; l < kS - 1; ++l) g[l] = 0.0;
 #pragma unroll
   for (int t = 0; t < kMMax / 8; ++t) {
     if (8 * t >= j) break;
     const int k = s + 8 * t;
-    const double x = L.H[k * kLdh + r] * L.h[k];
-    if (k < j && k >= r - 1) acc += x;
+    const bool on = k < j && k >= r - 1;
+    const double x = on ? L.H[hcol(k) + r] : 0.0;
+#pragma unroll
+    for (int l = 0; l < kS - 1; ++l) g[l] += on ? x * L.c[l][k] : 0.0;
   }
-  acc += dpp_mov<0xB1>(acc);
-  acc += dpp_mov<0x4E>(acc);
-  acc += dpp_mov<0x141>(acc);
-  const double hj = L.h[j];
-  if (s == 0 && r <= j) L.rp[r] = (L.q[r] - acc - hj * L.h[r]) / L.g1;
-  if (kp_tid() == 0) L.rp[j + 1] = L.e - hj;
+#pragma unroll
+  for (int l = 0; l < kS - 1; ++l) {
+    g[l] += dpp_mov<0xB1>(g[l]);
+    g[l] += dpp_mov<0x4E>(g[l]);
+    g[l] += dpp_mov<0x141>(g[l]);
+  }
+  const double th = L.theta_used, c0j = L.c[0][j], c1j = L.c[1][j];
+  if (s == 0 && r <= j) {
+    const double c0 = L.c[0][r], c1 = L.c[1][r];
+    const double u0 = c1 + th * c0 - g[0] - c0 * c0j;
+    const double u1 = L.c[2][r] + th * c1 - g[1] - c0 * c1j;
+    L.rp[0][r] = u0 * L.ri[0];
+    L.rp[1][r] = u0 * L.ri[1] + u1 * L.ri[3];
+  }
+  if (kp_tid() == 0) {
+    const double *R = L.rr, *I = L.ri;
+    const double x00 = R[1] + th * R[0] - R[0] * c0j, x01 = R[3];
+    const double x10 = R[2] + th * R[1] - R[0] * c1j, x11 = R[4] + th * R[3], x12 = R[5];
+    L.hx[0][0] = x00 * I[0];
+    L.hx[0][1] = x01 * I[0];
+    L.hx[1][0] = x00 * I[1] + x10 * I[3];
+    L.hx[1][1] = x01 * I[1] + x11 * I[3];
+    L.hx[1][2] = x12 * I[3];
+  }
   __syncthreads();
   if (kp_tid() == 0) {
     L.post = 0;
@@ -1127,35 +1285,40 @@ __device__ __attribute__((always_inline)) inline void block_post(int j, LeadB& L
   }
 }
 
-// Close of the Arnoldi process: exact norms of the newest column (nrm2) and,
-// after a pair, of the one before it (nrm2a), which complete H.
-__device__ __attribute__((always_inline)) inline void block_close(const Args& a, double nrm2, double nrm2a,
-                                                                  LeadB& L, Ctl& nx) {
+// Close of the Arnoldi process: the exact norms of the pending columns (nrm2[l]
+// of new column l of upd) complete H.
+__device__ __attribute__((always_inline)) inline void block_close(const Args& a, const double* nrm2, LeadB& L,
+                                                                  Ctl& nx) {
   State* st = a.st;
-  const int j = nx.j, c = j - 1;
-  const double nrm = sqrt(nrm2), nra = sqrt(nrm2a);
-  const bool pair = L.pend != 0;
+  const int j = nx.j, n = nx.upd;
+  double al[kS];
+  bool fin = true;
+#pragma unroll
+  for (int l = 0; l < kS; ++l) {
+    al[l] = l < n ? sqrt(nrm2[l]) : 1.0;
+    fin = fin && isfinite(al[l]) && (l + 1 >= n || al[l] > 0.0);
+  }
   __syncthreads();
-  if (pair && kp_tid() < 64) finish_pair_column(L, c, nra, nrm, kp_tid());
+  if (kp_tid() < 64) finish_block_columns(L, j - n, n, al, kp_tid());
   if (kp_tid() != 0) return;
-  if (pair)
-    L.sigma[c] = 1.0 / nra;
-  else
-    L.H[c * kLdh + j] = L.gamma[c] * nrm;
+#pragma unroll
+  for (int l = 0; l < kS - 1; ++l)
+    if (l + 1 < n) L.sigma[j - n + 1 + l] = 1.0 / al[l];
   L.pend = 0;
-  st->last_nrm2 = nrm2;
+  const double last2 = nrm2[n - 1];
+  st->last_nrm2 = last2;
   nx.upd = 0;
-  if (!isfinite(nrm2) || (pair && !(nra > 0.0 && isfinite(nrm2a)))) {
+  if (!fin) {
     nx.status = (int)KP_STATUS_NONFINITE;
     nx.phase = (int)PH_FINISH;
     return;
   }
-  if (L.fallback_cur && nrm <= a.eps_bd * sqrt(L.wn2[c])) {
-    L.H[c * kLdh + j] = 0.0;
+  if (L.fallback_cur && sqrt(last2) <= a.eps_bd * sqrt(L.wn2)) {
+    L.H[hcol(j - 1) + j] = 0.0;
     L.breakdown = 1;
   }
   nx.phase = (int)((L.breakdown || j >= L.m_target) ? PH_EXPM : PH_STEP);
-  nx.two = nx.phase == PH_STEP ? pair_ok(a, L, j) : 0;
+  nx.ns = block_steps(a, L, j);
 }
 
 }  // namespace kp

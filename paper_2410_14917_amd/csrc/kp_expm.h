@@ -123,11 +123,18 @@ __device__ inline void tiles_for_each(int n, const Tiles& T, F f) {
   }
 }
 
-// F[0..m] = exp(tau Hbar) e_1 for the Hessenberg H (column-major, leading
-// dimension ldh) of size (m+1) x m; zero_sub drops h_{m+1,m} (lucky
+// Entry (i, k) of a column-major Hessenberg matrix.
+struct HessCol {
+  const double* p;
+  int ld;
+  __device__ double operator()(int i, int k) const { return p[(int64_t)k * ld + i]; }
+};
+
+// F[0..m] = exp(tau Hbar) e_1 for the Hessenberg H (entries H(i, k)) of size
+// (m+1) x m; zero_sub drops h_{m+1,m} (lucky
 // breakdown).  Whole workgroup; lds holds at least 2 kNmPad^2 doubles.
-__device__ inline void expm_hbar(const Args& a, const double* H, int ldh, int m,
-                                 double tau, bool zero_sub, double* F, double* lds) {
+template <typename HT>
+__device__ inline void expm_hbar(const Args& a, const HT& H, int m, double tau, bool zero_sub, double* F, double* lds) {
   __shared__ double s_red[kWaves];
   __shared__ int s_s;
   double* sA = lds;
@@ -140,7 +147,7 @@ __device__ inline void expm_hbar(const Args& a, const double* H, int ldh, int m,
     const int i = idx / kNmPad, k = idx - i * kNmPad;
     double v = 0.0;
     if (k < m && i <= k + 1 && i < n) {
-      v = H[(int64_t)k * ldh + i];
+      v = H(i, k);
       if (zero_sub && k == m - 1 && i == m) v = 0.0;
     }
     sA[idx] = tau * v;

@@ -96,8 +96,8 @@ struct Pub {
   int pad_[2];
   double inv_mu;
   double xscale;            // MGS / ioCGS: unit scale of the column the next matvec multiplies
-  double coef[kMMax + 2];   // coefficients of the pending update / of the combine
-  double coef2[kMMax + 2];  // block steps: coefficients of the second pending column
+  double coefs[3][kMMax + 2];   // coefficients of the pending update(s) / of the combine ([0])
+  double shift;             // block steps: shift of the next products
 };
 
 // Private state of the call, read and written only by the leader (and by the
@@ -112,9 +112,10 @@ struct State {
   int zero;           // the start vector is zero
   int m_last;
   int onchip;         // vector passes of the two-pass count kept in LDS (keep_xw)
-  int nopair;         // block steps: this Arnoldi process goes on in single steps
+  int nopair;         // block steps: LeadB::nopair (above bit 0) and big (bit 0)
   int pad_;
   double t, tau, beta, mu, err_max, omega, err, last_nrm2;
+  double theta;       // block steps: shift of the next products
   double omega_prev;  // normalised error of the last accepted substep (PI control)
   double sigma[kMMax + 2];   // unit scale of stored basis column i
   double gamma[kMMax + 2];   // divisor applied to column i+1 when it was written
@@ -159,8 +160,8 @@ struct Args {
   int pb;             // number of phi terms beyond b_0 (columns b_1..b_pb of B)
   int tangent;        // 1: Van Loan block operator [[Atilde, dAtilde], [0, Atilde]]
   int nwg, rows_per_wg;   // workgroups that own rows; rows per workgroup
-  int block;          // one-reduction float64 kernels: two Arnoldi steps per reduction (k_blk)
-  int pairs;          // ... where the form allows pairs (0: single steps only)
+  int block;          // one-reduction float64 kernels: several Arnoldi steps per reduction (k_blk)
+  int pairs;          // ... where the form allows them (0: single steps only)
   int bstride;        // block steps: slots of a row of the step buffers
   int tile_r;         // block steps: element pairs per thread and sub-tile
   int part_rows;      // rows of each partial-sum buffer (>= nwg, the same for every team class)
@@ -291,17 +292,18 @@ struct Ctl {
   int last;     // the accepted substep ends at h
   int status;
   int i;        // PH_PROJ: column of the next inner product (j + 1: the norm)
-  int na;       // block steps: column j - 1 is unmeasured too
-  int two;      // block steps: the step phase makes two steps
+  int na;       // block steps: unmeasured columns before column j
+  int ns;       // block steps: steps this phase makes
+  int pns;      // block steps: steps the previous step phase set out to make
 };
 
-__device__ inline unsigned ctl_pack(const Ctl& c) {
+// (a kernel uses either i or the block steps' fields: block says which)
+__device__ inline unsigned ctl_pack(const Ctl& c, bool block) {
   return (unsigned)c.phase | ((unsigned)c.j << 4) | ((unsigned)(c.upd & 1) << 11) |
          ((unsigned)c.m_eff << 12) | ((unsigned)c.last << 19) | ((unsigned)c.status << 20) |
-         ((unsigned)c.i << 22) | ((unsigned)(c.upd >> 1) << 29) | ((unsigned)c.na << 30) |
-         ((unsigned)c.two << 31);
+         ((unsigned)(block ? c.na | (c.ns << 2) | (c.pns << 4) : c.i) << 22) | ((unsigned)(c.upd >> 1) << 29);
 }
-__device__ inline Ctl ctl_unpack(unsigned w) {
+__device__ inline Ctl ctl_unpack(unsigned w, bool block) {
   Ctl c;
   c.phase = (int)(w & 15u);
   c.j = (int)((w >> 4) & 127u);
@@ -309,9 +311,11 @@ __device__ inline Ctl ctl_unpack(unsigned w) {
   c.m_eff = (int)((w >> 12) & 127u);
   c.last = (int)((w >> 19) & 1u);
   c.status = (int)((w >> 20) & 3u);
-  c.i = (int)((w >> 22) & 127u);
-  c.na = (int)((w >> 30) & 1u);
-  c.two = (int)(w >> 31);
+  const int f = (int)((w >> 22) & 127u);
+  c.i = block ? 0 : f;
+  c.na = block ? f & 3 : 0;
+  c.ns = block ? (f >> 2) & 3 : 0;
+  c.pns = block ? (f >> 4) & 3 : 0;
   return c;
 }
 
@@ -407,7 +411,7 @@ __device__ inline void bar_release(const Args& a, unsigned k, const Ctl& nxt, Pu
     cstore(&pb->m_eff, nxt.m_eff);
     cstore(&pb->last, nxt.last);
     cstore(&pb->status, nxt.status);
-    cstore(release_word(a), ((unsigned long long)k << 32) | ctl_pack(nxt));
+    cstore(release_word(a), ((unsigned long long)k << 32) | ctl_pack(nxt, a.block != 0));
   }
 }
 
@@ -431,14 +435,14 @@ __device__ inline void bar_wait(const Args& a, unsigned k, Ctl* cur, int* ok) {
       }
     }
     *ok = good;
-    if (good) *cur = ctl_unpack((unsigned)w);
+    if (good) *cur = ctl_unpack((unsigned)w, a.block != 0);
   }
   __syncthreads();
 }
 
 // Point-to-point: this workgroup has published the halo rows / tail of the
-// vector numbered k (the phase's barrier number; block steps publish two per
-// phase, 2k and 2k + 1).
+// vector numbered k (the phase's barrier number; block steps publish up to
+// three per phase, 4k ..).
 __device__ inline void flag_publish(const Args& a, unsigned k) {
   wait_all_stores();
   __syncthreads();

@@ -142,14 +142,15 @@ __device__ inline int step_phase(const Args& a) {
   return orth_multi_sync(a.orth) ? (int)PH_MVEC : (int)PH_STEP;
 }
 
-// Opens the steps from column j on, without a pending update; na: column
-// j - 1 is unmeasured too (block steps).
+// Opens the steps from column j on, without a pending update; na: unmeasured
+// columns before it (block steps).
 template <typename LT>
 __device__ inline void begin_steps(const Args& a, const LT& L, Ctl& nx, int j, int na) {
   nx.j = j;
   nx.upd = 0;
   nx.na = na;
-  nx.two = pair_ok(a, L, j);
+  nx.ns = block_steps(a, L, j);
+  nx.pns = 0;
   nx.phase = step_phase(a);
 }
 
@@ -210,10 +211,10 @@ struct LeadLds {
 
 // What the shared controller code asks of a kernel's tables (the block
 // kernels' versions are with LeadB).
-__device__ inline int pair_ok(const Args&, const LeadLds&, int) { return 0; }
-__device__ inline void new_process(LeadLds&) {}
+__device__ inline int block_steps(const Args&, const LeadLds&, int) { return 0; }
+__device__ inline void new_process(const Args&, LeadLds&) {}
 __device__ inline double beta_of(const Args& a, const LeadLds&) { return a.st->beta; }
-__device__ inline const double* hess_of(const Args& a, const LeadLds&) { return a.st->H; }
+__device__ inline HessCol hess_of(const Args& a, const LeadLds&) { return HessCol{a.st->H, kLdh}; }
 
 __device__ inline void load_tables(const Args& a, LeadLds& L) {
   const State* st = a.st;
@@ -391,12 +392,12 @@ __device__ __attribute__((always_inline)) inline void scalar_step(const Args& a,
   }
   if (i <= jj) {
     st->H[(int64_t)jj * kLdh + i] = Hi;
-    cstore(&pb->coef[i], -Hi * sig / gam);
+    cstore(&pb->coefs[0][i], -Hi * sig / gam);
   }
   if (i == 0) {
     sg[jj] = sj;
     st->Minv[(int64_t)jj * kLdt + jj] = 1.0;
-    cstore(&pb->coef[jj + 1], sj / gam);
+    cstore(&pb->coefs[0][jj + 1], sj / gam);
     st->sigma[jj] = sj;
     st->gamma[jj] = gam;
     st->wn2[jj] = wn2;
@@ -498,18 +499,18 @@ __device__ inline void leader_mvec(const Args& a, int jj, const double* tv, Lead
     const double s0 = L.sigma[0];
     const double h = s0 * r * (jj == 0 ? xw : aw);
     Hc[0] = h;
-    cstore(&pb->coef[0], -h * s0 / r);
+    cstore(&pb->coefs[0][0], -h * s0 / r);
     nx.i = 1;                                // jj == 0: 1 = jj + 1, the norm
   } else {
     // ioCGS: both products of the window from the same w
     const double h = sj * r * xw;
     Hc[jj] = h;
-    cstore(&pb->coef[jj], -h * sj / r);
+    cstore(&pb->coefs[0][jj], -h * sj / r);
     if (jj >= 1) {
       const double sa = L.sigma[jj - 1];
       const double ha = sa * r * aw;
       Hc[jj - 1] = ha;
-      cstore(&pb->coef[jj - 1], -ha * sa / r);
+      cstore(&pb->coefs[0][jj - 1], -ha * sa / r);
     }
     nx.i = jj + 1;
   }
@@ -534,7 +535,7 @@ __device__ inline void leader_proj(const Args& a, int jj, int i, double s, LeadL
     const double si = L.sigma[i];
     const double h = si * r * s;
     Hc[i] = h;
-    cstore(&pb->coef[i], -h * si / r);
+    cstore(&pb->coefs[0][i], -h * si / r);
     nx.i = i + 1;
     nx.phase = (int)PH_PROJ;
     return;
@@ -601,7 +602,7 @@ __device__ __attribute__((always_inline)) inline void expm_phase(const Args& a, 
   if (happy && !fixed) tau = a.h - t;
   int dec = D_ACCEPT;
   while (true) {
-    expm_hbar(a, hess_of(a, L), kLdh, m, tau, happy, st->F, lds);
+    expm_hbar(a, hess_of(a, L), m, tau, happy, st->F, lds);
     if (kp_tid() == 0) {
       st->expm_evals += 1;
       const double err = happy ? 0.0 : beta * fabs(st->F[m]);
@@ -634,7 +635,7 @@ __device__ __attribute__((always_inline)) inline void expm_phase(const Args& a, 
   }
   if (dec == D_ACCEPT) {
     for (int i = kp_tid(); i < m; i += kThreads)
-      cstore(&pb->coef[i], beta * st->F[i] * L.sigma[i]);
+      cstore(&pb->coefs[0][i], beta * st->F[i] * L.sigma[i]);
     if (kp_tid() == 0) {
       st->tau = tau;
       const int last = fixed ? (st->substeps + 1 >= a.fixed_substeps) : (tau >= a.h - t);
@@ -699,7 +700,7 @@ __device__ __attribute__((always_inline)) inline void leader_combine(const Args&
   st->m_target = fixed ? a.fixed_m : st->m_cur;
   L.breakdown = 0;
   L.m_target = st->m_target;
-  new_process(L);
+  new_process(a, L);
   begin_steps(a, L, nx, 0, 0);
 }
 

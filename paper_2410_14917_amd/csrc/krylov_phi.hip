@@ -103,7 +103,7 @@ __device__ __attribute__((always_inline)) inline void run_phase(const Args& a, d
       // update directly follows the matvec pass of the same Arnoldi process
       // in the same launch, since a launch pauses only after a close)
       if (c.upd) {
-        update_pass<TB>(a, c.j - 1, a.pub->coef, red, false, xl ? hl : nullptr);
+        update_pass<TB>(a, c.j - 1, a.pub->coefs[0], red, false, xl ? hl : nullptr);
         flag_publish(a, k);
         KP_TS(a, k, 1);
         flag_wait_neighbours(a, k);
@@ -132,7 +132,7 @@ __device__ __attribute__((always_inline)) inline void run_phase(const Args& a, d
       }
       break;
     case PH_CLOSE:
-      update_pass<TB>(a, c.j - 1, a.pub->coef, red, true, xl ? hl : nullptr);
+      update_pass<TB>(a, c.j - 1, a.pub->coefs[0], red, true, xl ? hl : nullptr);
       break;
     case PH_MVEC:
       if constexpr (MS) {
@@ -149,14 +149,14 @@ __device__ __attribute__((always_inline)) inline void run_phase(const Args& a, d
         // MGS: subtract the projection on v_{i-1}, then v_i . w (or the
         // norm); ioCGS: subtract both projections of the window, then the norm
         if (a.orth == KP_ORTH_MGS)
-          proj_pass<TB>(a, c.j, c.i - 1, c.i - 1, a.pub->coef, c.i <= c.j ? c.i : -1, c.i > c.j,
+          proj_pass<TB>(a, c.j, c.i - 1, c.i - 1, a.pub->coefs[0], c.i <= c.j ? c.i : -1, c.i > c.j,
                         red);
         else
-          proj_pass<TB>(a, c.j, max(0, c.j - 1), c.j, a.pub->coef, -1, true, red);
+          proj_pass<TB>(a, c.j, max(0, c.j - 1), c.j, a.pub->coefs[0], -1, true, red);
       }
       break;
     case PH_COMBINE:
-      combine_pass<TB>(a, c.m_eff, a.pub->coef, c.last != 0);
+      combine_pass<TB>(a, c.m_eff, a.pub->coefs[0], c.last != 0);
       break;
     case PH_FINISH:
       finish_pass(a, c.status == KP_STATUS_NONFINITE);
@@ -237,17 +237,35 @@ __device__ __attribute__((always_inline)) inline void run_phase(const Args& a, d
 // ---- block steps (the one-reduction forms with a float64 basis) ---------------
 // LDS carve-up (doubles): per-wave sums (the leader's serial work reuses
 // them), block-reduction scratch, reduced sums (the workgroup's own row
-// first), the coefficients of two columns, and the region that holds the
-// halo rows or x_j, w1, w2 (matvec_block).  The small exponential uses the
-// whole buffer.
+// first), the tail's sums, the coefficients of the pending columns, and the
+// two buffers of the on-chip region (or the halo rows).  The small
+// exponential uses the whole buffer.
 constexpr int kOffBRed = kWaves * kBSlots;
 constexpr int kOffBTv = kOffBRed + 4 * kWaves;
-constexpr int kOffBCf = kOffBTv + kBSlots;
-constexpr int kOffBHl = (kOffBCf + 2 * kCoefLd + 15) / 16 * 16;
+constexpr int kOffBTs = kOffBTv + kBSlots;
+constexpr int kOffBCf = kOffBTs + kBSlots;
+constexpr int kOffBHl = (kOffBCf + kS * kCoefLd + 1 + 15) / 16 * 16;
 constexpr int kLdsDoublesB = kOffBHl + kHaloCap;
 static_assert(kLdsDoublesB >= 2 * kNmPad * kNmPad, "the small exponential does not fit the phase buffer");
-static_assert(8 * 72 <= kWaves * kBSlots && kRg * kKStride <= kWaves * kBSlots, "leader scratch");
-static_assert(kBSlots <= kThreads, "one thread per slot");
+static_assert(kS * 72 <= kWaves * kBSlots && kRg * kKStride <= kWaves * kBSlots, "leader scratch");
+static_assert(kBSlots <= kThreads && kS * kCoefLd < kThreads, "one thread per slot");
+static_assert(kS == 3 && kS <= kCStride, "coefficient arrays, projections and norms of three columns");
+
+// Element pairs per thread of a tile and tiles of the on-chip region: one pair
+// up to 1024 elements per workgroup, two above.
+constexpr int kRBlk = 2;
+template <int R> constexpr int kKeepTiles = R == 1 ? 1 : kR / R;
+
+template <int R>
+__device__ __attribute__((always_inline)) inline void update_pending(const Args& a, const Ctl& c, const double* cf,
+                                                                     double* hl, double* red, bool want_norm) {
+  if (c.upd == 3)
+    update_block<R, 3>(a, c.j, c.pns, cf, hl, red, want_norm);
+  else if (c.upd == 2)
+    update_block<R, 2>(a, c.j, c.pns, cf, hl, red, want_norm);
+  else
+    update_block<R, 1>(a, c.j, c.pns, cf, hl, red, want_norm);
+}
 
 // One phase of the call for this workgroup (as run_phase).
 template <int R>
@@ -256,11 +274,12 @@ __device__ __attribute__((always_inline)) inline void run_phase_block(const Args
   double* sacc = lds;
   double* red = lds + kOffBRed;
   double* tv = lds + kOffBTv;
+  double* ts = lds + kOffBTs;
   double* cf = lds + kOffBCf;
   double* hl = lds + kOffBHl;
   const bool lead = wg_rank(a) == 0, owner = wg_rank(a) < a.nwg;
   const Ctl c = cur;
-  const int nslot = 4 * (c.j - c.na) + 10;
+  const int nslot = block_slots(c.j - c.na);
   KP_TS(a, k, 0);
   if (lead) KP_TSV(a, k, 4, c.phase * 1000 + c.j);
   if (owner) block_reset(a, k);
@@ -268,28 +287,32 @@ __device__ __attribute__((always_inline)) inline void run_phase_block(const Args
     case PH_STAGE:
       stage_pass(a, red);
       break;
-    case PH_STEP:
+    case PH_STEP: {
+      for (int t = kp_tid(); t < kWaves * kBSlots; t += kThreads) sacc[t] = 0.0;
+      const double inv_mu = cload(&a.pub->inv_mu);
+      load_coefs(a, cf);
+      const double theta = cf[kS * kCoefLd];
       if (c.upd) {
-        load_coefs(a, cf);
-        if (c.upd == 2)
-          update_block<R, 2>(a, c.j, cf, hl, red, false);
-        else
-          update_block<R, 1>(a, c.j, cf, hl, red, false);
-        flag_publish(a, 2 * k);
+        update_pending<R>(a, c, cf, hl, red, false);
+        flag_publish(a, 4 * k);
         KP_TS(a, k, 1);
-        flag_wait_neighbours(a, 2 * k);
-        KP_TS(a, k, 2);
       } else {
         wait_all_stores();   // (the resets, before the partial sums)
       }
+      if (lead && kp_tid() >= kThreads - 64) tail_block(a, c.j, c.na, c.ns, theta, ts);
+      if (c.upd) {
+        flag_wait_neighbours(a, 4 * k);
+        KP_TS(a, k, 2);
+      }
       if (a.keep_xw)         // (implies halo_lds)
-        matvec_block<R, true, true>(a, c.j, c.na, c.two, c.upd != 0, sacc, hl, k);
+        matvec_keep<R, kKeepTiles<R>, true>(a, c.j, c.na, c.ns, c.upd != 0, theta, inv_mu, sacc, hl, k);
       else if (a.halo_lds)
-        matvec_block<R, false, true>(a, c.j, c.na, c.two, c.upd != 0, sacc, hl, k);
+        matvec_stream<R, true>(a, c.j, c.na, c.ns, theta, inv_mu, sacc, hl, k);
       else
-        matvec_block<R, false, false>(a, c.j, c.na, c.two, c.upd != 0, sacc, hl, k);
+        matvec_stream<R, false>(a, c.j, c.na, c.ns, theta, inv_mu, sacc, hl, k);
+      __syncthreads();
       if (kp_tid() < nslot) {
-        double s = 0.0;
+        double s = lead ? ts[kp_tid()] : 0.0;
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) s += sacc[w * kBSlots + kp_tid()];
         if (lead) tv[kp_tid()] = s;
@@ -297,12 +320,10 @@ __device__ __attribute__((always_inline)) inline void run_phase_block(const Args
           cstore(block_part(a, k) + (int64_t)wg_rank(a) * a.bstride + kp_tid(), s);
       }
       break;
+    }
     case PH_CLOSE:
       load_coefs(a, cf);
-      if (c.upd == 2)
-        update_block<R, 2>(a, c.j, cf, hl, red, true);
-      else
-        update_block<R, 1>(a, c.j, cf, hl, red, true);
+      update_pending<R>(a, c, cf, hl, red, true);
       break;
     case PH_COMBINE:
       load_coefs(a, cf);
@@ -343,7 +364,7 @@ __device__ __attribute__((always_inline)) inline void run_phase_block(const Args
       block_gather(a, k, nslot, tv, tv, &ok);
       if (!ok) return;
       KP_TS(a, k, 5);
-      block_scalar(a, c.j, c.na, c.two, tv, L, sacc, nxt);
+      block_scalar(a, c.j, c.na, c.ns, tv, L, sacc, nxt);
       // vector passes of Algorithm 4's count that stayed in LDS: 4 per step
       // (x_j and w in the update, x_j in the matvec, the store of w), but 1
       // where the step starts without an update
@@ -352,8 +373,8 @@ __device__ __attribute__((always_inline)) inline void run_phase_block(const Args
       break;
     }
     case PH_CLOSE:
-      reduce_partials(a, 2, tv, sacc);
-      block_close(a, tv[0], tv[1], L, nxt);
+      reduce_partials(a, kS, tv, sacc);
+      block_close(a, tv, L, nxt);
       break;
     case PH_EXPM:
       store_tables_b(a, L, false, c.j);
@@ -389,7 +410,7 @@ __global__ __launch_bounds__(kThreads) void k_blk(Args a, int arnoldi_only) {
   if (kp_tid() == 0) {
     const unsigned long long w = cload(release_word(a));
     s_k = (unsigned)(w >> 32);
-    cur = ctl_unpack((unsigned)w);
+    cur = ctl_unpack((unsigned)w, a.block != 0);
     ok = aborted(a) ? 0 : 1;
   }
   if (wg_rank(a) == 0) load_tables_b(a, lead, arnoldi_only != 0);
@@ -421,7 +442,7 @@ __global__ __launch_bounds__(kThreads) void k_run(Args a, int arnoldi_only) {
     // barriers released by earlier launches, and the control they announced
     const unsigned long long w = cload(release_word(a));
     s_k = (unsigned)(w >> 32);
-    cur = ctl_unpack((unsigned)w);
+    cur = ctl_unpack((unsigned)w, a.block != 0);
     ok = aborted(a) ? 0 : 1;
   }
   if (wg_rank(a) == 0) load_tables(a, lead);
@@ -453,7 +474,7 @@ __device__ inline void init_problem(const Args& a, int m_target, int nflags, int
     for (int i = b * (int)blockDim.x + kp_tid(); i < n; i += nb * (int)blockDim.x) sp[i] = empty;
   }
   if (b != 0) return;
-  for (int i = kp_tid(); i < kMMax + 2; i += blockDim.x) a.pub->coef[i] = a.pub->coef2[i] = 0.0;
+  for (int i = kp_tid(); i < kMMax + 2; i += blockDim.x) a.pub->coefs[0][i] = a.pub->coefs[1][i] = a.pub->coefs[2][i] = 0.0;
   for (int i = kp_tid(); i < nflags; i += blockDim.x) a.flags[i] = 0u;
   if (!a.block) for (int i = kp_tid(); i < kLdh * kMMax; i += blockDim.x) st->H[i] = 0.0;
   if (!a.block)
@@ -472,6 +493,7 @@ __device__ inline void init_problem(const Args& a, int m_target, int nflags, int
   pb->status = KP_STATUS_OK;
   pb->inv_mu = 1.0;
   pb->xscale = 1.0;
+  pb->shift = 0.0;
   st->m_target = m_target;
   st->m_cur = m_target;
   st->breakdown = 0;
@@ -481,6 +503,7 @@ __device__ inline void init_problem(const Args& a, int m_target, int nflags, int
   st->m_last = 0;
   st->onchip = 0;
   st->nopair = 0;
+  st->theta = 0.0;
   st->t = 0.0;
   st->tau = a.tau0;
   st->beta = 0.0;
@@ -492,7 +515,7 @@ __device__ inline void init_problem(const Args& a, int m_target, int nflags, int
 // object and its placement does not move when the other kernels change size
 // (its run time varied by about 1 % with placement alone, with identical
 // instructions).
-template __global__ void k_blk<kR>(Args, int);
+template __global__ void k_blk<kRBlk>(Args, int);
 template __global__ void k_blk<1>(Args, int);
 template __global__ void k_run<float, false>(Args, int);
 template __global__ void k_run<double, true>(Args, int);
@@ -623,7 +646,7 @@ __global__ __launch_bounds__(kThreads) void k_batch(BatchDesc d) {
     if (kp_tid() == 0) {
       const unsigned long long w = cload(release_word(a));
       s_k = (unsigned)(w >> 32);
-      cur = ctl_unpack((unsigned)w);
+      cur = ctl_unpack((unsigned)w, a.block != 0);
       ok = aborted(a) ? 0 : 1;
     }
     if (wg_rank(a) == 0) {
@@ -639,7 +662,7 @@ __global__ __launch_bounds__(kThreads) void k_batch(BatchDesc d) {
       if (!ok || cur.phase == PH_DONE) break;
       ++k;
       if constexpr (BLK)
-        run_phase_block<kR>(a, lds, lead, cur, nxt, ok, k);
+        run_phase_block<kRBlk>(a, lds, lead, cur, nxt, ok, k);
       else
         run_phase<TB, MS>(a, lds, lead, cur, nxt, ok, kept, k);
     }
@@ -887,7 +910,7 @@ __global__ __launch_bounds__(kThreads) void k_read_probe(const double2* x, int64
 // Small exponential alone (test entry): F = exp(tau Hbar_m) e_1 from st->H.
 __global__ __launch_bounds__(kThreads) void k_expm_test(Args a, int m, double tau) {
   __shared__ __attribute__((aligned(16))) double lds[kLdsDoubles];
-  expm_hbar(a, a.st->H, kLdh, m, tau, false, a.st->F, lds);
+  expm_hbar(a, HessCol{a.st->H, kLdh}, m, tau, false, a.st->F, lds);
 }
 
 // Workspace of the allocation-free entry point (kp_phi_combo_noalloc): one
@@ -1061,15 +1084,15 @@ int build_args(const kp_ctx* ctx, const kp_op* A, const double* B, int p, int64_
   r.stop_j = INT_MAX;
   r.basis_f32 = cfg.basis_dtype == KP_BASIS_F32 ? 1 : 0;
   r.block = (!r.basis_f32 && !kp::orth_multi_sync(r.orth)) ? 1 : 0;
-  r.bstride = 4 * m_max + 8;
-  r.tile_r = kp::kR;
+  r.bstride = kp::kNv * m_max + 24;
+  r.tile_r = kp::kRBlk;
   r.h = h;
   r.tol = tol > 0.0 ? tol : 1.0;
   r.delta = cfg.fallback_delta == 0.0 ? 1e-10 : (cfg.fallback_delta < 0.0 ? 0.0 : cfg.fallback_delta);
   r.eps_bd = cfg.breakdown_eps == 0.0 ? 1e-12 : cfg.breakdown_eps;
-  // two steps per reduction: H-GSMGS only (see kp_block.h); a fallback
-  // threshold above the pair guard takes the exact norm at every step, so
-  // there is no estimate to divide a first vector by
+  // several steps per reduction: H-GSMGS only (see kp_block.h); a fallback
+  // threshold above the guard takes the exact norm at every step, so there is
+  // no estimate to divide a first vector by
   r.pairs = (r.block && r.orth == KP_ORTH_H_GSMGS && r.delta <= kp::kGuard) ? 1 : 0;
   *a = r;
   return KP_OK;
@@ -1089,7 +1112,7 @@ int occupancy(kp_ctx* ctx, const void* kernel, int which) {
 const void* run_kernel(const Args& a) {
   if (a.block)
     return a.tile_r == 1 ? reinterpret_cast<const void*>(&kp::k_blk<1>)
-                         : reinterpret_cast<const void*>(&kp::k_blk<kp::kR>);
+                         : reinterpret_cast<const void*>(&kp::k_blk<kp::kRBlk>);
   if (kp::orth_multi_sync(a.orth))
     return a.basis_f32 ? reinterpret_cast<const void*>(&kp::k_run<float, true>)
                        : reinterpret_cast<const void*>(&kp::k_run<double, true>);
@@ -1101,7 +1124,7 @@ const void* run_kernel(const Args& a) {
 int kernel_occupancy(kp_ctx* ctx, const Args& a) {
   if (!a.block)
     return occupancy(ctx, run_kernel(a), kp::orth_multi_sync(a.orth) ? (a.basis_f32 ? 3 : 2) : 1);
-  return std::min(occupancy(ctx, reinterpret_cast<const void*>(&kp::k_blk<kp::kR>), 0),
+  return std::min(occupancy(ctx, reinterpret_cast<const void*>(&kp::k_blk<kp::kRBlk>), 0),
                   occupancy(ctx, reinterpret_cast<const void*>(&kp::k_blk<1>), 4));
 }
 
@@ -1188,7 +1211,7 @@ void geometry(int ncu_slots, int rows_cfg, Args* a, bool spread = true) {
                 2 * (int64_t)a->nx <= 2 * (int64_t)kp::kThreads * kp::kR &&
                 !kp::orth_multi_sync(a->orth) && 4 * kp::kR * kp::kThreads <= kp::kHaloCap)
                    ? 1 : 0;
-  if (a->block) a->tile_r = rows * a->nx <= 2 * (int64_t)kp::kThreads ? 1 : kp::kR;
+  if (a->block) a->tile_r = rows * a->nx <= 2 * (int64_t)kp::kThreads ? 1 : kp::kRBlk;
 }
 
 // Partial sums (doubles) of nwg workgroups: the counted buffer, the two step

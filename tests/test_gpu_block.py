@@ -1,12 +1,12 @@
-"""Block steps (two Arnoldi steps per reduction, float64 H-GSMGS) on the
-partitions where their kernels can go wrong: one and four element pairs per
-thread at the edges of their tiles, the leader's own gather (up to 16 partial
-rows) and the two-hop one, x_j and w on chip or in memory, halo rows in LDS or
-not, two planes, odd and even Krylov dimensions (the last step of an odd one is
-single), and the points where a pair has to stop after its first vector.
+"""Block steps (up to three Arnoldi steps per reduction, float64 H-GSMGS) on the
+partitions where their kernels can go wrong: one and two element pairs per
+thread at the edges of their tiles, one and two tiles on chip, the leader's own
+gather (up to 16 partial rows) and the two-hop one, the block's vectors on chip
+or in memory, halo rows in LDS or not, two planes, Krylov dimensions of every
+remainder modulo three, and the points where a block has to stop early.
 
-Tolerances: the pair's Hessenberg matrix has the single steps' error to a small
-factor (its second vector costs one more cancellation, 12 at most on a
+Tolerances: the block's Hessenberg matrix has the single steps' error to a small
+factor (its later vectors cost one more cancellation each, 12 at most on a
 diffusion operator), so the Arnoldi bounds of the single steps hold: 1e-12 for
 H and for the loss of orthogonality at m <= 30, 1e-10 for results."""
 import numpy as np
@@ -30,8 +30,10 @@ GRIDS = [
     (W.OP_ADR, 64, 34, 3, 3),           # 12: the leader's gather, a ragged last one
     (W.OP_ADR, 64, 32, 2, 2),           # 16, the most it takes
     (W.OP_ALLEN_CAHN, 1024, 20, 1, 1),  # 1024 elements: the largest one-pair tile
-    (W.OP_ALLEN_CAHN, 1026, 20, 1, 1),  # 1026: the smallest four-pair tile
-    (W.OP_ADR, 512, 40, 2, 8),          # 4096: the largest tile on chip
+    (W.OP_ALLEN_CAHN, 1026, 20, 1, 1),  # 1026: the smallest two-pair tile
+    (W.OP_ADR, 512, 40, 2, 4),          # 2048: one full two-pair tile
+    (W.OP_ADR, 514, 40, 2, 4),          # 2056: the second tile's first pairs
+    (W.OP_ADR, 512, 40, 2, 8),          # 4096: the largest region on chip
     (W.OP_ADR, 512, 40, 2, 9),          # 4608: two tiles, nothing on chip
     (W.OP_ADR, 333, 36, 2, 4),          # odd rows: padding element, pair alignment
     (W.OP_ADR, 2050, 18, 2, 1),         # rows too wide for the on-chip path
@@ -43,7 +45,7 @@ GRIDS = [
 
 
 @pytest.mark.parametrize("grid", GRIDS, ids=lambda g: f"{g[0]}-{g[1]}x{g[2]}-r{g[4]}")
-@pytest.mark.parametrize("m", [16, 13])
+@pytest.mark.parametrize("m", [14, 15, 16])
 def test_block_steps_match_single_reduction_oracle(grid, m):
     kind, nx, ny, p, rows = grid
     print(f"block: kind={kind} {nx}x{ny} p={p} rows={rows} m={m}", flush=True)
@@ -71,7 +73,7 @@ def test_block_steps_match_single_reduction_oracle(grid, m):
     assert torch.equal(y, y2)
 
 
-@pytest.mark.parametrize("m", [1, 2, 3, 4])
+@pytest.mark.parametrize("m", [1, 2, 3, 4, 5])
 def test_block_steps_of_the_shortest_processes(m):
     pr = W.random_problem(43, nx=40, ny=36, p=1, h=1e-3, nu=1e-3)
     op = kp.Operator.from_host(pr.op)
@@ -84,9 +86,9 @@ def test_block_steps_of_the_shortest_processes(m):
 
 @pytest.mark.parametrize("nval", [1, 2, 3, 4, 5, 6])
 @pytest.mark.parametrize("p", [0, 1])
-def test_pair_stops_at_an_invariant_subspace(nval, p):
+def test_block_stops_at_an_invariant_subspace(nval, p):
     """A diagonal operator with nval values: the process ends at nval + p
-    columns, in the first or in the second vector of a pair."""
+    columns, in the first or in a later vector of a block."""
     d = np.linspace(-3.0, 1.0, nval)
     nx, ny = 70, 40
     diag = d[np.random.default_rng(5).integers(0, nval, nx * ny)]
@@ -102,7 +104,7 @@ def test_pair_stops_at_an_invariant_subspace(nval, p):
 
 def test_nearly_scalar_operator_takes_single_steps():
     """A = -50 I + (small): every vector lies almost in the span of the ones
-    before, the pair's guard keeps single steps, with the oracle's result."""
+    before, the guard keeps single steps, with the oracle's result."""
     rng = np.random.default_rng(8)
     op_h = W.Operator(kind=W.OP_ADR, nx=60, ny=50, nu=1e-6, react=-50.0,
                       field0=0.1 * rng.standard_normal(3000))
