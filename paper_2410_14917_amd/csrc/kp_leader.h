@@ -587,7 +587,7 @@ __device__ inline double tau_factor_pi(double omega, double omega_prev, int m) {
   return fmin(4.0, fmax(0.2, f));
 }
 
-template <typename LT>
+template <bool F32, typename LT>
 __device__ __attribute__((always_inline)) inline void expm_phase(const Args& a, double* lds, LT& L,
                                                                 Ctl& nx) {
   __shared__ int s_dec;
@@ -602,7 +602,10 @@ __device__ __attribute__((always_inline)) inline void expm_phase(const Args& a, 
   if (happy && !fixed) tau = a.h - t;
   int dec = D_ACCEPT;
   while (true) {
-    expm_hbar(a, hess_of(a, L), m, tau, happy, st->F, lds);
+    if constexpr (F32)
+      expm_hbar65(a, hess_of(a, L), m, tau, happy, st->F, lds);
+    else
+      expm_hbar(hess_of(a, L), m, tau, happy, st->F, lds);
     if (kp_tid() == 0) {
       st->expm_evals += 1;
       const double err = happy ? 0.0 : beta * fabs(st->F[m]);

@@ -51,7 +51,7 @@ constexpr int kLdsDoubles = (2 * kNmPad * kNmPad > kOffHl + kHaloCap) ? 2 * kNmP
 static_assert(kOffGrp + kRg * kKStride <= kOffCoef, "grp overlaps coef");
 static_assert(kOffWk + kWkDoubles <= kOffCoef, "wk overlaps coef");
 static_assert(kOffOwn + kKStride <= kOffHl, "tv / own overlap the halo copy");
-static_assert(kLdsDoubles >= 2 * kNmPad * kNmPad, "the small exponential does not fit the phase buffer");
+static_assert(kLdsDoubles >= kExDoubles, "the small exponential does not fit the phase buffer");
 
 // One phase of the call for this workgroup.  MS: the kernel also runs the
 // processes with one reduction per inner product (MGS) or per window
@@ -216,7 +216,7 @@ __device__ __attribute__((always_inline)) inline void run_phase(const Args& a, d
       }
       break;
     case PH_EXPM:
-      expm_phase(a, lds, L, nxt);
+      expm_phase<sizeof(TB) == 4>(a, lds, L, nxt);
       break;
     case PH_COMBINE:
       leader_combine(a, L, nxt);
@@ -246,7 +246,7 @@ constexpr int kOffBTs = kOffBTv + kBSlots;
 constexpr int kOffBCf = kOffBTs + kBSlots;
 constexpr int kOffBHl = (kOffBCf + kS * kCoefLd + 1 + 15) / 16 * 16;
 constexpr int kLdsDoublesB = kOffBHl + kHaloCap;
-static_assert(kLdsDoublesB >= 2 * kNmPad * kNmPad, "the small exponential does not fit the phase buffer");
+static_assert(kLdsDoublesB >= kExDoubles, "the small exponential does not fit the phase buffer");
 static_assert(kS * 72 <= kWaves * kBSlots && kRg * kKStride <= kWaves * kBSlots, "leader scratch");
 static_assert(kBSlots <= kThreads && kS * kCoefLd < kThreads, "one thread per slot");
 static_assert(kS == 3 && kS <= kCStride, "coefficient arrays, projections and norms of three columns");
@@ -378,7 +378,7 @@ __device__ __attribute__((always_inline)) inline void run_phase_block(const Args
       break;
     case PH_EXPM:
       store_tables_b(a, L, false, c.j);
-      expm_phase(a, lds, L, nxt);
+      expm_phase<false>(a, lds, L, nxt);
       break;
     case PH_COMBINE:
       leader_combine(a, L, nxt);
@@ -910,7 +910,7 @@ __global__ __launch_bounds__(kThreads) void k_read_probe(const double2* x, int64
 // Small exponential alone (test entry): F = exp(tau Hbar_m) e_1 from st->H.
 __global__ __launch_bounds__(kThreads) void k_expm_test(Args a, int m, double tau) {
   __shared__ __attribute__((aligned(16))) double lds[kLdsDoubles];
-  expm_hbar(a, HessCol{a.st->H, kLdh}, m, tau, false, a.st->F, lds);
+  expm_hbar(HessCol{a.st->H, kLdh}, m, tau, false, a.st->F, lds);
 }
 
 // Workspace of the allocation-free entry point (kp_phi_combo_noalloc): one
