@@ -39,7 +39,9 @@
 // steps per reduction, then three): 64 x 64, m = 40 fixed 1576, 708, 622 us;
 // 256^2 adaptive (tol 1e-8, m <= 48) 10.48, 5.16, 4.40 ms; 1024^2 Allen-Cahn
 // benchmark call 93.7, 59.5, 51.3 ms; 2 x 1000 x 1200 Brusselator 102.3, 66.8,
-// 49.8 ms; 512 uneven problems in one launch 1333, 841, 603 ms.
+// 49.8 ms; 512 uneven problems in one launch 1333, 841, 603 ms.  With the
+// stencil from LDS and small_dots: 64 x 64 519 us, 256^2 3.75 ms, 512^2 forward
+// and backward 39.9 -> 34.6 ms.
 #pragma once
 
 #include "kp_leader.h"
@@ -72,7 +74,7 @@ struct HessPacked {
 };
 
 // What the leader's serial work reads, in LDS for the whole launch.
-struct LeadB {
+struct alignas(16) LeadB {
   double tab[kMMax * kTabLd];      // <u_r, u_k> at [r * kTabLd + k], r != k (L + L')
   double H[kMMax * (kMMax + 3) / 2 + 8];   // Hessenberg, packed (hcol)
   double sigma[kMMax + 8];         // unit scale of column i
@@ -198,11 +200,20 @@ __device__ inline double wave_sum4(double v0, double v1, double v2, double v3) {
 
 // ---- passes ------------------------------------------------------------------
 //
-// A workgroup's on-chip region (keep_xw; one plane) is two LDS buffers of kR *
-// kThreads pairs.  A holds the vector the next product multiplies (x_j, then
-// the w_k but the last) and B its halo rows; after the last product B takes
-// the last w.  So at the next update the last w is in B, the one before it in
-// A, and a third one in memory (w_1 of three steps).
+// On chip (keep_xw; one plane, at most kKeepMax elements per workgroup): the
+// vector the next product multiplies (x_j, then the w_k but the last) sits in
+// LDS between its two halo rows, so the stencil is five LDS reads at fixed
+// offsets for every product of a phase.  Afterwards the last w takes its place.
+// Up to 1024 elements (R = 1) the other vectors of the block sit in LDS too
+// (kSmallVec each, after the halo row: x_{j-2}, x_{j-1}, x_j, w_1, w_2).  Above, the w
+// before the last one takes the space of the leader's tables, which the other
+// workgroups do not use (the leader keeps it in memory), and the first of three
+// is in memory.
+constexpr int kKeepMax = 2 * kR * kThreads;
+constexpr int kSmallVec = 2 * kThreads;
+__device__ inline int keep_off(const Args& a) { return (a.nx + 1) & ~1; }   // own elements in the LDS vector
+// (first of the five vectors: R = 1 has n <= kSmallVec and so nx <= kSmallVec)
+__device__ inline double* small_vec(double* hl, int q) { return hl + kHaloCap - (5 - q) * kSmallVec; }
 
 template <int R>
 __device__ inline void tile_pairs_r(int64_t q0, int64_t pend, uint32_t* lo, bool* ok) {
@@ -309,18 +320,21 @@ __device__ inline void tail_update_b(const Args& a, double* V, int nc, const dou
 
 // The U pending columns j - U + 1 .. j (column l: weights cf[l] on the columns
 // 0 .. j - U, then on w_1 .. w_{l+1}), in place of the w_k.  pns: vectors the
-// previous phase made (>= U), which says where keep_xw left them.  keep_xw
-// also leaves x_j in A.  The halo rows of x_j are published.  want_norm:
+// previous phase made (>= U), which says where keep_xw left them (wbuf: the
+// workgroup's second buffer, null in the leader).  keep_xw also leaves x_j in
+// LDS.  The halo rows of x_j are published.  want_norm:
 // partial slot l = the squared norm of new column l.
 template <int R, int U>
 __device__ __attribute__((always_inline)) inline void update_block(const Args& a, int j, int pns, const double* cf,
-                                                                   double* hl, double* red, bool want_norm) {
+                                                                   double* hl, const double* wbuf, double* red,
+                                                                   bool want_norm) {
   double* V = reinterpret_cast<double*>(a.V);
   const int64_t ld = a.ld;
   const int nc = j - U + 1;
   const bool keep = a.keep_xw != 0;
-  double2* A2 = reinterpret_cast<double2*>(hl);
-  const double2* B2 = reinterpret_cast<const double2*>(hl) + kR * kThreads;
+  const bool small = R == 1 && keep;   // (every vector of the block in LDS)
+  double2* X2 = reinterpret_cast<double2*>(hl + keep_off(a));
+  const double2* W2 = reinterpret_cast<const double2*>(wbuf);
   const Rows o = own_rows(a);
   double ss[U];
 #pragma unroll
@@ -348,10 +362,16 @@ __device__ __attribute__((always_inline)) inline void update_block(const Args& a
 #pragma unroll
         for (int r = 0; r < R; ++r) {
           double2 w;
-          if (keep && k >= pns - 2)
-            w = (k == pns - 1) ? B2[slot + r * kThreads] : A2[slot + r * kThreads];
-          else
+          if (keep && k == pns - 1) {
+            w = X2[slot + r * kThreads];
+            if (t0 + lo[r] + 1 >= sg.end) w.y = 0.0;   // (a halo row follows an odd end)
+          } else if (small) {
+            w = reinterpret_cast<const double2*>(small_vec(hl, kS + k))[slot + r * kThreads];
+          } else if (keep && k == pns - 2 && wbuf) {
+            w = W2[slot + r * kThreads];
+          } else {
             w = Pair<double>::load(wcol + lo[r]);
+          }
 #pragma unroll
           for (int l = k; l < U; ++l) {
             const double c = cf[l * kCoefLd + nc + k];
@@ -371,7 +391,11 @@ __device__ __attribute__((always_inline)) inline void update_block(const Args& a
             ss[l] += acc[l][r].x * acc[l][r].x + acc[l][r].y * acc[l][r].y;
           }
           const double2 x = acc[U - 1][r];
-          if (keep) A2[(int)(q0 - pbeg) + kp_tid() + r * kThreads] = x;
+          if (keep) X2[(int)(q0 - pbeg) + kp_tid() + r * kThreads] = x;
+          if (small)
+#pragma unroll
+            for (int l = 0; l < U; ++l)
+              reinterpret_cast<double2*>(small_vec(hl, kS - U + l))[kp_tid()] = acc[l][r];
           publish_pair(a, a.hx, sg, t0 + lo[r], x.x, x.y);
         }
       }
@@ -447,6 +471,102 @@ __device__ __attribute__((always_inline)) inline void columns_block(
     const int i2 = i1 + C;
     if (i2 < jo) load_block<R, C>(V, ld, t0, i2, min(C, jo - i2), lo, va);
     dots_block<R, C, FULL>(vb, b, i1, min(C, jo - i1), sacc);
+  }
+}
+
+// The same products where all vectors of the block sit in LDS (R = 1, n <=
+// kSmallVec elements): wave by wave a column of its own, 4 pairs per lane, so
+// each column is reduced by one wave once (twice above 512 elements) instead
+// of by every wave: the reductions, about 70 instructions each on a lone wave
+// per SIMD, were what these workgroups spent their time on (64 x 64, 512
+// elements: 0.33 us per column before, 0.1 after).  The loads of
+// two columns are in flight while two are reduced.
+__device__ __attribute__((always_inline)) inline void small_dots(const Args& a, int64_t beg, int n, int j, int jo,
+                                                                 int ns, double* hl, double* srow) {
+  const double* V = reinterpret_cast<const double*>(a.V) + beg;
+  const int64_t ld = a.ld;
+  const int lane = kp_tid() & 63, wv = __builtin_amdgcn_readfirstlane(kp_tid() >> 6);
+  const int np = (n + 1) >> 1;
+  const double* xl = hl + keep_off(a);
+  for (int h = 0; h * 256 < np; ++h) {
+    int e[4];
+    bool ok[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int q = h * 256 + r * 64 + lane;
+      ok[r] = q < np;
+      e[r] = 2 * min(q, np - 1);
+    }
+    auto load = [&](int i, double2 (&v)[2][4]) {   // columns i, i + kWaves
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const double* vc = uniform_ptr(V + (int64_t)min(i + c * kWaves, max(jo - 1, 0)) * ld);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[c][r] = load_at(vc, (uint32_t)e[r] * 8u);
+      }
+    };
+    double2 va[2][4], vb[2][4];
+    if (wv < jo) load(wv, va);
+    double2 b[kNv][4];
+#pragma unroll
+    for (int q = 0; q < kNv; ++q) {
+      const bool on = q < kS ? (q == kS - 1 || j - (kS - 1) + q >= jo) : (q - kS < ns);
+      const bool last = q - kS == ns - 1;
+      const double* src = last ? xl : small_vec(hl, min(q, 4));
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const double2 x = on ? *reinterpret_cast<const double2*>(src + e[r]) : make_double2(0.0, 0.0);
+        b[q][r] = make_double2(ok[r] ? x.x : 0.0, (ok[r] && e[r] + 1 < n) ? x.y : 0.0);
+      }
+    }
+    // products among the block's vectors: four per wave
+    if (wv * 4 < kGram) {
+      double g[4] = {0.0, 0.0, 0.0, 0.0};
+      int id = 0;
+#pragma unroll
+      for (int p = 0; p < kNv; ++p)
+#pragma unroll
+        for (int q = p; q < kNv; ++q, ++id)
+          if ((id >> 2) == wv) {
+            double s = 0.0;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) s = __builtin_fma(b[p][r].y, b[q][r].y, __builtin_fma(b[p][r].x, b[q][r].x, s));
+            g[id & 3] = s;
+          }
+      const double s = wave_sum4(g[0], g[1], g[2], g[3]);
+      if (lane < 4 && wv * 4 + lane < kGram) srow[kNv * jo + wv * 4 + lane] += s;
+    }
+    auto dots = [&](int i, const double2 (&v)[2][4]) {
+      double s[2][kNv];
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int q = 0; q < kNv; ++q) {
+          s[c][q] = 0.0;
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            s[c][q] = __builtin_fma(v[c][r].y, b[q][r].y, __builtin_fma(v[c][r].x, b[q][r].x, s[c][q]));
+        }
+      const double t0 = wave_sum4(s[0][0], s[0][1], s[0][2], s[0][3]);
+      const double t1 = wave_sum4(s[1][0], s[1][1], s[1][2], s[1][3]);
+      const double t2 = wave_sum4(s[0][4], s[0][5], s[1][4], s[1][5]);
+      if (lane < 4) {
+        const bool two = i + kWaves < jo;
+        srow[kNv * i + lane] += t0;
+        if (two) srow[kNv * (i + kWaves) + lane] += t1;
+        if (lane < 2)
+          srow[kNv * i + 4 + lane] += t2;
+        else if (two)
+          srow[kNv * (i + kWaves) + 2 + lane] += t2;
+      }
+    };
+    for (int i = wv; i < jo; i += 4 * kWaves) {
+      if (i + 2 * kWaves < jo) load(i + 2 * kWaves, vb);
+      dots(i, va);
+      if (i + 2 * kWaves >= jo) break;
+      if (i + 4 * kWaves < jo) load(i + 4 * kWaves, va);
+      dots(i + 2 * kWaves, vb);
+    }
   }
 }
 
@@ -559,79 +679,168 @@ __device__ inline void tail_next(const Args& a, double shift, double* tt) {
 
 // The block step from column j: w_1 .. w_ns and the partial sums of the
 // reduction.  na: unmeasured columns before x_j.  upd: the update of this
-// phase has left x_j in A (keep_xw).  The rows of w_k the neighbours need go
-// through the two halo buffers in turn (a neighbour has read the rows of w_{k-1}
-// before it publishes w_k, which this workgroup has seen before it publishes
-// w_{k+1}) and the same flags (value 4k + e; the update published 4k).
-template <int R, int T, bool HL>
+// phase has left x_j in LDS and published its halo rows.  The rows of w_k the
+// neighbours need go through the two halo buffers in turn (a neighbour has read
+// the rows of w_{k-1} before it publishes w_k, which this workgroup has seen
+// before it publishes w_{k+1}) and the same flags (value 4k + e; the update
+// published 4k).
+//
+// On chip.  What a product costs here is latency, not bytes: the fields, the
+// neighbour offsets and the first columns of B are read once per phase, before
+// the wait for the halo rows, and kept in registers.
+template <int R, int T>
 __device__ __attribute__((always_inline)) inline void matvec_keep(const Args& a, int j, int na, int ns, bool upd,
                                                                   double theta, double inv_mu, double* sacc,
-                                                                  double* hl, unsigned k) {
+                                                                  double* hl, double* wbuf, unsigned k) {
   double* V = reinterpret_cast<double*>(a.V);
   const int64_t ld = a.ld;
   const Rows o = own_rows(a);
-  const int jo = j - na;
+  const int jo = j - na, nx = a.nx;
   constexpr int C = kDotCols<R>;
-  double* lA = hl;
-  double* lB = hl + 2 * kR * kThreads;
-  double2* A2 = reinterpret_cast<double2*>(lA);
-  double2* B2 = reinterpret_cast<double2*>(lB);
+  constexpr int kBc = R == 1 ? 4 : 2;          // columns of B kept in registers
   double* xcol = V + (int64_t)j * ld;
   const Seg sg = seg_at(a, o, 0);
   const int64_t pend = (sg.end + 1) >> 1, pbeg = sg.beg >> 1;
+  const int n = (int)(sg.end - sg.beg);
+  double* X = hl + keep_off(a);                // own elements; row r0 - 1 before, row r1 after
   if (!upd) {
     const double* src = j == 0 ? a.u : xcol;
     for (int64_t q = pbeg + kp_tid(); q < pend; q += kThreads) {
       const double2 v = Pair<double>::load(src + 2 * q);
-      A2[q - pbeg] = v;
+      X[2 * (q - pbeg)] = v.x;
+      if (2 * q + 1 < sg.end) X[2 * (q - pbeg) + 1] = v.y;
       if (j == 0) Pair<double>::store(xcol + 2 * q, v.x, v.y);
     }
   }
-  double tt[kPMax];
-  tail_of_x(a, 0, inv_mu, tt);
-  stage_halo<double>(a, a.hx, o, lB);
-  __syncthreads();
-  double2 w[T][R];
-  for (int s = 0; s < ns; ++s) {
-    const LdsX x{lA, sg.beg};
+  // per pair: own offset (-1: none), wrapped east / west offsets of both
+  // elements, diagonal factor, columns of B
+  int e0[T][R], off[T][R][4];
+  double2 dg[T][R], bc[kBc][T][R];
 #pragma unroll
-    for (int t = 0; t < T; ++t) {
-      const int64_t q0 = pbeg + (int64_t)t * kThreads * R;
-      if (wave_in_tile(q0, pend)) {
-        uint32_t lo[R];
-        bool ok[R];
-        tile_pairs_r<R>(q0, pend, lo, ok);
-        aug_tile<double, HL, LdsX, R>(a, a.hx, o, sg, x, lB, 2 * q0, lo, tt, w[t]);
-        if (s)
+  for (int t = 0; t < T; ++t)
 #pragma unroll
-          for (int r = 0; r < R; ++r) {
-            const double2 c = A2[(int)(q0 - pbeg) + (lo[r] >> 1)];
-            w[t][r].x = __builtin_fma(-theta, c.x, w[t][r].x);
-            w[t][r].y = __builtin_fma(-theta, c.y, w[t][r].y);
-          }
-      }
+    for (int r = 0; r < R; ++r) {
+      const int e = 2 * ((t * R + r) * kThreads + kp_tid());
+      const int c = min(e, n - 1);             // (a lane without a pair repeats the last element)
+      const int64_t g = sg.beg + c;
+      const bool v1 = c + 1 < n;
+      const int64_t g1 = v1 ? g + 1 : g;
+      e0[t][r] = e < n ? c : -1;
+      const int row = (int)((unsigned)c / (unsigned)nx), ix = c - row * nx;
+      const bool last = ix == nx - 1;
+      const int c1 = v1 ? c + 1 : c, ix1 = v1 ? (last ? 0 : ix + 1) : ix;
+      off[t][r][0] = last ? c - ix : c + 1;
+      off[t][r][1] = ix == 0 ? c + nx - 1 : c - 1;
+      off[t][r][2] = ix1 == nx - 1 ? c1 - ix1 : c1 + 1;
+      off[t][r][3] = ix1 == 0 ? c1 + nx - 1 : c1 - 1;
+      const double u0 = a.f0 ? a.f0[g] : 0.0, u1 = a.f0 ? a.f0[g1] : 0.0;
+      if (a.kind == KP_OP_ADR)
+        dg[t][r] = make_double2(a.react + u0, a.react + u1);
+      else
+        dg[t][r] = make_double2(__builtin_fma(-3.0 * u0, u0, 1.0), __builtin_fma(-3.0 * u1, u1, 1.0));
+#pragma unroll
+      for (int b = 0; b < kBc; ++b)
+        if (b < a.pb) {
+          const double* col = a.B + (int64_t)(a.pb - b) * a.ldb;
+          bc[b][t][r] = make_double2(col[g], col[g1]);
+        }
     }
-    __syncthreads();   // every stencil read of A and B is done
-    if (s + 1 == ns) break;
-    double* const hxs = (s & 1) ? a.hx : a.hx2;
+  double tt[kPMax];
+  if (upd) {
+    flag_wait_neighbours(a, 4 * k);
+    KP_TS(a, k, 2);
+  }
+  tail_of_x(a, 0, inv_mu, tt);
+  const int bb = wg_rank(a);
+  const int wn = (o.r1 == a.ny) ? 0 : bb + 1, ws = (o.r0 == 0) ? a.nwg - 1 : bb - 1;
+  auto stage = [&](const double* hx) {
+    for (int ix = kp_tid(); ix < nx; ix += kThreads) {
+      const double vn = cload(hx + halo_at(a, wn, 0, 0, ix)), vs = cload(hx + halo_at(a, ws, 0, 1, ix));
+      X[n + ix] = vn;
+      X[ix - nx] = vs;
+    }
+    __syncthreads();
+  };
+  stage(a.hx);
+  for (int s = 0; s < ns; ++s) {
+    const double th = s ? theta : 0.0;
+    const bool last = s + 1 == ns;
+    double2 w[T][R];
 #pragma unroll
-    for (int t = 0; t < T; ++t) {
-      const int64_t q0 = pbeg + (int64_t)t * kThreads * R;
+    for (int t = 0; t < T; ++t)
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        const int64_t q = q0 + (int64_t)r * kThreads + kp_tid();
-        if (q < pend) {
-          A2[q - pbeg] = w[t][r];
-          publish_pair(a, hxs, sg, 2 * q, w[t][r].x, w[t][r].y);
-          if (s + 3 == ns) Pair<double>::store(V + (int64_t)(j + 1) * ld + 2 * q, w[t][r].x, w[t][r].y);
+        const int c = max(e0[t][r], 0);
+        const bool v1 = e0[t][r] >= 0 && c + 1 < n;
+        const int c1 = v1 ? c + 1 : c;
+        auto at = [&](int cc, int ie, int iw, double d) {
+          const double x = X[cc], xe = X[ie], xw = X[iw], xn = X[cc + nx], xs = X[cc - nx];
+          const double lap = __builtin_fma(a.cx, __builtin_fma(-2.0, x, xe + xw),
+                                           a.cy * __builtin_fma(-2.0, x, xn + xs));
+          const double adv = __builtin_fma(a.adx, xe - xw, a.ady * (xn - xs));
+          return __builtin_fma(d - th, x, a.kind == KP_OP_ADR ? lap + (a.transpose ? adv : -adv) : lap);
+        };
+        double y0 = at(c, off[t][r][0], off[t][r][1], dg[t][r].x);
+        double y1 = at(c1, off[t][r][2], off[t][r][3], dg[t][r].y);
+#pragma unroll
+        for (int b = 0; b < kBc; ++b)
+          if (b < a.pb) {
+            y0 = __builtin_fma(tt[b], bc[b][t][r].x, y0);
+            y1 = __builtin_fma(tt[b], bc[b][t][r].y, y1);
+          }
+        for (int b = kBc; b < a.pb; ++b) {
+          const double* col = a.B + (int64_t)(a.pb - b) * a.ldb + sg.beg;
+          double tb = tt[kPMax - 1];
+#pragma unroll
+          for (int q = kBc; q < kPMax - 1; ++q) tb = b == q ? tt[q] : tb;
+          y0 = __builtin_fma(tb, col[c], y0);
+          y1 = __builtin_fma(tb, col[c1], y1);
         }
+        w[t][r] = make_double2(e0[t][r] >= 0 ? y0 : 0.0, v1 ? y1 : 0.0);
       }
+    __syncthreads();   // every read of X is done
+    double* const hxs = (s & 1) ? a.hx : a.hx2;
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if (e0[t][r] >= 0) {
+          const int c = e0[t][r];
+          X[c] = w[t][r].x;
+          if (c + 1 < n) X[c + 1] = w[t][r].y;
+          if (!last) {
+            publish_pair(a, hxs, sg, sg.beg + c, w[t][r].x, w[t][r].y);
+            // its place for the inner products and the next update
+            if (R == 1)
+              *reinterpret_cast<double2*>(small_vec(hl, kS + s) + c) = w[t][r];
+            else if (s + 2 == ns && wbuf)
+              *reinterpret_cast<double2*>(wbuf + c) = w[t][r];
+            else
+              Pair<double>::store(V + (int64_t)(j + 1 + s) * ld + sg.beg + c, w[t][r].x, w[t][r].y);
+          }
+        }
+    if (!last) {
+      flag_publish(a, 4 * k + 1 + s);
+      tail_next(a, th, tt);
+      flag_wait_neighbours(a, 4 * k + 1 + s);
+      stage(hxs);
     }
-    flag_publish(a, 4 * k + 1 + s);
-    tail_next(a, s ? theta : 0.0, tt);
-    flag_wait_neighbours(a, 4 * k + 1 + s);
-    stage_halo<double>(a, hxs, o, lB);
+  }
+  if (R == 1 && !upd)
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (e0[0][r] >= 0)
+#pragma unroll
+        for (int q = 0; q < kS; ++q) {
+          const int col = j - (kS - 1) + q;
+          if (q == kS - 1 || col >= jo)
+            *reinterpret_cast<double2*>(small_vec(hl, q) + e0[0][r]) =
+                Pair<double>::load(V + (int64_t)max(col, 0) * ld + sg.beg + e0[0][r]);
+        }
+  if constexpr (R == 1) {
     __syncthreads();
+    small_dots(a, sg.beg, n, j, jo, ns, hl, sacc);
+    return;
   }
 #pragma unroll
   for (int t = 0; t < T; ++t) {
@@ -642,23 +851,23 @@ __device__ __attribute__((always_inline)) inline void matvec_keep(const Args& a,
     tile_pairs_r<R>(q0, pend, lo, ok);
     double2 va[C][R], b[kNv][R];
     if (jo > 0) load_block<R, C>(V, ld, t0, 0, min(C, jo), lo, va);
+    // (own pairs, as this thread left them)
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const int slot = (int)(q0 - pbeg) + r * kThreads + kp_tid();
-      const double2 z = make_double2(0.0, 0.0);
+      const int c = (int)(t0 - sg.beg) + 2 * (r * kThreads + kp_tid());
 #pragma unroll
-      for (int q = 0; q < kS; ++q) {
+      for (int q = 0; q < kNv; ++q) {
         const int col = j - (kS - 1) + q;
-        b[q][r] = (ok[r] && (q == kS - 1 || col >= jo))
-                      ? Pair<double>::load(V + (int64_t)max(col, 0) * ld + t0 + lo[r]) : z;
-      }
-      if (ok[r]) B2[slot] = w[t][r];
-#pragma unroll
-      for (int s = 0; s < kS; ++s) b[kS + s][r] = z;
-      if (ok[r]) {
-        b[kS][r] = ns == 1 ? w[t][r] : (ns == 2 ? A2[slot] : Pair<double>::load(V + (int64_t)(j + 1) * ld + t0 + lo[r]));
-        if (ns >= 2) b[kS + 1][r] = ns == 2 ? w[t][r] : A2[slot];
-        if (ns >= 3) b[kS + 2][r] = w[t][r];
+        double2 v = make_double2(0.0, 0.0);
+        if (ok[r]) {
+          if (q - kS == ns - 1)
+            v = make_double2(X[c], c + 1 < n ? X[c + 1] : 0.0);
+          else if (q - kS == ns - 2 && q >= kS && wbuf)
+            v = *reinterpret_cast<const double2*>(wbuf + c);
+          else if (q < kS ? (q == kS - 1 || col >= jo) : (q - kS < ns))
+            v = Pair<double>::load(V + (int64_t)max(col, 0) * ld + t0 + lo[r]);
+        }
+        b[q][r] = v;
       }
     }
     tile_dots<R>(V, ld, t0, jo, na + ns > 1, lo, b, va, sacc);

@@ -50,6 +50,7 @@ constexpr int kLdt = kMMax;               // leading dimension of L, M^{-1}
 constexpr int kLogMax = 8192;             // logged substeps
 constexpr int kNmPad = 68;                // small-exponential matrices, padded
 constexpr int kExSlots = 6;               // scratch matrices of the small exp
+constexpr int kHaloCap = 8192;            // LDS copy of the halo rows: 2 * nplanes * nx doubles at most
 constexpr int kTailPad = 64;              // augmented tail region (>= KP_PMAX)
 constexpr int kPlaneAlign = 128;          // plane offset alignment (elements)
 // Two-species operators: the second plane starts kPlaneSkew elements past the

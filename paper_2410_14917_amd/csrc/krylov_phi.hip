@@ -45,7 +45,6 @@ constexpr int kOffRed = kOffCoef + kMMax + 8;
 constexpr int kOffTv = kOffRed + kWaves;
 constexpr int kOffOwn = kOffTv + kKStride;   // the leader's own step sums
 constexpr int kOffHl = 1536;
-constexpr int kHaloCap = 8192;            // 2 * nplanes * nx doubles at most
 constexpr int kLdsDoubles = (2 * kNmPad * kNmPad > kOffHl + kHaloCap) ? 2 * kNmPad * kNmPad
                                                                       : kOffHl + kHaloCap;
 static_assert(kOffGrp + kRg * kKStride <= kOffCoef, "grp overlaps coef");
@@ -258,13 +257,14 @@ template <int R> constexpr int kKeepTiles = R == 1 ? 1 : kR / R;
 
 template <int R>
 __device__ __attribute__((always_inline)) inline void update_pending(const Args& a, const Ctl& c, const double* cf,
-                                                                     double* hl, double* red, bool want_norm) {
+                                                                     double* hl, const double* wbuf, double* red,
+                                                                     bool want_norm) {
   if (c.upd == 3)
-    update_block<R, 3>(a, c.j, c.pns, cf, hl, red, want_norm);
+    update_block<R, 3>(a, c.j, c.pns, cf, hl, wbuf, red, want_norm);
   else if (c.upd == 2)
-    update_block<R, 2>(a, c.j, c.pns, cf, hl, red, want_norm);
+    update_block<R, 2>(a, c.j, c.pns, cf, hl, wbuf, red, want_norm);
   else
-    update_block<R, 1>(a, c.j, c.pns, cf, hl, red, want_norm);
+    update_block<R, 1>(a, c.j, c.pns, cf, hl, wbuf, red, want_norm);
 }
 
 // One phase of the call for this workgroup (as run_phase).
@@ -278,6 +278,7 @@ __device__ __attribute__((always_inline)) inline void run_phase_block(const Args
   double* cf = lds + kOffBCf;
   double* hl = lds + kOffBHl;
   const bool lead = wg_rank(a) == 0, owner = wg_rank(a) < a.nwg;
+  double* wbuf = lead ? nullptr : reinterpret_cast<double*>(&L);   // (keep_xw; only the leader uses its tables)
   const Ctl c = cur;
   const int nslot = block_slots(c.j - c.na);
   KP_TS(a, k, 0);
@@ -293,23 +294,25 @@ __device__ __attribute__((always_inline)) inline void run_phase_block(const Args
       load_coefs(a, cf);
       const double theta = cf[kS * kCoefLd];
       if (c.upd) {
-        update_pending<R>(a, c, cf, hl, red, false);
+        update_pending<R>(a, c, cf, hl, wbuf, red, false);
         flag_publish(a, 4 * k);
         KP_TS(a, k, 1);
       } else {
         wait_all_stores();   // (the resets, before the partial sums)
       }
       if (lead && kp_tid() >= kThreads - 64) tail_block(a, c.j, c.na, c.ns, theta, ts);
-      if (c.upd) {
-        flag_wait_neighbours(a, 4 * k);
-        KP_TS(a, k, 2);
+      if (a.keep_xw) {
+        matvec_keep<R, kKeepTiles<R>>(a, c.j, c.na, c.ns, c.upd != 0, theta, inv_mu, sacc, hl, wbuf, k);
+      } else {
+        if (c.upd) {
+          flag_wait_neighbours(a, 4 * k);
+          KP_TS(a, k, 2);
+        }
+        if (a.halo_lds)
+          matvec_stream<R, true>(a, c.j, c.na, c.ns, theta, inv_mu, sacc, hl, k);
+        else
+          matvec_stream<R, false>(a, c.j, c.na, c.ns, theta, inv_mu, sacc, hl, k);
       }
-      if (a.keep_xw)         // (implies halo_lds)
-        matvec_keep<R, kKeepTiles<R>, true>(a, c.j, c.na, c.ns, c.upd != 0, theta, inv_mu, sacc, hl, k);
-      else if (a.halo_lds)
-        matvec_stream<R, true>(a, c.j, c.na, c.ns, theta, inv_mu, sacc, hl, k);
-      else
-        matvec_stream<R, false>(a, c.j, c.na, c.ns, theta, inv_mu, sacc, hl, k);
       __syncthreads();
       if (kp_tid() < nslot) {
         double s = lead ? ts[kp_tid()] : 0.0;
@@ -323,7 +326,7 @@ __device__ __attribute__((always_inline)) inline void run_phase_block(const Args
     }
     case PH_CLOSE:
       load_coefs(a, cf);
-      update_pending<R>(a, c, cf, hl, red, true);
+      update_pending<R>(a, c, cf, hl, wbuf, red, true);
       break;
     case PH_COMBINE:
       load_coefs(a, cf);
@@ -427,6 +430,8 @@ __global__ __launch_bounds__(kThreads) void k_blk(Args a, int arnoldi_only) {
   }
   if (arnoldi_only && wg_rank(a) == 0) store_tables_b(a, lead, true, cur.j);
 }
+
+static_assert(sizeof(LeadB) >= kKeepMax * sizeof(double) && kHaloCap >= 2 * kKeepMax, "on-chip buffers");
 
 // The whole call (or, for the step-by-step entry, the steps up to stop_j).
 template <typename TB, bool MS>
