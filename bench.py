@@ -45,7 +45,7 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0
 METRIC = "Arnoldi steps/s and phi_combo/s at N=1M,m=64; HBM GB/s vs peak; err vs FP64"
-KERNEL = "kp::k_blk<2>"
+KERNEL = "kp::k_blk<4>"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_run_allen_cahn_1024_traffic.txt")
 BATCH_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_batch_uneven_512_traffic.txt")
 FP32_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_run_fp32_basis_brusselator_2048_traffic.txt")

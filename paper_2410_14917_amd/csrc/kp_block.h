@@ -164,40 +164,6 @@ __device__ inline void new_process(const Args& a, LeadB& L) {
 __device__ inline double beta_of(const Args&, const LeadB& L) { return L.beta; }
 __device__ inline HessPacked hess_of(const Args&, const LeadB& L) { return HessPacked{L.H}; }
 
-// ---- reductions of four values ------------------------------------------------
-
-// Sums of four values over the 64 lanes of a wave: lane l gets the total of
-// value l & 3.  The first two levels pair the values (a lane keeps the value
-// of its index bits and passes the other on), so four sums cost little more
-// than one; fixed order.
-__device__ inline double add_perm16(double v) {
-  const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
-  const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
-  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
-}
-__device__ inline double add_perm32(double v) {
-  const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
-  const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
-  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
-}
-__device__ inline double wave_sum2(double v0, double v1) {   // lane l: value l & 1
-  const bool b0 = kp_tid() & 1;
-  double s = (b0 ? v1 : v0) + dpp_mov<0xB1>(b0 ? v0 : v1);   // quad_perm [1,0,3,2]
-  s += dpp_mov<0x4E>(s);                                     // quad_perm [2,3,0,1]
-  s += dpp_mov<0x124>(s);                                    // row_ror:4
-  s += dpp_mov<0x128>(s);                                    // row_ror:8
-  return add_perm32(add_perm16(s));
-}
-__device__ inline double wave_sum4(double v0, double v1, double v2, double v3) {
-  const bool b0 = kp_tid() & 1, b1 = kp_tid() & 2;
-  const double s01 = (b0 ? v1 : v0) + dpp_mov<0xB1>(b0 ? v0 : v1);
-  const double s23 = (b0 ? v3 : v2) + dpp_mov<0xB1>(b0 ? v2 : v3);
-  double s = (b1 ? s23 : s01) + dpp_mov<0x4E>(b1 ? s01 : s23);
-  s += dpp_mov<0x124>(s);
-  s += dpp_mov<0x128>(s);
-  return add_perm32(add_perm16(s));
-}
-
 // ---- passes ------------------------------------------------------------------
 //
 // On chip (keep_xw; one plane, at most kKeepMax elements per workgroup): the
@@ -411,16 +377,17 @@ __device__ __attribute__((always_inline)) inline void update_block(const Args& a
   }
 }
 
-// Products of C columns with the block's vectors, added to the wave's row of
-// sacc.  FULL: all kNv; else only x and w_1 (a single step after a single
-// step), in the same slots.
-template <int R, int C, bool FULL>
+// Products of C columns with the block's vectors, put into (ACC: added to) the
+// wave's row of sacc.  FULL: all kNv; else only x and w_1 (a single step after a
+// single step), in the same slots.  A whole chunk is one straight line, so that
+// the reductions of its columns overlap.
+template <int R, int C, bool FULL, bool ACC>
 __device__ inline void dots_block(const double2 (&v)[C][R], const double2 (&b)[kNv][R], int i0, int nc,
                                   double* sacc) {
   const int lane = kp_tid() & 63;
   double* srow = sacc + (kp_tid() >> 6) * kBSlots + kNv * i0;
-#pragma unroll
-  for (int c = 0; c < C; ++c) {
+  auto put = [](double* p, double x) { *p = ACC ? *p + x : x; };
+  auto column = [&](int c) {
     double s[kNv];
 #pragma unroll
     for (int q = 0; q < kNv; ++q) {
@@ -431,16 +398,22 @@ __device__ inline void dots_block(const double2 (&v)[C][R], const double2 (&b)[k
           s[q] = __builtin_fma(v[c][r].y, b[q][r].y, __builtin_fma(v[c][r].x, b[q][r].x, s[q]));
       }
     }
-    if (c < nc) {
-      if constexpr (FULL) {
-        const double s4 = wave_sum4(s[0], s[1], s[2], s[3]), s2 = wave_sum2(s[4], s[5]);
-        if (lane < 4) srow[kNv * c + lane] += s4;
-        if (lane < 2) srow[kNv * c + 4 + lane] += s2;
-      } else {
-        const double s2 = wave_sum2(s[kS - 1], s[kS]);
-        if (lane < 2) srow[kNv * c + kS - 1 + lane] += s2;
-      }
+    if constexpr (FULL) {
+      const double s4 = wave_sum4(s[0], s[1], s[2], s[3]), s2 = wave_sum2(s[4], s[5]);
+      if (lane < 4) put(srow + kNv * c + lane, s4);
+      if (lane < 2) put(srow + kNv * c + 4 + lane, s2);
+    } else {
+      const double s2 = wave_sum2(s[kS - 1], s[kS]);
+      if (lane < 2) put(srow + kNv * c + kS - 1 + lane, s2);
     }
+  };
+  if (nc == C) {
+#pragma unroll
+    for (int c = 0; c < C; ++c) column(c);
+  } else {
+#pragma unroll
+    for (int c = 0; c < C - 1; ++c)
+      if (c < nc) column(c);
   }
 }
 
@@ -457,7 +430,7 @@ __device__ inline void load_block(const double* V, int64_t ld, int64_t t0, int i
 
 // The older columns of one sub-tile, double-buffered chunks (the first one is
 // in flight in va already).
-template <int R, bool FULL>
+template <int R, bool FULL, bool ACC>
 __device__ __attribute__((always_inline)) inline void columns_block(
     const double* V, int64_t ld, int64_t t0, int jo, const uint32_t* lo, const double2 (&b)[kNv][R],
     double2 (&va)[kDotCols<R>][R], double* sacc) {
@@ -466,11 +439,11 @@ __device__ __attribute__((always_inline)) inline void columns_block(
   for (int i0 = 0; i0 < jo; i0 += 2 * C) {
     const int i1 = i0 + C;
     if (i1 < jo) load_block<R, C>(V, ld, t0, i1, min(C, jo - i1), lo, vb);
-    dots_block<R, C, FULL>(va, b, i0, min(C, jo - i0), sacc);
+    dots_block<R, C, FULL, ACC>(va, b, i0, min(C, jo - i0), sacc);
     if (i1 >= jo) break;
     const int i2 = i1 + C;
     if (i2 < jo) load_block<R, C>(V, ld, t0, i2, min(C, jo - i2), lo, va);
-    dots_block<R, C, FULL>(vb, b, i1, min(C, jo - i1), sacc);
+    dots_block<R, C, FULL, ACC>(vb, b, i1, min(C, jo - i1), sacc);
   }
 }
 
@@ -571,7 +544,7 @@ __device__ __attribute__((always_inline)) inline void small_dots(const Args& a, 
 }
 
 // All products of one sub-tile.
-template <int R>
+template <int R, bool ACC>
 __device__ __attribute__((always_inline)) inline void tile_dots(const double* V, int64_t ld, int64_t t0, int jo,
                                                                 bool full, const uint32_t* lo,
                                                                 const double2 (&b)[kNv][R],
@@ -595,13 +568,13 @@ __device__ __attribute__((always_inline)) inline void tile_dots(const double* V,
 #pragma unroll
     for (int k = 0; k < kGram; k += 4) {
       const double s = wave_sum4(g[k], g[k + 1], g[k + 2], g[k + 3]);
-      if (lane < 4 && k + lane < kGram) srow[k + lane] += s;
+      if (lane < 4 && k + lane < kGram) srow[k + lane] = ACC ? srow[k + lane] + s : s;
     }
   }
   if (full)
-    columns_block<R, true>(V, ld, t0, jo, lo, b, va, sacc);
+    columns_block<R, true, ACC>(V, ld, t0, jo, lo, b, va, sacc);
   else
-    columns_block<R, false>(V, ld, t0, jo, lo, b, va, sacc);
+    columns_block<R, false, ACC>(V, ld, t0, jo, lo, b, va, sacc);
 }
 
 // Tail rows of a block step (the last wave of workgroup 0, while the others
@@ -688,7 +661,7 @@ __device__ inline void tail_next(const Args& a, double shift, double* tt) {
 // On chip.  What a product costs here is latency, not bytes: the fields, the
 // neighbour offsets and the first columns of B are read once per phase, before
 // the wait for the halo rows, and kept in registers.
-template <int R, int T>
+template <int R>
 __device__ __attribute__((always_inline)) inline void matvec_keep(const Args& a, int j, int na, int ns, bool upd,
                                                                   double theta, double inv_mu, double* sacc,
                                                                   double* hl, double* wbuf, unsigned k) {
@@ -714,35 +687,33 @@ __device__ __attribute__((always_inline)) inline void matvec_keep(const Args& a,
   }
   // per pair: own offset (-1: none), wrapped east / west offsets of both
   // elements, diagonal factor, columns of B
-  int e0[T][R], off[T][R][4];
-  double2 dg[T][R], bc[kBc][T][R];
-#pragma unroll
-  for (int t = 0; t < T; ++t)
+  int e0[R], off[R][4];
+  double2 dg[R], bc[kBc][R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const int e = 2 * ((t * R + r) * kThreads + kp_tid());
+      const int e = 2 * (r * kThreads + kp_tid());
       const int c = min(e, n - 1);             // (a lane without a pair repeats the last element)
       const int64_t g = sg.beg + c;
       const bool v1 = c + 1 < n;
       const int64_t g1 = v1 ? g + 1 : g;
-      e0[t][r] = e < n ? c : -1;
+      e0[r] = e < n ? c : -1;
       const int row = (int)((unsigned)c / (unsigned)nx), ix = c - row * nx;
       const bool last = ix == nx - 1;
       const int c1 = v1 ? c + 1 : c, ix1 = v1 ? (last ? 0 : ix + 1) : ix;
-      off[t][r][0] = last ? c - ix : c + 1;
-      off[t][r][1] = ix == 0 ? c + nx - 1 : c - 1;
-      off[t][r][2] = ix1 == nx - 1 ? c1 - ix1 : c1 + 1;
-      off[t][r][3] = ix1 == 0 ? c1 + nx - 1 : c1 - 1;
+      off[r][0] = last ? c - ix : c + 1;
+      off[r][1] = ix == 0 ? c + nx - 1 : c - 1;
+      off[r][2] = ix1 == nx - 1 ? c1 - ix1 : c1 + 1;
+      off[r][3] = ix1 == 0 ? c1 + nx - 1 : c1 - 1;
       const double u0 = a.f0 ? a.f0[g] : 0.0, u1 = a.f0 ? a.f0[g1] : 0.0;
       if (a.kind == KP_OP_ADR)
-        dg[t][r] = make_double2(a.react + u0, a.react + u1);
+        dg[r] = make_double2(a.react + u0, a.react + u1);
       else
-        dg[t][r] = make_double2(__builtin_fma(-3.0 * u0, u0, 1.0), __builtin_fma(-3.0 * u1, u1, 1.0));
+        dg[r] = make_double2(__builtin_fma(-3.0 * u0, u0, 1.0), __builtin_fma(-3.0 * u1, u1, 1.0));
 #pragma unroll
       for (int b = 0; b < kBc; ++b)
         if (b < a.pb) {
           const double* col = a.B + (int64_t)(a.pb - b) * a.ldb;
-          bc[b][t][r] = make_double2(col[g], col[g1]);
+          bc[b][r] = make_double2(col[g], col[g1]);
         }
     }
   double tt[kPMax];
@@ -765,13 +736,11 @@ __device__ __attribute__((always_inline)) inline void matvec_keep(const Args& a,
   for (int s = 0; s < ns; ++s) {
     const double th = s ? theta : 0.0;
     const bool last = s + 1 == ns;
-    double2 w[T][R];
-#pragma unroll
-    for (int t = 0; t < T; ++t)
+    double2 w[R];
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        const int c = max(e0[t][r], 0);
-        const bool v1 = e0[t][r] >= 0 && c + 1 < n;
+        const int c = max(e0[r], 0);
+        const bool v1 = e0[r] >= 0 && c + 1 < n;
         const int c1 = v1 ? c + 1 : c;
         auto at = [&](int cc, int ie, int iw, double d) {
           const double x = X[cc], xe = X[ie], xw = X[iw], xn = X[cc + nx], xs = X[cc - nx];
@@ -780,13 +749,13 @@ __device__ __attribute__((always_inline)) inline void matvec_keep(const Args& a,
           const double adv = __builtin_fma(a.adx, xe - xw, a.ady * (xn - xs));
           return __builtin_fma(d - th, x, a.kind == KP_OP_ADR ? lap + (a.transpose ? adv : -adv) : lap);
         };
-        double y0 = at(c, off[t][r][0], off[t][r][1], dg[t][r].x);
-        double y1 = at(c1, off[t][r][2], off[t][r][3], dg[t][r].y);
+        double y0 = at(c, off[r][0], off[r][1], dg[r].x);
+        double y1 = at(c1, off[r][2], off[r][3], dg[r].y);
 #pragma unroll
         for (int b = 0; b < kBc; ++b)
           if (b < a.pb) {
-            y0 = __builtin_fma(tt[b], bc[b][t][r].x, y0);
-            y1 = __builtin_fma(tt[b], bc[b][t][r].y, y1);
+            y0 = __builtin_fma(tt[b], bc[b][r].x, y0);
+            y1 = __builtin_fma(tt[b], bc[b][r].y, y1);
           }
         for (int b = kBc; b < a.pb; ++b) {
           const double* col = a.B + (int64_t)(a.pb - b) * a.ldb + sg.beg;
@@ -796,27 +765,25 @@ __device__ __attribute__((always_inline)) inline void matvec_keep(const Args& a,
           y0 = __builtin_fma(tb, col[c], y0);
           y1 = __builtin_fma(tb, col[c1], y1);
         }
-        w[t][r] = make_double2(e0[t][r] >= 0 ? y0 : 0.0, v1 ? y1 : 0.0);
+        w[r] = make_double2(e0[r] >= 0 ? y0 : 0.0, v1 ? y1 : 0.0);
       }
     __syncthreads();   // every read of X is done
     double* const hxs = (s & 1) ? a.hx : a.hx2;
 #pragma unroll
-    for (int t = 0; t < T; ++t)
-#pragma unroll
       for (int r = 0; r < R; ++r)
-        if (e0[t][r] >= 0) {
-          const int c = e0[t][r];
-          X[c] = w[t][r].x;
-          if (c + 1 < n) X[c + 1] = w[t][r].y;
+        if (e0[r] >= 0) {
+          const int c = e0[r];
+          X[c] = w[r].x;
+          if (c + 1 < n) X[c + 1] = w[r].y;
           if (!last) {
-            publish_pair(a, hxs, sg, sg.beg + c, w[t][r].x, w[t][r].y);
+            publish_pair(a, hxs, sg, sg.beg + c, w[r].x, w[r].y);
             // its place for the inner products and the next update
             if (R == 1)
-              *reinterpret_cast<double2*>(small_vec(hl, kS + s) + c) = w[t][r];
+              *reinterpret_cast<double2*>(small_vec(hl, kS + s) + c) = w[r];
             else if (s + 2 == ns && wbuf)
-              *reinterpret_cast<double2*>(wbuf + c) = w[t][r];
+              *reinterpret_cast<double2*>(wbuf + c) = w[r];
             else
-              Pair<double>::store(V + (int64_t)(j + 1 + s) * ld + sg.beg + c, w[t][r].x, w[t][r].y);
+              Pair<double>::store(V + (int64_t)(j + 1 + s) * ld + sg.beg + c, w[r].x, w[r].y);
           }
         }
     if (!last) {
@@ -829,23 +796,22 @@ __device__ __attribute__((always_inline)) inline void matvec_keep(const Args& a,
   if (R == 1 && !upd)
 #pragma unroll
     for (int r = 0; r < R; ++r)
-      if (e0[0][r] >= 0)
+      if (e0[r] >= 0)
 #pragma unroll
         for (int q = 0; q < kS; ++q) {
           const int col = j - (kS - 1) + q;
           if (q == kS - 1 || col >= jo)
-            *reinterpret_cast<double2*>(small_vec(hl, q) + e0[0][r]) =
-                Pair<double>::load(V + (int64_t)max(col, 0) * ld + sg.beg + e0[0][r]);
+            *reinterpret_cast<double2*>(small_vec(hl, q) + e0[r]) =
+                Pair<double>::load(V + (int64_t)max(col, 0) * ld + sg.beg + e0[r]);
         }
   if constexpr (R == 1) {
     __syncthreads();
     small_dots(a, sg.beg, n, j, jo, ns, hl, sacc);
     return;
   }
-#pragma unroll
-  for (int t = 0; t < T; ++t) {
-    const int64_t q0 = pbeg + (int64_t)t * kThreads * R, t0 = 2 * q0;
-    if (!wave_in_tile(q0, pend)) break;
+  {
+    const int64_t q0 = pbeg, t0 = 2 * q0;
+    if (!wave_in_tile(q0, pend)) return;
     uint32_t lo[R];
     bool ok[R];
     tile_pairs_r<R>(q0, pend, lo, ok);
@@ -854,7 +820,7 @@ __device__ __attribute__((always_inline)) inline void matvec_keep(const Args& a,
     // (own pairs, as this thread left them)
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const int c = (int)(t0 - sg.beg) + 2 * (r * kThreads + kp_tid());
+      const int c = 2 * (r * kThreads + kp_tid());
 #pragma unroll
       for (int q = 0; q < kNv; ++q) {
         const int col = j - (kS - 1) + q;
@@ -870,7 +836,7 @@ __device__ __attribute__((always_inline)) inline void matvec_keep(const Args& a,
         b[q][r] = v;
       }
     }
-    tile_dots<R>(V, ld, t0, jo, na + ns > 1, lo, b, va, sacc);
+    tile_dots<R, false>(V, ld, t0, jo, na + ns > 1, lo, b, va, sacc);
   }
 }
 
@@ -932,7 +898,7 @@ __device__ __attribute__((always_inline)) inline void matvec_stream(const Args& 
                                : (isw ? w[r] : (on ? Pair<double>::load(V + (int64_t)max(col, 0) * ld + t0 + lo[r])
                                                    : make_double2(0.0, 0.0)));
           }
-          tile_dots<R>(V, ld, t0, jo, na + ns > 1, lo, b, va, sacc);
+          tile_dots<R, true>(V, ld, t0, jo, na + ns > 1, lo, b, va, sacc);
         }
       }
     }

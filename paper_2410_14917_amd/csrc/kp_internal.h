@@ -232,6 +232,38 @@ __device__ inline double wave_sum(double v) {
   return (readlane_d(v, 0) + readlane_d(v, 16)) + (readlane_d(v, 32) + readlane_d(v, 48));
 }
 
+// Sums of four values over the 64 lanes of a wave: lane l gets the total of
+// value l & 3.  The first two levels pair the values (a lane keeps the value
+// of its index bits and passes the other on), so four sums cost little more
+// than one; fixed order.
+__device__ inline double add_perm16(double v) {
+  const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+__device__ inline double add_perm32(double v) {
+  const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+__device__ inline double wave_sum2(double v0, double v1) {   // lane l: value l & 1
+  const bool b0 = kp_tid() & 1;
+  double s = (b0 ? v1 : v0) + dpp_mov<0xB1>(b0 ? v0 : v1);   // quad_perm [1,0,3,2]
+  s += dpp_mov<0x4E>(s);                                     // quad_perm [2,3,0,1]
+  s += dpp_mov<0x124>(s);                                    // row_ror:4
+  s += dpp_mov<0x128>(s);                                    // row_ror:8
+  return add_perm32(add_perm16(s));
+}
+__device__ inline double wave_sum4(double v0, double v1, double v2, double v3) {
+  const bool b0 = kp_tid() & 1, b1 = kp_tid() & 2;
+  const double s01 = (b0 ? v1 : v0) + dpp_mov<0xB1>(b0 ? v0 : v1);
+  const double s23 = (b0 ? v3 : v2) + dpp_mov<0xB1>(b0 ? v2 : v3);
+  double s = (b1 ? s23 : s01) + dpp_mov<0x4E>(b1 ? s01 : s23);
+  s += dpp_mov<0x124>(s);
+  s += dpp_mov<0x128>(s);
+  return add_perm32(add_perm16(s));
+}
+
 __device__ inline double wave_max(double v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));

@@ -250,10 +250,9 @@ static_assert(kS * 72 <= kWaves * kBSlots && kRg * kKStride <= kWaves * kBSlots,
 static_assert(kBSlots <= kThreads && kS * kCoefLd < kThreads, "one thread per slot");
 static_assert(kS == 3 && kS <= kCStride, "coefficient arrays, projections and norms of three columns");
 
-// Element pairs per thread of a tile and tiles of the on-chip region: one pair
-// up to 1024 elements per workgroup, two above.
-constexpr int kRBlk = 2;
-template <int R> constexpr int kKeepTiles = R == 1 ? 1 : kR / R;
+// Element pairs per thread of a batched problem's tiles (single calls choose
+// 1, 2 or 4 by their partition, see geometry).
+constexpr int kRBatch = 4;
 
 template <int R>
 __device__ __attribute__((always_inline)) inline void update_pending(const Args& a, const Ctl& c, const double* cf,
@@ -302,7 +301,7 @@ __device__ __attribute__((always_inline)) inline void run_phase_block(const Args
       }
       if (lead && kp_tid() >= kThreads - 64) tail_block(a, c.j, c.na, c.ns, theta, ts);
       if (a.keep_xw) {
-        matvec_keep<R, kKeepTiles<R>>(a, c.j, c.na, c.ns, c.upd != 0, theta, inv_mu, sacc, hl, wbuf, k);
+        matvec_keep<R>(a, c.j, c.na, c.ns, c.upd != 0, theta, inv_mu, sacc, hl, wbuf, k);
       } else {
         if (c.upd) {
           flag_wait_neighbours(a, 4 * k);
@@ -520,9 +519,10 @@ __device__ inline void init_problem(const Args& a, int m_target, int nflags, int
 // object and its placement does not move when the other kernels change size
 // (its run time varied by about 1 % with placement alone, with identical
 // instructions).
-template __global__ void k_blk<kRBlk>(Args, int);
-template __global__ void k_blk<1>(Args, int);
+template __global__ void k_blk<4>(Args, int);
 template __global__ void k_run<float, false>(Args, int);
+template __global__ void k_blk<2>(Args, int);
+template __global__ void k_blk<1>(Args, int);
 template __global__ void k_run<double, true>(Args, int);
 template __global__ void k_run<float, true>(Args, int);
 
@@ -667,7 +667,7 @@ __global__ __launch_bounds__(kThreads) void k_batch(BatchDesc d) {
       if (!ok || cur.phase == PH_DONE) break;
       ++k;
       if constexpr (BLK)
-        run_phase_block<kRBlk>(a, lds, lead, cur, nxt, ok, k);
+        run_phase_block<kRBatch>(a, lds, lead, cur, nxt, ok, k);
       else
         run_phase<TB, MS>(a, lds, lead, cur, nxt, ok, kept, k);
     }
@@ -963,7 +963,7 @@ struct kp_ctx {
   size_t aux_bytes = 0;
   double* integ = nullptr;         // integrators: state and right-hand-side history, columns
   size_t integ_bytes = 0;
-  int occ[5] = {-1, -1, -1, -1, -1};
+  int occ[6] = {-1, -1, -1, -1, -1, -1};
   Args last{};
   int have_begin = 0;
   int arn_target = 0;
@@ -1090,7 +1090,7 @@ int build_args(const kp_ctx* ctx, const kp_op* A, const double* B, int p, int64_
   r.basis_f32 = cfg.basis_dtype == KP_BASIS_F32 ? 1 : 0;
   r.block = (!r.basis_f32 && !kp::orth_multi_sync(r.orth)) ? 1 : 0;
   r.bstride = kp::kNv * m_max + 24;
-  r.tile_r = kp::kRBlk;
+  r.tile_r = kp::kRBatch;
   r.h = h;
   r.tol = tol > 0.0 ? tol : 1.0;
   r.delta = cfg.fallback_delta == 0.0 ? 1e-10 : (cfg.fallback_delta < 0.0 ? 0.0 : cfg.fallback_delta);
@@ -1116,21 +1116,23 @@ int occupancy(kp_ctx* ctx, const void* kernel, int which) {
 // The persistent kernel that runs a's process.
 const void* run_kernel(const Args& a) {
   if (a.block)
-    return a.tile_r == 1 ? reinterpret_cast<const void*>(&kp::k_blk<1>)
-                         : reinterpret_cast<const void*>(&kp::k_blk<kp::kRBlk>);
+    return a.tile_r == 1   ? reinterpret_cast<const void*>(&kp::k_blk<1>)
+           : a.tile_r == 2 ? reinterpret_cast<const void*>(&kp::k_blk<2>)
+                           : reinterpret_cast<const void*>(&kp::k_blk<4>);
   if (kp::orth_multi_sync(a.orth))
     return a.basis_f32 ? reinterpret_cast<const void*>(&kp::k_run<float, true>)
                        : reinterpret_cast<const void*>(&kp::k_run<double, true>);
   return reinterpret_cast<const void*>(&kp::k_run<float, false>);
 }
 
-// Co-resident workgroups per CU of that kernel (block steps: of both tile
-// sizes, since the geometry, which needs it, chooses between them).
+// Co-resident workgroups per CU of that kernel (block steps: of every tile
+// size, since the geometry, which needs it, chooses among them).
 int kernel_occupancy(kp_ctx* ctx, const Args& a) {
   if (!a.block)
     return occupancy(ctx, run_kernel(a), kp::orth_multi_sync(a.orth) ? (a.basis_f32 ? 3 : 2) : 1);
-  return std::min(occupancy(ctx, reinterpret_cast<const void*>(&kp::k_blk<kp::kRBlk>), 0),
-                  occupancy(ctx, reinterpret_cast<const void*>(&kp::k_blk<1>), 4));
+  return std::min({occupancy(ctx, reinterpret_cast<const void*>(&kp::k_blk<4>), 0),
+                   occupancy(ctx, reinterpret_cast<const void*>(&kp::k_blk<2>), 4),
+                   occupancy(ctx, reinterpret_cast<const void*>(&kp::k_blk<1>), 5)});
 }
 
 int device_setup(kp_ctx* ctx) {
@@ -1216,7 +1218,22 @@ void geometry(int ncu_slots, int rows_cfg, Args* a, bool spread = true) {
                 2 * (int64_t)a->nx <= 2 * (int64_t)kp::kThreads * kp::kR &&
                 !kp::orth_multi_sync(a->orth) && 4 * kp::kR * kp::kThreads <= kp::kHaloCap)
                    ? 1 : 0;
-  if (a->block) a->tile_r = rows * a->nx <= 2 * (int64_t)kp::kThreads ? 1 : kp::kRBlk;
+  if (a->block) {
+    // on chip, the smallest tile that holds the rows; otherwise the fewest
+    // pairs per thread, counting a tile's reductions as 0.7 of a pair (1024^2:
+    // 44.8 ms with one tile of 4 pairs, 49.3 with two of 2; the 5000 elements of
+    // 2 x 1000 x 1200: 50.8 with two of 4, 49.1 with three of 2, 51.6 with five of 1)
+    double best = 0.0;
+    for (int r : {4, 2, 1}) {
+      const int64_t tile = (int64_t)2 * kp::kThreads * r, tiles = (rows * a->nx + tile - 1) / tile;
+      const double cost = (double)tiles * (r + 0.7);
+      if (a->keep_xw && tiles > 1) continue;
+      if (best == 0.0 || cost < best) {
+        best = cost;
+        a->tile_r = r;
+      }
+    }
+  }
 }
 
 // Partial sums (doubles) of nwg workgroups: the counted buffer, the two step
