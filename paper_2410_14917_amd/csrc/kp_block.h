@@ -1173,6 +1173,15 @@ __device__ inline void finish_block_columns(LeadB& L, int base, int n, const dou
   }
 }
 
+// 1 / sqrt(x), x > 0 and normal: the hardware estimate and two Newton steps
+// (within 2 ulp; a tenth of the dependent instructions of sqrt and divide).
+__device__ inline double inv_sqrt(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+#pragma unroll
+  for (int t = 0; t < 2; ++t) y = __builtin_fma(0.5 * y, __builtin_fma(-x * y, y, 1.0), y);
+  return y;
+}
+
 // tv: the reduced sums of the step from column j (slots: block_slots).
 // Stored columns carry unit scales sigma_i as in scalar_step; the single-step
 // rules (lagged norm, norm estimate, fallback, breakdown) are those of
@@ -1187,12 +1196,15 @@ __device__ __attribute__((always_inline)) inline void block_scalar(const Args& a
   const int jo = j - na;
   const double* G = tv + kNv * jo;
   // norms of the columns jo .. j (vectors kS - 1 - na .. kS - 1)
-  double al[kS];
+  double al[kS], ial[kS];
   bool okn = true;
 #pragma unroll
   for (int q = 0; q < kS; ++q) {
     const double g = (q >= kS - 1 - na) ? G[gram_at(q, q)] : 1.0;
-    al[q] = sqrt(g);
+    // (tiny norms, whose squares leave the normal range, take the slow way)
+    const bool fast = g > 1e-290 && g < 1e290;
+    ial[q] = fast ? inv_sqrt(g) : 1.0 / sqrt(g);
+    al[q] = fast ? g * ial[q] : sqrt(g);
     if (q < kS - 1) okn = okn && al[q] > 0.0 && isfinite(al[q]);
   }
   const double alj = al[kS - 1], cww = G[gram_at(kS, kS)];
@@ -1244,43 +1256,29 @@ __device__ __attribute__((always_inline)) inline void block_scalar(const Args& a
     }
     return;
   }
-  // vector q (< kS) is column j - (kS - 1) + q; a lane's own vector, if any
-  const int qi = i - (j - (kS - 1));
+  // Vector q (< kS) is column j - (kS - 1) + q.  A measured column's lane reads
+  // its kNv sums, a new column's lane (vector p) the products of its row.
   double sig = 0.0;
   if (w0) {
-    const double sj = 1.0 / alj;
-    if (i < jo) {
-      sig = L.sigma[i];
+    const double sj = ial[kS - 1];
+    const int p = i - (j - (kS - 1));
+    const bool old = i < jo, in = i <= j;
+    sig = old ? L.sigma[i] : (p == 0 ? ial[0] : (p == 1 ? ial[1] : sj));
+    // slot of the product with vector q: column slots, or the Gram rows
+    const double* row = old ? tv + kNv * i : G + (in ? p * kNv - p * (p + 1) / 2 : 0);
+    int big = 0;
 #pragma unroll
-      for (int q = 0; q < kS; ++q) {
-        const int col = j - (kS - 1) + q;
-        if (col >= jo) {
-          const double l = sig / al[q] * tv[kNv * i + q];
-          L.tab[i * kTabLd + col] = L.tab[col * kTabLd + i] = l;
-          if (!(fabs(l) <= kSmallL)) L.big = 1;
-        }
-        sb[72 * q + i] = sig * sj * tv[kNv * i + kS + q];
+    for (int q = 0; q < kS; ++q) {
+      const int col = j - (kS - 1) + q;
+      if (in && col >= jo && (old || q > p)) {
+        const double l = sig * ial[q] * row[q];
+        L.tab[i * kTabLd + col] = L.tab[col * kTabLd + i] = l;
+        big |= !(fabs(l) <= kSmallL);
       }
-    } else if (i <= j) {
-#pragma unroll
-      for (int p = 0; p < kS; ++p) {
-        if (qi == p) {
-          sig = 1.0 / al[p];
-#pragma unroll
-          for (int q = p + 1; q < kS; ++q) {
-            const int col = j - (kS - 1) + q;
-            const double l = sig / al[q] * G[gram_at(p, q)];
-            L.tab[i * kTabLd + col] = L.tab[col * kTabLd + i] = l;
-            if (!(fabs(l) <= kSmallL)) L.big = 1;
-          }
-#pragma unroll
-          for (int q = 0; q < kS; ++q) sb[72 * q + i] = sig * sj * G[gram_at(p, kS + q)];
-        }
-      }
-    } else {
-#pragma unroll
-      for (int q = 0; q < kS; ++q) sb[72 * q + i] = 0.0;
     }
+#pragma unroll
+    for (int q = 0; q < kS; ++q) sb[72 * q + i] = in ? sig * sj * row[kS + q] : 0.0;
+    if (big) L.big = 1;
   }
   __syncthreads();
   const bool ncwy = a.orth == KP_ORTH_H_NCWY, gs = a.orth == KP_ORTH_H_GSMGS;
@@ -1302,7 +1300,7 @@ __device__ __attribute__((always_inline)) inline void block_scalar(const Args& a
   __syncthreads();
   if (!w0) return;
   const bool in = i <= j;
-  const double sj = 1.0 / alj, sj2 = sj * sj;
+  const double sj = ial[kS - 1], sj2 = sj * sj;
   double b[kS], c[kS];
 #pragma unroll
   for (int q = 0; q < kS; ++q) {
@@ -1320,31 +1318,35 @@ __device__ __attribute__((always_inline)) inline void block_scalar(const Args& a
   // R'R = W'W - B'C, as far as the guard lets it
   int done = 1;
   double r00 = gam, r01 = 0.0, r02 = 0.0, r11 = 1.0, r12 = 0.0, r22 = 1.0;
+  double i00 = 0.0, i11 = 1.0, i22 = 1.0;
   if (ns > 1 && !bad && !fallback && !bd && est2 > kGuard * wn2) {
     const double u4 = wave_sum4(b[1] * c[1], b[1] * c[2], b[2] * c[2], 0.0);
     const double n00 = wn2 - readlane_d(t4, 1), n01 = G[gram_at(kS, kS + 1)] * sj2 - readlane_d(t4, 2);
     const double g11 = G[gram_at(kS + 1, kS + 1)] * sj2, n11 = g11 - readlane_d(u4, 0);
-    const double q00 = sqrt(n00), q01 = n01 / q00, d1 = n11 - q01 * q01;
-    if (n00 > 0.0 && isfinite(g11) && d1 > kGuard * g11) {
+    const double q00 = inv_sqrt(n00), q01 = n01 * q00, d1 = n11 - q01 * q01;
+    if (n00 > 1e-290 && n00 < 1e290 && g11 < 1e290 && d1 > kGuard * g11 && d1 > 1e-290) {
       done = 2;
-      r00 = q00;
+      i00 = q00;
+      r00 = n00 * q00;
       r01 = q01;
-      r11 = sqrt(d1);
+      i11 = inv_sqrt(d1);
+      r11 = d1 * i11;
       if (ns > 2) {
         const double g22 = G[gram_at(kS + 2, kS + 2)] * sj2, n22 = g22 - readlane_d(u4, 2);
         const double n02 = G[gram_at(kS, kS + 2)] * sj2 - readlane_d(t4, 3);
         const double n12 = G[gram_at(kS + 1, kS + 2)] * sj2 - readlane_d(u4, 1);
-        const double q02 = n02 / r00, q12 = (n12 - r01 * q02) / r11, d2 = n22 - q02 * q02 - q12 * q12;
-        if (isfinite(g22) && d2 > kGuard * g22) {
+        const double q02 = n02 * i00, q12 = (n12 - r01 * q02) * i11, d2 = n22 - q02 * q02 - q12 * q12;
+        if (g22 < 1e290 && d2 > kGuard * g22 && d2 > 1e-290) {
           done = 3;
           r02 = q02;
           r12 = q12;
-          r22 = sqrt(d2);
+          i22 = inv_sqrt(d2);
+          r22 = d2 * i22;
         }
       }
     }
   }
-  const double i00 = 1.0 / r00, i11 = 1.0 / r11, i22 = 1.0 / r22;
+  if (done == 1) i00 = 1.0 / r00;
   const double i01 = -r01 * i00 * i11, i12 = -r12 * i11 * i22, i02 = -(r01 * i12 + r02 * i22) * i00;
   if (in) {
     L.H[hcol(j) + i] = c[0];
