@@ -181,6 +181,65 @@ __device__ inline int keep_off(const Args& a) { return (a.nx + 1) & ~1; }   // o
 // (first of the five vectors: R = 1 has n <= kSmallVec and so nx <= kSmallVec)
 __device__ inline double* small_vec(double* hl, int q) { return hl + kHaloCap - (5 - q) * kSmallVec; }
 
+// ---- tagged exchange (ll) ---------------------------------------------------------
+//
+// Between small workgroups an exchange of halo rows is all latency: the rows are
+// stored, the stores awaited, the flag stored, the flags polled, the rows loaded.
+// Where rows are short (at most 256, and 1024 elements per workgroup) every double
+// of a halo row, and of the tail, goes as two 8-byte words that carry half of it
+// and a 32-bit tag each, and the reader polls the words themselves (8-byte
+// accesses are single).  64 x 64 call 466 -> 446 us, 256^2 3.10 -> 3.05 ms; at rows
+// of 512 the doubled bytes cost 3 %.  The tag is 4k + e for vector e of phase k;
+// the buffers are cleared before each call.  Vector e goes through buffer e & 1:
+// a neighbour that has sent vector e + 1 has read e, and the barrier separates
+// the phases.  Phases without an update read the plain rows, which the stage,
+// close and combine phases publish.
+
+__device__ inline int64_t ll_doubles(const Args& a) { return (int64_t)a.nwg * 4 * a.nx; }   // one buffer, one plane
+__device__ inline unsigned long long* ll_at(const Args& a, int e, int64_t i) {
+  return reinterpret_cast<unsigned long long*>(a.hx2) + (e & 1) * ll_doubles(a) + 2 * i;
+}
+__device__ inline unsigned long long* ll_tail(const Args& a) {
+  return reinterpret_cast<unsigned long long*>(a.hx2) + 2 * ll_doubles(a);
+}
+__device__ inline void ll_store(unsigned long long* p, double v, unsigned tag) {
+  const unsigned long long t = (unsigned long long)tag << 32;
+  cstore(p, t | (unsigned)__double2loint(v));
+  cstore(p + 1, t | (unsigned)__double2hiint(v));
+}
+// Two values (the rows above and below), polled together until both are there.
+__device__ inline void ll_load2(const Args& a, const unsigned long long* p, const unsigned long long* q,
+                                unsigned tag, double& u, double& v) {
+  int64_t t0 = 0;
+  for (unsigned it = 0;; ++it) {
+    const unsigned long long p0 = cload(p), p1 = cload(p + 1), q0 = cload(q), q1 = cload(q + 1);
+    if ((unsigned)(p0 >> 32) == tag && (unsigned)(p1 >> 32) == tag && (unsigned)(q0 >> 32) == tag &&
+        (unsigned)(q1 >> 32) == tag) {
+      u = __hiloint2double((int)(unsigned)p1, (int)(unsigned)p0);
+      v = __hiloint2double((int)(unsigned)q1, (int)(unsigned)q0);
+      return;
+    }
+    if (it == 0) t0 = wall_clock64();
+    if ((it & 31u) == 31u && (aborted(a) || wait_expired(a, t0))) {
+      u = v = 0.0;
+      return;
+    }
+  }
+}
+// The pair (e, e + 1) of the one plane, as publish_pair.
+__device__ inline void ll_publish_pair(const Args& a, const Seg& sg, int64_t e, double v0, double v1, int ev,
+                                       unsigned tag) {
+  const int64_t n = sg.end - sg.beg;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int64_t off = e - sg.beg + h;
+    const double v = h ? v1 : v0;
+    if (off >= n) continue;
+    if (off < a.nx) ll_store(ll_at(a, ev, halo_at(a, wg_rank(a), 0, 0, (int)off)), v, tag);
+    if (off >= n - a.nx) ll_store(ll_at(a, ev, halo_at(a, wg_rank(a), 0, 1, (int)(off - (n - a.nx)))), v, tag);
+  }
+}
+
 template <int R>
 __device__ inline void tile_pairs_r(int64_t q0, int64_t pend, uint32_t* lo, bool* ok) {
 #pragma unroll
@@ -244,7 +303,7 @@ __device__ inline void load_coefs(const Args& a, double* cf) {
 // The tails (p <= 8 entries per column) of the U new columns: lane i of the
 // last wave of workgroup 0 takes column i; the newest one is published.
 template <int U>
-__device__ inline void tail_update_b(const Args& a, double* V, int nc, const double* cf, double (&ss)[U]) {
+__device__ inline void tail_update_b(const Args& a, double* V, int nc, const double* cf, unsigned tag, double (&ss)[U]) {
   const int t = kp_tid() & 63;
   const int64_t T0 = a.tail_off, ld = a.ld;
   double p[U][kPMax];
@@ -276,7 +335,10 @@ __device__ inline void tail_update_b(const Args& a, double* V, int nc, const dou
         const double y = wave_sum(p[l][k]);
         if (t == 0) {
           V[(int64_t)(nc + l) * ld + T0 + k] = y;
-          if (l == U - 1) cstore(a.tx + k, y);
+          if (l == U - 1) {
+            cstore(a.tx + k, y);
+            if (tag) ll_store(ll_tail(a) + 2 * k, y, tag);
+          }
           ss[l] += y * y;
         }
       }
@@ -288,12 +350,12 @@ __device__ inline void tail_update_b(const Args& a, double* V, int nc, const dou
 // 0 .. j - U, then on w_1 .. w_{l+1}), in place of the w_k.  pns: vectors the
 // previous phase made (>= U), which says where keep_xw left them (wbuf: the
 // workgroup's second buffer, null in the leader).  keep_xw also leaves x_j in
-// LDS.  The halo rows of x_j are published.  want_norm:
+// LDS.  tag: of the tagged exchange, 0 for plain halo rows.  The halo rows of x_j are published.  want_norm:
 // partial slot l = the squared norm of new column l.
 template <int R, int U>
 __device__ __attribute__((always_inline)) inline void update_block(const Args& a, int j, int pns, const double* cf,
                                                                    double* hl, const double* wbuf, double* red,
-                                                                   bool want_norm) {
+                                                                   bool want_norm, unsigned tag) {
   double* V = reinterpret_cast<double*>(a.V);
   const int64_t ld = a.ld;
   const int nc = j - U + 1;
@@ -305,7 +367,7 @@ __device__ __attribute__((always_inline)) inline void update_block(const Args& a
   double ss[U];
 #pragma unroll
   for (int l = 0; l < U; ++l) ss[l] = 0.0;
-  if (wg_rank(a) == 0 && kp_tid() >= kThreads - 64) tail_update_b<U>(a, V, nc, cf, ss);
+  if (wg_rank(a) == 0 && kp_tid() >= kThreads - 64) tail_update_b<U>(a, V, nc, cf, tag, ss);
   constexpr int C = kUpdCols<R>;
   for (int si = 0; si < num_segs(a); ++si) {
     const Seg sg = seg_at(a, o, si);
@@ -362,7 +424,10 @@ __device__ __attribute__((always_inline)) inline void update_block(const Args& a
 #pragma unroll
             for (int l = 0; l < U; ++l)
               reinterpret_cast<double2*>(small_vec(hl, kS - U + l))[kp_tid()] = acc[l][r];
-          publish_pair(a, a.hx, sg, t0 + lo[r], x.x, x.y);
+          if (R == 1 && tag)
+            ll_publish_pair(a, sg, t0 + lo[r], x.x, x.y, 0, tag);
+          else
+            publish_pair(a, a.hx, sg, t0 + lo[r], x.x, x.y);
         }
       }
     }
@@ -455,7 +520,7 @@ __device__ __attribute__((always_inline)) inline void columns_block(
 // elements: 0.33 us per column before, 0.1 after).  The loads of
 // two columns are in flight while two are reduced.
 __device__ __attribute__((always_inline)) inline void small_dots(const Args& a, int64_t beg, int n, int j, int jo,
-                                                                 int ns, double* hl, double* srow) {
+                                                                 int ns, bool full, double* hl, double* srow) {
   const double* V = reinterpret_cast<const double*>(a.V) + beg;
   const int64_t ld = a.ld;
   const int lane = kp_tid() & 63, wv = __builtin_amdgcn_readfirstlane(kp_tid() >> 6);
@@ -510,6 +575,23 @@ __device__ __attribute__((always_inline)) inline void small_dots(const Args& a, 
       if (lane < 4 && wv * 4 + lane < kGram) srow[kNv * jo + wv * 4 + lane] += s;
     }
     auto dots = [&](int i, const double2 (&v)[2][4]) {
+      if (!full) {   // x and w_1 alone (a single step after a single step)
+        double s[2][2];
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            s[c][q] = 0.0;
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              s[c][q] = __builtin_fma(v[c][r].y, b[kS - 1 + q][r].y,
+                                      __builtin_fma(v[c][r].x, b[kS - 1 + q][r].x, s[c][q]));
+          }
+        const double t = wave_sum4(s[0][0], s[0][1], s[1][0], s[1][1]);
+        if (lane < 2 || (lane < 4 && i + kWaves < jo))
+          srow[kNv * (i + (lane >> 1) * kWaves) + kS - 1 + (lane & 1)] += t;
+        return;
+      }
       double s[2][kNv];
 #pragma unroll
       for (int c = 0; c < 2; ++c)
@@ -717,11 +799,11 @@ __device__ __attribute__((always_inline)) inline void matvec_keep(const Args& a,
         }
     }
   double tt[kPMax];
-  if (upd) {
+  const bool ll = R == 1 && a.ll;
+  if (upd && !ll) {
     flag_wait_neighbours(a, 4 * k);
     KP_TS(a, k, 2);
   }
-  tail_of_x(a, 0, inv_mu, tt);
   const int bb = wg_rank(a);
   const int wn = (o.r1 == a.ny) ? 0 : bb + 1, ws = (o.r0 == 0) ? a.nwg - 1 : bb - 1;
   auto stage = [&](const double* hx) {
@@ -732,7 +814,28 @@ __device__ __attribute__((always_inline)) inline void matvec_keep(const Args& a,
     }
     __syncthreads();
   };
-  stage(a.hx);
+  auto stage_ll = [&](int e) {
+    for (int ix = kp_tid(); ix < nx; ix += kThreads) {
+      double vn, vs;
+      ll_load2(a, ll_at(a, e, halo_at(a, wn, 0, 0, ix)), ll_at(a, e, halo_at(a, ws, 0, 1, ix)), 4 * k + e, vn, vs);
+      X[n + ix] = vn;
+      X[ix - nx] = vs;
+    }
+    __syncthreads();
+  };
+  if (ll && upd) {
+    stage_ll(0);
+    KP_TS(a, k, 2);
+    // (lane c polls entry c; the wave takes it from there)
+    double t = 0.0, t2;
+    const int c0 = kp_tid() & 63;
+    if (c0 < a.pb) ll_load2(a, ll_tail(a) + 2 * c0, ll_tail(a) + 2 * c0, 4 * k, t, t2);
+#pragma unroll
+    for (int c = 0; c < kPMax; ++c) tt[c] = (c < a.pb) ? readlane_d(t, c) * inv_mu : 0.0;
+  } else {
+    tail_of_x(a, 0, inv_mu, tt);
+    stage(a.hx);
+  }
   for (int s = 0; s < ns; ++s) {
     const double th = s ? theta : 0.0;
     const bool last = s + 1 == ns;
@@ -776,7 +879,10 @@ __device__ __attribute__((always_inline)) inline void matvec_keep(const Args& a,
           X[c] = w[r].x;
           if (c + 1 < n) X[c + 1] = w[r].y;
           if (!last) {
-            publish_pair(a, hxs, sg, sg.beg + c, w[r].x, w[r].y);
+            if (ll)
+              ll_publish_pair(a, sg, sg.beg + c, w[r].x, w[r].y, s + 1, 4 * k + 1 + s);
+            else
+              publish_pair(a, hxs, sg, sg.beg + c, w[r].x, w[r].y);
             // its place for the inner products and the next update
             if (R == 1)
               *reinterpret_cast<double2*>(small_vec(hl, kS + s) + c) = w[r];
@@ -787,10 +893,14 @@ __device__ __attribute__((always_inline)) inline void matvec_keep(const Args& a,
           }
         }
     if (!last) {
-      flag_publish(a, 4 * k + 1 + s);
       tail_next(a, th, tt);
-      flag_wait_neighbours(a, 4 * k + 1 + s);
-      stage(hxs);
+      if (ll) {
+        stage_ll(s + 1);
+      } else {
+        flag_publish(a, 4 * k + 1 + s);
+        flag_wait_neighbours(a, 4 * k + 1 + s);
+        stage(hxs);
+      }
     }
   }
   if (R == 1 && !upd)
@@ -806,7 +916,7 @@ __device__ __attribute__((always_inline)) inline void matvec_keep(const Args& a,
         }
   if constexpr (R == 1) {
     __syncthreads();
-    small_dots(a, sg.beg, n, j, jo, ns, hl, sacc);
+    small_dots(a, sg.beg, n, j, jo, ns, na + ns > 1, hl, sacc);
     return;
   }
   {

@@ -153,7 +153,7 @@ struct Args {
   Pub* pub;           // coherent
   double* ex;         // small-exponential scratch (the leader)
   double* hx;         // halo rows [nwg][nplanes][2][nx]      (coherent)
-  double* hx2;        // block steps: the halo rows of w1     (coherent)
+  double* hx2;        // block steps: the halo rows of w_1, or the tagged exchange buffers (ll) (coherent)
   double* tx;         // tail values [kTailPad]               (coherent)
   unsigned* flags;    // per-workgroup production counters, kFlagStride apart
   int64_t ld, npt_pad, tail_off;
@@ -165,6 +165,7 @@ struct Args {
   int pairs;          // ... where the form allows them (0: single steps only)
   int bstride;        // block steps: slots of a row of the step buffers
   int tile_r;         // block steps: element pairs per thread and sub-tile
+  int ll;             // block steps: halo rows and tail of a step go as tagged words (kp_block.h)
   int part_rows;      // rows of each partial-sum buffer (>= nwg, the same for every team class)
   int nteam, wg0;     // workgroups meeting at the barriers (>= nwg); first workgroup of the run of such teams
   int kind, transpose;

@@ -257,13 +257,13 @@ constexpr int kRBatch = 4;
 template <int R>
 __device__ __attribute__((always_inline)) inline void update_pending(const Args& a, const Ctl& c, const double* cf,
                                                                      double* hl, const double* wbuf, double* red,
-                                                                     bool want_norm) {
+                                                                     bool want_norm, unsigned tag) {
   if (c.upd == 3)
-    update_block<R, 3>(a, c.j, c.pns, cf, hl, wbuf, red, want_norm);
+    update_block<R, 3>(a, c.j, c.pns, cf, hl, wbuf, red, want_norm, tag);
   else if (c.upd == 2)
-    update_block<R, 2>(a, c.j, c.pns, cf, hl, wbuf, red, want_norm);
+    update_block<R, 2>(a, c.j, c.pns, cf, hl, wbuf, red, want_norm, tag);
   else
-    update_block<R, 1>(a, c.j, c.pns, cf, hl, wbuf, red, want_norm);
+    update_block<R, 1>(a, c.j, c.pns, cf, hl, wbuf, red, want_norm, tag);
 }
 
 // One phase of the call for this workgroup (as run_phase).
@@ -293,8 +293,11 @@ __device__ __attribute__((always_inline)) inline void run_phase_block(const Args
       load_coefs(a, cf);
       const double theta = cf[kS * kCoefLd];
       if (c.upd) {
-        update_pending<R>(a, c, cf, hl, wbuf, red, false);
-        flag_publish(a, 4 * k);
+        update_pending<R>(a, c, cf, hl, wbuf, red, false, a.ll ? 4 * k : 0u);
+        if (a.ll)
+          __syncthreads();
+        else
+          flag_publish(a, 4 * k);
         KP_TS(a, k, 1);
       } else {
         wait_all_stores();   // (the resets, before the partial sums)
@@ -312,6 +315,7 @@ __device__ __attribute__((always_inline)) inline void run_phase_block(const Args
         else
           matvec_stream<R, false>(a, c.j, c.na, c.ns, theta, inv_mu, sacc, hl, k);
       }
+      if (a.ll) wait_all_stores();   // (the resets; nothing above waited for them)
       __syncthreads();
       if (kp_tid() < nslot) {
         double s = lead ? ts[kp_tid()] : 0.0;
@@ -325,7 +329,7 @@ __device__ __attribute__((always_inline)) inline void run_phase_block(const Args
     }
     case PH_CLOSE:
       load_coefs(a, cf);
-      update_pending<R>(a, c, cf, hl, wbuf, red, true);
+      update_pending<R>(a, c, cf, hl, wbuf, red, true, 0u);
       break;
     case PH_COMBINE:
       load_coefs(a, cf);
@@ -476,6 +480,10 @@ __device__ inline void init_problem(const Args& a, int m_target, int nflags, int
     const int n = a.block ? 2 * (a.part_rows + 1) * a.bstride : 2 * a.part_rows * kKStride;
     const double empty = __builtin_bit_cast(double, kPartEmpty);
     for (int i = b * (int)blockDim.x + kp_tid(); i < n; i += nb * (int)blockDim.x) sp[i] = empty;
+  }
+  if (a.ll) {
+    const int64_t n = 2 * ll_doubles(a) + 2 * kPMax;
+    for (int64_t i = b * (int)blockDim.x + kp_tid(); i < n; i += nb * (int)blockDim.x) a.hx2[i] = 0.0;
   }
   if (b != 0) return;
   for (int i = kp_tid(); i < kMMax + 2; i += blockDim.x) a.pub->coefs[0][i] = a.pub->coefs[1][i] = a.pub->coefs[2][i] = 0.0;
@@ -1182,12 +1190,17 @@ int grow(kp_ctx* ctx, void** p, size_t* have, size_t need) {
 // workgroups still cover the grid with it: x_j and w then stay on chip
 // between the passes (keep_xw below).
 //
-// Block steps (kp_block.h) spread a grid further: down to kSpread elements
-// per workgroup, since below one workgroup per CU a finer split takes the
-// streaming time down and adds only partial rows to the reduction.
+// Block steps (kp_block.h) spread a grid further: down to kSpreadFew elements per
+// workgroup while there are at most kFewWgs of them, else to kSpread: a finer
+// split takes the streaming time down and adds partial rows to the reduction
+// (one call, elements per workgroup: 97 x 61 584 449 us, 388 409; 64 x 64 512
+// 444, 256 437, 128 458; 128^2 512 1.76 ms, 256 1.71, 128 1.80; 256^2 1024 3.44 ms,
+// 512 3.04, 256 3.56).
 // spread = false: the partition without that rule (kp_phi_combo_noalloc's
 // capacity is stated for it).
-constexpr int64_t kSpread = 512;
+constexpr int64_t kSpread = 512, kSpreadFew = 256;
+constexpr int kFewWgs = 64;
+constexpr int kLlMax = 256;   // widest rows of the tagged exchange (kp_block.h)
 
 void geometry(int ncu_slots, int rows_cfg, Args* a, bool spread = true) {
   const int64_t per_wg_min = (int64_t)kp::kThreads * kp::kR * 2;
@@ -1199,7 +1212,9 @@ void geometry(int ncu_slots, int rows_cfg, Args* a, bool spread = true) {
     if (rk >= 1 && rk < rows && (a->ny + rk - 1) / rk <= ncu_slots) rows = rk;
   }
   if (rows_cfg <= 0 && a->block && spread) {
-    rows = (kSpread + (int64_t)a->nx * a->nplanes - 1) / ((int64_t)a->nx * a->nplanes);
+    const int64_t row = (int64_t)a->nx * a->nplanes;
+    rows = (kSpreadFew + row - 1) / row;
+    if ((a->ny + rows - 1) / rows > kFewWgs) rows = (kSpread + row - 1) / row;
   }
   if (rows_cfg > 0) rows = rows_cfg;
   rows = std::max<int64_t>(rows, (a->ny + ncu_slots - 1) / ncu_slots);
@@ -1233,6 +1248,7 @@ void geometry(int ncu_slots, int rows_cfg, Args* a, bool spread = true) {
         a->tile_r = r;
       }
     }
+    a->ll = (a->keep_xw && a->tile_r == 1 && a->nx <= kLlMax) ? 1 : 0;
   }
 }
 
@@ -1245,7 +1261,11 @@ size_t part_doubles(const Args& a, int nwg) {
 
 // Halo rows (doubles) of nwg workgroups, one buffer; pairs need a second one.
 size_t halo_doubles(const Args& a, int nwg) { return (size_t)nwg * a.nplanes * 2 * a.nx; }
-int halo_buffers(const Args& a) { return a.pairs ? 2 : 1; }
+// Doubles of the halo area: the plain rows, then the second buffer or the
+// tagged ones with the tail's words.
+size_t halo_area(const Args& a, int nwg) {
+  return halo_doubles(a, nwg) * (a.ll ? 5 : (a.pairs ? 2 : 1)) + (a.ll ? 2 * kp::kPMax : 0);
+}
 
 // Allocate the workspace for a problem and finish Args.
 int prepare(kp_ctx* ctx, Args* a) {
@@ -1267,7 +1287,7 @@ int prepare(kp_ctx* ctx, Args* a) {
                  part_doubles(*a, a->nwg) * sizeof(double))))
     return rc;
   if ((rc = grow(ctx, reinterpret_cast<void**>(&ctx->hx), &ctx->hx_bytes,
-                 halo_buffers(*a) * halo_doubles(*a, a->nwg) * sizeof(double))))
+                 halo_area(*a, a->nwg) * sizeof(double))))
     return rc;
   if ((rc = grow(ctx, reinterpret_cast<void**>(&ctx->flags), &ctx->flags_bytes,
                  (size_t)a->nwg * kp::kFlagStride * sizeof(unsigned))))
@@ -1314,7 +1334,7 @@ size_t carve(Args* a, char* base) {
   char* ex = take(sizeof(double) * kp::kExSlots * kp::kNmPad * kp::kNmPad);
   char* tx = take(sizeof(double) * kp::kTailPad);
   char* part = take(part_doubles(*a, a->nwg) * sizeof(double));
-  char* hx = take(halo_buffers(*a) * halo_doubles(*a, a->nwg) * sizeof(double));
+  char* hx = take(halo_area(*a, a->nwg) * sizeof(double));
   char* flags = take((size_t)a->nwg * kp::kFlagStride * sizeof(unsigned));
   char* u = take((size_t)a->ld * sizeof(double));
   char* V = take((size_t)a->ld * (size_t)(a->m_max + 2) * esz);
@@ -1364,7 +1384,7 @@ int launch(kp_ctx* ctx, Args a, int arnoldi_only) {
 }
 
 int launch_init(kp_ctx* ctx, const Args& a, int m_target) {
-  hipLaunchKernelGGL(kp::k_init, dim3((a.nwg + 7) / 8), dim3(256), 0, ctx->stream, a, m_target);
+  hipLaunchKernelGGL(kp::k_init, dim3(a.ll ? a.nwg : (a.nwg + 7) / 8), dim3(256), 0, ctx->stream, a, m_target);
   KP_HIP(ctx, hipGetLastError());
   return KP_OK;
 }
@@ -1525,7 +1545,7 @@ ProbBufs prob_bufs(const Args& a, int nwg_max) {
   r.v = align256((size_t)a.ld * (a.m_max + 2) * esz);
   r.u = align256((size_t)a.ld * sizeof(double));
   r.part = align256(part_doubles(a, nwg_max) * sizeof(double));
-  r.hx = align256(halo_buffers(a) * halo_doubles(a, nwg_max) * sizeof(double));
+  r.hx = align256(halo_area(a, nwg_max) * sizeof(double));
   r.ex = align256(sizeof(double) * kp::kExSlots * kp::kNmPad * kp::kNmPad);
   r.tx = align256(sizeof(double) * kp::kTailPad);
   return r;

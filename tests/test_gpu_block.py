@@ -41,6 +41,10 @@ GRIDS = [
     (W.OP_BRUSSELATOR, 130, 36, 2, 2),  # two planes, one-pair tiles, 18 workgroups
     (W.OP_BRUSSELATOR, 2049, 6, 1, 2),  # two planes, wide odd rows, halo rows from memory
     (W.OP_ADR, 7, 3, 8, 0),             # one workgroup, every tail entry
+    (W.OP_ADR, 256, 34, 2, 2),          # the widest rows of the tagged exchange
+    (W.OP_ADR, 258, 34, 2, 2),          # one pair wider: flags
+    (W.OP_ALLEN_CAHN, 97, 2, 1, 1),     # one row per workgroup is both halo rows
+    (W.OP_ADR, 63, 2, 8, 2),            # one workgroup, its own neighbour
 ]
 
 
