@@ -180,7 +180,7 @@ __device__ __attribute__((always_inline)) inline void run_phase(const Args& a, d
     bar_gather(a, k, &ok);
     if (!ok) return;
   }
-  if (kp_tid() == 0) nxt = c;
+  if (kp_tid() == 0) nxt = cur;   // (re-read: c need not stay live through the pass)
   if (a.keep_xw && kp_tid() == 0 && (c.phase == PH_STEP || c.phase == PH_CLOSE)) {
     // vector passes of the two-pass count that stayed in LDS: the update's
     // x_{j-1} and w, the matvec's x_j, and the w it did not store
@@ -358,7 +358,7 @@ __device__ __attribute__((always_inline)) inline void run_phase_block(const Args
     bar_gather(a, k, &ok);
     if (!ok) return;
   }
-  if (kp_tid() == 0) nxt = c;
+  if (kp_tid() == 0) nxt = cur;   // (re-read: c need not stay live through the pass)
   if (a.keep_xw && kp_tid() == 0 && c.phase == PH_CLOSE) L.onchip += 2;
   switch (c.phase) {
     case PH_STAGE:
