@@ -175,9 +175,7 @@ __device__ inline HessPacked hess_of(const Args&, const LeadB& L) { return HessP
 // before the last one takes the space of the leader's tables, which the other
 // workgroups do not use (the leader keeps it in memory), and the first of three
 // is in memory.
-constexpr int kKeepMax = 2 * kR * kThreads;
 constexpr int kSmallVec = 2 * kThreads;
-__device__ inline int keep_off(const Args& a) { return (a.nx + 1) & ~1; }   // own elements in the LDS vector
 // (first of the five vectors: R = 1 has n <= kSmallVec and so nx <= kSmallVec)
 __device__ inline double* small_vec(double* hl, int q) { return hl + kHaloCap - (5 - q) * kSmallVec; }
 

@@ -180,6 +180,8 @@ struct Args {
   int halo_lds;       // the stencil halo rows fit the LDS copy of the matvec
   int keep_xw;        // one plane, one sub-tile per workgroup, one-reduction form: the
                       // matvec pass leaves x_j and w in LDS for the next update
+  int keep_ms;        // ioCGS with a float64 basis, one plane, at most kKeepMax elements per
+                      // workgroup: x_j and w stay in LDS (iocgs_mvec, iocgs_proj)
 #ifdef KP_TIMELINE
   long long* ts;      // device timeline (see KP_TS), null when not recording
   int ts_kmax;        // phases the timeline holds

@@ -200,7 +200,7 @@ __device__ __attribute__((always_inline)) inline void leader_stage(const Args& a
 // gamma, the squared norms ||A u_j||^2, and three controller flags.
 constexpr int kTabLd = kMMax + 1;
 
-struct LeadLds {
+struct __attribute__((aligned(16))) LeadLds {
   double Mi[kMMax * kTabLd];
   double Li[kMMax * kTabLd];
   double sigma[kMMax + 8];

@@ -1221,6 +1221,164 @@ __device__ __attribute__((always_inline)) inline void proj_pass(const Args& a, i
   if (kp_tid() == 0) cstore(a.part + (int64_t)wg_rank(a) * kCStride, ss);
 }
 
+// ---- ioCGS on chip (keep_ms) -------------------------------------------------
+//
+// A step of ioCGS moves few vectors (x_{j-1}, B, the field and the new column) and
+// synchronises twice, so at 1024^2 its two phases were mostly latency and
+// re-reads: 48 us per step against 11 of streaming.  Where a workgroup's rows
+// fit one tile, x_j sits in LDS between its halo rows and w in the space of the
+// one-reduction forms' tables, neither is read or written in memory between the
+// phases (column j + 1 is stored once, projected), and the sums go through the
+// polled step buffers instead of a counted arrival.
+
+constexpr int kKeepMax = 2 * kR * kThreads;   // elements of a workgroup on chip
+__device__ inline int keep_off(const Args& a) { return (a.nx + 1) & ~1; }   // own elements in the LDS vector
+
+// Stores this workgroup's sums (n <= 4, thread i holds s of slot i) in its row of
+// the step buffer, after all its stores (the leader: in own).
+__device__ inline void put_sums(int n, double s, double* prow, double* own) {
+  if (kp_tid() < n) {
+    if (own)
+      own[kp_tid()] = s;
+    else
+      cstore(prow + kp_tid(), s);
+  }
+}
+
+// Matvec of step jj: w = Atilde (s x_jj) into wbuf, and x.x, x.w, w.w, x_acol . w.
+// have: x_jj is in LDS already.
+__device__ __attribute__((always_inline)) inline void iocgs_mvec(const Args& a, int jj, int acol, bool have,
+                                                                 double* sacc, double* hl, double* wbuf,
+                                                                 double* prow, double* own) {
+  double* V = reinterpret_cast<double*>(a.V);
+  const int64_t ld = a.ld;
+  const int lane = kp_tid() & 63, wv = kp_tid() >> 6, nx = a.nx;
+  const Rows o = own_rows(a);
+  const Seg sg = seg_at(a, o, 0);
+  const int n = (int)(sg.end - sg.beg);
+  double* X = hl + keep_off(a);
+  double* xcol = V + (int64_t)jj * ld + sg.beg;
+  const double* acp = V + (int64_t)(acol >= 0 ? acol : 0) * ld + sg.beg;
+  const double inv_mu = cload(&a.pub->inv_mu);
+  const double xs = jj == 0 ? 1.0 : cload(&a.pub->xscale);
+  double tc[kPMax];
+#pragma unroll
+  for (int c = 0; c < kPMax; ++c) tc[c] = (c < a.pb) ? cload(a.tx + c) * inv_mu : 0.0;
+  const int bb = wg_rank(a);
+  const int wn = (o.r1 == a.ny) ? 0 : bb + 1, ws = (o.r0 == 0) ? a.nwg - 1 : bb - 1;
+  for (int ix = kp_tid(); ix < nx; ix += kThreads) {
+    const double vn = cload(a.hx + halo_at(a, wn, 0, 0, ix)), vs = cload(a.hx + halo_at(a, ws, 0, 1, ix));
+    X[n + ix] = vn;
+    X[ix - nx] = vs;
+  }
+  if (!have) {
+    const double* src = jj == 0 ? a.u + sg.beg : xcol;
+    for (int c = 2 * kp_tid(); c < n; c += 2 * kThreads) {
+      const double2 v = Pair<double>::load(src + c);
+      X[c] = v.x;
+      if (c + 1 < n) X[c + 1] = v.y;
+      if (jj == 0) Pair<double>::store(xcol + c, v.x, v.y);
+    }
+  }
+  __syncthreads();
+  double sxx = 0.0, sxw = 0.0, sww = 0.0, saw = 0.0;
+#pragma unroll
+  for (int r = 0; r < kR; ++r) {
+    const int c = 2 * (r * kThreads + kp_tid());
+    if (c >= n) break;
+    const double2 av = acol >= 0 ? Pair<double>::load(acp + c) : make_double2(0.0, 0.0);
+    double y[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int e = c + h < n ? c + h : c;
+      const int64_t g = sg.beg + e;
+      const double u = a.f0 ? a.f0[g] : 0.0;
+      double bt = 0.0;
+#pragma unroll
+      for (int b = 0; b < kPMax; ++b)
+        if (b < a.pb) bt = __builtin_fma(tc[b], a.B[(int64_t)(a.pb - b) * a.ldb + g], bt);
+      const int row = (int)((unsigned)e / (unsigned)nx), ix = e - row * nx;
+      const double x = X[e], xe = X[ix == nx - 1 ? e - ix : e + 1], xw = X[ix == 0 ? e + nx - 1 : e - 1];
+      const double xn = X[e + nx], xd = X[e - nx];
+      const double lap = __builtin_fma(a.cx, __builtin_fma(-2.0, x, xe + xw),
+                                       a.cy * __builtin_fma(-2.0, x, xn + xd));
+      double v;
+      if (a.kind == KP_OP_ADR) {
+        const double adv = __builtin_fma(a.adx, xe - xw, a.ady * (xn - xd));
+        v = __builtin_fma(a.react + u, x, lap + (a.transpose ? adv : -adv));
+      } else {
+        v = __builtin_fma(__builtin_fma(-3.0 * u, u, 1.0), x, lap);
+      }
+      y[h] = xs * (v + bt);
+    }
+    const double x0 = X[c], x1 = c + 1 < n ? X[c + 1] : 0.0;
+    if (c + 1 >= n) y[1] = 0.0;
+    *reinterpret_cast<double2*>(wbuf + c) = make_double2(y[0], y[1]);
+    sxx = __builtin_fma(x1, x1, __builtin_fma(x0, x0, sxx));
+    sxw = __builtin_fma(x1, y[1], __builtin_fma(x0, y[0], sxw));
+    sww = __builtin_fma(y[1], y[1], __builtin_fma(y[0], y[0], sww));
+    saw = __builtin_fma(av.y, y[1], __builtin_fma(av.x, y[0], saw));
+  }
+  const double s4 = wave_sum4(sxx, sxw, sww, saw);
+  if (lane < kMvSlots) sacc[wv * kMvSlots + lane] = s4;
+  if (bb == 0) {
+    const Src<double> x{V + (int64_t)jj * ld, a.u, jj == 0};   // (the tail entries)
+    tail_mvec<double>(a, jj, x, V, acol, xs, sacc);   // (thread 0, wave 0's sums)
+  }
+  wait_all_stores();   // (the reset of the next step buffer, before the sums)
+  __syncthreads();
+  double s = 0.0;
+  if (kp_tid() < kMvSlots)
+    for (int w = 0; w < kWaves; ++w) s += sacc[w * kMvSlots + kp_tid()];
+  put_sums(kMvSlots, s, prow, own);
+}
+
+// Projection of step jj: column jj + 1 = w + sum_{c = ca..jj} coef[c] x_c, its
+// squared norm, and its halo rows; x_{jj+1} takes x_jj's place in LDS.
+__device__ __attribute__((always_inline)) inline void iocgs_proj(const Args& a, int jj, int ca, const double* coef,
+                                                                 double* red, double* hl, const double* wbuf,
+                                                                 double* prow, double* own) {
+  double* V = reinterpret_cast<double*>(a.V);
+  const int64_t ld = a.ld;
+  const Rows o = own_rows(a);
+  const Seg sg = seg_at(a, o, 0);
+  const int n = (int)(sg.end - sg.beg);
+  double* X = hl + keep_off(a);
+  double* wcol = V + (int64_t)(jj + 1) * ld;
+  const double* acp = V + (int64_t)ca * ld + sg.beg;
+  const bool older = ca < jj;
+  const double cx = cload(coef + jj), co = older ? cload(coef + ca) : 0.0;
+  double ss = 0.0;
+#pragma unroll
+  for (int r = 0; r < kR; ++r) {
+    const int c = 2 * (r * kThreads + kp_tid());
+    if (c >= n) break;
+    const double2 w = *reinterpret_cast<const double2*>(wbuf + c);
+    const double2 p = older ? Pair<double>::load(acp + c) : make_double2(0.0, 0.0);
+    const bool v1 = c + 1 < n;
+    const double y0 = __builtin_fma(cx, X[c], __builtin_fma(co, p.x, w.x));
+    const double y1 = v1 ? __builtin_fma(cx, X[c + 1], __builtin_fma(co, p.y, w.y)) : 0.0;
+    Pair<double>::store(wcol + sg.beg + c, y0, y1);
+    X[c] = y0;
+    if (v1) X[c + 1] = y1;
+    ss += y0 * y0 + y1 * y1;
+    publish_pair(a, a.hx, sg, sg.beg + c, y0, y1);
+  }
+  if (wg_rank(a) == 0 && kp_tid() == 0) {
+    const int64_t T0 = a.tail_off;
+    for (int k = 0; k < a.p; ++k) {
+      double y = wcol[T0 + k];
+      for (int c = ca; c <= jj; ++c) y += cload(coef + c) * V[(int64_t)c * ld + T0 + k];
+      wcol[T0 + k] = y;
+      cstore(a.tx + k, y);
+      ss += y * y;
+    }
+  }
+  wait_all_stores();   // (the halo rows, the tail and the reset, before the sum that announces them)
+  ss = block_sum(ss, red);
+  put_sums(1, ss, prow, own);
+}
+
 // ---- finish: out = u_top (or NaN when the input was not finite) -------------
 __device__ __attribute__((always_inline)) inline void finish_pass(const Args& a, bool nonfinite) {
   const Rows o = own_rows(a);

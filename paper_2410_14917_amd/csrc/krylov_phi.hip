@@ -50,6 +50,7 @@ constexpr int kLdsDoubles = (2 * kNmPad * kNmPad > kOffHl + kHaloCap) ? 2 * kNmP
 static_assert(kOffGrp + kRg * kKStride <= kOffCoef, "grp overlaps coef");
 static_assert(kOffWk + kWkDoubles <= kOffCoef, "wk overlaps coef");
 static_assert(kOffOwn + kKStride <= kOffHl, "tv / own overlap the halo copy");
+static_assert(sizeof(((LeadLds*)0)->Mi) >= kKeepMax * sizeof(double), "w of ioCGS on chip");
 static_assert(kLdsDoubles >= kExDoubles, "the small exponential does not fit the phase buffer");
 
 // One phase of the call for this workgroup.  MS: the kernel also runs the
@@ -76,6 +77,9 @@ __device__ __attribute__((always_inline)) inline void run_phase(const Args& a, d
   double* hl = lds + kOffHl;
   const bool lead = wg_rank(a) == 0;
   const Ctl c = cur;
+  // ioCGS on chip: its phases' sums go through the polled step buffers
+  const bool keep_ms = MS && sizeof(TB) == 8 && a.keep_ms;
+  const bool polled = c.phase == PH_STEP || (keep_ms && (c.phase == PH_MVEC || c.phase == PH_PROJ));
   // the matvec pass of the previous phase left x_{j-1} and w in LDS
   const bool xl = a.keep_xw && kept == c.j - 1;
   KP_TS(a, k, 0);
@@ -137,7 +141,11 @@ __device__ __attribute__((always_inline)) inline void run_phase(const Args& a, d
       if constexpr (MS) {
         // MGS multiplies and takes v_1 . w; ioCGS takes v_{j-1} . w and v_j . w
         const int acol = c.j == 0 ? -1 : (a.orth == KP_ORTH_MGS ? 0 : c.j - 1);
-        if (a.halo_lds)
+        if (keep_ms) {
+          if constexpr (sizeof(TB) == 8)
+            iocgs_mvec(a, c.j, acol, kept == c.j, sacc, hl, L.Mi,
+                       step_part(a, k) + (int64_t)wg_rank(a) * kKStride, lead ? own : nullptr);
+        } else if (a.halo_lds)
           mvec_pass<TB, true>(a, c.j, acol, sacc, hl);
         else
           mvec_pass<TB, false>(a, c.j, acol, sacc, hl);
@@ -147,7 +155,12 @@ __device__ __attribute__((always_inline)) inline void run_phase(const Args& a, d
       if constexpr (MS) {
         // MGS: subtract the projection on v_{i-1}, then v_i . w (or the
         // norm); ioCGS: subtract both projections of the window, then the norm
-        if (a.orth == KP_ORTH_MGS)
+        if (keep_ms) {
+          if constexpr (sizeof(TB) == 8)
+            iocgs_proj(a, c.j, max(0, c.j - 1), a.pub->coefs[0], red, hl, L.Mi,
+                       step_part(a, k) + (int64_t)wg_rank(a) * kKStride, lead ? own : nullptr);
+          if (kp_tid() == 0) kept = c.j + 1;   // (column in LDS)
+        } else if (a.orth == KP_ORTH_MGS)
           proj_pass<TB>(a, c.j, c.i - 1, c.i - 1, a.pub->coefs[0], c.i <= c.j ? c.i : -1, c.i > c.j,
                         red);
         else
@@ -166,7 +179,7 @@ __device__ __attribute__((always_inline)) inline void run_phase(const Args& a, d
   KP_TS(a, k, 3);
   // (the leader counts its arrival at a step barrier after the release, so
   // that the atomic is not outstanding while it polls)
-  if (c.phase != PH_STEP)
+  if (!polled)
     bar_arrive(a);
   else if (!lead)
     bar_count(a);
@@ -176,7 +189,7 @@ __device__ __attribute__((always_inline)) inline void run_phase(const Args& a, d
     return;
   }
   // serial part (workgroup 0)
-  if (c.phase != PH_STEP) {
+  if (!polled) {
     bar_gather(a, k, &ok);
     if (!ok) return;
   }
@@ -204,17 +217,26 @@ __device__ __attribute__((always_inline)) inline void run_phase(const Args& a, d
       break;
     case PH_MVEC:
       if constexpr (MS) {
-        reduce_partials(a, kMvSlots, tv, grp);
+        if (keep_ms)
+          gather_step_partials(a, step_part(a, k), kMvSlots, own, tv, grp, &ok);
+        else
+          reduce_partials(a, kMvSlots, tv, grp);
+        if (!ok) return;
         leader_mvec(a, c.j, tv, L, nxt);
       }
       break;
     case PH_PROJ:
       if constexpr (MS) {
-        reduce_partials(a, 1, tv, grp);
+        if (keep_ms)
+          gather_step_partials(a, step_part(a, k), 1, own, tv, grp, &ok);
+        else
+          reduce_partials(a, 1, tv, grp);
+        if (!ok) return;
         leader_proj(a, c.j, c.i, tv[0], L, nxt);
       }
       break;
     case PH_EXPM:
+      if (keep_ms && kp_tid() == 0) kept = -1;   // (it uses the whole buffer)
       expm_phase<sizeof(TB) == 4>(a, lds, L, nxt);
       break;
     case PH_COMBINE:
@@ -229,7 +251,7 @@ __device__ __attribute__((always_inline)) inline void run_phase(const Args& a, d
   KP_TS(a, k, 6);
   bar_release(a, k, nxt, a.pub);
   KP_TS(a, k, 7);
-  if (c.phase == PH_STEP) bar_count(a);
+  if (polled) bar_count(a);
   if (kp_tid() == 0) cur = nxt;
 }
 
@@ -1211,7 +1233,7 @@ void geometry(int ncu_slots, int rows_cfg, Args* a, bool spread = true) {
     if ((a->nx & 1) && (rk & 1) && rk < a->ny) --rk;
     if (rk >= 1 && rk < rows && (a->ny + rk - 1) / rk <= ncu_slots) rows = rk;
   }
-  if (rows_cfg <= 0 && a->block && spread) {
+  if (rows_cfg <= 0 && spread && (a->block || (a->orth == KP_ORTH_IOCGS && !a->basis_f32))) {
     const int64_t row = (int64_t)a->nx * a->nplanes;
     rows = (kSpreadFew + row - 1) / row;
     if ((a->ny + rows - 1) / rows > kFewWgs) rows = (kSpread + row - 1) / row;
@@ -1229,6 +1251,9 @@ void geometry(int ncu_slots, int rows_cfg, Args* a, bool spread = true) {
   // halo region of LDS (2 * kR * kThreads pairs) for the next update, which
   // leaves x_{j+1} there for the next matvec pass; that pass's halo copy (two
   // rows) goes to the w half
+  a->keep_ms = (a->orth == KP_ORTH_IOCGS && !a->basis_f32 && a->nplanes == 1 && spread &&
+                rows * a->nx <= kp::kKeepMax && 2 * (int64_t)a->nx <= kp::kKeepMax)
+                   ? 1 : 0;
   a->keep_xw = (a->nplanes == 1 && rows * a->nx <= 2 * (int64_t)kp::kThreads * kp::kR &&
                 2 * (int64_t)a->nx <= 2 * (int64_t)kp::kThreads * kp::kR &&
                 !kp::orth_multi_sync(a->orth) && 4 * kp::kR * kp::kThreads <= kp::kHaloCap)

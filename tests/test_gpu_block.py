@@ -120,3 +120,50 @@ def test_nearly_scalar_operator_takes_single_steps():
     ref, _ = krylov.phi_combo(op_h, Bh, 0.05, 2, fixed_m=9, fixed_substeps=2, m_max=9)
     assert info["status"] == 0 and info["arnoldi_steps"] == 18
     assert rel(y.cpu().numpy(), ref) <= 1e-10
+
+
+# (kind, nx, ny, p, rows per workgroup: 0 automatic)
+IOCGS_GRIDS = [
+    (W.OP_ADR, 512, 40, 2, 8),          # 4096 elements: the largest tile on chip
+    (W.OP_ALLEN_CAHN, 2048, 18, 1, 2),  # the widest rows on chip
+    (W.OP_ADR, 2050, 18, 2, 1),         # wider: through memory
+    (W.OP_ADR, 1025, 20, 1, 4),         # 4100 elements: through memory
+    (W.OP_ADR, 333, 36, 3, 4),          # odd rows: padding element
+    (W.OP_ADR, 333, 35, 3, 2),          # odd size: the last workgroup's padding element
+    (W.OP_ALLEN_CAHN, 98, 2, 1, 1),     # one row per workgroup is both halo rows
+    (W.OP_ADR, 7, 3, 8, 0),             # one workgroup, every tail entry
+    (W.OP_ADR, 63, 61, 0, 0),           # spread, no augmentation
+]
+
+
+@pytest.mark.parametrize("grid", IOCGS_GRIDS, ids=lambda g: f"{g[0]}-{g[1]}x{g[2]}-r{g[4]}")
+def test_iocgs_on_chip_matches_oracle(grid):
+    """ioCGS with its window on chip at the edges of that path, paused and
+    resumed (the resumed launch reloads), and over two substeps; the bounds are
+    those of the orthogonalization tests."""
+    kind, nx, ny, p, rows = grid
+    m = 15
+    print(f"iocgs: kind={kind} {nx}x{ny} p={p} rows={rows}", flush=True)
+    pr = W.random_problem(51 + nx, kind=kind, nx=nx, ny=ny, p=p, h=0.02, with_diag=True,
+                          nu=0.02 / max(nx, ny), react=0.1)
+    op = kp.Operator.from_host(pr.op)
+    B = torch.as_tensor(np.ascontiguousarray(pr.B[:, :p + 1].T), device="cuda")
+    with kp.Context(orth="iocgs", rows_per_wg=rows) as ctx:
+        ctx.arnoldi_begin(op, B, m)
+        ctx.arnoldi_step(4)
+        ctx.arnoldi_step(m - 4)
+        r = ctx.arnoldi_read()
+    mu = krylov.balance_scale(pr.B, p)
+    iop = arnoldi.IOPArnoldi(lambda x: krylov.aug_apply(pr.op, pr.B, p, mu, x),
+                             krylov.start_vector(pr.B, p, mu), m, window=2)
+    iop.extend(m)
+    assert r["j"] == m and not r["breakdown"]
+    assert rel(r["H"][:m + 1, :m], iop.H[:m + 1, :m]) <= 1e-11
+    assert rel(r["V"], iop.V[:, :m + 1]) <= 1e-10
+    with kp.Context(orth="iocgs", rows_per_wg=rows, fixed_m=m, fixed_substeps=2) as ctx:
+        y, info = ctx.phi_combo(op, B, pr.h, m_max=m, info=True)
+        y2 = ctx.phi_combo(op, B, pr.h, m_max=m)
+    ref, _ = krylov.phi_combo(pr.op, pr.B, pr.h, p, fixed_m=m, fixed_substeps=2, m_max=m, orth="iop")
+    assert info["status"] == 0 and info["arnoldi_steps"] == 2 * m
+    assert rel(y.cpu().numpy(), ref) <= 1e-10
+    assert torch.equal(y, y2)
