@@ -53,12 +53,14 @@ static_assert(kOffOwn + kKStride <= kOffHl, "tv / own overlap the halo copy");
 static_assert(sizeof(((LeadLds*)0)->Mi) >= kKeepMax * sizeof(double), "w of ioCGS on chip");
 static_assert(kLdsDoubles >= kExDoubles, "the small exponential does not fit the phase buffer");
 
-// One phase of the call for this workgroup.  MS: the kernel also runs the
-// processes with one reduction per inner product (MGS) or per window
-// (ioCGS); the one-reduction kernels are compiled without those phases.  cur: control of the phase (LDS,
-// identical in every workgroup); nxt: the leader's control of the next phase;
-// ok: cleared when a bounded wait gives up (the launch is aborting).  On
-// return cur holds the control of the next phase.
+// One phase of the call for this workgroup.  MS: the processes with one
+// reduction per inner product (MGS) or per window (ioCGS), else the
+// one-reduction forms with a float basis; each kind is compiled without the
+// other's phases (the registers of the update and dot passes cost the MS kernels
+// 459 scalar and 38 vector spills: 355 and 2 without).  cur: control of the
+// phase (LDS, identical in every workgroup); nxt: the leader's control of the
+// next phase; ok: cleared when a bounded wait gives up (the launch is
+// aborting).  On return cur holds the control of the next phase.
 // The Brusselator's matvec pass takes both species of a grid point together
 // (joint sub-tiles) with a float basis; with a float64 one the joint tile's
 // extra registers spill and cost what the shared loads save (measured), so it
@@ -79,9 +81,9 @@ __device__ __attribute__((always_inline)) inline void run_phase(const Args& a, d
   const Ctl c = cur;
   // ioCGS on chip: its phases' sums go through the polled step buffers
   const bool keep_ms = MS && sizeof(TB) == 8 && a.keep_ms;
-  const bool polled = c.phase == PH_STEP || (keep_ms && (c.phase == PH_MVEC || c.phase == PH_PROJ));
+  const bool polled = (!MS && c.phase == PH_STEP) || (keep_ms && (c.phase == PH_MVEC || c.phase == PH_PROJ));
   // the matvec pass of the previous phase left x_{j-1} and w in LDS
-  const bool xl = a.keep_xw && kept == c.j - 1;
+  const bool xl = !MS && a.keep_xw && kept == c.j - 1;
   KP_TS(a, k, 0);
   if (lead) KP_TSV(a, k, 4, c.phase * 1000 + c.j);
   // this workgroup's row of the step buffer of barrier k + 1 is free again
@@ -97,6 +99,7 @@ __device__ __attribute__((always_inline)) inline void run_phase(const Args& a, d
       stage_pass(a, red);
       break;
     case PH_STEP:
+      if constexpr (MS) break;
       // the update that produces x_j (coefficients of the previous scalar
       // step), then the matvec + grouped dots of step j: one grid-wide sync
       // (flag_publish also completes the reset above before the partial
@@ -135,6 +138,7 @@ __device__ __attribute__((always_inline)) inline void run_phase(const Args& a, d
       }
       break;
     case PH_CLOSE:
+      if constexpr (MS) break;
       update_pass<TB>(a, c.j - 1, a.pub->coefs[0], red, true, xl ? hl : nullptr);
       break;
     case PH_MVEC:
@@ -194,7 +198,7 @@ __device__ __attribute__((always_inline)) inline void run_phase(const Args& a, d
     if (!ok) return;
   }
   if (kp_tid() == 0) nxt = cur;   // (re-read: c need not stay live through the pass)
-  if (a.keep_xw && kp_tid() == 0 && (c.phase == PH_STEP || c.phase == PH_CLOSE)) {
+  if (!MS && a.keep_xw && kp_tid() == 0 && (c.phase == PH_STEP || c.phase == PH_CLOSE)) {
     // vector passes of the two-pass count that stayed in LDS: the update's
     // x_{j-1} and w, the matvec's x_j, and the w it did not store
     const bool upd = (c.phase == PH_CLOSE || c.upd) && xl;
@@ -206,12 +210,14 @@ __device__ __attribute__((always_inline)) inline void run_phase(const Args& a, d
       leader_stage(a, red, L, nxt);
       break;
     case PH_STEP:
+      if constexpr (MS) break;
       gather_step_partials(a, step_part(a, k), 2 * c.j + 3, own, tv, grp, &ok);
       if (!ok) return;
       KP_TS(a, k, 5);
       scalar_step(a, c.j, tv, L, wk, nxt);
       break;
     case PH_CLOSE:
+      if constexpr (MS) break;
       reduce_partials(a, 1, tv, grp);
       leader_close(a, tv[0], L, nxt);
       break;
