@@ -137,6 +137,57 @@ __device__ __attribute__((always_inline)) inline void gather_step_partials(const
   __syncthreads();
 }
 
+// The same for a few slots (n <= 4) of all rows, a thread per row: the slot
+// groups above leave most threads idle there and each of the others 32 loads
+// deep (256 rows, 4 slots: 9.7 us from the last arrival to the release, 6.3 here; the
+// leader's serial work is in both).
+// red: kWaves * 4 doubles.  Slots n.. of dst are not written.
+__device__ inline void gather_few(const Args& a, const double* buf, int n, const double* own, double* dst,
+                                  double* red, int* ok) {
+  constexpr unsigned kEmptyLo = (unsigned)kPartEmpty, kEmptyHi = (unsigned)(kPartEmpty >> 32);
+  const int lane = kp_tid() & 63, wv = kp_tid() >> 6;
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<double*>(buf), (short)0, a.nwg * kKStride * (int)sizeof(double), kBufWord3);
+  __syncthreads();   // (own, and red's other uses)
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int w = kp_tid(); w < a.nwg; w += kThreads) {
+    if (w == 0) {
+      for (int k = 0; k < n; ++k) s[k] = own[k];
+      continue;
+    }
+    decltype(__builtin_amdgcn_raw_buffer_load_b128(rs, 0, 0, 0)) v[2];
+    int64_t t0 = 0;
+    for (unsigned it = 0;; ++it) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        v[q] = __builtin_amdgcn_raw_buffer_load_b128(rs, (w * kKStride + 2 * q) * (int)sizeof(double), 0,
+                                                     kCoherentAux);
+      bool empty = false;
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        empty |= k < n && v[k / 2][2 * (k & 1)] == kEmptyLo && v[k / 2][2 * (k & 1) + 1] == kEmptyHi;
+      if (!empty) break;
+      if (it == 0) t0 = wall_clock64();
+      if ((it & 15u) == 15u && (aborted(a) || wait_expired(a, t0))) {
+        *ok = 0;
+        break;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (k < n) s[k] += lo_double(v[k / 2][2 * (k & 1)], v[k / 2][2 * (k & 1) + 1]);
+  }
+  const double s4 = wave_sum4(s[0], s[1], s[2], s[3]);
+  if (lane < 4) red[wv * 4 + lane] = s4;
+  __syncthreads();
+  if (kp_tid() < n) {
+    double t = 0.0;
+    for (int w = 0; w < kWaves; ++w) t += red[w * 4 + kp_tid()];
+    dst[kp_tid()] = t;
+  }
+  __syncthreads();
+}
+
 // First phase of an Arnoldi step for the configured process.
 __device__ inline int step_phase(const Args& a) {
   return orth_multi_sync(a.orth) ? (int)PH_MVEC : (int)PH_STEP;

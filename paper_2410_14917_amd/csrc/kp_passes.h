@@ -1225,11 +1225,13 @@ __device__ __attribute__((always_inline)) inline void proj_pass(const Args& a, i
 //
 // A step of ioCGS moves few vectors (x_{j-1}, B, the field and the new column) and
 // synchronises twice, so at 1024^2 its two phases were mostly latency and
-// re-reads: 48 us per step against 11 of streaming.  Where a workgroup's rows
+// re-reads: 47 us per step against 11 of streaming.  Where a workgroup's rows
 // fit one tile, x_j sits in LDS between its halo rows and w in the space of the
 // one-reduction forms' tables, neither is read or written in memory between the
 // phases (column j + 1 is stored once, projected), and the sums go through the
-// polled step buffers instead of a counted arrival.
+// polled step buffers, a row per thread (gather_few), instead of a counted arrival.
+// adaptive call at 1024^2: 43.8 ms before, 36.4 on chip, 32.9 with gather_few and the
+// caller's vectors loaded before the halo rows.
 
 constexpr int kKeepMax = 2 * kR * kThreads;   // elements of a workgroup on chip
 __device__ inline int keep_off(const Args& a) { return (a.nx + 1) & ~1; }   // own elements in the LDS vector
@@ -1266,6 +1268,23 @@ __device__ __attribute__((always_inline)) inline void iocgs_mvec(const Args& a, 
   for (int c = 0; c < kPMax; ++c) tc[c] = (c < a.pb) ? cload(a.tx + c) * inv_mu : 0.0;
   const int bb = wg_rank(a);
   const int wn = (o.r1 == a.ny) ? 0 : bb + 1, ws = (o.r0 == 0) ? a.nwg - 1 : bb - 1;
+  // the vectors of the caller and x_acol first: one round trip for everything
+  // (the lanes past the end repeat the last element)
+  constexpr int kBc = 2;                       // columns of B kept in registers
+  double2 f[kR], av[kR], bc[kBc][kR];
+#pragma unroll
+  for (int r = 0; r < kR; ++r) {
+    const int c = min(2 * (r * kThreads + kp_tid()), n - 1), c1 = min(c + 1, n - 1);
+    const int64_t g = sg.beg + c, g1 = sg.beg + c1;
+    f[r] = a.f0 ? make_double2(a.f0[g], a.f0[g1]) : make_double2(0.0, 0.0);
+#pragma unroll
+    for (int b = 0; b < kBc; ++b)
+      if (b < a.pb) {
+        const double* col = a.B + (int64_t)(a.pb - b) * a.ldb;
+        bc[b][r] = make_double2(col[g], col[g1]);
+      }
+    av[r] = acol >= 0 ? make_double2(acp[c], acp[c1]) : make_double2(0.0, 0.0);
+  }
   for (int ix = kp_tid(); ix < nx; ix += kThreads) {
     const double vn = cload(a.hx + halo_at(a, wn, 0, 0, ix)), vs = cload(a.hx + halo_at(a, ws, 0, 1, ix));
     X[n + ix] = vn;
@@ -1286,16 +1305,18 @@ __device__ __attribute__((always_inline)) inline void iocgs_mvec(const Args& a, 
   for (int r = 0; r < kR; ++r) {
     const int c = 2 * (r * kThreads + kp_tid());
     if (c >= n) break;
-    const double2 av = acol >= 0 ? Pair<double>::load(acp + c) : make_double2(0.0, 0.0);
     double y[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int e = c + h < n ? c + h : c;
       const int64_t g = sg.beg + e;
-      const double u = a.f0 ? a.f0[g] : 0.0;
+      const double u = h ? f[r].y : f[r].x;
       double bt = 0.0;
 #pragma unroll
-      for (int b = 0; b < kPMax; ++b)
+      for (int b = 0; b < kBc; ++b)
+        if (b < a.pb) bt = __builtin_fma(tc[b], h ? bc[b][r].y : bc[b][r].x, bt);
+#pragma unroll
+      for (int b = kBc; b < kPMax; ++b)
         if (b < a.pb) bt = __builtin_fma(tc[b], a.B[(int64_t)(a.pb - b) * a.ldb + g], bt);
       const int row = (int)((unsigned)e / (unsigned)nx), ix = e - row * nx;
       const double x = X[e], xe = X[ix == nx - 1 ? e - ix : e + 1], xw = X[ix == 0 ? e + nx - 1 : e - 1];
@@ -1317,7 +1338,7 @@ __device__ __attribute__((always_inline)) inline void iocgs_mvec(const Args& a, 
     sxx = __builtin_fma(x1, x1, __builtin_fma(x0, x0, sxx));
     sxw = __builtin_fma(x1, y[1], __builtin_fma(x0, y[0], sxw));
     sww = __builtin_fma(y[1], y[1], __builtin_fma(y[0], y[0], sww));
-    saw = __builtin_fma(av.y, y[1], __builtin_fma(av.x, y[0], saw));
+    saw = __builtin_fma(av[r].y, y[1], __builtin_fma(av[r].x, y[0], saw));
   }
   const double s4 = wave_sum4(sxx, sxw, sww, saw);
   if (lane < kMvSlots) sacc[wv * kMvSlots + lane] = s4;

@@ -224,7 +224,7 @@ __device__ __attribute__((always_inline)) inline void run_phase(const Args& a, d
     case PH_MVEC:
       if constexpr (MS) {
         if (keep_ms)
-          gather_step_partials(a, step_part(a, k), kMvSlots, own, tv, grp, &ok);
+          gather_few(a, step_part(a, k), kMvSlots, own, tv, grp, &ok);
         else
           reduce_partials(a, kMvSlots, tv, grp);
         if (!ok) return;
@@ -234,7 +234,7 @@ __device__ __attribute__((always_inline)) inline void run_phase(const Args& a, d
     case PH_PROJ:
       if constexpr (MS) {
         if (keep_ms)
-          gather_step_partials(a, step_part(a, k), 1, own, tv, grp, &ok);
+          gather_few(a, step_part(a, k), 1, own, tv, grp, &ok);
         else
           reduce_partials(a, 1, tv, grp);
         if (!ok) return;
