@@ -25,9 +25,10 @@
 // with the next reduction (the lagged norms of Algorithm 4, for s columns).
 // Where a w_k lies almost inside the span already there (guard kGuard on the
 // squared norms), the columns before it are made and the next block starts
-// there; kMaxShort blocks in a row that made one step end the attempts.  The forms H-CWY and H-NCWY always take single steps: their
-// one-sided corrections do not remove the measured loss of orthogonality to
-// first order, which a block needs.
+// there; kMaxShort blocks in a row that made one step end the attempts.  The
+// forms H-CWY and H-NCWY always take single steps: their one-sided corrections
+// do not remove the measured loss of orthogonality to first order, which a
+// block needs.
 //
 // What bounds it: HBM (or Infinity Cache) bytes of the basis at large grids,
 // the latency chain of a phase (release, coefficients, halo flags, partial
@@ -41,7 +42,9 @@
 // benchmark call 93.7, 59.5, 51.3 ms; 2 x 1000 x 1200 Brusselator 102.3, 66.8,
 // 49.8 ms; 512 uneven problems in one launch 1333, 841, 603 ms.  With the
 // stencil from LDS and small_dots: 64 x 64 519 us, 256^2 3.75 ms, 512^2 forward
-// and backward 39.9 -> 34.6 ms.
+// and backward 39.9 -> 34.6 ms.  With the sections below and the partition of
+// krylov_phi.hip: 64 x 64 438 us, 256^2 3.04 ms, 1024^2 44.9, the Brusselator 48.7,
+// the 512 problems 605.
 #pragma once
 
 #include "kp_leader.h"

@@ -1,7 +1,8 @@
 // libkrylov_phi: kernels and the C ABI declared in include/krylov_phi.h.
 //
 // Execution model (one MI355X, gfx950).  A whole phi_combo call is ONE
-// cooperative launch of k_run: every workgroup loops over the phases published
+// cooperative launch of k_blk (the one-reduction forms with a float64 basis) or
+// k_run (a float basis, MGS, ioCGS): every workgroup loops over the phases published
 // by workgroup 0 (stage, Arnoldi step = matvec+dots then update+norm, small
 // exponential + controller, combine, finish) and meets the others at
 // grid-wide barriers.  The grid-wide reduction of an Arnoldi step is the
@@ -1224,7 +1225,13 @@ int grow(kp_ctx* ctx, void** p, size_t* have, size_t need) {
 // (one call, elements per workgroup: 97 x 61 584 449 us, 388 409; 64 x 64 512
 // 444, 256 437, 128 458; 128^2 512 1.76 ms, 256 1.71, 128 1.80; 256^2 1024 3.44 ms,
 // 512 3.04, 256 3.56).
-// spread = false: the partition without that rule (kp_phi_combo_noalloc's
+// ioCGS (float64 basis) also starts at kSpreadFew, but keeps to kFewWgs workgroups up
+// to the 4096 elements its window on chip allows: its phases are short, and every
+// arrival costs the leader's gather (two substeps of 40 steps, us by elements per
+// workgroup: 64^2 256 1200, 1024 1219, 4096 1398; 256^2 512 1382, 1024 1284, 4096
+// 1572; 512^2 1024 2058, 2048 1592, 4096 1687; with 4096 elements, the counted
+// barriers and nothing on chip 2015, 2207 and 2438).
+// spread = false: the partition without these rules (kp_phi_combo_noalloc's
 // capacity is stated for it).
 constexpr int64_t kSpread = 512, kSpreadFew = 256;
 constexpr int kFewWgs = 64;
@@ -1239,7 +1246,17 @@ void geometry(int ncu_slots, int rows_cfg, Args* a, bool spread = true) {
     if ((a->nx & 1) && (rk & 1) && rk < a->ny) --rk;
     if (rk >= 1 && rk < rows && (a->ny + rk - 1) / rk <= ncu_slots) rows = rk;
   }
-  if (rows_cfg <= 0 && spread && (a->block || (a->orth == KP_ORTH_IOCGS && !a->basis_f32))) {
+  if (rows_cfg <= 0 && spread && a->orth == KP_ORTH_IOCGS && !a->basis_f32) {
+    const int64_t row = (int64_t)a->nx * a->nplanes;
+    for (int64_t e = kSpreadFew; e <= kp::kKeepMax; e *= 2) {
+      rows = (e + row - 1) / row;
+      if ((a->ny + rows - 1) / rows <= kFewWgs) break;
+    }
+    int64_t cap = kp::kKeepMax / row;          // (whole rows, even ones when nx is odd)
+    if (a->nx & 1) cap &= ~(int64_t)1;
+    if (cap >= 1) rows = std::min(rows, cap);
+  }
+  if (rows_cfg <= 0 && spread && a->block) {
     const int64_t row = (int64_t)a->nx * a->nplanes;
     rows = (kSpreadFew + row - 1) / row;
     if ((a->ny + rows - 1) / rows > kFewWgs) rows = (kSpread + row - 1) / row;
@@ -1253,10 +1270,9 @@ void geometry(int ncu_slots, int rows_cfg, Args* a, bool spread = true) {
   a->nteam = a->nwg;
   a->part_rows = a->nwg;
   // one plane whose rows per workgroup fit one sub-tile (kThreads * kR
-  // pairs), a one-reduction form: the matvec pass leaves x_j and w in the
-  // halo region of LDS (2 * kR * kThreads pairs) for the next update, which
-  // leaves x_{j+1} there for the next matvec pass; that pass's halo copy (two
-  // rows) goes to the w half
+  // pairs): the products read x_j in LDS, where the update before left it, and
+  // leave w there for the next update (kp_block.h; with a float basis
+  // matvec_dots_pass; ioCGS: iocgs_mvec)
   a->keep_ms = (a->orth == KP_ORTH_IOCGS && !a->basis_f32 && a->nplanes == 1 && spread &&
                 rows * a->nx <= kp::kKeepMax && 2 * (int64_t)a->nx <= kp::kKeepMax)
                    ? 1 : 0;
