@@ -147,10 +147,10 @@ typedef struct kp_config {
                                 0 -> h (clipped to h)                           */
     int32_t controller;      /* KP_CTRL_*, default KP_CTRL_POWER              */
     int32_t rows_per_wg;     /* grid rows owned by each workgroup of a single
-                                call; 0 -> automatic (at least 4096 elements per
-                                workgroup, one workgroup per CU at most).  A
-                                smaller value spreads a small grid over more
-                                CUs (raised to what the CU count needs).      */
+                                call; 0 -> automatic (256 elements or more per
+                                workgroup, 4096 or more for MGS and a float
+                                basis; one workgroup per CU at most).  Raised
+                                to what the CU count needs.                   */
 } kp_config;
 
 /* Outcome of a call (filled after the stream is synchronised). */
