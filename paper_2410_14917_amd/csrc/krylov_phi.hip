@@ -562,6 +562,7 @@ template __global__ void k_blk<2>(Args, int);
 template __global__ void k_blk<1>(Args, int);
 template __global__ void k_run<double, true>(Args, int);
 template __global__ void k_run<float, true>(Args, int);
+template __global__ void k_run<double, false>(Args, int);
 
 __global__ __launch_bounds__(256) void k_init(Args a, int m_target) {
   init_problem(a, m_target, a.nwg * kFlagStride, (int)blockIdx.x, (int)gridDim.x);
@@ -1000,7 +1001,7 @@ struct kp_ctx {
   size_t aux_bytes = 0;
   double* integ = nullptr;         // integrators: state and right-hand-side history, columns
   size_t integ_bytes = 0;
-  int occ[6] = {-1, -1, -1, -1, -1, -1};
+  int occ[7] = {-1, -1, -1, -1, -1, -1, -1};
   Args last{};
   int have_begin = 0;
   int arn_target = 0;
@@ -1159,14 +1160,25 @@ const void* run_kernel(const Args& a) {
   if (kp::orth_multi_sync(a.orth))
     return a.basis_f32 ? reinterpret_cast<const void*>(&kp::k_run<float, true>)
                        : reinterpret_cast<const void*>(&kp::k_run<double, true>);
-  return reinterpret_cast<const void*>(&kp::k_run<float, false>);
+  return a.basis_f32 ? reinterpret_cast<const void*>(&kp::k_run<float, false>)
+                     : reinterpret_cast<const void*>(&kp::k_run<double, false>);
+}
+
+// Single calls of the forms without block steps on large grids: k_blk holds six
+// vectors' registers for their two and streams with shorter chunks, which costs
+// more there than its shorter latencies save (H-CWY, one substep of 64 steps:
+// 1024^2 7.57 ms, 6.50 in k_run; 700^2 4.29, 3.92; 634 x 348 adaptive 2.75, 3.55).
+constexpr int64_t kSinglesMax = 1 << 18;   // elements up to which k_blk runs single steps
+void choose_kernel(Args* a) {
+  if (a->block && !a->pairs && (int64_t)a->npt * a->nplanes > kSinglesMax) a->block = 0;
 }
 
 // Co-resident workgroups per CU of that kernel (block steps: of every tile
 // size, since the geometry, which needs it, chooses among them).
 int kernel_occupancy(kp_ctx* ctx, const Args& a) {
   if (!a.block)
-    return occupancy(ctx, run_kernel(a), kp::orth_multi_sync(a.orth) ? (a.basis_f32 ? 3 : 2) : 1);
+    return occupancy(ctx, run_kernel(a),
+                     kp::orth_multi_sync(a.orth) ? (a.basis_f32 ? 3 : 2) : (a.basis_f32 ? 1 : 6));
   return std::min({occupancy(ctx, reinterpret_cast<const void*>(&kp::k_blk<4>), 0),
                    occupancy(ctx, reinterpret_cast<const void*>(&kp::k_blk<2>), 4),
                    occupancy(ctx, reinterpret_cast<const void*>(&kp::k_blk<1>), 5)});
@@ -1324,6 +1336,7 @@ int prepare(kp_ctx* ctx, Args* a) {
   if ((rc = grow(ctx, reinterpret_cast<void**>(&ctx->u), &ctx->u_bytes,
                  (size_t)a->ld * sizeof(double))))
     return rc;
+  choose_kernel(a);
   const int occ = kernel_occupancy(ctx, *a);
   if (occ <= 0) {
     snprintf(ctx->err, sizeof(ctx->err), "the persistent kernel does not fit on a CU");

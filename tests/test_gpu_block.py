@@ -167,3 +167,20 @@ def test_iocgs_on_chip_matches_oracle(grid):
     assert info["status"] == 0 and info["arnoldi_steps"] == 2 * m
     assert rel(y.cpu().numpy(), ref) <= 1e-10
     assert torch.equal(y, y2)
+
+
+@pytest.mark.parametrize("nx,ny", [(512, 512), (512, 513), (513, 514)])
+@pytest.mark.parametrize("orth", ["h-cwy", "h-ncwy"])
+def test_single_steps_on_both_sides_of_the_kernel_choice(nx, ny, orth):
+    """The forms without block steps: the largest grid of the block kernel, and
+    the next ones, against the oracle's modified Gram-Schmidt."""
+    print(f"singles: {orth} {nx}x{ny}", flush=True)
+    m = 7
+    pr = W.random_problem(61, kind=W.OP_ADR, nx=nx, ny=ny, p=1, h=0.02, nu=0.02 / nx, with_diag=True)
+    op = kp.Operator.from_host(pr.op)
+    B = torch.as_tensor(np.ascontiguousarray(pr.B[:, :2].T), device="cuda")
+    with kp.Context(orth=orth, fixed_m=m, fixed_substeps=1) as ctx:
+        y, info = ctx.phi_combo(op, B, pr.h, m_max=m, info=True)
+    ref, _ = krylov.phi_combo(pr.op, pr.B, pr.h, 1, fixed_m=m, fixed_substeps=1, m_max=m)
+    assert info["status"] == 0 and info["arnoldi_steps"] == m
+    assert rel(y.cpu().numpy(), ref) <= 1e-10
