@@ -1532,6 +1532,13 @@ kp::PlanProblem plan_problem(const kp_op& A, int p, int m_max, double h) {
 
 size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
+// Sizes of a problem's own buffers (bytes, each 256-aligned): basis, state
+// vector, partial sums, halo rows, small-exponential scratch, tail values.
+struct ProbBufs {
+  size_t v, u, part, hx, ex, tx;
+  size_t total() const { return v + u + part + hx + ex + tx; }
+};
+
 }  // namespace
 
 struct BatchCache {
@@ -1543,6 +1550,7 @@ struct BatchCache {
   std::vector<int> class_size;        // team size of class c
   std::vector<int> class_wg0;         // first workgroup of class c's run of teams
   std::vector<size_t> prob_off;       // arena offset of each problem's buffers
+  std::vector<ProbBufs> prob_buf;     // their sizes, as the arena was laid out
   std::vector<int> prob_nwg;          // largest row-owning workgroup count over the classes
   std::vector<int> prob_class;        // class the plan gave each problem
   std::vector<int64_t> flag_off;      // per problem, in unsigned
@@ -1591,13 +1599,6 @@ void batch_geometry(int g, int wg0, Args* a) {
   a->nteam = g;
   a->wg0 = wg0;
 }
-
-// Sizes of a problem's own buffers (bytes, each 256-aligned): basis, state
-// vector, partial sums, halo rows, small-exponential scratch, tail values.
-struct ProbBufs {
-  size_t v, u, part, hx, ex, tx;
-  size_t total() const { return v + u + part + hx + ex + tx; }
-};
 
 ProbBufs prob_bufs(const Args& a, int nwg_max) {
   const size_t esz = a.basis_f32 ? sizeof(float) : sizeof(double);
@@ -1675,7 +1676,8 @@ int batch_create(kp_ctx* ctx, const std::vector<Args>& as, const std::vector<kp:
   int64_t nflags = 0;
   for (int i = 0; i < np; ++i) {
     b->prob_off[i] = off;
-    off += prob_bufs(as[i], b->prob_nwg[i]).total();
+    b->prob_buf.push_back(prob_bufs(as[i], b->prob_nwg[i]));
+    off += b->prob_buf[i].total();
     b->flag_off[i] = nflags;
     nflags += (int64_t)b->prob_nwg[i] * kp::kFlagStride;
   }
@@ -1768,7 +1770,7 @@ void batch_fill_args(BatchCache* b, const std::vector<Args>& as, int64_t wait_ti
   b->hargs.resize((size_t)b->nclass * np);
   for (int i = 0; i < np; ++i) {
     Args a = as[i];
-    const ProbBufs z = prob_bufs(a, b->prob_nwg[i]);
+    const ProbBufs& z = b->prob_buf[i];
     char* base = static_cast<char*>(b->arena) + b->prob_off[i];
     a.V = base;
     a.u = reinterpret_cast<double*>(base + z.v);
@@ -2455,7 +2457,10 @@ int kp_phi_combo_batched(kp_ctx* ctx, int32_t nprob, const kp_op* ops, const dou
   for (int i = 1; i < nprob; ++i)
     if (spans[i].first < spans[i - 1].second) return KP_EINVAL;
   std::vector<long long> key = {nprob, m_max, ctx->cfg.basis_dtype, ctx->cfg.orth,
-                                ctx->cfg.fixed_m, ctx->cfg.fixed_substeps, ctx->model_gen};
+                                ctx->cfg.fixed_m, ctx->cfg.fixed_substeps, ctx->model_gen,
+                                // the workspace's layout (prob_bufs) also depends on what
+                                // build_args derives from the rest of the configuration
+                                as[0].block, as[0].pairs, as[0].bstride, as[0].ll};
   for (int i = 0; i < nprob; ++i) {
     key.push_back(ops[i].kind);
     key.push_back(ops[i].nx);
