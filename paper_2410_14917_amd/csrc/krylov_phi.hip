@@ -1968,6 +1968,7 @@ int kp_phi_combo_noalloc(kp_ctx* ctx, const kp_op* A, const double* B, int32_t p
              ctx->device, cur);
     return KP_EINVAL;
   }
+  choose_kernel(&a);
   const int occ = kernel_occupancy(ctx, a);
   if (occ <= 0) {
     snprintf(ctx->err, sizeof(ctx->err), "the persistent kernel does not fit on a CU");
