@@ -1416,14 +1416,18 @@ size_t carve(Args* a, char* base) {
 
 // Bytes by which kp_phi_combo_noalloc's capacity is counted: the workspace on
 // the partition of at least 4096 elements per workgroup, with three partial
-// rows and one halo buffer.  The block steps' own layout takes up to 32 N
-// bytes more of halo rows, which the array holds beyond KP_NOALLOC_BYTES, so
-// the problems accepted do not depend on the partition.
+// rows, one halo buffer and 768 bytes for the control block, whatever the
+// kernels keep there, so the problems accepted depend on neither.  What the
+// finer partition takes beyond that is in the array above KP_NOALLOC_BYTES: two
+// halo buffers of at most 32 N bytes (a row per workgroup), or the tagged
+// exchange's five of at most 256 workgroups and 256 elements per row (5.3 MB),
+// and 1.7 MB of partial sums.
+constexpr size_t kCountedPub = 768;
 size_t noalloc_need(int ncu_slots, int rows_cfg, const Args& a) {
   Args g = a;
   geometry(ncu_slots, rows_cfg, &g, false);
   const size_t esz = a.basis_f32 ? sizeof(float) : sizeof(double);
-  const size_t parts[] = {sizeof(State), sizeof(Pub), 64,
+  const size_t parts[] = {sizeof(State), kCountedPub, 64,
                           sizeof(double) * kp::kExSlots * kp::kNmPad * kp::kNmPad,
                           sizeof(double) * kp::kTailPad,
                           (size_t)3 * g.nwg * kp::kKStride * sizeof(double),

@@ -1,6 +1,7 @@
 """kp_phi_combo_noalloc against kp_phi_combo where the kernel depends on the
 form and the grid: the forms without block steps run another kernel above 2^18
-elements, and both entry points have to choose alike.
+elements, and both entry points have to choose alike.  And the capacity at the
+edge: what is accepted does not move with the size of internal records.
 Runs with the no-alloc tests at the end (one static array per GPU)."""
 import ctypes
 
@@ -53,3 +54,12 @@ def test_noalloc_runs_the_kernel_of_the_allocating_call(nx, ny, cfg):
     (ya, yb), ((ra, ia), (rb, ib)) = _both(nx, ny, 1, 20, **cfg)
     assert ra == 0 and rb == 0 and ia["status"] == 0
     assert ib == ia and torch.equal(ya, yb)
+
+
+def test_noalloc_capacity_at_its_edge():
+    """413 x 737 with m_max = 24 takes KP_NOALLOC_BYTES - 768 as the header
+    counts it; 413 x 739 takes more than all."""
+    (ya, yb), ((ra, ia), (rb, ib)) = _both(413, 737, 1, 24)
+    assert ra == 0 and rb == 0 and ib == ia and torch.equal(ya, yb)
+    _, ((ra, _), (rb, _)) = _both(413, 739, 1, 24)
+    assert ra == 0 and rb == _lib.KP_ETOOLARGE
