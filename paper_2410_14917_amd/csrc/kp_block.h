@@ -1,6 +1,6 @@
 // The one-reduction Arnoldi process with a float64 basis, up to kS = 3 steps per
 // grid-wide reduction (block steps): streaming passes and the leader's scalar
-// work of kernels k_blk and k_batch<double, false>.
+// work of kernels k_blk and k_batch<double, false, true>.
 //
 // A step of Algorithm 4 reads the basis twice (inner products, then the
 // projection) and synchronises the grid once.  Both costs are shared by kS

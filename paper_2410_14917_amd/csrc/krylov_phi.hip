@@ -641,9 +641,9 @@ __global__ __launch_bounds__(256) void k_batch_init(BatchDesc d) {
   }
 }
 
-template <typename TB, bool MS>
+// BLK: block steps, as in k_blk; else the phases of k_run.
+template <typename TB, bool MS, bool BLK = false>
 __global__ __launch_bounds__(kThreads) void k_batch(BatchDesc d) {
-  constexpr bool BLK = sizeof(TB) == 8 && !MS;   // block steps, as in k_blk
   __shared__ __attribute__((aligned(16))) double lds[BLK ? kLdsDoublesB : kLdsDoubles];
   __shared__ std::conditional_t<BLK, LeadB, LeadLds> lead;
   __shared__ Ctl cur, nxt;
@@ -1586,11 +1586,26 @@ void batch_free(BatchCache* b) {
   delete b;
 }
 
-template <typename TB, bool MS>
-int batch_occupancy(kp_ctx* ctx, int* occ) {
-  KP_HIP(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                  occ, reinterpret_cast<const void*>(&kp::k_batch<TB, MS>), kp::kThreads, 0));
-  return KP_OK;
+// The kernel of a batched call's problems (they share the configuration).
+// The forms without block steps take k_run's phases, unless every problem has
+// two planes: single steps in the block kernel, with two columns per chunk and
+// the registers of six vectors, cost 5 % on 256 problems of sides 16 to 64
+// (H-CWY: 4.46 ms, 4.23 in k_run's phases), 7 % on six of sides 300 to 700
+// (7.37, 6.88), 0.4 to 0.8 % on sides up to 256 and 512, and gain 1 % on 128
+// Brusselators of sides 32 to 256 (38.8, 39.2).
+void choose_batch_kernel(std::vector<Args>& as) {
+  bool two = true;
+  for (const Args& a : as) two = two && a.nplanes == 2;
+  if (!two && !as[0].pairs)
+    for (Args& a : as) a.block = 0;
+}
+const void* batch_kernel(const Args& a) {
+  if (a.block) return reinterpret_cast<const void*>(&kp::k_batch<double, false, true>);
+  if (kp::orth_multi_sync(a.orth))
+    return a.basis_f32 ? reinterpret_cast<const void*>(&kp::k_batch<float, true>)
+                       : reinterpret_cast<const void*>(&kp::k_batch<double, true>);
+  return a.basis_f32 ? reinterpret_cast<const void*>(&kp::k_batch<float, false>)
+                     : reinterpret_cast<const void*>(&kp::k_batch<double, false>);
 }
 
 // Geometry of a problem on the teams of one class (team size g, first
@@ -1623,15 +1638,14 @@ int batch_create(kp_ctx* ctx, const std::vector<Args>& as, const std::vector<kp:
   b->key = std::move(key);
   const int np = (int)as.size();
   b->nprob = np;
-  const bool f32 = as[0].basis_f32 != 0;
+  const void* kernel = batch_kernel(as[0]);
   int occ = 0;
-  const bool ms = kp::orth_multi_sync(as[0].orth);
-  int rc = ms ? (f32 ? batch_occupancy<float, true>(ctx, &occ) : batch_occupancy<double, true>(ctx, &occ))
-              : (f32 ? batch_occupancy<float, false>(ctx, &occ) : batch_occupancy<double, false>(ctx, &occ));
-  if (rc || occ < 1) {
+  hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, kp::kThreads, 0);
+  if (e != hipSuccess || occ < 1) {
     batch_free(b);
-    if (!rc) snprintf(ctx->err, sizeof(ctx->err), "the batched kernel does not fit on a CU");
-    return rc ? rc : KP_EHIP;
+    if (e != hipSuccess) return hip_fail(ctx, e, "batched occupancy");
+    snprintf(ctx->err, sizeof(ctx->err), "the batched kernel does not fit on a CU");
+    return KP_EHIP;
   }
   b->n_wg = ctx->ncu * occ;
   const kp::PlanModel model = ctx->model;
@@ -1685,7 +1699,7 @@ int batch_create(kp_ctx* ctx, const std::vector<Args>& as, const std::vector<kp:
     b->flag_off[i] = nflags;
     nflags += (int64_t)b->prob_nwg[i] * kp::kFlagStride;
   }
-  hipError_t e = hipMalloc(&b->arena, std::max<size_t>(off, 256));
+  e = hipMalloc(&b->arena, std::max<size_t>(off, 256));
   if (e == hipSuccess) e = hipMalloc(&b->st, sizeof(State) * np);
   if (e == hipSuccess) e = hipMalloc(&b->pub, sizeof(Pub) * np);
   if (e == hipSuccess) e = hipMalloc(&b->sync, 64 * (size_t)np);
@@ -1740,10 +1754,7 @@ int batch_create(kp_ctx* ctx, const std::vector<Args>& as, const std::vector<kp:
   p1.gridDim = dim3(np);
   p1.blockDim = dim3(256);
   p1.kernelParams = a1;
-  p2.func = ms ? (f32 ? reinterpret_cast<void*>(&kp::k_batch<float, true>)
-                      : reinterpret_cast<void*>(&kp::k_batch<double, true>))
-               : (f32 ? reinterpret_cast<void*>(&kp::k_batch<float, false>)
-                      : reinterpret_cast<void*>(&kp::k_batch<double, false>));
+  p2.func = const_cast<void*>(kernel);
   p2.gridDim = dim3(b->n_wg);
   p2.blockDim = dim3(kp::kThreads);
   p2.kernelParams = a2;
@@ -2461,6 +2472,7 @@ int kp_phi_combo_batched(kp_ctx* ctx, int32_t nprob, const kp_op* ops, const dou
   std::sort(spans.begin(), spans.end());
   for (int i = 1; i < nprob; ++i)
     if (spans[i].first < spans[i - 1].second) return KP_EINVAL;
+  choose_batch_kernel(as);
   std::vector<long long> key = {nprob, m_max, ctx->cfg.basis_dtype, ctx->cfg.orth,
                                 ctx->cfg.fixed_m, ctx->cfg.fixed_substeps, ctx->model_gen,
                                 // the workspace's layout (prob_bufs) also depends on what

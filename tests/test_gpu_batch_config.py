@@ -9,6 +9,7 @@ import pytest
 import torch
 
 import workloads as W
+from oracle import krylov
 import paper_2410_14917_amd as kp
 
 pytestmark = pytest.mark.gpu
@@ -38,3 +39,33 @@ def test_batched_call_after_a_configuration_change(first, second):
         want = call(ctx)
     for y, y1 in zip(got, want):
         assert torch.equal(y, y1)
+
+
+@pytest.mark.parametrize("grids", [
+    [(W.OP_ADR, 7, 3), (W.OP_ADR, 45, 33), (W.OP_ALLEN_CAHN, 301, 210), (W.OP_BRUSSELATOR, 64, 41),
+     (W.OP_ADR, 600, 450)],
+    [(W.OP_BRUSSELATOR, 64, 41), (W.OP_BRUSSELATOR, 33, 150)]], ids=["mixed", "two-plane"])
+@pytest.mark.parametrize("cfg,tform", [({"orth": "h-cwy"}, "cwy"), ({"orth": "h-ncwy"}, "ncwy"),
+                                       ({"fallback_delta": 1e-3}, "gsmgs"), ({}, "gsmgs")],
+                         ids=["h-cwy", "h-ncwy", "h-gsmgs-delta", "h-gsmgs"])
+def test_batched_forms_with_and_without_block_steps(cfg, tform, grids):
+    """Single steps (k_run's phases, or the block kernel's where every problem has
+    two planes) and block steps: one workgroup, teams, odd rows, two species;
+    against the oracle, and the same bits from a graph replay."""
+    print(f"batch forms: {cfg}", flush=True)
+    probs = [W.random_problem(920 + i, kind=k, nx=nx, ny=ny, p=2, h=0.02, nu=0.02 / nx)
+             for i, (k, nx, ny) in enumerate(grids)]
+    ops = [kp.Operator.from_host(q.op) for q in probs]
+    Bs = [torch.as_tensor(np.ascontiguousarray(q.B[:, :3].T), device="cuda") for q in probs]
+    m = 13
+    with kp.Context(fixed_m=m, fixed_substeps=2, **cfg) as ctx:
+        ys, infos = ctx.phi_combo_batched(ops, Bs, [q.h for q in probs], m_max=m, info=True)
+        ys = [y.clone() for y in ys]
+        again = ctx.phi_combo_batched(ops, Bs, [q.h for q in probs], m_max=m)
+    delta = cfg.get("fallback_delta", 1e-10)
+    for q, y, y2, inf in zip(probs, ys, again, infos):
+        ref, rinfo = krylov.phi_combo(q.op, q.B, q.h, 2, fixed_m=m, fixed_substeps=2, m_max=m,
+                                      orth="hybrid", tform=tform, delta=delta)
+        assert inf["status"] == 0 and inf["arnoldi_steps"] == rinfo.arnoldi_steps
+        assert np.linalg.norm(y.cpu().numpy() - ref) <= 1e-10 * np.linalg.norm(ref)
+        assert torch.equal(y, y2)
