@@ -950,11 +950,14 @@ __global__ __launch_bounds__(kThreads) void k_read_probe(const double2* x, int64
   if ((threadIdx.x & 63) == 0) sink[(int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6)] = s;
 }
 
-// Small exponential alone (test entry): F = exp(tau Hbar_m) e_1 from st->H.
-__global__ __launch_bounds__(kThreads) void k_expm_test(Args a, int m, double tau) {
+// Small exponential alone (test entry): F = exp(tau Hbar_m) e_1.  H and F are in
+// the small exponential's scratch, not in the State: a paused Arnoldi process
+// resumes from the H there (block steps make their columns from it).
+__global__ __launch_bounds__(kThreads) void k_expm_test(const double* H, double* F, int m, double tau) {
   __shared__ __attribute__((aligned(16))) double lds[kLdsDoubles];
-  expm_hbar(HessCol{a.st->H, kLdh}, m, tau, false, a.st->F, lds);
+  expm_hbar(HessCol{H, kLdh}, m, tau, false, F, lds);
 }
+static_assert(kLdh * kMMax + kNmPad <= kExSlots * kNmPad * kNmPad, "H and F of the test entry");
 
 // Workspace of the allocation-free entry point (kp_phi_combo_noalloc): one
 // array per GPU, 32 MiB above KP_NOALLOC_BYTES for the halo rows and partial
@@ -2682,13 +2685,11 @@ int kp_calibrate(kp_ctx* ctx, int32_t force, double* model_host) {
       for (int r = 0; r <= c + 1; ++r)
         Hs[(size_t)c * kp::kLdh + r] = (r == c) ? -2.0 - 0.05 * c : 0.3 * std::sin(1.0 + r + 7.0 * c);
     KP_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    KP_HIP(ctx, hipMemcpy(ctx->st->H, Hs.data(), Hs.size() * sizeof(double), hipMemcpyHostToDevice));
-    Args a{};
-    a.st = ctx->st;
-    a.ex = ctx->ex;
+    KP_HIP(ctx, hipMemcpy(ctx->ex, Hs.data(), Hs.size() * sizeof(double), hipMemcpyHostToDevice));
     double t = 0.0;
     rc = timed([&]() {
-      hipLaunchKernelGGL(kp::k_expm_test, dim3(1), dim3(kp::kThreads), 0, ctx->stream, a, m, 1.0);
+      hipLaunchKernelGGL(kp::k_expm_test, dim3(1), dim3(kp::kThreads), 0, ctx->stream, ctx->ex,
+                         ctx->ex + Hs.size(), m, 1.0);
       return hipGetLastError() == hipSuccess ? KP_OK : KP_EHIP;
     }, 5, &t);
     if (rc) return rc;
@@ -2785,14 +2786,12 @@ int kp_expm_hbar(kp_ctx* ctx, const double* H_host, int32_t ldh, int32_t m, doub
   for (int c = 0; c < m; ++c)
     for (int r = 0; r <= m; ++r) Hs[(size_t)c * kp::kLdh + r] = H_host[(size_t)c * ldh + r];
   KP_HIP(ctx, hipStreamSynchronize(ctx->stream));
-  KP_HIP(ctx, hipMemcpy(ctx->st->H, Hs.data(), Hs.size() * sizeof(double), hipMemcpyHostToDevice));
-  Args a{};
-  a.st = ctx->st;
-  a.ex = ctx->ex;
-  hipLaunchKernelGGL(kp::k_expm_test, dim3(1), dim3(kp::kThreads), 0, ctx->stream, a, m, tau);
+  double* F = ctx->ex + Hs.size();
+  KP_HIP(ctx, hipMemcpy(ctx->ex, Hs.data(), Hs.size() * sizeof(double), hipMemcpyHostToDevice));
+  hipLaunchKernelGGL(kp::k_expm_test, dim3(1), dim3(kp::kThreads), 0, ctx->stream, ctx->ex, F, m, tau);
   KP_HIP(ctx, hipGetLastError());
   KP_HIP(ctx, hipStreamSynchronize(ctx->stream));
-  KP_HIP(ctx, hipMemcpy(F_host, ctx->st->F, (m + 1) * sizeof(double), hipMemcpyDeviceToHost));
+  KP_HIP(ctx, hipMemcpy(F_host, F, (m + 1) * sizeof(double), hipMemcpyDeviceToHost));
   return KP_OK;
 }
 

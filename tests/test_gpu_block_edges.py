@@ -1,0 +1,37 @@
+"""Block steps (up to three Arnoldi steps per reduction, float64 H-GSMGS) where
+other calls or unusual data meet them."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+import paper_2410_14917_amd as kp
+
+pytestmark = pytest.mark.gpu
+
+
+def _dev(pr):
+    return (kp.Operator.from_host(pr.op),
+            torch.as_tensor(np.ascontiguousarray(pr.B[:, :pr.p + 1].T), device="cuda"))
+
+
+@pytest.mark.parametrize("orth", ["h-gsmgs", "mgs"])
+def test_paused_process_is_not_touched_by_a_small_exponential(orth):
+    """arnoldi_begin, 5 steps, expm_hbar, 7 more: the bits of the same process
+    without the call between (the later columns of a block are made from the
+    Hessenberg columns of the steps before the pause)."""
+    print(f"expm between steps: {orth}", flush=True)
+    pr = W.random_problem(71, kind=W.OP_ADR, nx=61, ny=40, p=2, h=0.02, nu=1e-3)
+    op, B = _dev(pr)
+    H = np.triu(np.random.default_rng(3).standard_normal((12, 11)), -1)
+    res = []
+    for between in (False, True):
+        with kp.Context(orth=orth) as ctx:
+            ctx.arnoldi_begin(op, B, 20)
+            ctx.arnoldi_step(5)
+            if between:
+                ctx.expm_hbar(H, 11, 0.3)
+            ctx.arnoldi_step(7)
+            res.append(ctx.arnoldi_read())
+    assert res[0]["j"] == res[1]["j"] == 12
+    assert np.array_equal(res[0]["H"], res[1]["H"]) and np.array_equal(res[0]["V"], res[1]["V"])
