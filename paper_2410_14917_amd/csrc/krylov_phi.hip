@@ -1136,10 +1136,12 @@ int build_args(const kp_ctx* ctx, const kp_op* A, const double* B, int p, int64_
   r.tol = tol > 0.0 ? tol : 1.0;
   r.delta = cfg.fallback_delta == 0.0 ? 1e-10 : (cfg.fallback_delta < 0.0 ? 0.0 : cfg.fallback_delta);
   r.eps_bd = cfg.breakdown_eps == 0.0 ? 1e-12 : cfg.breakdown_eps;
-  // several steps per reduction: H-GSMGS only (see kp_block.h); a fallback
+  // several steps per reduction: H-GSMGS only (see kp_block.h).  A fallback
   // threshold above the guard takes the exact norm at every step, so there is
-  // no estimate to divide a first vector by
-  r.pairs = (r.block && r.orth == KP_ORTH_H_GSMGS && r.delta <= kp::kGuard) ? 1 : 0;
+  // no estimate to divide a first vector by.  The later vectors of a block are
+  // held against the guard alone (0.01 of a norm), so a breakdown threshold
+  // that comes near it (default 1e-12) is tested step by step.
+  r.pairs = (r.block && r.orth == KP_ORTH_H_GSMGS && r.delta <= kp::kGuard && r.eps_bd <= kp::kGuard) ? 1 : 0;
   *a = r;
   return KP_OK;
 }

@@ -5,6 +5,7 @@ import pytest
 import torch
 
 import workloads as W
+from oracle import arnoldi, krylov
 import paper_2410_14917_amd as kp
 
 pytestmark = pytest.mark.gpu
@@ -35,3 +36,28 @@ def test_paused_process_is_not_touched_by_a_small_exponential(orth):
             res.append(ctx.arnoldi_read())
     assert res[0]["j"] == res[1]["j"] == 12
     assert np.array_equal(res[0]["H"], res[1]["H"]) and np.array_equal(res[0]["V"], res[1]["V"])
+
+
+@pytest.mark.parametrize("nval,noise,eps", [(2, 0.06, 0.05), (3, 0.04, 0.08)])
+def test_a_large_breakdown_threshold_is_tested_at_every_step(nval, noise, eps):
+    """A diagonal operator of nval clusters: the process nearly closes after nval
+    columns, in a later vector of what would be a block of three, above the
+    guard and below the threshold.  It ends where the oracle's does."""
+    d = np.linspace(-3.0, 1.0, nval)
+    rng = np.random.default_rng(5)
+    diag = d[rng.integers(0, nval, 2800)] + noise * rng.uniform(-1.0, 1.0, 2800)
+    op_h = W.Operator(kind=W.OP_ADR, nx=70, ny=40, field0=diag)
+    Bh = np.random.default_rng(6).standard_normal((2800, 1))
+    ref = arnoldi.HybridArnoldi(lambda x: krylov.aug_apply(op_h, Bh, 0, 1.0, x),
+                                krylov.start_vector(Bh, 0, 1.0), 8, tform="gsmgs", eps_bd=eps)
+    ref.extend(8)
+    assert ref.breakdown and ref.j == nval
+    op = kp.Operator.from_host(op_h)
+    B = torch.as_tensor(np.ascontiguousarray(Bh.T), device="cuda")
+    with kp.Context(breakdown_eps=eps) as ctx:
+        ctx.arnoldi_begin(op, B, 8)
+        ctx.arnoldi_step(8)
+        r = ctx.arnoldi_read()
+    assert r["breakdown"] and r["j"] == nval
+    H, Hr = r["H"][:nval, :nval], ref.H[:nval, :nval]
+    assert np.linalg.norm(H - Hr) <= 1e-12 * np.linalg.norm(Hr)
