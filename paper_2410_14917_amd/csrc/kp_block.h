@@ -1388,7 +1388,7 @@ __device__ __attribute__((always_inline)) inline void block_scalar(const Args& a
       }
     }
 #pragma unroll
-    for (int q = 0; q < kS; ++q) sb[72 * q + i] = in ? sig * sj * row[kS + q] : 0.0;
+    for (int q = 0; q < kS; ++q) sb[72 * q + i] = in ? sig * row[kS + q] * sj : 0.0;
     if (big) L.big = 1;
   }
   __syncthreads();
@@ -1411,14 +1411,16 @@ __device__ __attribute__((always_inline)) inline void block_scalar(const Args& a
   __syncthreads();
   if (!w0) return;
   const bool in = i <= j;
-  const double sj = ial[kS - 1], sj2 = sj * sj;
+  // (products are scaled by s_j twice, not by its square, which overflows where
+  // ||x_j||^2 is subnormal)
+  const double sj = ial[kS - 1];
   double b[kS], c[kS];
 #pragma unroll
   for (int q = 0; q < kS; ++q) {
     b[q] = in ? sb[72 * q + i] : 0.0;
     c[q] = in ? L.c[q][i] : 0.0;
   }
-  const double wn2 = cww * sj2;
+  const double wn2 = cww * sj * sj;
   const double t4 = wave_sum4(b[0] * b[0], b[0] * c[0], b[0] * c[1], b[0] * c[2]);
   const double ss = readlane_d(t4, 0);
   const double est2 = wn2 - ss;
@@ -1432,8 +1434,8 @@ __device__ __attribute__((always_inline)) inline void block_scalar(const Args& a
   double i00 = 0.0, i11 = 1.0, i22 = 1.0;
   if (ns > 1 && !bad && !fallback && !bd && est2 > kGuard * wn2) {
     const double u4 = wave_sum4(b[1] * c[1], b[1] * c[2], b[2] * c[2], 0.0);
-    const double n00 = wn2 - readlane_d(t4, 1), n01 = G[gram_at(kS, kS + 1)] * sj2 - readlane_d(t4, 2);
-    const double g11 = G[gram_at(kS + 1, kS + 1)] * sj2, n11 = g11 - readlane_d(u4, 0);
+    const double n00 = wn2 - readlane_d(t4, 1), n01 = G[gram_at(kS, kS + 1)] * sj * sj - readlane_d(t4, 2);
+    const double g11 = G[gram_at(kS + 1, kS + 1)] * sj * sj, n11 = g11 - readlane_d(u4, 0);
     const double q00 = inv_sqrt(n00), q01 = n01 * q00, d1 = n11 - q01 * q01;
     if (n00 > 1e-290 && n00 < 1e290 && g11 < 1e290 && d1 > kGuard * g11 && d1 > 1e-290) {
       done = 2;
@@ -1443,9 +1445,9 @@ __device__ __attribute__((always_inline)) inline void block_scalar(const Args& a
       i11 = inv_sqrt(d1);
       r11 = d1 * i11;
       if (ns > 2) {
-        const double g22 = G[gram_at(kS + 2, kS + 2)] * sj2, n22 = g22 - readlane_d(u4, 2);
-        const double n02 = G[gram_at(kS, kS + 2)] * sj2 - readlane_d(t4, 3);
-        const double n12 = G[gram_at(kS + 1, kS + 2)] * sj2 - readlane_d(u4, 1);
+        const double g22 = G[gram_at(kS + 2, kS + 2)] * sj * sj, n22 = g22 - readlane_d(u4, 2);
+        const double n02 = G[gram_at(kS, kS + 2)] * sj * sj - readlane_d(t4, 3);
+        const double n12 = G[gram_at(kS + 1, kS + 2)] * sj * sj - readlane_d(u4, 1);
         const double q02 = n02 * i00, q12 = (n12 - r01 * q02) * i11, d2 = n22 - q02 * q02 - q12 * q12;
         if (g22 < 1e290 && d2 > kGuard * g22 && d2 > 1e-290) {
           done = 3;

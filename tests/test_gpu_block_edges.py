@@ -61,3 +61,23 @@ def test_a_large_breakdown_threshold_is_tested_at_every_step(nval, noise, eps):
     assert r["breakdown"] and r["j"] == nval
     H, Hr = r["H"][:nval, :nval], ref.H[:nval, :nval]
     assert np.linalg.norm(H - Hr) <= 1e-12 * np.linalg.norm(Hr)
+
+
+@pytest.mark.parametrize("kind,nx,ny", [(W.OP_ADR, 64, 48), (W.OP_BRUSSELATOR, 40, 36)])
+def test_right_hand_sides_of_subnormal_squared_norm(kind, nx, ny):
+    """B scaled by 2^-524, so that ||b||^2 is subnormal: the result is 2^-524
+    times the result for B.  A square there is rounded to 2^-1074, 2^-20 or less
+    of its value for the entries that carry the norm, at random over thousands
+    of entries: 1e-6."""
+    print(f"subnormal: kind {kind} {nx}x{ny}", flush=True)
+    pr = W.random_problem(83, kind=kind, nx=nx, ny=ny, p=1, h=0.02, nu=1e-3)
+    op, B = _dev(pr)
+    s = 2.0 ** -524
+    n2 = float(((s * B[0]) ** 2).sum())
+    assert 0.0 < n2 < 2.0 ** -1022
+    with kp.Context(fixed_m=12, fixed_substeps=2) as ctx:
+        y, _ = ctx.phi_combo(op, B, pr.h, m_max=12, info=True)
+        z, info = ctx.phi_combo(op, s * B, pr.h, m_max=12, info=True)
+    assert info["status"] == 0 and info["arnoldi_steps"] == 24
+    z = z / s
+    assert float(torch.linalg.vector_norm(z - y) / torch.linalg.vector_norm(y)) <= 1e-6
