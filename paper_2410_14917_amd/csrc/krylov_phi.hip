@@ -1331,6 +1331,28 @@ size_t halo_area(const Args& a, int nwg) {
   return halo_doubles(a, nwg) * (a.ll ? 5 : (a.pairs ? 2 : 1)) + (a.ll ? 2 * kp::kPMax : 0);
 }
 
+// Workspace that a context keeps beside the basis and the state vector, sized so
+// that a call whose coarse partition (geometry without spread) and vectors are
+// no larger than those of an earlier call never grows it: the finer partitions
+// give a smaller grid more workgroups, tags or halo rows than a larger one, and
+// growing stops the stream, is refused under capture and frees what captured
+// graphs of earlier calls use.  Partial sums and flags: every slot of the chip at
+// the largest stride (1.7 MB).  Halo rows: with nx * planes of 4096 or more both
+// partitions are the same, so twice the coarse count; below, two buffers take
+// at most 4 N doubles and at most 4 * 4096 per workgroup slot; the tagged
+// exchange at most kLlMax elements a row and five buffers per slot.
+size_t part_kept(int slots) {
+  return (size_t)slots * kp::kCStride + 2 * (size_t)(slots + 1) * (kp::kNv * kp::kMMax + 24);
+}
+static_assert(kp::kNv * kp::kMMax + 24 >= kp::kKStride, "the larger stride of a step buffer");
+size_t halo_kept(int slots, int rows_cfg, const Args& a, size_t u_doubles) {
+  Args g = a;
+  geometry(slots, rows_cfg, &g, false);
+  return std::max({halo_area(a, a.nwg), 2 * halo_doubles(g, g.nwg),
+                   std::min(4 * u_doubles, (size_t)slots * 4 * 4096),
+                   (size_t)slots * 2 * kLlMax * 5 + 2 * kp::kPMax});
+}
+
 // Allocate the workspace for a problem and finish Args.
 int prepare(kp_ctx* ctx, Args* a) {
   int rc = device_setup(ctx);
@@ -1347,15 +1369,17 @@ int prepare(kp_ctx* ctx, Args* a) {
     snprintf(ctx->err, sizeof(ctx->err), "the persistent kernel does not fit on a CU");
     return KP_EHIP;
   }
-  geometry(ctx->ncu * occ, ctx->cfg.rows_per_wg, a);
+  const int slots = ctx->ncu * occ;
+  geometry(slots, ctx->cfg.rows_per_wg, a);
   if ((rc = grow(ctx, reinterpret_cast<void**>(&ctx->part), &ctx->part_bytes,
-                 part_doubles(*a, a->nwg) * sizeof(double))))
+                 part_kept(slots) * sizeof(double))))
     return rc;
   if ((rc = grow(ctx, reinterpret_cast<void**>(&ctx->hx), &ctx->hx_bytes,
-                 halo_area(*a, a->nwg) * sizeof(double))))
+                 halo_kept(slots, ctx->cfg.rows_per_wg, *a, ctx->u_bytes / sizeof(double)) *
+                     sizeof(double))))
     return rc;
   if ((rc = grow(ctx, reinterpret_cast<void**>(&ctx->flags), &ctx->flags_bytes,
-                 (size_t)a->nwg * kp::kFlagStride * sizeof(unsigned))))
+                 (size_t)slots * kp::kFlagStride * sizeof(unsigned))))
     return rc;
   if (!ctx->st) {
     KP_HIP(ctx, hipMalloc(&ctx->st, sizeof(State)));
