@@ -24,7 +24,18 @@
 //               + (S / m_eff + r) t_expm(m_eff)              (small exponentials)
 // bw_wg is one workgroup's share of HBM bandwidth with the whole grid
 // streaming, e_min the element count below which a workgroup's passes are
-// latency-bound.
+// latency-bound.  P counts two passes over the basis per step; block steps make
+// two per three steps and share a reduction among them, so the constants are
+// effective ones of that form, 0.45 of those of single steps (19.5e9 bytes/s,
+// 5, 4 and 0.5 us): the other forms take the same plan and 2.2 times the time.
+// One common factor, since the assignment depends on ratios only and these are
+// the measured best: with P, the reductions and e_min of block steps written
+// out, the predictions are as good (596 ms) and the assignments worse (six
+// problems of sides 300 to 700 4.84 ms against 4.16; the 512 problems 598, 594).
+// Measured, predicted in brackets (block steps, identical problems on the whole
+// grid, m = 48, two substeps, p = 3; ms): 256 of 128^2 on one workgroup each 16.6
+// (16.9), of 256^2 64.9 (66.6), 16 of 512^2 on sixteen each 15.6 (17.2), four of
+// 512^2 on 64 each 4.1 (4.8); with m = 16 256 of 256^2 15.0 (9.8).
 //
 // Search (the autotuner): team-size mixes  k_big teams of g_big, k_mid teams
 // of g_mid, the rest single workgroups; for each mix the problems, heaviest
@@ -50,12 +61,12 @@ struct PlanProblem {
 };
 
 struct PlanModel {
-  double bw_wg = 19.5e9;     // bytes/s per workgroup, whole grid streaming
-  double e_min = 4096.0;     // elements per workgroup below which passes are latency-bound
-  double t_step = 5.0e-6;    // serial work + pass latencies per Arnoldi step
-  double t_team = 4.0e-6;    // team barriers per step (g > 1)
-  double t_log = 0.5e-6;     // per doubling of the team (reductions, waits)
-  double t_expm64 = 2.6e-4;  // small exponential at m = 64 (scales with m^2)
+  double bw_wg = 19.5e9 / 0.45;      // bytes/s per workgroup, whole grid streaming
+  double e_min = 4096.0;             // elements per workgroup below which passes are latency-bound
+  double t_step = 0.45 * 5.0e-6;     // serial work + pass latencies per Arnoldi step
+  double t_team = 0.45 * 4.0e-6;     // team barriers per step (g > 1)
+  double t_log = 0.45 * 0.5e-6;      // per doubling of the team (reductions, waits)
+  double t_expm64 = 0.45 * 2.6e-4;   // small exponential at m = 64 (scales with m^2)
   int rejects = 4;           // rejected trials per problem (extra exponentials)
 };
 
