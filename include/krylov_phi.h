@@ -405,18 +405,21 @@ int kp_batch_plan(int32_t nprob, const kp_op* ops, const int32_t* p, const doubl
  * call's autotuner): the small exponential's time at m = 64 is measured
  * directly, and the streaming rate of one workgroup with the whole grid
  * streaming, the serial time per Arnoldi step, per step of a multi-workgroup
- * team and per doubling of a team come from a least-squares fit of the model
- * to seven fixed-schedule advection-diffusion solves (one substep, m = 8..24,
- * 64 x 64 to 2048 x 1024 grids, one to 256 workgroups).  The context's later
+ * team and per doubling of a team come from a non-negative least-squares fit of
+ * the model to seven fixed-schedule runs of the batched kernel on uniform teams
+ * of 1 to 64 workgroups (advection-diffusion, one substep, m = 24 or 48,
+ * 64 x 64 to 512 x 512 grids).  The context's later
  * batched calls plan with the result.  With the environment variable
  * KP_AUTOTUNE_CACHE naming a file, a cached result for this device (GPU
- * architecture, CU count, library version) is read instead of measuring
+ * architecture, CU count, library version, kernels) is read instead of measuring
  * unless force != 0, and a measured one is stored there.
  *   model_host: optional, 5 doubles: bytes/s per workgroup, serial seconds
  *               per step, per team step, per team doubling, and seconds per
  *               small exponential at m = 64.
- * Returns 0 (measured) or 1 (read from the cache), or a KP_E code.  About
- * 0.1 s of device work on the context's stream; synchronises it.
+ * Returns 0 (measured), 1 (read from the cache) or 2 (the measured times have no
+ * usable fit: the built-in constants are kept and nothing is cached), or a KP_E
+ * code.  About 0.1 s of device work on the context's stream and 1.7 GB of device
+ * memory for it; synchronises the stream.
  */
 int kp_calibrate(kp_ctx* ctx, int32_t force, double* model_host);
 

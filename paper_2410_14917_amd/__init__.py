@@ -267,13 +267,14 @@ class Context:
     def calibrate(self, force: bool = False):
         """Measure (or read from KP_AUTOTUNE_CACHE) the batched planner's cost
         model on this device; later batched calls of this context plan with
-        it.  Returns (source: "measured" | "cache", model dict)."""
+        it.  Returns (source: "measured" | "cache" | "default", model dict);
+        "default": no usable fit, the built-in constants are kept."""
         import numpy as np
         v = np.zeros(5)
         rc = _lib.check(self.lib.kp_calibrate(self.h, int(bool(force)),
                                               v.ctypes.data_as(ctypes.c_void_p)), self.h)
         keys = ("bw_wg_Bps", "t_step_s", "t_team_s", "t_log_s", "t_expm64_s")
-        return ("cache" if rc == 1 else "measured"), dict(zip(keys, v.tolist()))
+        return ("measured", "cache", "default")[rc], dict(zip(keys, v.tolist()))
 
     def read_bandwidth(self, nbytes: int = 1 << 30, reps: int = 20) -> float:
         """Practical HBM read rate in GB/s (kp_read_bandwidth: a plain

@@ -97,15 +97,20 @@ inline void plan_rows(int nx, int ny, int g, int* rows, int* nwg_rows) {
   *nwg_rows = (ny + r - 1) / r;
 }
 
-inline double plan_time(const PlanProblem& q, int g, const PlanModel& md) {
-  const double S = plan_steps(q);
-  const double m = std::min<double>(S, q.m_max);
+// Bytes streamed by a workgroup of a team of g for S steps in substeps of m.
+inline double plan_bytes(const PlanProblem& q, double S, double m, int g, const PlanModel& md) {
   const double passes = S * (m + q.p + q.c + 6.0);
   int rows, nw;
   plan_rows(q.nx, q.ny, g, &rows, &nw);
   const double per_wg = std::max((double)rows * q.nx * ((double)q.n / ((double)q.nx * q.ny)),
                                  md.e_min);
-  const double stream = 8.0 * passes * per_wg / md.bw_wg;
+  return 8.0 * passes * per_wg;
+}
+
+inline double plan_time(const PlanProblem& q, int g, const PlanModel& md) {
+  const double S = plan_steps(q);
+  const double m = std::min<double>(S, q.m_max);
+  const double stream = plan_bytes(q, S, m, g, md) / md.bw_wg;
   const double serial = S * (md.t_step + (g > 1 ? md.t_team : 0.0) + std::log2((double)g) * md.t_log);
   const double expm = (std::ceil(S / m) + md.rejects) * md.t_expm64 * (m * m) / (64.0 * 64.0);
   return stream + serial + expm;
@@ -156,6 +161,22 @@ inline double lpt(const std::vector<PlanProblem>& qs, const std::vector<int>& he
 }
 
 }  // namespace detail
+
+// np problems spread evenly over teams of g workgroups (the calibration's sets).
+inline Plan uniform_plan(int np, int n_wg, int g) {
+  Plan pl;
+  const int nt = n_wg / g;
+  pl.team_of_wg.assign(n_wg, -1);
+  pl.team_first.assign(1, 0);
+  for (int t = 0; t < nt; ++t) {
+    pl.team_size.push_back(g);
+    pl.team_wg0.push_back(t * g);
+    for (int i = 0; i < g; ++i) pl.team_of_wg[t * g + i] = t;
+    for (int i = t; i < np; i += nt) pl.order.push_back(i);
+    pl.team_first.push_back((int)pl.order.size());
+  }
+  return pl;
+}
 
 // Plan nprob problems on a grid of n_wg workgroups.  Deterministic.
 inline Plan make_plan(const std::vector<PlanProblem>& qs, int n_wg, const PlanModel& md) {

@@ -1661,8 +1661,9 @@ ProbBufs prob_bufs(const Args& a, int nwg_max) {
 }
 
 // New plan, allocations and graph for the problem set of `as` (validated).
+// (forced: this plan instead of the planner's).
 int batch_create(kp_ctx* ctx, const std::vector<Args>& as, const std::vector<kp::PlanProblem>& qs,
-                 std::vector<long long>&& key, BatchCache** out) {
+                 std::vector<long long>&& key, BatchCache** out, const kp::Plan* forced = nullptr) {
   BatchCache* b = new BatchCache();
   b->key = std::move(key);
   const int np = (int)as.size();
@@ -1678,7 +1679,7 @@ int batch_create(kp_ctx* ctx, const std::vector<Args>& as, const std::vector<kp:
   }
   b->n_wg = ctx->ncu * occ;
   const kp::PlanModel model = ctx->model;
-  b->plan = kp::make_plan(qs, b->n_wg, model);
+  b->plan = forced ? *forced : kp::make_plan(qs, b->n_wg, model);
   const kp::Plan& pl = b->plan;
   const int nt = (int)pl.team_size.size();
   // classes: the runs of equal-size teams (the plan lays them out big, mid,
@@ -2659,7 +2660,8 @@ int kp_calibrate(kp_ctx* ctx, int32_t force, double* model_host) {
   hipDeviceProp_t prop;
   KP_HIP(ctx, hipGetDeviceProperties(&prop, ctx->device));
   char kbuf[256];
-  snprintf(kbuf, sizeof(kbuf), "%s/cu%d/lib%d", prop.gcnArchName, ctx->ncu, kp_version());
+  // (the steps per reduction and "batch" name the kernels that the fit is of)
+  snprintf(kbuf, sizeof(kbuf), "%s/cu%d/lib%d/batch%d", prop.gcnArchName, ctx->ncu, kp_version(), kp::kS);
   const std::string key(kbuf);
   const char* path = std::getenv("KP_AUTOTUNE_CACHE");
   kp::PlanModel md;
@@ -2721,61 +2723,73 @@ int kp_calibrate(kp_ctx* ctx, int32_t force, double* model_host) {
     if (rc) return rc;
     md.t_expm64 = t;
   }
-  // fixed-schedule solves (one substep of m steps, advection-diffusion, p = 1)
-  struct Cal { int nx, ny, rows, m; };
-  const Cal cals[] = {{1024, 1024, 0, 24}, {1024, 1024, 0, 8},  {2048, 1024, 0, 16},
-                      {64, 64, 0, 24},     {64, 64, 1, 24},     {256, 256, 16, 24},
-                      {512, 512, 8, 16}};
+  // fixed-schedule sets (one substep of m steps, advection-diffusion, p = 1) through
+  // the batched kernel itself, identical problems on uniform teams that fill the
+  // grid: teams of one and of more workgroups, 4096 and more elements each, so
+  // that the four columns of the fit are independent
+  struct Cal { int side, g, m; };
+  const Cal cals[] = {{128, 1, 48}, {64, 1, 48}, {128, 2, 48}, {128, 4, 48}, {256, 16, 48}, {512, 16, 24}, {512, 64, 48}};
   const int ncal = (int)(sizeof(cals) / sizeof(cals[0]));
-  const int p = 1;
-  const int64_t nmax = 2048 * 1024;
+  const int p = 1, n_wg = ctx->ncu;            // (one workgroup per CU at least is resident)
+  size_t nb = 0, ny = 0;
+  for (const Cal& c : cals) {
+    const size_t n = (size_t)c.side * c.side;
+    nb = std::max(nb, n * (p + 1));
+    ny = std::max(ny, n * (size_t)std::max(1, n_wg / c.g));
+  }
   double* Bd = nullptr;
   double* yd = nullptr;
-  KP_HIP(ctx, hipMalloc(&Bd, sizeof(double) * (size_t)nmax * (p + 1)));
-  if (hipMalloc(&yd, sizeof(double) * (size_t)nmax) != hipSuccess) {
+  KP_HIP(ctx, hipMalloc(&Bd, sizeof(double) * nb));
+  if (hipMalloc(&yd, sizeof(double) * ny) != hipSuccess) {
     hipFree(Bd);
     return KP_ENOMEM;
   }
-  hipLaunchKernelGGL(kp::k_fill_pattern, dim3(4096), dim3(256), 0, ctx->stream, Bd,
-                     (int64_t)nmax * (p + 1));
+  hipLaunchKernelGGL(kp::k_fill_pattern, dim3(4096), dim3(256), 0, ctx->stream, Bd, (int64_t)nb);
   const kp_config saved = ctx->cfg;
-  double AtA[16] = {0}, Atb[4] = {0};
+  ctx->cfg = kp_config{};                      // H-GSMGS, float64, the default controller
+  ctx->cfg.stream = saved.stream;
+  double A[ncal][4], y[ncal];
+  int used = 0;
   for (int i = 0; i < ncal && rc == KP_OK; ++i) {
     const Cal& c = cals[i];
+    if (c.g > n_wg) continue;
+    const int np = n_wg / c.g;
     kp_op op{};
     op.kind = KP_OP_ADR;
-    op.nx = c.nx;
-    op.ny = c.ny;
-    op.dx = 1.0 / c.nx;
-    op.dy = 1.0 / c.ny;
+    op.nx = op.ny = c.side;
+    op.dx = op.dy = 1.0 / c.side;
     op.nu = 0.01;
     op.ax = 1.0;
     op.ay = 0.5;
-    op.brus_a = 1.0;
-    op.brus_b = 3.0;
-    ctx->cfg = saved;
-    ctx->cfg.orth = KP_ORTH_H_GSMGS;
-    ctx->cfg.basis_dtype = KP_BASIS_F64;
-    ctx->cfg.controller = KP_CTRL_POWER;
     ctx->cfg.fixed_m = c.m;
     ctx->cfg.fixed_substeps = 1;
-    ctx->cfg.rows_per_wg = c.rows;
-    const int64_t n = (int64_t)c.nx * c.ny;
-    double t = 0.0;
-    rc = timed([&]() { return kp_phi_combo(ctx, &op, Bd, p, n, 0.01, 1.0, c.m, yd, nullptr); },
-               3, &t);
+    const int64_t n = (int64_t)c.side * c.side;
+    std::vector<Args> as(np);
+    std::vector<kp::PlanProblem> qs(np, plan_problem(op, p, c.m, 1e-4));
+    for (int q = 0; q < np && rc == KP_OK; ++q)
+      rc = build_args(ctx, &op, Bd, p, n, 1e-4, 1.0, c.m, yd + q * n, true, &as[q]);
     if (rc) break;
-    const Args& a = ctx->last;             // the geometry of the timed call
-    const double g = a.nwg;
+    choose_batch_kernel(as);
+    const kp::Plan plan = kp::uniform_plan(np, n_wg, c.g);
+    BatchCache* b = nullptr;
+    if ((rc = batch_create(ctx, as, qs, {}, &b, &plan))) break;
+    batch_fill_args(b, as, ctx->wait_ticks);
+    double t = 0.0;
+    rc = timed([&]() -> int {
+      KP_HIP(ctx, hipMemcpyAsync(b->d_args, b->hargs.data(), sizeof(Args) * b->hargs.size(),
+                                 hipMemcpyHostToDevice, ctx->stream));
+      KP_HIP(ctx, hipGraphLaunch(b->exec, ctx->stream));
+      return KP_OK;
+    }, 3, &t);
+    hipStreamSynchronize(ctx->stream);
+    batch_free(b);
     const double S = c.m;
-    const double P = S * (S + p + 0 + 6.0);
-    const double X = 8.0 * P * std::max((double)a.rows_per_wg * c.nx, md.e_min);
-    const double f[4] = {X, S, g > 1 ? S : 0.0, S * std::log2(g)};
-    const double y = t - md.t_expm64 * (S * S) / (64.0 * 64.0);
-    for (int r = 0; r < 4; ++r) {
-      Atb[r] += f[r] * y;
-      for (int k = 0; k < 4; ++k) AtA[r * 4 + k] += f[r] * f[k];
-    }
+    y[used] = t - md.t_expm64 * (S * S) / (64.0 * 64.0);
+    A[used][0] = kp::plan_bytes(qs[0], S, S, c.g, md);
+    A[used][1] = S;
+    A[used][2] = c.g > 1 ? S : 0.0;
+    A[used][3] = S * std::log2((double)c.g);
+    ++used;
   }
   ctx->cfg = saved;
   ctx->have_begin = 0;
@@ -2784,13 +2798,40 @@ int kp_calibrate(kp_ctx* ctx, int32_t force, double* model_host) {
   hipEventDestroy(e0);
   hipEventDestroy(e1);
   if (rc) return rc;
-  double x[4] = {0, 0, 0, 0};
-  if (solve_small(4, AtA, Atb, x) && x[0] > 0.0) {
-    md.bw_wg = 1.0 / x[0];
-    md.t_step = std::max(x[1], 1e-7);
-    md.t_team = std::max(x[2], 0.0);
-    md.t_log = std::max(x[3], 0.0);
+  // least squares of the relative errors, the coefficients not negative: the most
+  // negative of a solution is left out and the rest fitted again
+  double x[4] = {0};
+  bool in[4] = {true, true, true, true}, ok = false;
+  for (int round = 0; round < 4; ++round) {
+    double AtA[16], Atb[4], z[4];
+    for (int r = 0; r < 4; ++r) {
+      Atb[r] = 0.0;
+      for (int k = 0; k < 4; ++k) AtA[r * 4 + k] = (r == k && !in[r]) ? 1.0 : 0.0;
+      for (int i = 0; i < used && in[r]; ++i) {
+        Atb[r] += A[i][r] / y[i];
+        for (int k = 0; k < 4; ++k)
+          if (in[k]) AtA[r * 4 + k] += A[i][r] * A[i][k] / (y[i] * y[i]);
+      }
+    }
+    if (!solve_small(4, AtA, Atb, z)) break;
+    int worst = -1;
+    for (int k = 1; k < 4; ++k)
+      if (in[k] && z[k] < 0.0 && (worst < 0 || z[k] * A[used - 1][k] < z[worst] * A[used - 1][worst])) worst = k;
+    if (worst < 0) {
+      std::copy(z, z + 4, x);
+      ok = x[0] > 0.0;
+      break;
+    }
+    in[worst] = false;
   }
+  if (!ok) {   // no usable fit: the built-in constants, and nothing cached
+    md = kp::PlanModel();
+    return finish(2);
+  }
+  md.bw_wg = 1.0 / x[0];
+  md.t_step = std::max(x[1], 1e-7);
+  md.t_team = x[2];
+  md.t_log = x[3];
   if (path && *path) cache_write(path, key, md);
   return finish(0);
 }

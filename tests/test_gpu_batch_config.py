@@ -69,3 +69,22 @@ def test_batched_forms_with_and_without_block_steps(cfg, tform, grids):
         assert inf["status"] == 0 and inf["arnoldi_steps"] == rinfo.arnoldi_steps
         assert np.linalg.norm(y.cpu().numpy() - ref) <= 1e-10 * np.linalg.norm(ref)
         assert torch.equal(y, y2)
+
+
+def test_calibration_is_a_fit_of_the_present_kernels(tmp_path, monkeypatch):
+    """The model is fitted (none of the built-in constants comes back), and a
+    cached fit of the kernels before block steps is not taken."""
+    dev = torch.cuda.get_device_properties(0)
+    cache = tmp_path / "autotune.txt"
+    old = f"{dev.gcnArchName}/cu{dev.multi_processor_count}/lib{kp._lib.load().kp_version()}"
+    cache.write_text(f"{old} 1.9e10 1e-7 0 7e-6 9e-5\n")
+    monkeypatch.setenv("KP_AUTOTUNE_CACHE", str(cache))
+    with kp.Context() as ctx:
+        src, md = ctx.calibrate()
+    print(src, md, flush=True)
+    assert src == "measured" and len(cache.read_text().splitlines()) == 2
+    assert abs(md["bw_wg_Bps"] / (19.5e9 / 0.45) - 1) > 1e-9
+    assert abs(md["t_expm64_s"] / (0.45 * 2.6e-4) - 1) > 1e-9
+    assert md["t_step_s"] >= 1e-7 and md["t_team_s"] >= 0.0 and md["t_log_s"] >= 0.0
+    # (streaming: 256 workgroups at 10 to 200 GB/s of two-pass bytes each)
+    assert 1e10 < md["bw_wg_Bps"] < 2e11
