@@ -137,6 +137,18 @@ def basis_bytes_per_call(schedule, p, c, n, s):
     return (total + 8) * n
 
 
+def block_starts(m):
+    """(newest column, steps) of the blocks of an m-step process of the float64
+    H-GSMGS form where the guard shortens none: the remainder of m / 3 first,
+    then three steps each; one grid-wide reduction per block, one at the close."""
+    j, out = 0, []
+    while j < m:
+        n = m % 3 if j == 0 and m % 3 else 3
+        out.append((j, n))
+        j += n
+    return out
+
+
 def block_vectors_per_call(schedule, p, c, keep):
     """Vector passes (each N float64) that a call of the float64 H-GSMGS form
     moves: its kernel makes up to three Arnoldi steps per reduction, so a pass
@@ -152,8 +164,7 @@ def block_vectors_per_call(schedule, p, c, keep):
     total = (p + 1) + 1
     for _, m in schedule:
         total += 2                                     # column 0 from the state
-        for j in range(0, m, 3):
-            n = min(3, m - j)
+        for j, n in block_starts(m):
             total += 2 * (j + 1) + p + c + n
             total += (3 if n == 3 else 0) if keep else 4 * n - 1 + (n - 1) * (p + c)
         total += m + 1

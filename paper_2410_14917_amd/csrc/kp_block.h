@@ -6,7 +6,7 @@
 // projection) and synchronises the grid once.  Both costs are shared by kS
 // Krylov vectors from one reduction: with x_j the newest column and theta a
 // shift (the last diagonal entry of H, which keeps the w_k apart),
-//     w_1 = Atilde x_j,  w_{k+1} = (Atilde - theta) w_k,
+//     w_1 = (Atilde - theta) x_j,  w_{k+1} = (Atilde - theta) w_k,
 // one pass over the basis forms the inner products of every column with the
 // unmeasured columns and with the w_k, and one pass forms the new columns
 //     [x_{j+1} .. x_{j+s}] = (W - U C) R^{-1},  C = T U'W,  R'R = W'W - (U'W)'C
@@ -14,21 +14,35 @@
 // measured columns.  The Hessenberg columns are exact combinations: with
 // Atilde w_k = w_{k+1} + theta w_k and Atilde U_{<j} = U H_{<j} (the columns
 // made before),
-//     Atilde u_j = U c_1 + X R e_1,
-//     Atilde (W - U C)_k = U (c_{k+1} + theta c_k - H_{<j} c_k - c_{kj} c_1)
+//     Atilde u_j = U h_j + X R e_1,  h_j = c_1 + theta e_j,
+//     Atilde (W - U C)_k = U (c_{k+1} + theta c_k - H_{<j} c_k - c_{kj} h_j)
 //                          + X (R_{k+1} + theta R_k - c_{kj} R_1),
-// times R^{-1}: the same H as single steps to rounding (Krylov dimension 64 on
-// the benchmark operators: 3e-14 to 7e-14 relative, single steps 2e-14 to 4e-14,
-// both against modified Gram-Schmidt; loss of orthogonality 2e-13.  Four
-// steps with the shift lose 4e-12, and two steps without it what three lose
-// with it).  The new columns are unmeasured: their norms and products come
-// with the next reduction (the lagged norms of Algorithm 4, for s columns).
+// times R^{-1}: the same H as single steps to rounding.  The new columns are
+// unmeasured: their norms and products come with the next reduction (the
+// lagged norms of Algorithm 4, for s columns).
 // Where a w_k lies almost inside the span already there (guard kGuard on the
 // squared norms), the columns before it are made and the next block starts
 // there; kMaxShort blocks in a row that made one step end the attempts.  The
-// forms H-CWY and H-NCWY always take single steps: their one-sided corrections
-// do not remove the measured loss of orthogonality to first order, which a
-// block needs.
+// forms H-CWY and H-NCWY always take single steps (theta = 0): their one-sided
+// corrections do not remove the measured loss of orthogonality to first order,
+// which a block needs.
+//
+// What a block loses: a vector whose norm falls by rho in the projection passes
+// 1 / rho of the rounding to the new column, and three of them in a row multiply
+// from block to block.  The shift of every product, the first one too, keeps rho
+// near the spread of the spectrum whatever its distance from zero; the guard
+// bounds what is left (the first block of a process, which has no shift yet and
+// takes the remainder of the steps, smooth start vectors, operators that the tail
+// couples).  Loss of orthogonality on the device, a diagonal at -50 (1 +- 0.05), p = 1,
+// 24 columns: 3.7e-14, single steps 2.1e-14, without the shift of the first product
+// 8.7e-8.  Error of the 64 x 64 call, 40 steps, against the closed form (mean of 30
+// inputs): 1.1e-15, as single steps; 2.1e-15 without that shift and with the
+// remainder at the end.  In a model in numpy,
+// 40 random operators with reaction terms up to -500 and 36 columns: at most
+// 4.4e-12, 1.6e-13 in the geometric mean; residual ||A V - V H|| / ||H|| on
+// diffusion operators, 64 columns, 1e-15 to 2e-15 (single steps 2e-16).  A guard of 1e-3
+// takes the mean to 8e-14 and costs a seventeenth block in some processes of 48
+// steps (256^2 call 3.05 -> 3.11 ms).  Four steps lose 4e-12 on diffusion operators.
 //
 // What bounds it: HBM (or Infinity Cache) bytes of the basis at large grids,
 // the latency chain of a phase (release, coefficients, halo flags, partial
@@ -156,6 +170,14 @@ __device__ inline void store_tables_b(const Args& a, const LeadB& L, bool all, i
 __device__ inline int block_steps(const Args& a, const LeadB& L, int j) {
   if (!a.pairs || L.nopair >= kMaxShort) return 1;
   return max(1, min(kS, min(L.m_target, a.stop_j) - j));
+}
+// ... and the first phase of a run of steps from column j (no update pending): the
+// remainder, so that the blocks after it are whole.  It has no shift at the start
+// of a process, and the short block reads fewest columns there: one at j = 0
+// instead of one at j = 63 is 3 % of the columns of 64 steps.
+__device__ inline int first_steps(const Args& a, const LeadB& L, int j) {
+  const int n = block_steps(a, L, j), left = min(L.m_target, a.stop_j) - j;
+  return (n == kS && left % kS) ? left % kS : n;
 }
 // (The shift starts from 0: the last one of the substep before belongs to the
 // end of its process, and the first vectors of this one are smooth.)
@@ -661,7 +683,7 @@ __device__ __attribute__((always_inline)) inline void tile_dots(const double* V,
 }
 
 // Tail rows of a block step (the last wave of workgroup 0, while the others
-// wait for their neighbours' halo rows): t_1 = K x, t_{k+1} = (K - theta) t_k
+// wait for their neighbours' halo rows): t_{k+1} = (K - theta) t_k from t_0 = x
 // (upward shift within each block of pb entries), stored, and their products
 // (column t by lane t; those of the block's vectors by lane 0), in ts.
 __device__ inline void tail_block(const Args& a, int j, int na, int ns, double theta, double* ts) {
@@ -683,7 +705,7 @@ __device__ inline void tail_block(const Args& a, int j, int na, int ns, double t
 #pragma unroll
     for (int k = 0; k < kPMax; ++k) {
       const double up = (k + 1 < kPMax && tail_shift_in(a, k)) ? b[kS - 1 + s][(k + 1) % kPMax] : 0.0;
-      b[kS + s][k] = (s < ns) ? (s ? up - theta * b[kS - 1 + s][k] : up) : 0.0;
+      b[kS + s][k] = (s < ns) ? up - theta * b[kS - 1 + s][k] : 0.0;
       if (t == 0 && k < p && s < ns) V[(int64_t)(j + 1 + s) * ld + T0 + k] = b[kS + s][k];
     }
   }
@@ -838,7 +860,6 @@ __device__ __attribute__((always_inline)) inline void matvec_keep(const Args& a,
     stage(a.hx);
   }
   for (int s = 0; s < ns; ++s) {
-    const double th = s ? theta : 0.0;
     const bool last = s + 1 == ns;
     double2 w[R];
 #pragma unroll
@@ -851,7 +872,7 @@ __device__ __attribute__((always_inline)) inline void matvec_keep(const Args& a,
           const double lap = __builtin_fma(a.cx, __builtin_fma(-2.0, x, xe + xw),
                                            a.cy * __builtin_fma(-2.0, x, xn + xs));
           const double adv = __builtin_fma(a.adx, xe - xw, a.ady * (xn - xs));
-          return __builtin_fma(d - th, x, a.kind == KP_OP_ADR ? lap + (a.transpose ? adv : -adv) : lap);
+          return __builtin_fma(d - theta, x, a.kind == KP_OP_ADR ? lap + (a.transpose ? adv : -adv) : lap);
         };
         double y0 = at(c, off[r][0], off[r][1], dg[r].x);
         double y1 = at(c1, off[r][2], off[r][3], dg[r].y);
@@ -894,7 +915,7 @@ __device__ __attribute__((always_inline)) inline void matvec_keep(const Args& a,
           }
         }
     if (!last) {
-      tail_next(a, th, tt);
+      tail_next(a, theta, tt);
       if (ll) {
         stage_ll(s + 1);
       } else {
@@ -965,7 +986,6 @@ __device__ __attribute__((always_inline)) inline void matvec_stream(const Args& 
   const double* hxs = a.hx;
   for (int s = 0; s < ns; ++s) {
     const bool last = s + 1 == ns;
-    const double th = s ? theta : 0.0;
     if (HL) stage_halo<double>(a, hxs, o, hl);
     __syncthreads();
     const Col<double> xc{V + (int64_t)(j + s) * ld};
@@ -976,7 +996,7 @@ __device__ __attribute__((always_inline)) inline void matvec_stream(const Args& 
       const int64_t pend = (sg.end + 1) >> 1;
       double tt[kPMax];
       tail_of_x(a, sg.plane, inv_mu, tt);
-      for (int e = 0; e < s; ++e) tail_next(a, e ? theta : 0.0, tt);
+      for (int e = 0; e < s; ++e) tail_next(a, theta, tt);
       for (int64_t q0 = sg.beg >> 1; q0 < pend; q0 += (int64_t)kThreads * R) {
         if (!wave_in_tile(q0, pend)) break;
         const int64_t t0 = 2 * q0;
@@ -989,8 +1009,8 @@ __device__ __attribute__((always_inline)) inline void matvec_stream(const Args& 
 #pragma unroll
         for (int r = 0; r < R; ++r) {
           const double2 c = xc.pair(t0 + lo[r]);
-          w[r].x = __builtin_fma(-th, c.x, w[r].x);
-          w[r].y = __builtin_fma(-th, c.y, w[r].y);
+          w[r].x = __builtin_fma(-theta, c.x, w[r].x);
+          w[r].y = __builtin_fma(-theta, c.y, w[r].y);
           if (ok[r]) {
             Pair<double>::store(wcol + t0 + lo[r], w[r].x, w[r].y);
             if (!last) publish_pair(a, hxn, sg, t0 + lo[r], w[r].x, w[r].y);
@@ -1420,10 +1440,13 @@ __device__ __attribute__((always_inline)) inline void block_scalar(const Args& a
     b[q] = in ? sb[72 * q + i] : 0.0;
     c[q] = in ? L.c[q][i] : 0.0;
   }
-  const double wn2 = cww * sj * sj;
+  // ||A u_j||^2 = ||w_1 + theta u_j||^2 for the fallback and breakdown rules
+  // (block_steps' theta is 0 for the forms without blocks)
+  const double th = L.theta, ws2 = cww * sj * sj;
+  const double wn2 = fmax(__builtin_fma(th, __builtin_fma(2.0, readlane_d(b[0], j), th), ws2), 0.0);
   const double t4 = wave_sum4(b[0] * b[0], b[0] * c[0], b[0] * c[1], b[0] * c[2]);
   const double ss = readlane_d(t4, 0);
-  const double est2 = wn2 - ss;
+  const double est2 = ws2 - ss;
   const int fallback = (est2 <= a.delta * wn2) ? 1 : 0;
   const double gam = fallback ? 1.0 : sqrt(est2);
   const int bd = (!fallback && gam <= a.eps_bd * sqrt(wn2)) ? 1 : 0;
@@ -1432,9 +1455,9 @@ __device__ __attribute__((always_inline)) inline void block_scalar(const Args& a
   int done = 1;
   double r00 = gam, r01 = 0.0, r02 = 0.0, r11 = 1.0, r12 = 0.0, r22 = 1.0;
   double i00 = 0.0, i11 = 1.0, i22 = 1.0;
-  if (ns > 1 && !bad && !fallback && !bd && est2 > kGuard * wn2) {
+  if (ns > 1 && !bad && !fallback && !bd && est2 > kGuard * ws2) {
     const double u4 = wave_sum4(b[1] * c[1], b[1] * c[2], b[2] * c[2], 0.0);
-    const double n00 = wn2 - readlane_d(t4, 1), n01 = G[gram_at(kS, kS + 1)] * sj * sj - readlane_d(t4, 2);
+    const double n00 = ws2 - readlane_d(t4, 1), n01 = G[gram_at(kS, kS + 1)] * sj * sj - readlane_d(t4, 2);
     const double g11 = G[gram_at(kS + 1, kS + 1)] * sj * sj, n11 = g11 - readlane_d(u4, 0);
     const double q00 = inv_sqrt(n00), q01 = n01 * q00, d1 = n11 - q01 * q01;
     if (n00 > 1e-290 && n00 < 1e290 && g11 < 1e290 && d1 > kGuard * g11 && d1 > 1e-290) {
@@ -1462,14 +1485,14 @@ __device__ __attribute__((always_inline)) inline void block_scalar(const Args& a
   if (done == 1) i00 = 1.0 / r00;
   const double i01 = -r01 * i00 * i11, i12 = -r12 * i11 * i22, i02 = -(r01 * i12 + r02 * i22) * i00;
   if (in) {
-    L.H[hcol(j) + i] = c[0];
+    L.H[hcol(j) + i] = i == j ? c[0] + th : c[0];
     cstore(&pb->coefs[0][i], -c[0] * i00 * sig);
     if (done > 1) cstore(&pb->coefs[1][i], -(c[0] * i01 + c[1] * i11) * sig);
     if (done > 2) cstore(&pb->coefs[2][i], -(c[0] * i02 + c[1] * i12 + c[2] * i22) * sig);
   }
   // the unit scales of the columns measured here
   if (in && i >= jo) L.sigma[i] = sig;
-  if (i == j) cstore(&pb->shift, c[0]);   // theta of the next block: H_jj
+  if (i == j && a.pairs) cstore(&pb->shift, c[0] + th);   // theta of the next block: H_jj
   if (i == 0) {
     cstore(&pb->coefs[0][j + 1], i00 * sj);
     if (done > 1) {
@@ -1492,8 +1515,8 @@ __device__ __attribute__((always_inline)) inline void block_scalar(const Args& a
     L.ri[1] = i01;
     L.ri[3] = i11;
     L.wn2 = wn2;
-    L.theta_used = L.theta;
-    L.theta = L.c[0][j];
+    L.theta_used = th;
+    if (a.pairs) L.theta = L.c[0][j] + th;
     if (j == 0) L.beta = alj;
     L.fallback_cur = fallback;
     L.n_fallback += fallback;
@@ -1552,9 +1575,9 @@ __device__ __attribute__((always_inline)) inline void block_post(int j, LeadB& L
   }
   const double th = L.theta_used, c0j = L.c[0][j], c1j = L.c[1][j];
   if (s == 0 && r <= j) {
-    const double c0 = L.c[0][r], c1 = L.c[1][r];
-    const double u0 = c1 + th * c0 - g[0] - c0 * c0j;
-    const double u1 = L.c[2][r] + th * c1 - g[1] - c0 * c1j;
+    const double c0 = L.c[0][r], c1 = L.c[1][r], hj = r == j ? c0 + th : c0;
+    const double u0 = c1 + th * c0 - g[0] - hj * c0j;
+    const double u1 = L.c[2][r] + th * c1 - g[1] - hj * c1j;
     L.rp[0][r] = u0 * L.ri[0];
     L.rp[1][r] = u0 * L.ri[1] + u1 * L.ri[3];
   }

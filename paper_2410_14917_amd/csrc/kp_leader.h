@@ -200,7 +200,7 @@ __device__ inline void begin_steps(const Args& a, const LT& L, Ctl& nx, int j, i
   nx.j = j;
   nx.upd = 0;
   nx.na = na;
-  nx.ns = block_steps(a, L, j);
+  nx.ns = first_steps(a, L, j);
   nx.pns = 0;
   nx.phase = step_phase(a);
 }
@@ -262,7 +262,7 @@ struct __attribute__((aligned(16))) LeadLds {
 
 // What the shared controller code asks of a kernel's tables (the block
 // kernels' versions are with LeadB).
-__device__ inline int block_steps(const Args&, const LeadLds&, int) { return 0; }
+__device__ inline int first_steps(const Args&, const LeadLds&, int) { return 0; }
 __device__ inline void new_process(const Args&, LeadLds&) {}
 __device__ inline double beta_of(const Args& a, const LeadLds&) { return a.st->beta; }
 __device__ inline HessCol hess_of(const Args& a, const LeadLds&) { return HessCol{a.st->H, kLdh}; }
