@@ -140,7 +140,9 @@ typedef struct kp_config {
     int32_t fixed_substeps;  /* with fixed_m: number of equal substeps (>=1)   */
     double  fallback_delta;  /* exact norm replaces the estimate when
                                 ||w||^2 - ss <= delta ||w||^2; 0 -> 1e-10,
-                                negative -> 0 (the printed rule)              */
+                                negative -> 0 (the printed rule).  Above 1e-4
+                                (breakdown_eps too) every step has a reduction
+                                of its own                                     */
     double  breakdown_eps;   /* lucky breakdown when ||v|| <= eps ||A v_j||;
                                 0 -> 1e-12                                     */
     double  tau_init;        /* first substep length of the adaptive controller;
@@ -165,15 +167,19 @@ typedef struct kp_info {
     int32_t breakdowns;      /* lucky breakdowns */
     int32_t schedule_len;    /* entries available through kp_get_schedule */
     int32_t onchip_passes;   /* vector passes (N elements each) of the two-pass
-                                count of Algorithm 4 that stayed in LDS: where
-                                each workgroup's rows fit one sub-tile (one
-                                plane, at most 4096 elements and rows of at
-                                most 2048, a one-reduction form) the update
-                                takes x_j and w from the matvec pass before
-                                it, that pass reads the updated x_{j+1} from
-                                LDS, and w is never stored: 4 per step (1 at a
-                                step without an update, 2 at the close), also
-                                where two steps share one pass; 0 otherwise */
+                                count of Algorithm 4 that the on-chip path does
+                                away with: where each workgroup's rows fit one
+                                sub-tile (one plane, at most 4096 elements and
+                                rows of at most 2048, a one-reduction form) the
+                                update takes x_j and w from LDS, the matvec reads
+                                x_{j+1} there, and w is not stored: 4 per step
+                                (1 at a step without an update, 2 at the close),
+                                0 otherwise.  Where up to three steps share a
+                                phase each counts its 4; above 1024 elements per
+                                workgroup w_1 of a phase of three (and w_2 of the
+                                first workgroup) is stored and read all the same,
+                                three passes per phase that the count does not
+                                take off */
     double  err_max;         /* largest substep error estimate */
     double  mu;              /* power-of-two balance of the augmented block */
     double  t_end;           /* time reached (h on success) */
