@@ -110,6 +110,15 @@ def syncs_per_step(jj, orth="h-gsmgs"):
     return jj + 2 if orth == "mgs" else (2 if orth == "iocgs" else 1)
 
 
+def process_syncs(m, orth="h-gsmgs", basis="f64"):
+    """Grid-wide reductions of an Arnoldi process of m steps: those of its steps,
+    or of its blocks where the form makes them (block_starts), and the close of
+    the one-reduction forms."""
+    if orth in ("mgs", "iocgs"):
+        return sum(syncs_per_step(jj, orth) for jj in range(m))
+    return (len(block_starts(m)) if orth == "h-gsmgs" and basis == "f64" else m) + 1
+
+
 def vectors_per_call(schedule, p, c, orth="h-gsmgs"):
     """Algorithmic vector passes (each N float64) of one phi_combo call:
     stage (p+1 reads + 1 write), every Arnoldi step (step_vectors), the
@@ -592,10 +601,7 @@ def main():
             leg = {"ms_per_substep": round(fms, 4),
                    "us_per_arnoldi_step": round(1e3 * fms / 64, 2),
                    "arnoldi_steps_per_s": round(64 / (fms * 1e-3), 1),
-                   "grid_syncs_per_substep": (
-                       23 if orth == "h-gsmgs" and args.basis == "f64"
-                       else sum(syncs_per_step(jj, orth) for jj in range(64))
-                       + (1 if orth not in ("mgs", "iocgs") else 0)),
+                   "grid_syncs_per_substep": process_syncs(64, orth, args.basis),
                    "achieved_GBps": round(fvec * 8.0 * N / (fms * 1e-3) / 1e9, 1),
                    "frac": round(fvec * 8.0 * N / (fms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
                    "bytes_per_launch": fvec * 8.0 * N}
@@ -625,7 +631,7 @@ def main():
         o1 = torch.empty(p1.op.n, dtype=torch.float64, device=dev)
         leg = {"workload": "advection-diffusion 64x64 periodic, nu=0.01, a=(1,0.5), N=4096, "
                            "p=3, h=0.05, one substep of fixed m=40"}
-        for rows, label in ((0, "one_workgroup"), (1, "64_workgroups")):
+        for rows, label in ((0, "automatic"), (64, "one_workgroup"), (1, "64_workgroups")):
             part = {}
             for orth in ORTHS:
                 c1 = kp.Context(orth=orth, fixed_m=40, fixed_substeps=1, rows_per_wg=rows,
@@ -637,8 +643,7 @@ def main():
                 med = float(np.median(ms))
                 part[orth] = {"ms_per_call": round(med, 4),
                               "us_per_arnoldi_step": round(1e3 * med / 40, 2),
-                              "grid_syncs": sum(syncs_per_step(jj, orth) for jj in range(40))
-                              + (1 if orth not in ("mgs", "iocgs") else 0),
+                              "grid_syncs": process_syncs(40, orth),
                               **errors(o1.cpu().numpy(), ref1)}
             for orth in ORTHS:
                 part[orth]["ratio_vs_mgs"] = round(part[orth]["ms_per_call"] /
