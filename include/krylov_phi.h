@@ -97,7 +97,10 @@ extern "C" {
 
 /* ---- basis storage ------------------------------------------------------ */
 #define KP_BASIS_F64 0
-#define KP_BASIS_F32 1   /* basis streamed in FP32; H, T, exp, combination in FP64 */
+#define KP_BASIS_F32 1   /* basis streamed in FP32; H, T, exp, combination in FP64.
+                            Half the basis memory; one reduction per step, so
+                            slower than H-GSMGS in FP64 (2 x 2048^2 Brusselator
+                            394 ms against 312)                              */
 
 /* Limits. */
 #define KP_MMAX 64   /* largest Krylov dimension m_max */
@@ -150,8 +153,9 @@ typedef struct kp_config {
     int32_t controller;      /* KP_CTRL_*, default KP_CTRL_POWER              */
     int32_t rows_per_wg;     /* grid rows owned by each workgroup of a single
                                 call; 0 -> automatic (256 elements or more per
-                                workgroup, 4096 or more for MGS and a float
-                                basis; one workgroup per CU at most).  Raised
+                                workgroup, 4096 or more for MGS, a float basis
+                                and, above 2^18 elements, the forms without block
+                                steps; one workgroup per CU at most).  Raised
                                 to what the CU count needs.                   */
 } kp_config;
 
@@ -398,7 +402,8 @@ int kp_get_batch_schedule(kp_ctx* ctx, int32_t i, double* tau_host, int32_t* m_h
  * single-workgroup time of all problems (work; may be NULL), in seconds.
  * Cost model: Arnoldi steps ~ max(16, 8 sqrt(h rho)) with rho a bound of
  * ||A||; streaming bytes per step ~ 8 N (m + p + c + 6); a serial cost per
- * step and per small exponential; problems, heaviest first, go to the team
+ * step and per small exponential, with the effective constants of the default
+ * form (H-GSMGS, FP64); problems, heaviest first, go to the team
  * that finishes them earliest, over a search of team-size mixes.
  * Errors: KP_EINVAL.
  */

@@ -57,8 +57,8 @@
 // 49.8 ms; 512 uneven problems in one launch 1333, 841, 603 ms.  With the
 // stencil from LDS and small_dots: 64 x 64 519 us, 256^2 3.75 ms, 512^2 forward
 // and backward 39.9 -> 34.6 ms.  With the sections below and the partition of
-// krylov_phi.hip: 64 x 64 438 us, 256^2 3.04 ms, 1024^2 44.9, the Brusselator 48.7,
-// the 512 problems 605.
+// krylov_phi.hip: 64 x 64 442 us, 256^2 3.03 ms, 1024^2 44.4, the Brusselator 47.9,
+// the 512 problems 595 to 620.
 #pragma once
 
 #include "kp_leader.h"

@@ -1,8 +1,9 @@
 // libkrylov_phi: kernels and the C ABI declared in include/krylov_phi.h.
 //
 // Execution model (one MI355X, gfx950).  A whole phi_combo call is ONE
-// cooperative launch of k_blk (the one-reduction forms with a float64 basis) or
-// k_run (a float basis, MGS, ioCGS): every workgroup loops over the phases published
+// cooperative launch of k_blk (the one-reduction forms with a float64 basis; above
+// 2^18 elements those with block steps) or k_run (the others, a float basis, MGS,
+// ioCGS): every workgroup loops over the phases published
 // by workgroup 0 (stage, Arnoldi step = matvec+dots then update+norm, small
 // exponential + controller, combine, finish) and meets the others at
 // grid-wide barriers.  The grid-wide reduction of an Arnoldi step is the
@@ -1299,9 +1300,12 @@ void geometry(int ncu_slots, int rows_cfg, Args* a, bool spread = true) {
                    ? 1 : 0;
   if (a->block) {
     // on chip, the smallest tile that holds the rows; otherwise the fewest
-    // pairs per thread, counting a tile's reductions as 0.7 of a pair (1024^2:
-    // 44.8 ms with one tile of 4 pairs, 49.3 with two of 2; the 5000 elements of
-    // 2 x 1000 x 1200: 50.8 with two of 4, 49.1 with three of 2, 51.6 with five of 1)
+    // pairs per thread, counting a tile's reductions as 0.7 of a pair: the fastest
+    // of the three on 14 of 15 partitions of 256 to 16384 elements per plane, one
+    // and two planes, and 2 % from it at 2100 (one substep of 48 steps, us with 1, 2
+    // and 4 pairs: two planes of 1024 1740, 1941, 2434; 2100 3081, 2965, 3022; 4096
+    // 5357, 4780, 4659; 5000 6396, 6014, 6313; 8400 10604, 9645, 9749; one plane of
+    // 6000 3914, 3461, 3570).  It does not rank the slower two
     double best = 0.0;
     for (int r : {4, 2, 1}) {
       const int64_t tile = (int64_t)2 * kp::kThreads * r, tiles = (rows * a->nx + tile - 1) / tile;
