@@ -148,11 +148,12 @@ def basis_bytes_per_call(schedule, p, c, n, s):
 
 def block_starts(m):
     """(newest column, steps) of the blocks of an m-step process of the float64
-    H-GSMGS form where the guard shortens none: the remainder of m / 3 first,
-    then three steps each; one grid-wide reduction per block, one at the close."""
+    H-GSMGS form where the guard shortens none: three steps each, the first two
+    where m is no multiple of three, the last what is left; one grid-wide
+    reduction per block, one at the close."""
     j, out = 0, []
     while j < m:
-        n = m % 3 if j == 0 and m % 3 else 3
+        n = min(2 if j == 0 and m % 3 else 3, m - j)
         out.append((j, n))
         j += n
     return out

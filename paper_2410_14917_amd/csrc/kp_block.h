@@ -31,13 +31,12 @@
 // 1 / rho of the rounding to the new column, and three of them in a row multiply
 // from block to block.  The shift of every product, the first one too, keeps rho
 // near the spread of the spectrum whatever its distance from zero; the guard
-// bounds what is left (the first block of a process, which has no shift yet and
-// takes the remainder of the steps, smooth start vectors, operators that the tail
-// couples).  Loss of orthogonality on the device, a diagonal at -50 (1 +- 0.05), p = 1,
+// bounds what is left (the first block of a process, which has no shift yet,
+// smooth start vectors, operators that the tail couples).  Loss of orthogonality on the device, a diagonal at -50 (1 +- 0.05), p = 1,
 // 24 columns: 3.7e-14, single steps 2.1e-14, without the shift of the first product
 // 8.7e-8.  Error of the 64 x 64 call, 40 steps, against the closed form (mean of 30
-// inputs): 1.1e-15, as single steps; 2.1e-15 without that shift and with the
-// remainder at the end.  In a model in numpy,
+// inputs): 1.2e-15, single steps 1.1e-15; 2.1e-15 without that shift and with a
+// whole block first.  In a model in numpy,
 // 40 random operators with reaction terms up to -500 and 36 columns: at most
 // 4.4e-12, 1.6e-13 in the geometric mean; residual ||A V - V H|| / ||H|| on
 // diffusion operators, 64 columns, 1e-15 to 2e-15 (single steps 2e-16).  A guard of 1e-3
@@ -57,8 +56,8 @@
 // 49.8 ms; 512 uneven problems in one launch 1333, 841, 603 ms.  With the
 // stencil from LDS and small_dots: 64 x 64 519 us, 256^2 3.75 ms, 512^2 forward
 // and backward 39.9 -> 34.6 ms.  With the sections below and the partition of
-// krylov_phi.hip: 64 x 64 442 us, 256^2 3.03 ms, 1024^2 44.4, the Brusselator 47.9,
-// the 512 problems 595 to 620.
+// krylov_phi.hip: 64 x 64 443 us, 256^2 3.04 ms, 1024^2 44.8, the Brusselator 48.0,
+// the 512 problems 595 to 630 (boxes).
 #pragma once
 
 #include "kp_leader.h"
@@ -171,13 +170,16 @@ __device__ inline int block_steps(const Args& a, const LeadB& L, int j) {
   if (!a.pairs || L.nopair >= kMaxShort) return 1;
   return max(1, min(kS, min(L.m_target, a.stop_j) - j));
 }
-// ... and the first phase of a run of steps from column j (no update pending): the
-// remainder, so that the blocks after it are whole.  It has no shift at the start
-// of a process, and the short block reads fewest columns there: one at j = 0
-// instead of one at j = 63 is 3 % of the columns of 64 steps.
+// ... and the first phase of a run of steps from column j (no update pending): two
+// where the run is no multiple of three (16 = 2 + 3 + 3 + 3 + 3 + 2, as many phases
+// as whole blocks first).  The first block of a process has no shift yet, and a
+// smooth start vector often lets it make only two; the last block's free place
+// takes a step that the guard puts off on the way.  All of the remainder first
+// reads 2 % fewer columns and has no such place: 1024^2 call 44.5 ms against
+// 44.8, but EPI4 steps of Allen-Cahn at 100^2 to 256^2 6 % longer (a phase more).
 __device__ inline int first_steps(const Args& a, const LeadB& L, int j) {
   const int n = block_steps(a, L, j), left = min(L.m_target, a.stop_j) - j;
-  return (n == kS && left % kS) ? left % kS : n;
+  return (n == kS && left % kS) ? kS - 1 : n;
 }
 // (The shift starts from 0: the last one of the substep before belongs to the
 // end of its process, and the first vectors of this one are smooth.)
