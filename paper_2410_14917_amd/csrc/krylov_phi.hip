@@ -1342,9 +1342,9 @@ size_t halo_area(const Args& a, int nwg) {
 // growing stops the stream, is refused under capture and frees what captured
 // graphs of earlier calls use.  Partial sums and flags: every slot of the chip at
 // the largest stride (1.7 MB).  Halo rows: with nx * planes of 4096 or more both
-// partitions are the same, so twice the coarse count; below, two buffers take
-// at most 4 N doubles and at most 4 * 4096 per workgroup slot; the tagged
-// exchange at most kLlMax elements a row and five buffers per slot.
+// partitions are the same, so twice the coarse count; below, two buffers take at
+// most 4 N doubles (a row per workgroup) and 4 * 4096 per workgroup slot, the
+// tagged exchange's five at most 10 N and 10 kLlMax per slot.
 size_t part_kept(int slots) {
   return (size_t)slots * kp::kCStride + 2 * (size_t)(slots + 1) * (kp::kNv * kp::kMMax + 24);
 }
@@ -1354,7 +1354,7 @@ size_t halo_kept(int slots, int rows_cfg, const Args& a, size_t u_doubles) {
   geometry(slots, rows_cfg, &g, false);
   return std::max({halo_area(a, a.nwg), 2 * halo_doubles(g, g.nwg),
                    std::min(4 * u_doubles, (size_t)slots * 4 * 4096),
-                   (size_t)slots * 2 * kLlMax * 5 + 2 * kp::kPMax});
+                   std::min(10 * u_doubles, (size_t)slots * 2 * kLlMax * 5) + 2 * kp::kPMax});
 }
 
 // Allocate the workspace for a problem and finish Args.
